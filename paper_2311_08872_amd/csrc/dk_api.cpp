@@ -78,6 +78,7 @@ int dk_cnn_loss_grad(dk_context* ctx, const float* params, int32_t n, int32_t ba
     if ((rc = ctx->cv_loss.ensure(sizeof(double)))) return rc;
     HIP_TRY(hipMemcpyAsync(ctx->cv_prm.p, params, sizeof(float) * dk::cnn::NPARAM, hipMemcpyHostToDevice, s));
     HIP_TRY(hipMemsetAsync(ctx->cv_loss.p, 0, sizeof(double), s));
+    ctx->cnn.keep = true;
     HIP_TRY(ctx->cnn.reserve(n, batch));
     HIP_TRY(dk::cnn::pack(ctx->cnn, (const float*)ctx->cv_prm.p, s));
     HIP_TRY(dk::cnn::forward(ctx->cnn, (const float*)ctx->cv_prm.p, x, batch, (float*)ctx->cv_r.p, s));
@@ -152,6 +153,7 @@ int dk_cv_train(dk_context* ctx, const dk_problem* problem, int32_t level, uint6
     HIP_TRY(hipMemsetAsync(ctx->cv_m.p, 0, 4 * NPARAM, s));
     HIP_TRY(hipMemsetAsync(ctx->cv_v.p, 0, 4 * NPARAM, s));
     HIP_TRY(hipMemsetAsync(ctx->cv_loss.p, 0, sizeof(double) * epochs, s));
+    ctx->cnn.keep = true;
     HIP_TRY(ctx->cnn.reserve(nc, batch));
     const uint64_t steps_per_epoch = n_train / (uint64_t)batch;
     int t = 0;

@@ -19,16 +19,16 @@ constexpr int OFF_U2 = 5888;   // [1][64]
 constexpr int OFF_C2 = 5952;
 constexpr int NPARAM = 5953;
 
-constexpr int kPixPerWave = 2048;   // pixels reduced by one wavefront in the weight-gradient GEMM
-constexpr int kPixPerBlock = 1024;  // pixels per block in the bias / first-layer gradients
-
-// Activation and gradient buffers for a batch of n x n inputs.
+// Buffers for a batch of n x n inputs.  keep (set before reserve and forward): hold what backward()
+// needs, the activations among it; without it a forward pass keeps 16 sums per tile.
 struct Workspace {
-    int n = 0, batch = 0, nwaves = 0, nblk = 0;
-    uint16_t *a1 = nullptr, *a2 = nullptr, *a3 = nullptr, *dz = nullptr, *dz2 = nullptr;   // BF16 [pixels][16]
-    float *g = nullptr, *h1 = nullptr, *dg = nullptr, *sq = nullptr, *contrib = nullptr, *hsum = nullptr;
-    float *partial = nullptr, *bpart = nullptr, *bsum = nullptr;
-    uint16_t *wt2 = nullptr, *wb2 = nullptr, *wt3 = nullptr, *wb3 = nullptr;   // BF16 GEMM weights
+    int n = 0, batch = 0, kept = 0;                                             // kept: batch of the training buffers
+    bool keep = true;
+    float *gpart = nullptr, *g_ = nullptr;                                      // pool: per tile, per sample
+    uint16_t *wt2 = nullptr, *wb2 = nullptr, *wt3 = nullptr, *wb3 = nullptr;    // BF16 GEMM weights
+    uint16_t *a1 = nullptr, *a2 = nullptr, *dz2 = nullptr;                      // BF16 [pixels][16]
+    uint16_t *m3 = nullptr, *dgs = nullptr;                                     // ReLU mask [pixels], BF16 [batch][16]
+    float *sq = nullptr, *drs = nullptr, *dh = nullptr, *da = nullptr, *part = nullptr;
     hipError_t reserve(int n, int batch);
     void release();
     ~Workspace() { release(); }
@@ -36,7 +36,7 @@ struct Workspace {
 
 // BF16 GEMM weight layouts from the FP32 parameters (call after every parameter change).
 hipError_t pack(Workspace& W, const float* prm, hipStream_t s);
-// r[batch] = network(x[batch][n][n]); keeps the activations for backward().
+// r[batch] = network(x[batch][n][n]); with keep, holds the activations for backward().
 hipError_t forward(Workspace& W, const float* prm, const float* x, int batch, float* r, hipStream_t s);
 // grad[NPARAM] of mean_b (r_b - y_b)^2 after forward(); per-sample squared errors in W.sq.
 hipError_t backward(Workspace& W, const float* prm, const float* x, const float* r, const float* y, int batch, float* grad,

@@ -6,15 +6,35 @@
 // Parameters are FP32 masters, flat in the order W1 b1 W2 b2 W3 b3 U1 c1 U2 c2 with conv
 // weights [o][c][ky][kx] and dense weights [out][in] (5953 values).
 //
-// The two 16->16 convolutions run as implicit GEMMs on v_mfma_f32_16x16x32_bf16: activations are
-// BF16, pixel-major with the 16 channels contiguous ([pixel][16]); one wavefront computes a tile
-// of 16 pixels x 16 output channels, K = 9 neighbour positions x 16 channels = 144, padded to 160
-// (5 MFMAs).  The same kernel computes the input gradient (neighbours mirrored, weights stored
-// [c][pos][o]).  Weight gradients are a second GEMM reducing over pixels (32 per MFMA) into
-// per-wavefront partials that are summed in a fixed order.  The 1->16 convolution, pooling and
-// the dense head are small and run on the vector ALU in FP32.
+// Numbers: the 16->16 convolutions multiply BF16 operands on v_mfma_f32_16x16x32_bf16 with FP32
+// accumulation; each layer's output (and each gradient at a layer's output) is rounded to BF16
+// once; the first layer, pooling and the dense head are FP32 throughout, as is the first layer's
+// weight gradient (v_mfma_f32_16x16x4_f32).
+//
+// Forward (one block per tile of at most 32 x 16 pixels): the tile of x with a halo of 3 comes to
+// LDS once, the first layer writes its 16 channels there with a halo of 2, the second reads it and
+// writes beside it, the third overwrites the first, and the tile's channel sums are formed from
+// LDS: nothing but x is read from HBM and nothing but 16 sums per tile is written (the training
+// pass also writes the two activations and a 16-bit ReLU mask per pixel).  Grids of at most 16 x 16
+// put several samples into one block.  A layer as its own pass over HBM moved 64 B per pixel and
+// layer and summed the pool in one thread per (sample, channel): 4.64 ms for 4000 inputs of 64 x 64
+// (0.85 ms per 1024 of it the pool) against 0.52 ms now.
+// An activation image is two planes of 8 channels, 16 B per pixel each, so the 16 pixels of an MFMA
+// operand are 256 consecutive bytes; the convolution runs over the image's linear index (tile rows
+// and their halo columns alike) and the results in halo columns are not used.
+//
+// Backward: per layer one kernel whose blocks stride over tiles (halo 1) and hold the weight
+// gradient in MFMA accumulators for their whole run: A = gradient [o][pixel], B = activation
+// [pixel][c], both from LDS images transposed to [channel][pixel]; the nine neighbour shifts are the
+// three rows of the image times {funnel shift left, none, funnel shift right} of one 16-byte row
+// piece.  The bias gradient is a tenth product with a column of ones.  The same kernel convolves the
+// gradient back to the layer's input.  Per-block partial sums are added in block order by the last
+// kernel, which also forms the dense head's gradients.  Loss and gradient at 64 x 64, batch 256:
+// 4.01 ms with one kernel per product (2-byte gathers, serial column sums, 27 launches), 0.28 ms now.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <algorithm>
 
 #include "dk_cnn.h"
 
@@ -22,303 +42,611 @@ namespace dk {
 namespace cnn {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
 
-__device__ __forceinline__ uint16_t f2bf(float f)
-{
-    uint32_t u = __float_as_uint(f);
-    u += 0x7FFFu + ((u >> 16) & 1u);   // round to nearest even
-    return (uint16_t)(u >> 16);
-}
+// rounded to nearest even by the hardware conversion (a pair is one instruction, where the integer
+// sequence takes nine)
+__device__ __forceinline__ uint16_t f2bf(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
 __device__ __forceinline__ float bf2f(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
-
-__device__ __forceinline__ int shifted_pixel(int P, int n, int dy, int dx)
+__device__ __forceinline__ uint32_t pack2(float lo, float hi)
 {
-    const int nn = n * n;
-    const int b = P / nn;
-    const int r = P - b * nn;
-    const int y = r / n, x = r - (r / n) * n;
-    int yy = y + dy, xx = x + dx;
-    yy = yy < 0 ? yy + n : (yy >= n ? yy - n : yy);
-    xx = xx < 0 ? xx + n : (xx >= n ? xx - n : xx);
-    return b * nn + yy * n + xx;
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(floatx2{lo, hi}, bf16x2));
 }
 
+// x / d for 0 <= x < 2^16 and 1 <= d < 2^11 by one high product (exact: the error x / 2^32 of the
+// rounded reciprocal stays below 1/d)
+struct Div {
+    uint32_t d, m;
+    __host__ __device__ Div(uint32_t v = 1) : d(v), m(v <= 1 ? 0u : 0xFFFFFFFFu / v + 1u) {}
+    __device__ __forceinline__ uint32_t q(uint32_t x) const { return m == 0u ? x : __umulhi(x, m); }
+};
+
+__device__ __forceinline__ int wrapn(int v, int n) { return v < 0 ? v + n : (v >= n ? v - n : v); }
+
 // ---------------------------------------------------------------------------------------
-// conv 1->16 (FP32 in, BF16 out), ReLU.  One thread per pixel.
+// Tiles.  A sample's n x n pixels are cut into tx x ty tiles of tw x th pixels (the last ones may
+// be smaller); a block holds S samples when one tile covers a sample, one tile otherwise.
 // ---------------------------------------------------------------------------------------
-__global__ void conv1_fwd(const float* __restrict__ x, const float* __restrict__ prm, uint16_t* __restrict__ a1, int n,
-                          int npix)
+struct Geo {
+    int n, batch, tw, th, tx, ty, S;
+    int H;              // halo of the image
+    int P, img, L;      // image pitch, pixels of one sample's image, of all S
+    int groups;         // ceil(batch / S) x tiles per sample: work items
+    Div dP, dImg, dTiles, dTx, dTw, dTile;
+};
+
+constexpr int kTileW = 32, kTileH = 16;
+constexpr int kFwdThreads = 256;    // three blocks per compute unit (LDS); 512 threads run at the same speed
+constexpr int kFwdL = 728;          // image pixels (halo 2) of a forward block: 36 x 20 fit
+constexpr int kFwdX = 1040;         // x pixels (halo 3)
+constexpr int kBwdL = 616;          // image pixels (halo 1) of a backward block: 34 x 18 fit
+constexpr int kBwdA = 872;          // transposed activation image: pixels per channel (18 rows of 48 fit)
+constexpr int kBwdZ = 520;          // transposed gradient tile: pixels per channel
+constexpr int kBlocks = 512;        // two blocks per compute unit: the backward grid, and what small grids are spread to
+
+static inline int cdiv(int a, int b) { return (a + b - 1) / b; }
+
+static Geo make_geo(int n, int batch, int H)
 {
-    const int P = blockIdx.x * blockDim.x + threadIdx.x;
-    if (P >= npix) return;
-    float v[9];
-#pragma unroll
-    for (int pos = 0; pos < 9; ++pos) v[pos] = x[shifted_pixel(P, n, pos / 3 - 1, pos % 3 - 1)];
-    uint16_t o16[16];
-#pragma unroll
-    for (int o = 0; o < 16; ++o) {
-        float s = prm[OFF_B1 + o];
-#pragma unroll
-        for (int pos = 0; pos < 9; ++pos) s = fmaf(prm[OFF_W1 + o * 9 + pos], v[pos], s);
-        o16[o] = f2bf(fmaxf(s, 0.0f));
+    Geo g;
+    g.n = n;
+    g.batch = batch;
+    g.H = H;
+    g.tx = cdiv(n, kTileW);
+    g.tw = 4 * cdiv(n / 4, g.tx);
+    g.tx = cdiv(n, g.tw);
+    g.ty = cdiv(n, kTileH);
+    g.th = cdiv(n, g.ty);
+    g.ty = cdiv(n, g.th);
+    g.P = g.tw + 2 * H;
+    g.img = g.P * (g.th + 2 * H);
+    g.S = 1;
+    if (g.tx * g.ty == 1) {
+        const int units = cdiv(g.tw, 8), rp = 8 * units + 16;
+        int most;
+        if (H == 2) most = std::min(kFwdL / g.img, kFwdX / ((g.tw + 6) * (g.th + 6)));
+        else most = std::min({kBwdL / g.img, (kBwdA - 8) / ((g.th + 2) * rp), (kBwdZ - 8) / (g.th * units * 8)});
+        // as many samples as fit, unless that leaves compute units idle
+        g.S = std::max(1, std::min(most, cdiv(batch, kBlocks)));
     }
-    uint4* dst = (uint4*)(a1 + (size_t)P * 16);
-    dst[0] = make_uint4(o16[0] | (o16[1] << 16), o16[2] | (o16[3] << 16), o16[4] | (o16[5] << 16), o16[6] | (o16[7] << 16));
-    dst[1] = make_uint4(o16[8] | (o16[9] << 16), o16[10] | (o16[11] << 16), o16[12] | (o16[13] << 16),
-                        o16[14] | (o16[15] << 16));
+    g.L = g.S * g.img;
+    g.groups = cdiv(batch, g.S) * g.tx * g.ty;
+    g.dP = Div(g.P);
+    g.dImg = Div(g.img);
+    g.dTiles = Div(g.tx * g.ty);
+    g.dTx = Div(g.tx);
+    g.dTw = Div(g.tw);
+    g.dTile = Div(g.tw * g.th);
+    return g;
 }
 
-// ---------------------------------------------------------------------------------------
-// Implicit-GEMM 3x3 16->16 convolution on MFMA.
-//   MODE 0 (forward):        out[p][o] = ReLU(b[o] + sum_{pos,c} W[o][c][pos] in[p + d(pos)][c])
-//   MODE 1 (input gradient): out[p][c] = mask(p,c) sum_{pos,o} W[o][c][pos] in[p - d(pos)][o]
-// Wk: BF16 [16][160], row j holds the B-matrix column j: k = pos*16 + (c or o), zero-padded.
-// One wavefront per 16-pixel tile, 4 wavefronts per block.
-// ---------------------------------------------------------------------------------------
-template <int MODE>
-__global__ void __launch_bounds__(256) conv_gemm(const uint16_t* __restrict__ in, const uint16_t* __restrict__ Wk,
-                                                 const float* __restrict__ bias, const uint16_t* __restrict__ mask,
-                                                 uint16_t* __restrict__ out, int n, int npix)
+struct TileAt {
+    int b0, x0, y0, tw, th;     // first sample, first pixel, pixels of this tile
+};
+
+__device__ __forceinline__ TileAt tile_at(const Geo& g, int item)
 {
-    const int lane = threadIdx.x & 63;
-    const int tile = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (tile * 16 >= npix) return;
-    const int i = lane & 15;
-    const int kg = lane >> 4;
-    const int P = tile * 16 + i;
+    const int tiles = g.tx * g.ty;
+    const int grp = item / tiles, t = item - grp * tiles;
+    const int ty = t / g.tx, txx = t - ty * g.tx;
+    TileAt a;
+    a.b0 = grp * g.S;
+    a.x0 = txx * g.tw;
+    a.y0 = ty * g.th;
+    a.tw = min(g.tw, g.n - a.x0);
+    a.th = min(g.th, g.n - a.y0);
+    return a;
+}
+
+// MFMA operand of the weights: row i of the packed layout [16][160], k = 32 s + 8 kg ..
+__device__ __forceinline__ void load_weights(uint4 (&w)[5], const uint16_t* __restrict__ Wk, int lane)
+{
+#pragma unroll
+    for (int s = 0; s < 5; ++s) w[s] = *(const uint4*)(Wk + (lane & 15) * 160 + 32 * s + 8 * (lane >> 4));
+}
+
+// 3x3 16->16 products of 16 consecutive image pixels starting at idx0: D[row = output channel]
+// [column = pixel], K = 9 neighbours x 16 channels = 144 padded to 160.  off[s]: the lane's
+// neighbour offset of K-step s.
+__device__ __forceinline__ floatx4 conv16(const uint4* __restrict__ img, int plane, int idx0, const int (&off)[5],
+                                          const uint4 (&w)[5], int lane)
+{
     floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+    const int i = lane & 15, kg = lane >> 4;
+    const uint4* p = img + (kg & 1) * plane + idx0 + i;
 #pragma unroll
     for (int s = 0; s < 5; ++s) {
-        const int pos = 2 * s + (kg >> 1);
-        uint4 av = make_uint4(0, 0, 0, 0);
-        if (pos < 9) {
-            int dy = pos / 3 - 1, dx = pos % 3 - 1;
-            if (MODE == 1) { dy = -dy; dx = -dx; }
-            const int q = shifted_pixel(P, n, dy, dx);
-            av = *(const uint4*)(in + (size_t)q * 16 + 8 * (kg & 1));
-        }
-        const uint4 bv = *(const uint4*)(Wk + i * 160 + 32 * s + 8 * kg);
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av), __builtin_bit_cast(bf16x8, bv),
-                                                       acc, 0, 0, 0);
+        uint4 v = p[off[s]];
+        if (s == 4 && kg >= 2) v = make_uint4(0, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[s]), __builtin_bit_cast(bf16x8, v), acc, 0,
+                                                       0, 0);
     }
-    // D[row][col]: col = lane & 15 (output channel), rows 4 kg .. 4 kg + 3 (pixels of the tile)
-    const int ch = lane & 15;
+    return acc;
+}
+
+__device__ __forceinline__ void neighbour_offsets(int (&off)[5], int P, int lane, int sign)
+{
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int Pr = tile * 16 + 4 * kg + r;
-        float v = acc[r];
-        if (MODE == 0) {
-            v = fmaxf(v + bias[ch], 0.0f);
-        } else {
-            if (bf2f(mask[(size_t)Pr * 16 + ch]) <= 0.0f) v = 0.0f;
-        }
-        out[(size_t)Pr * 16 + ch] = f2bf(v);
+    for (int s = 0; s < 5; ++s) {
+        const int pos = 2 * s + (lane >> 5);
+        off[s] = pos < 9 ? sign * ((pos / 3 - 1) * P + (pos % 3 - 1)) : 0;
     }
 }
 
 // ---------------------------------------------------------------------------------------
-// Weight gradient of a 16->16 conv: dW[o][c][pos] = sum_p dz[p][o] x[p + d(pos)][c].
-// GEMM with the reduction over pixels, 32 per MFMA; each wavefront reduces a pixel range into
-// 9 accumulators (one per neighbour position) and writes a partial [9][16][16].
+// Forward: the three convolutions of one tile.  KEEP: also writes the activations a1, a2 ([pixel][16]
+// BF16) and the third layer's ReLU mask for the backward pass.  gpart[sample][tile][16] receives the
+// tile's channel sums.
 // ---------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) conv_dw(const uint16_t* __restrict__ x, const uint16_t* __restrict__ dz,
-                                               float* __restrict__ partial, int n, int npix, int pix_per_wave)
+template <bool KEEP>
+__global__ void __launch_bounds__(kFwdThreads) conv_fwd(const Geo g, const float* __restrict__ x, const float* __restrict__ prm,
+                                                const uint16_t* __restrict__ wt2, const uint16_t* __restrict__ wt3,
+                                                float* __restrict__ gpart, uint16_t* __restrict__ a1g,
+                                                uint16_t* __restrict__ a2g, uint16_t* __restrict__ m3g)
 {
-    const int lane = threadIdx.x & 63;
-    const int w = blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int p0 = w * pix_per_wave;
-    if (p0 >= npix) return;
-    const int p1 = min(npix, p0 + pix_per_wave);
-    const int j = lane & 15;
-    const int kg = lane >> 4;
-    floatx4 acc[9];
-#pragma unroll
-    for (int pos = 0; pos < 9; ++pos) acc[pos] = floatx4{0.f, 0.f, 0.f, 0.f};
-    for (int c0 = p0; c0 < p1; c0 += 32) {
-        uint16_t a[8];
-        int pix[8];
-#pragma unroll
-        for (int t = 0; t < 8; ++t) {
-            const int P = c0 + 8 * kg + t;
-            pix[t] = P;
-            a[t] = P < p1 ? dz[(size_t)P * 16 + j] : (uint16_t)0;   // A[o = j][pixel]
-        }
-        const uint4 av = make_uint4(a[0] | (a[1] << 16), a[2] | (a[3] << 16), a[4] | (a[5] << 16), a[6] | (a[7] << 16));
-        const bf16x8 A = __builtin_bit_cast(bf16x8, av);
-#pragma unroll
-        for (int pos = 0; pos < 9; ++pos) {
-            uint16_t b[8];
-#pragma unroll
-            for (int t = 0; t < 8; ++t)
-                b[t] = pix[t] < p1 ? x[(size_t)shifted_pixel(pix[t], n, pos / 3 - 1, pos % 3 - 1) * 16 + j] : (uint16_t)0;
-            const uint4 bv = make_uint4(b[0] | (b[1] << 16), b[2] | (b[3] << 16), b[4] | (b[5] << 16), b[6] | (b[7] << 16));
-            acc[pos] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, __builtin_bit_cast(bf16x8, bv), acc[pos], 0, 0, 0);
+    constexpr int PL = kFwdL + 16;                 // plane: the last group of 16 reads past the image
+    __shared__ float sx[kFwdX];
+    __shared__ uint4 sA[2 * PL];
+    __shared__ uint4 sB[2 * PL];
+    constexpr int WAVES = kFwdThreads / 64;
+    __shared__ float sred[WAVES * 16];
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const TileAt T = tile_at(g, blockIdx.x);
+    const int n = g.n, P = g.P, L = g.L;
+    const size_t nn = (size_t)n * n;
+    // x with halo 3
+    {
+        const int xp = g.tw + 6, xi = xp * (g.th + 6);
+        const Div dxp(xp), dxi(xi);
+        for (int e = t; e < g.S * xi; e += kFwdThreads) {
+            const int s = dxi.q(e), r = e - s * xi, yy = dxp.q(r), xx = r - yy * xp;
+            const int b = min(T.b0 + s, g.batch - 1);
+            sx[e] = x[b * nn + (size_t)wrapn(T.y0 + yy - 3, n) * n + wrapn(T.x0 + xx - 3, n)];
         }
     }
-    // D[o][c]: c = lane & 15, o = 4 kg + r
-#pragma unroll
-    for (int pos = 0; pos < 9; ++pos)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) partial[((size_t)w * 9 + pos) * 256 + (4 * kg + r) * 16 + j] = acc[pos][r];
-}
-
-// Sum partials [nw][9][16][16] in wavefront order into dW[o][c][pos] of the flat gradient.
-__global__ void reduce_dw(const float* __restrict__ partial, int nw, float* __restrict__ grad, int off)
-{
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;   // over 9*256
-    if (t >= 9 * 256) return;
-    const int pos = t / 256, oc = t % 256, o = oc / 16, c = oc % 16;
-    float s = 0.f;
-    for (int w = 0; w < nw; ++w) s += partial[(size_t)w * 9 * 256 + t];
-    grad[off + o * 144 + c * 9 + pos] = s;
-}
-
-// Column sums of a [rows][cols] matrix in row order (deterministic), into dst[cols].
-__global__ void colsum(const float* __restrict__ m, int rows, int cols, float* __restrict__ dst)
-{
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= cols) return;
-    float s = 0.f;
-    for (int r = 0; r < rows; ++r) s += m[(size_t)r * cols + c];
-    dst[c] = s;
-}
-
-// Per-block partial sums of dz (BF16 [npix][16]) over pixels: out[block][16] (bias gradients)
-__global__ void bias_partial(const uint16_t* __restrict__ dz, int npix, int pix_per_block, float* __restrict__ out)
-{
-    __shared__ float sh[256];
-    const int c = threadIdx.x & 15, lane16 = threadIdx.x >> 4;
-    const int p0 = blockIdx.x * pix_per_block, p1 = min(npix, p0 + pix_per_block);
-    float s = 0.f;
-    for (int p = p0 + lane16; p < p1; p += 16) s += bf2f(dz[(size_t)p * 16 + c]);
-    sh[threadIdx.x] = s;
+    uint4 w2[5], w3[5];
+    load_weights(w2, wt2, lane);
+    load_weights(w3, wt3, lane);
     __syncthreads();
-    if (threadIdx.x < 16) {
-        float t = 0.f;
-        for (int k = 0; k < 16; ++k) t += sh[k * 16 + threadIdx.x];
-        out[blockIdx.x * 16 + threadIdx.x] = t;
-    }
-}
-
-// conv1 weight/bias gradient partials: per block, thread t < 144 -> (o, pos), t in [144,160) -> db1
-__global__ void conv1_dw(const float* __restrict__ x, const uint16_t* __restrict__ dz1, int n, int npix,
-                         int pix_per_block, float* __restrict__ out /* [blocks][160] */)
-{
-    const int t = threadIdx.x;
-    if (t >= 160) return;
-    const int p0 = blockIdx.x * pix_per_block, p1 = min(npix, p0 + pix_per_block);
-    float s = 0.f;
-    if (t < 144) {
-        const int o = t / 9, pos = t % 9;
-        for (int p = p0; p < p1; ++p) s += bf2f(dz1[(size_t)p * 16 + o]) * x[shifted_pixel(p, n, pos / 3 - 1, pos % 3 - 1)];
-    } else {
-        const int o = t - 144;
-        for (int p = p0; p < p1; ++p) s += bf2f(dz1[(size_t)p * 16 + o]);
-    }
-    out[blockIdx.x * 160 + t] = s;
-}
-
-// ---------------------------------------------------------------------------------------
-// Pooling and dense head (FP32).
-// ---------------------------------------------------------------------------------------
-__global__ void pool(const uint16_t* __restrict__ a3, int nn, int batch, float* __restrict__ g)
-{
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;   // (sample, channel)
-    if (t >= batch * 16) return;
-    const int b = t / 16, c = t % 16;
-    float s = 0.f;
-    for (int p = 0; p < nn; ++p) s += bf2f(a3[((size_t)b * nn + p) * 16 + c]);
-    g[t] = s / (float)nn;
-}
-
-__global__ void head_fwd(const float* __restrict__ g, const float* __restrict__ prm, int batch, float* __restrict__ h1,
-                         float* __restrict__ r)
-{
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= batch) return;
-    float gi[16];
+    // first layer on the whole image (halo 2)
+    {
+        const int xp = g.tw + 6, xi = xp * (g.th + 6);
+        for (int e = t; e < L; e += kFwdThreads) {
+            const int s = g.dImg.q(e), r = e - s * g.img, yy = g.dP.q(r), xx = r - yy * P;
+            const float* c = sx + s * xi + yy * xp + xx;
+            float v[9];
 #pragma unroll
-    for (int c = 0; c < 16; ++c) gi[c] = g[b * 16 + c];
-    float out = prm[OFF_C2];
-    for (int k = 0; k < 64; ++k) {
-        float s = prm[OFF_C1 + k];
+            for (int pos = 0; pos < 9; ++pos) v[pos] = c[(pos / 3) * xp + pos % 3];
+            // 8 outputs at a time: their 80 weights fit the scalar registers, 160 would spill
+#pragma unroll 1
+            for (int h = 0; h < 2; ++h) {
+                const float* w1 = prm + OFF_W1 + 72 * h;
+                const float* b1 = prm + OFF_B1 + 8 * h;
+                float o8[8];
 #pragma unroll
-        for (int c = 0; c < 16; ++c) s = fmaf(prm[OFF_U1 + k * 16 + c], gi[c], s);
-        if (h1) h1[b * 64 + k] = s;
-        out = fmaf(prm[OFF_U2 + k], fmaxf(s, 0.f), out);
-    }
-    r[b] = out;
-}
-
-// Per-sample head backward: gradient contributions [batch][GH] with GH = 64 (U2) + 1 (c2) +
-// 1024 (U1) + 64 (c1); dg [batch][16]; loss terms (r - y)^2 [batch].
-constexpr int GH = 64 + 1 + 1024 + 64;
-__global__ void head_bwd(const float* __restrict__ g, const float* __restrict__ h1, const float* __restrict__ r,
-                         const float* __restrict__ y, const float* __restrict__ prm, int batch, float* __restrict__ contrib,
-                         float* __restrict__ dg, float* __restrict__ sq)
-{
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= batch) return;
-    const float e = r[b] - y[b];
-    sq[b] = e * e;
-    const float dr = 2.0f * e / (float)batch;
-    float* cb = contrib + (size_t)b * GH;
-    float dgi[16];
+                for (int o = 0; o < 8; ++o) {
+                    float a = b1[o];
 #pragma unroll
-    for (int c = 0; c < 16; ++c) dgi[c] = 0.f;
-    for (int k = 0; k < 64; ++k) {
-        const float hk = h1[b * 64 + k];
-        const float a4 = fmaxf(hk, 0.f);
-        cb[k] = dr * a4;                                       // dU2
-        const float dh = hk > 0.f ? dr * prm[OFF_U2 + k] : 0.f;
-        cb[65 + 1024 + k] = dh;                                // dc1
-#pragma unroll
-        for (int c = 0; c < 16; ++c) {
-            cb[65 + k * 16 + c] = dh * g[b * 16 + c];          // dU1
-            dgi[c] = fmaf(prm[OFF_U1 + k * 16 + c], dh, dgi[c]);
+                    for (int pos = 0; pos < 9; ++pos) a = fmaf(w1[o * 9 + pos], v[pos], a);
+                    o8[o] = fmaxf(a, 0.0f);
+                }
+                sA[h * PL + e] = make_uint4(pack2(o8[0], o8[1]), pack2(o8[2], o8[3]), pack2(o8[4], o8[5]), pack2(o8[6], o8[7]));
+            }
         }
     }
-    cb[64] = dr;                                               // dc2
+    __syncthreads();
+    int off[5];
+    neighbour_offsets(off, P, lane, 1);
+    const int i = lane & 15, kg = lane >> 4;
+    // one layer: image pixels [lo, hi) of src -> dst
+    auto layer = [&](const uint4* src, uint4* dst, const uint4 (&w)[5], const float* bias, int lo, int hi) {
+        float b4[4];
 #pragma unroll
-    for (int c = 0; c < 16; ++c) dg[b * 16 + c] = dgi[c];
+        for (int r = 0; r < 4; ++r) b4[r] = bias[4 * kg + r];
+        for (int g0 = lo + 16 * wave; g0 < hi; g0 += 16 * WAVES) {
+            const floatx4 acc = conv16(src, PL, g0, off, w, lane);
+            uint2 o;
+            o.x = pack2(fmaxf(acc[0] + b4[0], 0.0f), fmaxf(acc[1] + b4[1], 0.0f));
+            o.y = pack2(fmaxf(acc[2] + b4[2], 0.0f), fmaxf(acc[3] + b4[3], 0.0f));
+            ((uint2*)&dst[(kg >> 1) * PL + g0 + i])[kg & 1] = o;
+        }
+    };
+    // interior pixels of an image in LDS to global memory, 16 B per thread
+    auto keep = [&](const uint4* src, uint16_t* dst) {
+        const int tile = g.tw * g.th;
+        for (int e = t; e < g.S * tile * 2; e += kFwdThreads) {
+            const int h = e & 1, q = e >> 1, s = g.dTile.q(q), r = q - s * tile, yy = g.dTw.q(r), xx = r - yy * g.tw;
+            if (T.b0 + s < g.batch && yy < T.th && xx < T.tw)
+                *(uint4*)(dst + ((T.b0 + s) * nn + (size_t)(T.y0 + yy) * n + T.x0 + xx) * 16 + 8 * h) =
+                    src[h * PL + s * g.img + (yy + 2) * P + xx + 2];
+        }
+    };
+    layer(sA, sB, w2, prm + OFF_B2, P + 1, L - P - 1);
+    if constexpr (KEEP) keep(sA, a1g);
+    __syncthreads();
+    layer(sB, sA, w3, prm + OFF_B3, 2 * P + 2, L - 2 * P - 2);
+    if constexpr (KEEP) keep(sB, a2g);
+    __syncthreads();
+    if constexpr (KEEP) {
+        const int tile = g.tw * g.th;
+        for (int q = t; q < g.S * tile; q += kFwdThreads) {
+            const int s = g.dTile.q(q), r = q - s * tile, yy = g.dTw.q(r), xx = r - yy * g.tw;
+            const int c = s * g.img + (yy + 2) * P + xx + 2;
+            uint32_t m = 0;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const uint4 v = sA[h * PL + c];
+                const uint32_t d[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    m |= (uint32_t)((d[k] & 0x7FFFu) != 0) << (8 * h + 2 * k);
+                    m |= (uint32_t)((d[k] & 0x7FFF0000u) != 0) << (8 * h + 2 * k + 1);
+                }
+            }
+            if (T.b0 + s < g.batch && yy < T.th && xx < T.tw)
+                m3g[(T.b0 + s) * nn + (size_t)(T.y0 + yy) * n + T.x0 + xx] = (uint16_t)m;
+        }
+    }
+    // channel sums of the tile: lanes of one parity hold one plane's 8 channels.  One sample: its
+    // pixels over the whole block; several: a sample per wavefront.
+    const int h = t & 1;
+    const int ntile = g.tx * g.ty;
+    const int step = g.S == 1 ? kFwdThreads / 2 : 32;
+    const int px = T.tw * T.th;
+    const Div dw(T.tw);
+    for (int s = g.S == 1 ? 0 : wave; s < g.S; s += g.S == 1 ? 1 : WAVES) {
+        float v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = 0.f;
+        for (int q = (g.S == 1 ? t : lane) >> 1; q < px; q += step) {
+            const int yy = dw.q(q), xx = q - yy * T.tw;
+            const uint4 u = sA[h * PL + s * g.img + (yy + 2) * P + xx + 2];
+            const uint32_t d[4] = {u.x, u.y, u.z, u.w};
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                v[2 * k] += __uint_as_float(d[k] << 16);
+                v[2 * k + 1] += __uint_as_float(d[k] & 0xFFFF0000u);
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+#pragma unroll
+            for (int o = 32; o >= 2; o >>= 1) v[k] += __shfl_xor(v[k], o, 64);
+        if (g.S == 1) {
+            if (lane < 2)
+#pragma unroll
+                for (int k = 0; k < 8; ++k) sred[wave * 16 + 8 * h + k] = v[k];
+            __syncthreads();
+            if (t < 16) {
+                float a = 0.f;
+#pragma unroll
+                for (int w = 0; w < WAVES; ++w) a += sred[16 * w + t];
+                gpart[((size_t)T.b0 * ntile + blockIdx.x % ntile) * 16 + t] = a;
+            }
+        } else if (lane < 2 && T.b0 + s < g.batch) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) gpart[(size_t)(T.b0 + s) * 16 + 8 * h + k] = v[k];
+        }
+    }
 }
 
-// scatter the head gradient sums [GH] into the flat gradient
-__global__ void head_scatter(const float* __restrict__ sums, float* __restrict__ grad)
+// ---------------------------------------------------------------------------------------
+// Dense head: 64 lanes per sample, lane k the hidden unit k.
+// ---------------------------------------------------------------------------------------
+__device__ __forceinline__ float head_hidden(const float* gs, const float* __restrict__ prm, int k)
 {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= GH) return;
-    if (t < 64) grad[OFF_U2 + t] = sums[t];
-    else if (t == 64) grad[OFF_C2] = sums[t];
-    else if (t < 65 + 1024) grad[OFF_U1 + (t - 65)] = sums[t];
-    else grad[OFF_C1 + (t - 65 - 1024)] = sums[t];
+    float s = prm[OFF_C1 + k];
+#pragma unroll
+    for (int c = 0; c < 16; ++c) s = fmaf(prm[OFF_U1 + k * 16 + c], gs[c], s);
+    return s;
 }
 
-// dz3[p][c] = dg[b][c] / nn * (a3[p][c] > 0)
-__global__ void pool_bwd(const float* __restrict__ dg, const uint16_t* __restrict__ a3, int nn, int npix,
-                         uint16_t* __restrict__ dz3)
+__global__ void __launch_bounds__(256) head_fwd(const float* __restrict__ gpart, int ntile, float nn, const float* __restrict__ prm,
+                                                int batch, float* __restrict__ gout, float* __restrict__ r)
 {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= npix * 16) return;
-    const int p = t / 16, c = t % 16, b = p / nn;
-    const float v = bf2f(a3[t]) > 0.f ? dg[b * 16 + c] / (float)nn : 0.f;
-    dz3[t] = f2bf(v);
+    __shared__ float sg[4][16];
+    const int k = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int b = blockIdx.x * 4 + w;
+    const bool on = b < batch;
+    if (on && k < 16) {
+        float s = 0.f;
+        for (int q = 0; q < ntile; ++q) s += gpart[((size_t)b * ntile + q) * 16 + k];
+        s /= nn;
+        sg[w][k] = s;
+        gout[(size_t)b * 16 + k] = s;
+    }
+    __syncthreads();
+    if (!on) return;
+    float v = prm[OFF_U2 + k] * fmaxf(head_hidden(sg[w], prm, k), 0.f);
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
+    if (k == 0) r[b] = prm[OFF_C2] + v;
 }
 
-// place per-block partial sums [blocks][cols] into the gradient at off (after colsum)
-__global__ void copy_to(const float* __restrict__ src, int n, float* __restrict__ dst, int off)
+// Per sample: squared error, dL/dr, the hidden layer's gradient dh and dr relu(h) (for U1, c1, U2), and
+// the gradient at the third convolution's output, dg / nn in BF16.
+__global__ void __launch_bounds__(256) head_bwd(const float* __restrict__ g, const float* __restrict__ r,
+                                                const float* __restrict__ y, const float* __restrict__ prm, int batch, float nn,
+                                                float* __restrict__ sq, float* __restrict__ drs, float* __restrict__ dh,
+                                                float* __restrict__ da, uint16_t* __restrict__ dgs)
 {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < n) dst[off + t] = src[t];
+    __shared__ float sg[4][16], sd[4][64];
+    const int k = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int b = blockIdx.x * 4 + w;
+    const bool on = b < batch;
+    if (on && k < 16) sg[w][k] = g[(size_t)b * 16 + k];
+    __syncthreads();
+    if (on) {
+        const float e = r[b] - y[b];
+        const float dr = 2.0f * e / (float)batch;
+        const float hk = head_hidden(sg[w], prm, k);
+        const float d = hk > 0.f ? dr * prm[OFF_U2 + k] : 0.f;
+        sd[w][k] = d;
+        dh[(size_t)b * 64 + k] = d;
+        da[(size_t)b * 64 + k] = dr * fmaxf(hk, 0.f);
+        if (k == 0) { sq[b] = e * e; drs[b] = dr; }
+    }
+    __syncthreads();
+    if (on && k < 16) {
+        float s = 0.f;
+#pragma unroll 8
+        for (int q = 0; q < 64; ++q) s = fmaf(prm[OFF_U1 + q * 16 + k], sd[w][q], s);
+        dgs[(size_t)b * 16 + k] = f2bf(s / nn);
+    }
 }
 
-// conv1 partial layout [144 W1 (o*9+pos) | 16 b1] -> grad
-__global__ void conv1_scatter(const float* __restrict__ sums, float* __restrict__ grad)
+// ---------------------------------------------------------------------------------------
+// Backward of one 16->16 convolution.
+//   LAYER 3: the gradient at its output is dgs[b][c] where the ReLU mask m3 is set; writes the
+//            gradient at its input (masked by act > 0) to dzo.
+//   LAYER 2: the gradient at its output is dzi; the gradient at its input stays in LDS and gives the
+//            first layer's weight gradient with x.
+// part [block][10][256]: the weight gradient per neighbour [o][c] and, last, the bias gradient in
+// column 0; part1 [block][256]: the first layer's [o][position 0..8 | 9: bias].
+// ---------------------------------------------------------------------------------------
+template <int LAYER>
+__global__ void __launch_bounds__(256) conv_bwd(const Geo g, const uint16_t* __restrict__ wb, const uint16_t* __restrict__ act,
+                                                const uint16_t* __restrict__ m3, const uint16_t* __restrict__ dgs,
+                                                const uint16_t* __restrict__ dzi, uint16_t* __restrict__ dzo,
+                                                const float* __restrict__ x, float* __restrict__ part,
+                                                float* __restrict__ part1)
 {
+    constexpr int PL = kBwdL + 24;
+    __shared__ uint4 sZ[2 * PL];                         // gradient image (halo 1), two planes
+    __shared__ __align__(16) uint16_t aT[16 * kBwdA];    // activation image, [channel][row][8 + pixel]
+    __shared__ __align__(16) uint16_t zT[16 * kBwdZ];    // gradient tile, [channel][8-pixel units]
+    __shared__ float sx[LAYER == 2 ? kBwdL + 64 : 1];    // x image (halo 1)
+    __shared__ uint16_t utab[kBwdZ / 8];                 // a unit's place in a row of aT
+    __shared__ uint16_t sdg[LAYER == 3 ? 64 * 16 : 1];
+    static_assert(16 * kBwdA * 2 >= 2560 * 4, "the block's sums reuse the activation image");
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, i = lane & 15, kg = lane >> 4;
+    const int n = g.n, P = g.P, L = g.L, S = g.S;
+    const size_t nn = (size_t)n * n;
+    const int upr = (g.tw + 7) >> 3, rp = 8 * upr + 16, rows = S * (g.th + 2), U = S * g.th * upr;
+    // channel strides of an odd number of 16-byte pieces: the 16 channels of an operand read without bank conflicts
+    const int ca = 8 * ((rows * rp / 8) | 1), cz = 8 * (U | 1);
+    const Div dU(upr), dRow(g.th), dRp(rp), dRows(g.th + 2), dUs(g.th * upr);
+    uint4 w[5];
+    load_weights(w, wb, lane);
+    int off[5];
+    neighbour_offsets(off, P, lane, -1);
+    for (int u = t; u < U; u += 256) {
+        const int row = dU.q(u), s = dRow.q(row);
+        utab[u] = (uint16_t)((row + 2 * s + 1) * rp + 8 + 8 * (u - row * upr));
+    }
+    if constexpr (LAYER == 2)
+        for (int e = L + t; e < kBwdL + 64; e += 256) sx[e] = 0.f;
+    floatx4 acc[10], acc1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int pos = 0; pos < 10; ++pos) acc[pos] = floatx4{0.f, 0.f, 0.f, 0.f};
+    const uint4 ones = make_uint4(0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u);
+
+    for (int item = blockIdx.x; item < g.groups; item += gridDim.x) {
+        const TileAt T = tile_at(g, item);
+        __syncthreads();                                 // the previous tile's readers are done
+        if constexpr (LAYER == 3) {
+            for (int e = t; e < S * 16; e += 256) sdg[e] = T.b0 + (e >> 4) < g.batch ? dgs[(size_t)T.b0 * 16 + e] : (uint16_t)0;
+            __syncthreads();
+        }
+        // the gradient's 8 channels h of pixel (s, y, x)
+        auto grad8 = [&](int s, int gy, int gx, int h) -> uint4 {
+            const size_t p = (size_t)(T.b0 + s) * nn + (size_t)gy * n + gx;
+            if (T.b0 + s >= g.batch) return make_uint4(0, 0, 0, 0);
+            if constexpr (LAYER == 3) {
+                const uint32_t m = (uint32_t)m3[p] >> (8 * h);
+                uint32_t d[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const uint32_t v = *(const uint32_t*)(sdg + s * 16 + 8 * h + 2 * k);
+                    d[k] = ((m >> (2 * k)) & 1u ? v & 0xFFFFu : 0u) | ((m >> (2 * k + 1)) & 1u ? v & 0xFFFF0000u : 0u);
+                }
+                return make_uint4(d[0], d[1], d[2], d[3]);
+            } else {
+                return *(const uint4*)(dzi + p * 16 + 8 * h);
+            }
+        };
+        auto scatter8 = [](uint16_t* dst, int stride, uint4 v) {
+            const uint32_t d[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                dst[(2 * k) * stride] = (uint16_t)d[k];
+                dst[(2 * k + 1) * stride] = (uint16_t)(d[k] >> 16);
+            }
+        };
+        for (int e = t; e < 2 * L; e += 256) {
+            const int h = e >= L ? 1 : 0, q = e - h * L, s = g.dImg.q(q), r = q - s * g.img, yy = g.dP.q(r), xx = r - yy * P;
+            sZ[h * PL + q] = grad8(s, wrapn(T.y0 + yy - 1, n), wrapn(T.x0 + xx - 1, n), h);
+        }
+        for (int e = t; e < 16 * U; e += 256) {          // (half, unit, pixel)
+            const int h = e >= 8 * U ? 1 : 0, q = e - h * 8 * U, u = q >> 3, row = dU.q(u), s = dRow.q(row);
+            const int yy = row - s * g.th, xx = 8 * (u - row * upr) + (q & 7);
+            const bool in = yy < T.th && xx < T.tw;
+            scatter8(zT + 8 * h * cz + q, cz, in ? grad8(s, T.y0 + yy, T.x0 + xx, h) : make_uint4(0, 0, 0, 0));
+        }
+        for (int e = t; e < 2 * rows * rp; e += 256) {   // (half, row, place)
+            const int h = e >= rows * rp ? 1 : 0, q = e - h * rows * rp, row = dRp.q(q), s = dRows.q(row);
+            const int yy = row - s * (g.th + 2) - 1, xx = q - row * rp - 8;
+            uint4 v = make_uint4(0, 0, 0, 0);
+            if (xx >= -1 && xx <= g.tw && T.b0 + s < g.batch)
+                v = *(const uint4*)(act + ((T.b0 + s) * nn + (size_t)wrapn(T.y0 + yy, n) * n + wrapn(T.x0 + xx, n)) * 16 + 8 * h);
+            scatter8(aT + 8 * h * ca + q, ca, v);
+        }
+        if constexpr (LAYER == 2) {
+            for (int e = t; e < L; e += 256) {
+                const int s = g.dImg.q(e), r = e - s * g.img, yy = g.dP.q(r), xx = r - yy * P;
+                const int b = min(T.b0 + s, g.batch - 1);
+                sx[e] = x[b * nn + (size_t)wrapn(T.y0 + yy - 1, n) * n + wrapn(T.x0 + xx - 1, n)];
+            }
+        }
+        __syncthreads();
+        // weight and bias gradients: 4 units of 8 pixels per MFMA
+        for (int u0 = 4 * wave; u0 < U; u0 += 16) {
+            const int u = u0 + kg;
+            uint4 za = make_uint4(0, 0, 0, 0);
+            int place = 8;
+            if (u < U) {
+                za = *(const uint4*)(zT + i * cz + 8 * u);
+                place = utab[u];
+            }
+            const bf16x8 A = __builtin_bit_cast(bf16x8, za);
+            const uint16_t* base = aT + i * ca + place;
+#pragma unroll
+            for (int dy = -1; dy <= 1; ++dy) {
+                const int ro = u < U ? dy * rp : 0;
+                const uint4 c = *(const uint4*)(base + ro);
+                const uint32_t lf = *(const uint32_t*)(base + ro - 2), rt = *(const uint32_t*)(base + ro + 8);
+                const uint32_t f0 = __builtin_amdgcn_alignbit(c.x, lf, 16), f1 = __builtin_amdgcn_alignbit(c.y, c.x, 16),
+                               f2 = __builtin_amdgcn_alignbit(c.z, c.y, 16), f3 = __builtin_amdgcn_alignbit(c.w, c.z, 16),
+                               f4 = __builtin_amdgcn_alignbit(rt, c.w, 16);
+                const int p0 = 3 * (dy + 1);
+                acc[p0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, __builtin_bit_cast(bf16x8, make_uint4(f0, f1, f2, f3)), acc[p0], 0, 0, 0);
+                acc[p0 + 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, __builtin_bit_cast(bf16x8, c), acc[p0 + 1], 0, 0, 0);
+                acc[p0 + 2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, __builtin_bit_cast(bf16x8, make_uint4(f1, f2, f3, f4)), acc[p0 + 2], 0, 0, 0);
+            }
+            acc[9] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, __builtin_bit_cast(bf16x8, ones), acc[9], 0, 0, 0);
+        }
+        if constexpr (LAYER == 2) __syncthreads();       // zT is overwritten below
+        // the gradient at the layer's input
+        for (int g0 = P + 1 + 16 * wave; g0 < L - P - 1; g0 += 64) {
+            const floatx4 d = conv16(sZ, PL, g0, off, w, lane);
+            const int q = g0 + i, s = g.dImg.q(q), r = q - s * g.img, yy = g.dP.q(r) - 1, xx = r - (yy + 1) * P - 1;
+            const bool in = s < S && T.b0 + s < g.batch && yy >= 0 && yy < T.th && xx >= 0 && xx < T.tw;
+            if (!in) continue;
+            const size_t p = (size_t)(T.b0 + s) * nn + (size_t)(T.y0 + yy) * n + T.x0 + xx;
+            const uint16_t* am = aT + (4 * kg) * ca + (s * (g.th + 2) + yy + 1) * rp + 8 + xx;
+            float v[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v[k] = (am[k * ca] & 0x7FFFu) != 0 ? d[k] : 0.0f;
+            if constexpr (LAYER == 3) {
+                *(uint2*)(dzo + p * 16 + 4 * kg) = make_uint2(pack2(v[0], v[1]), pack2(v[2], v[3]));
+            } else {
+                uint16_t* z = zT + 4 * kg * cz + ((s * g.th + yy) * upr) * 8 + xx;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) z[k * cz] = f2bf(v[k]);
+            }
+        }
+        if constexpr (LAYER == 2) {
+            __syncthreads();
+            // first layer: dW1[o][pos] = sum_p dz1[p][o] x[p + d(pos)], FP32 products; 4 pixels per MFMA
+            const int dpos = i < 9 ? (i / 3 - 1) * P + (i % 3 - 1) : 0;
+            for (int u = wave; u < U; u += 4) {
+                const int row = dU.q(u), s = dRow.q(row);
+                const int xi = s * g.img + (row - s * g.th + 1) * P + 1 + 8 * (u - row * upr) + kg;
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    const float za = bf2f(zT[i * cz + 8 * u + 4 * j + kg]);
+                    const float xv = i < 9 ? sx[xi + 4 * j + dpos] : (i == 9 ? 1.0f : 0.0f);
+                    acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(za, xv, acc1, 0, 0, 0);
+                }
+            }
+        }
+    }
+    // the block's sums, wavefront by wavefront
+    __syncthreads();
+    float* red = (float*)aT;
+    float* red1 = (float*)zT;
+    for (int v = 0; v < 4; ++v) {
+        if (wave == v) {
+#pragma unroll
+            for (int pos = 0; pos < 10; ++pos)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    float* d = red + pos * 256 + (4 * kg + r) * 16 + i;
+                    *d = v == 0 ? acc[pos][r] : *d + acc[pos][r];
+                }
+            if constexpr (LAYER == 2)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    float* d = red1 + (4 * kg + r) * 16 + i;
+                    *d = v == 0 ? acc1[r] : *d + acc1[r];
+                }
+        }
+        __syncthreads();
+    }
+    for (int e = t; e < 2560; e += 256) part[(size_t)blockIdx.x * 2560 + e] = red[e];
+    if constexpr (LAYER == 2) part1[(size_t)blockIdx.x * 256 + t] = red1[t];
+}
+
+// Sums of the blocks' partials, 16 slices of blocks per output in a fixed order, into the flat
+// gradient; and the dense head's gradients, a block per hidden unit over the batch.
+constexpr int kSumBlocks = (2 * 2560 + 256) / 64;
+
+__global__ void __launch_bounds__(1024) finish_grad(const float* __restrict__ p3, const float* __restrict__ p2,
+                                                    const float* __restrict__ p1, int nb, const float* __restrict__ g,
+                                                    const float* __restrict__ dh, const float* __restrict__ da,
+                                                    const float* __restrict__ drs, int batch, float* __restrict__ grad)
+{
+    __shared__ float sh[64 * 18];
     const int t = threadIdx.x;
-    if (t < 144) grad[OFF_W1 + t] = sums[t];
-    else if (t < 160) grad[OFF_B1 + t - 144] = sums[t];
+    if ((int)blockIdx.x < kSumBlocks) {
+        const int lane = t & 63, sl = t >> 6, e = blockIdx.x * 64 + lane;
+        const float* src = e < 2560 ? p3 + e : (e < 5120 ? p2 + (e - 2560) : p1 + (e - 5120));
+        const size_t stride = e < 5120 ? 2560 : 256;
+        const int b0 = nb * sl / 16, b1 = nb * (sl + 1) / 16;
+        float s = 0.f;
+#pragma unroll 8
+        for (int b = b0; b < b1; ++b) s += src[b * stride];
+        sh[sl * 64 + lane] = s;
+        __syncthreads();
+        if (sl != 0) return;
+        s = 0.f;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) s += sh[k * 64 + lane];
+        if (e < 5120) {
+            const int q = e < 2560 ? e : e - 2560, pos = q >> 8, o = (q >> 4) & 15, c = q & 15;
+            if (pos < 9) grad[(e < 2560 ? OFF_W3 : OFF_W2) + o * 144 + c * 9 + pos] = s;
+            else if (c == 0) grad[(e < 2560 ? OFF_B3 : OFF_B2) + o] = s;
+        } else {
+            const int q = e - 5120, o = q >> 4, pos = q & 15;
+            if (pos < 9) grad[OFF_W1 + o * 9 + pos] = s;
+            else if (pos == 9) grad[OFF_B1 + o] = s;
+        }
+        return;
+    }
+    const int k = (int)blockIdx.x - kSumBlocks;          // hidden unit; 64: the output bias
+    const int c = t & 15, sl = t >> 4;
+    float s = 0.f, sa = 0.f, sb = 0.f;
+    if (k < 64) {
+        for (int b = sl; b < batch; b += 64) {
+            const float d = dh[(size_t)b * 64 + k];
+            s += d * g[(size_t)b * 16 + c];
+            if (c == 0) { sa += da[(size_t)b * 64 + k]; sb += d; }
+        }
+    } else if (c == 0) {
+        for (int b = sl; b < batch; b += 64) sa += drs[b];
+    }
+    sh[sl * 18 + c] = s;
+    if (c == 0) { sh[sl * 18 + 16] = sa; sh[sl * 18 + 17] = sb; }
+    __syncthreads();
+    if (t >= 18) return;
+    s = 0.f;
+    for (int q = 0; q < 64; ++q) s += sh[q * 18 + t];
+    if (k == 64) { if (t == 16) grad[OFF_C2] = s; return; }
+    if (t < 16) grad[OFF_U1 + k * 16 + t] = s;
+    else if (t == 16) grad[OFF_U2 + k] = s;
+    else grad[OFF_C1 + k] = s;
 }
 
 // Adam (Kingma & Ba) with bias correction; t is the 1-based step.
@@ -337,11 +665,17 @@ __global__ void adam(float* __restrict__ p, const float* __restrict__ gr, float*
     p[k] -= lr * mh / (sqrtf(vh) + eps);
 }
 
-// BF16 GEMM layouts of a 16->16 conv: fwd[o][pos*16+c], bwd[c][pos*16+o] (rows of 160)
-__global__ void pack_weights(const float* __restrict__ prm, int off, uint16_t* __restrict__ fwd, uint16_t* __restrict__ bwd)
+// BF16 GEMM layouts of the two 16->16 convs: fwd[o][pos*16+c], bwd[c][pos*16+o] (rows of 160)
+__global__ void pack_weights(const float* __restrict__ prm, uint16_t* __restrict__ fwd2, uint16_t* __restrict__ bwd2,
+                             uint16_t* __restrict__ fwd3, uint16_t* __restrict__ bwd3)
 {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;   // 16 * 160
-    if (t >= 16 * 160) return;
+    int t = blockIdx.x * blockDim.x + threadIdx.x;   // 2 * 16 * 160
+    if (t >= 2 * 16 * 160) return;
+    const bool third = t >= 16 * 160;
+    if (third) t -= 16 * 160;
+    const int off = third ? OFF_W3 : OFF_W2;
+    uint16_t* fwd = third ? fwd3 : fwd2;
+    uint16_t* bwd = third ? bwd3 : bwd2;
     const int row = t / 160, k = t % 160;
     if (k >= 144) { fwd[t] = 0; bwd[t] = 0; return; }
     const int pos = k / 16, col = k % 16;
@@ -395,18 +729,24 @@ hipError_t combine_cv(const double* ps, int nobs, int j, const float* r, const f
     return hipGetLastError();
 }
 
-// sum of W.sq into acc[0] (ordered, one thread)
-__global__ void sum_into(const float* __restrict__ v, int n, double* __restrict__ acc)
+// acc[0] += sum of v, in double: 256 strided partial sums, then a fixed tree
+__global__ void __launch_bounds__(256) sum_into(const float* __restrict__ v, int n, double* __restrict__ acc)
 {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
+    __shared__ double sh[256];
     double s = 0.0;
-    for (int i = 0; i < n; ++i) s += (double)v[i];
-    acc[0] += s;
+    for (int i = threadIdx.x; i < n; i += 256) s += (double)v[i];
+    sh[threadIdx.x] = s;
+    __syncthreads();
+    for (int w = 128; w >= 1; w >>= 1) {
+        if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) acc[0] += sh[0];
 }
 
 hipError_t accumulate_sq(const Workspace& W, int batch, double* acc, hipStream_t s)
 {
-    hipLaunchKernelGGL(sum_into, dim3(1), dim3(64), 0, s, W.sq, batch, acc);
+    hipLaunchKernelGGL(sum_into, dim3(1), dim3(256), 0, s, W.sq, batch, acc);
     return hipGetLastError();
 }
 
@@ -415,104 +755,96 @@ hipError_t accumulate_sq(const Workspace& W, int batch, double* acc, hipStream_t
 // ---------------------------------------------------------------------------------------
 static inline unsigned blocks_for(size_t n, int bs) { return (unsigned)((n + bs - 1) / bs); }
 
+// The pool's sums grow with the forward batch, the rest with the training batch, so a program that
+// alternates evaluation and training on one grid size allocates once for each.
 hipError_t Workspace::reserve(int n_, int batch_)
 {
-    if (n_ == n && batch_ <= batch) return hipSuccess;
-    release();
+    if (n_ != n) release();
     n = n_;
-    batch = batch_;
-    const size_t npix = (size_t)batch * n * n;
     hipError_t e;
-#define ALLOC(ptr, bytes) if ((e = hipMalloc((void**)&ptr, bytes)) != hipSuccess) return e
-    ALLOC(a1, npix * 16 * 2);
-    ALLOC(a2, npix * 16 * 2);
-    ALLOC(a3, npix * 16 * 2);
-    ALLOC(dz, npix * 16 * 2);
-    ALLOC(dz2, npix * 16 * 2);
-    ALLOC(g, (size_t)batch * 16 * 4);
-    ALLOC(h1, (size_t)batch * 64 * 4);
-    ALLOC(dg, (size_t)batch * 16 * 4);
-    ALLOC(sq, (size_t)batch * 4);
-    ALLOC(contrib, (size_t)batch * GH * 4);
-    ALLOC(hsum, (size_t)GH * 4);
-    nwaves = (int)((npix + kPixPerWave - 1) / kPixPerWave);
-    ALLOC(partial, (size_t)nwaves * 9 * 256 * 4);
-    nblk = (int)((npix + kPixPerBlock - 1) / kPixPerBlock);
-    ALLOC(bpart, (size_t)nblk * 160 * 4);
-    ALLOC(bsum, 160 * 4);
-    ALLOC(wt2, 16 * 160 * 2);
-    ALLOC(wb2, 16 * 160 * 2);
-    ALLOC(wt3, 16 * 160 * 2);
-    ALLOC(wb3, 16 * 160 * 2);
-#undef ALLOC
+    auto take = [&](auto*& ptr, size_t bytes) {
+        if (ptr) (void)hipFree(ptr);
+        ptr = nullptr;
+        return hipMalloc((void**)&ptr, bytes);
+    };
+#define TAKE(ptr, bytes) if ((e = take(ptr, bytes)) != hipSuccess) { release(); return e; }
+    if (!wt2) {
+        TAKE(wt2, 16 * 160 * 2);
+        TAKE(wb2, 16 * 160 * 2);
+        TAKE(wt3, 16 * 160 * 2);
+        TAKE(wb3, 16 * 160 * 2);
+    }
+    if (batch_ > batch) {
+        const Geo g = make_geo(n_, batch_, 2);
+        TAKE(gpart, (size_t)batch_ * g.tx * g.ty * 16 * 4);
+        TAKE(g_, (size_t)batch_ * 16 * 4);
+        batch = batch_;
+    }
+    if (keep && batch_ > kept) {
+        const size_t npix = (size_t)batch_ * n_ * n_;
+        TAKE(a1, npix * 16 * 2);
+        TAKE(a2, npix * 16 * 2);
+        TAKE(dz2, npix * 16 * 2);
+        TAKE(m3, npix * 2);
+        TAKE(sq, (size_t)batch_ * 4);
+        TAKE(drs, (size_t)batch_ * 4);
+        TAKE(dh, (size_t)batch_ * 64 * 4);
+        TAKE(da, (size_t)batch_ * 64 * 4);
+        TAKE(dgs, (size_t)batch_ * 16 * 2);
+        TAKE(part, (size_t)kBlocks * (2 * 2560 + 256) * 4);
+        kept = batch_;
+    }
+#undef TAKE
     return hipSuccess;
 }
 
 void Workspace::release()
 {
-    void* ptrs[] = {a1, a2, a3, dz, dz2, g, h1, dg, sq, contrib, hsum, partial, bpart, bsum, wt2, wb2, wt3, wb3};
+    void* ptrs[] = {gpart, g_, wt2, wb2, wt3, wb3, a1, a2, dz2, m3, sq, drs, dh, da, dgs, part};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
-    a1 = a2 = a3 = dz = dz2 = nullptr;
-    g = h1 = dg = sq = contrib = hsum = partial = bpart = bsum = nullptr;
-    wt2 = wb2 = wt3 = wb3 = nullptr;
-    n = batch = 0;
+    gpart = g_ = sq = drs = dh = da = part = nullptr;
+    wt2 = wb2 = wt3 = wb3 = a1 = a2 = dz2 = m3 = dgs = nullptr;
+    n = batch = kept = 0;
 }
 
 hipError_t pack(Workspace& W, const float* prm, hipStream_t s)
 {
-    hipLaunchKernelGGL(pack_weights, dim3(blocks_for(16 * 160, 256)), dim3(256), 0, s, prm, OFF_W2, W.wt2, W.wb2);
-    hipLaunchKernelGGL(pack_weights, dim3(blocks_for(16 * 160, 256)), dim3(256), 0, s, prm, OFF_W3, W.wt3, W.wb3);
+    hipLaunchKernelGGL(pack_weights, dim3(blocks_for(2 * 16 * 160, 256)), dim3(256), 0, s, prm, W.wt2, W.wb2, W.wt3, W.wb3);
     return hipGetLastError();
 }
 
 hipError_t forward(Workspace& W, const float* prm, const float* x, int batch, float* r, hipStream_t s)
 {
-    const int n = W.n;
-    const int npix = batch * n * n;
-    hipLaunchKernelGGL(conv1_fwd, dim3(blocks_for(npix, 256)), dim3(256), 0, s, x, prm, W.a1, n, npix);
-    const unsigned gb = blocks_for((size_t)npix / 16, 4);
-    hipLaunchKernelGGL(conv_gemm<0>, dim3(gb), dim3(256), 0, s, W.a1, W.wt2, prm + OFF_B2, (const uint16_t*)nullptr, W.a2,
-                       n, npix);
-    hipLaunchKernelGGL(conv_gemm<0>, dim3(gb), dim3(256), 0, s, W.a2, W.wt3, prm + OFF_B3, (const uint16_t*)nullptr, W.a3,
-                       n, npix);
-    hipLaunchKernelGGL(pool, dim3(blocks_for((size_t)batch * 16, 256)), dim3(256), 0, s, W.a3, n * n, batch, W.g);
-    hipLaunchKernelGGL(head_fwd, dim3(blocks_for(batch, 128)), dim3(128), 0, s, W.g, prm, batch, W.h1, r);
+    if (batch < 1) return hipSuccess;
+    const Geo g = make_geo(W.n, batch, 2);
+    const dim3 grid((unsigned)g.groups);
+    if (W.keep)
+        hipLaunchKernelGGL(conv_fwd<true>, grid, dim3(kFwdThreads), 0, s, g, x, prm, W.wt2, W.wt3, W.gpart, W.a1, W.a2, W.m3);
+    else
+        hipLaunchKernelGGL(conv_fwd<false>, grid, dim3(kFwdThreads), 0, s, g, x, prm, W.wt2, W.wt3, W.gpart, (uint16_t*)nullptr,
+                           (uint16_t*)nullptr, (uint16_t*)nullptr);
+    hipLaunchKernelGGL(head_fwd, dim3(blocks_for(batch, 4)), dim3(256), 0, s, W.gpart, g.tx * g.ty, (float)(W.n * W.n), prm, batch,
+                       W.g_, r);
     return hipGetLastError();
 }
 
 hipError_t backward(Workspace& W, const float* prm, const float* x, const float* r, const float* y, int batch, float* grad,
                     hipStream_t s)
 {
-    const int n = W.n;
-    const int nn = n * n;
-    const int npix = batch * nn;
-    hipLaunchKernelGGL(head_bwd, dim3(blocks_for(batch, 128)), dim3(128), 0, s, W.g, W.h1, r, y, prm, batch, W.contrib,
-                       W.dg, W.sq);
-    hipLaunchKernelGGL(colsum, dim3(blocks_for(GH, 256)), dim3(256), 0, s, W.contrib, batch, GH, W.hsum);
-    hipLaunchKernelGGL(head_scatter, dim3(blocks_for(GH, 256)), dim3(256), 0, s, W.hsum, grad);
-    // conv3
-    hipLaunchKernelGGL(pool_bwd, dim3(blocks_for((size_t)npix * 16, 256)), dim3(256), 0, s, W.dg, W.a3, nn, npix, W.dz);
-    const int nwaves = (npix + kPixPerWave - 1) / kPixPerWave;
-    const int nblk = (npix + kPixPerBlock - 1) / kPixPerBlock;
-    const unsigned gb = blocks_for((size_t)npix / 16, 4);
-    hipLaunchKernelGGL(conv_dw, dim3(blocks_for(nwaves, 4)), dim3(256), 0, s, W.a2, W.dz, W.partial, n, npix, kPixPerWave);
-    hipLaunchKernelGGL(reduce_dw, dim3(blocks_for(9 * 256, 256)), dim3(256), 0, s, W.partial, nwaves, grad, OFF_W3);
-    hipLaunchKernelGGL(bias_partial, dim3(nblk), dim3(256), 0, s, W.dz, npix, kPixPerBlock, W.bpart);
-    hipLaunchKernelGGL(colsum, dim3(1), dim3(64), 0, s, W.bpart, nblk, 16, W.bsum);
-    hipLaunchKernelGGL(copy_to, dim3(1), dim3(64), 0, s, W.bsum, 16, grad, OFF_B3);
-    hipLaunchKernelGGL(conv_gemm<1>, dim3(gb), dim3(256), 0, s, W.dz, W.wb3, (const float*)nullptr, W.a2, W.dz2, n, npix);
-    // conv2 (dz2 holds the gradient at conv2's output, masked)
-    hipLaunchKernelGGL(conv_dw, dim3(blocks_for(nwaves, 4)), dim3(256), 0, s, W.a1, W.dz2, W.partial, n, npix, kPixPerWave);
-    hipLaunchKernelGGL(reduce_dw, dim3(blocks_for(9 * 256, 256)), dim3(256), 0, s, W.partial, nwaves, grad, OFF_W2);
-    hipLaunchKernelGGL(bias_partial, dim3(nblk), dim3(256), 0, s, W.dz2, npix, kPixPerBlock, W.bpart);
-    hipLaunchKernelGGL(colsum, dim3(1), dim3(64), 0, s, W.bpart, nblk, 16, W.bsum);
-    hipLaunchKernelGGL(copy_to, dim3(1), dim3(64), 0, s, W.bsum, 16, grad, OFF_B2);
-    hipLaunchKernelGGL(conv_gemm<1>, dim3(gb), dim3(256), 0, s, W.dz2, W.wb2, (const float*)nullptr, W.a1, W.dz, n, npix);
-    // conv1 (dz holds the gradient at conv1's output, masked)
-    hipLaunchKernelGGL(conv1_dw, dim3(nblk), dim3(256), 0, s, x, W.dz, n, npix, kPixPerBlock, W.bpart);
-    hipLaunchKernelGGL(colsum, dim3(1), dim3(256), 0, s, W.bpart, nblk, 160, W.bsum);
-    hipLaunchKernelGGL(conv1_scatter, dim3(1), dim3(256), 0, s, W.bsum, grad);
+    if (W.kept < batch) return hipErrorInvalidValue;
+    const Geo g = make_geo(W.n, batch, 1);
+    const int nb = std::min(g.groups, kBlocks);
+    float* p3 = W.part;
+    float* p2 = p3 + (size_t)kBlocks * 2560;
+    float* p1 = p2 + (size_t)kBlocks * 2560;
+    hipLaunchKernelGGL(head_bwd, dim3(blocks_for(batch, 4)), dim3(256), 0, s, W.g_, r, y, prm, batch, (float)(W.n * W.n), W.sq,
+                       W.drs, W.dh, W.da, W.dgs);
+    hipLaunchKernelGGL(conv_bwd<3>, dim3(nb), dim3(256), 0, s, g, W.wb3, W.a2, W.m3, W.dgs, (const uint16_t*)nullptr, W.dz2,
+                       (const float*)nullptr, p3, (float*)nullptr);
+    hipLaunchKernelGGL(conv_bwd<2>, dim3(nb), dim3(256), 0, s, g, W.wb2, W.a1, (const uint16_t*)nullptr,
+                       (const uint16_t*)nullptr, W.dz2, (uint16_t*)nullptr, x, p2, p1);
+    hipLaunchKernelGGL(finish_grad, dim3(kSumBlocks + 65), dim3(1024), 0, s, p3, p2, p1, nb, W.g_, W.dh, W.da, W.drs, batch, grad);
     return hipGetLastError();
 }
 

@@ -8,12 +8,6 @@
 
 namespace dkh {
 
-namespace {
-
-constexpr int kCnnBatch = 1024;   // inputs per network launch sequence
-
-}  // namespace
-
 // ------------------------------------------------------------------------------------------
 // Learned control variate
 // ------------------------------------------------------------------------------------------
@@ -33,14 +27,18 @@ int ensure_rbar(dk_context* ctx, const dk_problem* p, int level, LevelTables** o
     return DK_OK;
 }
 
-// r[count] = network(x[count][n][n]) in batches of kCnnBatch
+// r[count] = network(x[count][n][n]).  A forward pass keeps 64 B per tile of 32 x 16 pixels, so the
+// batch of one launch is bounded by pixels only (2^26: 8 MB of sums), not by activations.
 int cnn_forward_batched(dk_context* ctx, const float* prm, int n, uint64_t count, const float* x, float* r, hipStream_t s)
 {
     if (count == 0) return DK_OK;
-    HIP_TRY(ctx->cnn.reserve(n, kCnnBatch));
+    const uint64_t most = std::max<uint64_t>(64, (1ull << 26) / ((uint64_t)n * n));
+    const uint64_t batch = std::min(count, most);
+    ctx->cnn.keep = false;
+    HIP_TRY(ctx->cnn.reserve(n, (int)batch));
     HIP_TRY(dk::cnn::pack(ctx->cnn, prm, s));
-    for (uint64_t b = 0; b < count; b += kCnnBatch) {
-        const int c = (int)std::min<uint64_t>(kCnnBatch, count - b);
+    for (uint64_t b = 0; b < count; b += batch) {
+        const int c = (int)std::min<uint64_t>(batch, count - b);
         HIP_TRY(dk::cnn::forward(ctx->cnn, prm, x + b * n * n, c, r + b, s));
     }
     return DK_OK;
