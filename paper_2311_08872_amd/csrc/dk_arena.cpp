@@ -34,7 +34,8 @@ struct Carve {
 };
 
 // I_h rho0 (state type), I_h phi_j and the per-observable {scale, centre, psi} of level l into
-// the arena; the centring constants from a noise-free FP64 run in `tmp` (8 n^2 + 40 n_obs bytes).
+// the arena; the centring constants from the noise-free FP64 field formed in `tmp` (two fields and the
+// inner products: 16 n^2 + 8 n_obs (1 + kInnerParts) bytes).
 int arena_tables(const dk_problem* p, int l, void* rho0, double* phi, double* obs, void* tmp, hipStream_t s)
 {
     const int n = level_n(p, l), nobs = p->n_obs;
@@ -46,21 +47,17 @@ int arena_tables(const dk_problem* p, int l, void* rho0, double* phi, double* ob
     double centre[DK_MAX_OBS] = {0};
     bool any = false;
     for (int j = 0; j < nobs; ++j) any |= p->obs[j].centre != 0;
-    double unit[3 * DK_MAX_OBS], res[2 * DK_MAX_OBS], host_obs[3 * DK_MAX_OBS];
+    double host_obs[3 * DK_MAX_OBS];
     if (any) {
         double* r0 = (double*)tmp;
-        double* obs_unit = r0 + (size_t)n * n;
-        double* out = obs_unit + 3 * nobs;
+        double* r1 = r0 + (size_t)n * n;
+        double* out = r1 + (size_t)n * n;
+        double* fin = nullptr;
         HIP_TRY(dk::launch_field_eval(to_dev_on(p, p->rho0, n), p->box, n, r0, true, s));
-        for (int j = 0; j < nobs; ++j) { unit[3 * j] = 1.0; unit[3 * j + 1] = 0.0; unit[3 * j + 2] = 0.0; }
-        HIP_TRY(hipMemcpyAsync(obs_unit, unit, sizeof(double) * 3 * nobs, hipMemcpyHostToDevice, s));
-        dk::LevelArgs A{};
-        A.nf = n; A.level_id = l; A.count = 1; A.steps = (int)level_steps(p, steps0_of(p), l);
-        A.a = 0.5 * p->mu; A.h2f = h * h; A.rho0_f = r0; A.phi_f = phi; A.obs_f = obs_unit; A.n_obs = nobs; A.out = out;
-        HIP_TRY(dk::launch_level(dk::LevelKind{DK_PREC_F64, false, DK_FLUX_CENTRAL, false}, A, s));
-        HIP_TRY(hipMemcpyAsync(res, out, sizeof(double) * 2 * nobs, hipMemcpyDeviceToHost, s));
+        HIP_TRY(dk::launch_meanfield_stream(n, 0.5 * p->mu, (int)level_steps(p, steps0_of(p), l), r0, r1, &fin, s));
+        HIP_TRY(dk::launch_inner_products(fin, n, phi, nobs, h * h, out, s));
+        HIP_TRY(hipMemcpyAsync(centre, out, sizeof(double) * nobs, hipMemcpyDeviceToHost, s));
         HIP_TRY(hipStreamSynchronize(s));
-        for (int j = 0; j < nobs; ++j) centre[j] = res[2 * j];
     }
     for (int j = 0; j < nobs; ++j) {
         host_obs[3 * j + 0] = p->obs[j].scale_sqrtN ? std::sqrt(p->N) : 1.0;
@@ -103,7 +100,7 @@ int level_pair_arena(const dk_problem* p, int level, uint64_t first, uint64_t co
     void* rho0_c = pair ? C.take(esize * ncc) : nullptr;
     double* phi_c = pair ? (double*)C.take(8 * nobs * ncc) : nullptr;
     double* obs_c = pair ? (double*)C.take(8 * 3 * nobs) : nullptr;
-    void* tmp = C.take(8 * nn + 8 * 5 * (size_t)nobs);
+    void* tmp = C.take(16 * nn + 8 * (size_t)nobs * (1 + dk::kInnerParts));
     double* mom = (double*)C.take(8 * mom_stride * kGroup);
     if (!C.ok)
         return fail(DK_EINVAL, "level %d (%d x %d, %d observables) needs more than the %zu bytes of scratch of the "

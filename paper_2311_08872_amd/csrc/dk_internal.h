@@ -69,9 +69,12 @@ hipError_t launch_noise_dump(uint64_t seed, uint32_t tag, int level, int n, uint
                              hipStream_t s);
 hipError_t launch_gauss(const uint32_t* a, const uint32_t* b, uint64_t count, float* z0, float* z1, hipStream_t s);
 
-// Noise-free FP64 stepping for grids that do not fit on chip: one launch per step.
+// The noise-free scheme to step `steps` from the FP64 field in buf0 (n even, at most 4096; buf1: scratch of
+// the same size); *result is the buffer that holds the final field.
 hipError_t launch_meanfield_stream(int n, double a, int steps, double* buf0, double* buf1,
                                    double** result, hipStream_t s);
+// out[j] = h2 sum rho phi_j.  out: device [n_obs * (1 + kInnerParts)], partial sums behind the results.
+constexpr int kInnerParts = 64;
 hipError_t launch_inner_products(const double* rho, int n, const double* phi, int n_obs, double h2,
                                  double* out, hipStream_t s);
 

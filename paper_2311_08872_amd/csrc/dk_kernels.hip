@@ -1,7 +1,6 @@
 // dk_kernels.hip -- gfx950 kernels of the MLMC Dean--Kawasaki hot path: the resident level
 // kernel (grids up to 128 x 128; its building blocks and the scheme it implements are described
-// in dk_level.h), the ordered moment reduction, field evaluation, the noise dump and the FP64
-// noise-free stepping of large grids.
+// in dk_level.h), the ordered moment reduction, field evaluation and the noise dump.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -304,58 +303,6 @@ hipError_t launch_gauss(const uint32_t* a, const uint32_t* b, uint64_t count, fl
     const uint64_t blocks = (count + 255) / 256;
     if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
     hipLaunchKernelGGL(gauss_kernel, dim3((unsigned)blocks), dim3(256), 0, s, a, b, count, z0, z1);
-    return hipGetLastError();
-}
-
-// ---------------------------------------------------------------------------------------
-// Streaming noise-free FP64 step for large grids (one launch per step) and inner products.
-// ---------------------------------------------------------------------------------------
-__global__ void heat_step_kernel(const double* __restrict__ in, double* __restrict__ out, int n, double a)
-{
-    const int x = blockIdx.x * blockDim.x + threadIdx.x;
-    const int y = blockIdx.y;
-    if (x >= n) return;
-    const int xm = x == 0 ? n - 1 : x - 1, xp = x == n - 1 ? 0 : x + 1;
-    const int ym = y == 0 ? n - 1 : y - 1, yp = y == n - 1 ? 0 : y + 1;
-    const double c = in[(size_t)y * n + x];
-    const double lap = (in[(size_t)y * n + xm] + in[(size_t)y * n + xp]) + (in[(size_t)ym * n + x] + in[(size_t)yp * n + x]) - 4.0 * c;
-    out[(size_t)y * n + x] = c + a * lap;
-}
-
-hipError_t launch_meanfield_stream(int n, double a, int steps, double* buf0, double* buf1, double** result, hipStream_t s)
-{
-    double* in = buf0;
-    double* out = buf1;
-    const dim3 grid((n + 255) / 256, n);
-    for (int m = 0; m < steps; ++m) {
-        hipLaunchKernelGGL(heat_step_kernel, grid, dim3(256), 0, s, in, out, n, a);
-        double* t = in; in = out; out = t;
-    }
-    *result = in;
-    return hipGetLastError();
-}
-
-__global__ void inner_kernel(const double* __restrict__ rho, int n, const double* __restrict__ phi, double h2,
-                             double* __restrict__ out)
-{
-    const int j = blockIdx.x;
-    const double* ph = phi + (size_t)j * n * n;
-    double acc = 0.0;
-    for (int i = threadIdx.x; i < n * n; i += blockDim.x) acc = fma(rho[i], ph[i], acc);
-    __shared__ double sh[256];
-    sh[threadIdx.x] = acc;
-    __syncthreads();
-    for (int w = 128; w >= 1; w >>= 1) {
-        if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) out[j] = h2 * sh[0];
-}
-
-hipError_t launch_inner_products(const double* rho, int n, const double* phi, int n_obs, double h2, double* out,
-                                 hipStream_t s)
-{
-    hipLaunchKernelGGL(inner_kernel, dim3(n_obs), dim3(256), 0, s, rho, n, phi, h2, out);
     return hipGetLastError();
 }
 

@@ -440,47 +440,19 @@ int compute_centre(dk_context* ctx, const dk_problem* p, int level, LevelTables&
         T.have_centre = true;
         return DK_OK;
     }
-    if (dk::level_supported(n)) {
-        // FP64 rho0 for the noise-free resident kernel
-        DevBuf r0;
-        int rc = r0.ensure(sizeof(double) * n * n);
-        if (rc) return rc;
-        HIP_TRY(dk::launch_field_eval(to_dev_on(p, p->rho0, n), p->box, n, r0.p, true, s));
-        rc = ctx->per_sample.ensure(sizeof(double) * 2 * nobs);
-        if (rc) return rc;
-        std::vector<double> obs_host(3 * nobs);
-        for (int j = 0; j < nobs; ++j) { obs_host[3 * j] = 1.0; obs_host[3 * j + 1] = 0.0; obs_host[3 * j + 2] = 0.0; }
-        DevBuf obs_unit;
-        rc = obs_unit.ensure(sizeof(double) * 3 * nobs);
-        if (rc) return rc;
-        HIP_TRY(hipMemcpyAsync(obs_unit.p, obs_host.data(), sizeof(double) * 3 * nobs, hipMemcpyHostToDevice, s));
-        dk::LevelArgs A{};
-        A.nf = n; A.level_id = level; A.tag = 0; A.seed = 0; A.first = 0; A.count = 1; A.steps = (int)T.steps;
-        A.a = a; A.kf = 0; A.kc = 0; A.h2f = T.h * T.h; A.h2c = 0;
-        A.rho0_f = r0.p; A.rho0_c = nullptr; A.phi_f = (const double*)T.phi.p; A.phi_c = nullptr;
-        A.obs_f = (const double*)obs_unit.p; A.obs_c = nullptr; A.n_obs = nobs;
-        A.out = (double*)ctx->per_sample.p; A.field_f = rho_out; A.field_c = nullptr;
-        dk::LevelKind K{DK_PREC_F64, false, DK_FLUX_CENTRAL, false};
-        HIP_TRY(dk::launch_level(K, A, s));
-        std::vector<double> res(2 * nobs);
-        HIP_TRY(hipMemcpyAsync(res.data(), ctx->per_sample.p, sizeof(double) * 2 * nobs, hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipStreamSynchronize(s));
-        for (int j = 0; j < nobs; ++j) c[j] = res[2 * j];
-    } else {
-        int rc = ctx->mf0.ensure(sizeof(double) * n * n);
-        if (rc) return rc;
-        rc = ctx->mf1.ensure(sizeof(double) * n * n);
-        if (rc) return rc;
-        rc = ctx->scratch_c.ensure(sizeof(double) * nobs);
-        if (rc) return rc;
-        HIP_TRY(dk::launch_field_eval(to_dev_on(p, p->rho0, n), p->box, n, ctx->mf0.p, true, s));
-        double* res = nullptr;
-        HIP_TRY(dk::launch_meanfield_stream(n, a, (int)T.steps, (double*)ctx->mf0.p, (double*)ctx->mf1.p, &res, s));
-        HIP_TRY(dk::launch_inner_products(res, n, (const double*)T.phi.p, nobs, T.h * T.h, (double*)ctx->scratch_c.p, s));
-        HIP_TRY(hipMemcpyAsync(c.data(), ctx->scratch_c.p, sizeof(double) * nobs, hipMemcpyDeviceToHost, s));
-        if (rho_out) HIP_TRY(hipMemcpyAsync(rho_out, res, sizeof(double) * n * n, hipMemcpyDeviceToDevice, s));
-        HIP_TRY(hipStreamSynchronize(s));
-    }
+    int rc = ctx->mf0.ensure(sizeof(double) * n * n);
+    if (rc) return rc;
+    rc = ctx->mf1.ensure(sizeof(double) * n * n);
+    if (rc) return rc;
+    rc = ctx->scratch_c.ensure(sizeof(double) * nobs * (1 + dk::kInnerParts));
+    if (rc) return rc;
+    HIP_TRY(dk::launch_field_eval(to_dev_on(p, p->rho0, n), p->box, n, ctx->mf0.p, true, s));
+    double* res = nullptr;
+    HIP_TRY(dk::launch_meanfield_stream(n, a, (int)T.steps, (double*)ctx->mf0.p, (double*)ctx->mf1.p, &res, s));
+    HIP_TRY(dk::launch_inner_products(res, n, (const double*)T.phi.p, nobs, T.h * T.h, (double*)ctx->scratch_c.p, s));
+    HIP_TRY(hipMemcpyAsync(c.data(), ctx->scratch_c.p, sizeof(double) * nobs, hipMemcpyDeviceToHost, s));
+    if (rho_out) HIP_TRY(hipMemcpyAsync(rho_out, res, sizeof(double) * n * n, hipMemcpyDeviceToDevice, s));
+    HIP_TRY(hipStreamSynchronize(s));
     T.centre = c;
     T.have_centre = true;
     return DK_OK;

@@ -1,0 +1,241 @@
+// dk_meanfield.hip -- the noise-free scheme to its final time (the discrete mean field of Sec. 3,
+// which centres the observables) and its inner products with the test functions, in FP64.
+//
+// rho^M = (I + (mu/2) Lap_h)^M rho^0 is diagonal in the discrete Fourier basis, with the factor
+// g^M = (1 - 2 mu (sin^2(pi kx/n) + sin^2(pi ky/n)))^M (Appendix A, operator A_h), so M steps cost the
+// way into that basis and back whatever M is.  The basis used is the real one of the Hartley
+// transform, cas t = cos t + sin t: cas(2 pi k x/n) is an eigenvector of the periodic second
+// difference with the eigenvalue of cos and sin, the matrix C[k][x] = cas(2 pi k x/n) is symmetric and
+// C C = n I, so rho^M = n^-2 C (g^M .* (C rho^0 C)) C: four real n x n products on the FP64 matrix
+// cores (v_mfma_f64_16x16x4_f64).  One pass forms C X^T, so two passes are C X C and the rows read are
+// always contiguous; C itself is never stored, its entries are a table of n values in LDS indexed by
+// k x mod n.
+//
+// Bound by the FP64 matrix rate for n >= 1024 and by the latency of four dependent passes below.
+// One launch per step took 118 ms at 512 x 512 with 26624 steps (4.7 us a launch); now four of 18 us (145 us a call).
+// g^M comes from exp(M log1p(-lambda)), whose error does not grow with M, so the result is as near the
+// exact field as stepping is.
+#include <hip/hip_runtime.h>
+#include <math.h>
+#include <stdint.h>
+
+#include "dk_internal.h"
+
+namespace dk {
+
+namespace {
+
+typedef double doublex2 __attribute__((ext_vector_type(2)));
+typedef double doublex4 __attribute__((ext_vector_type(4)));
+
+constexpr int kOneBlock = 64;      // grids up to this size run in one block, the field in LDS
+
+__device__ __forceinline__ void cas_table(double* tab, int n)
+{
+    for (int m = threadIdx.x; m < n; m += blockDim.x) {
+        double s, c;
+        sincospi(2.0 * m / n, &s, &c);
+        tab[m] = c + s;
+    }
+}
+
+// g^M of mode (kx, ky), a = mu / 2.  1 - g = 4 a (sin^2 + sin^2) lies in [0, 2]; beyond 1 (mu > 1/4) the
+// factor is negative and its size is 1 - (2 - (1 - g)).
+__device__ __forceinline__ double mode_power(int kx, int ky, int n, double a, int M)
+{
+    const double sx = sinpi((double)kx / n), sy = sinpi((double)ky / n);
+    const double lam = 4.0 * a * (sx * sx + sy * sy);
+    if (lam <= 1.0) return exp(M * log1p(-lam));
+    const double p = exp(M * log1p(lam - 2.0));
+    return (M & 1) ? -p : p;
+}
+
+// Tile rows k0.., columns y0.. of C X^T: sum over x of cas(k x) X[y][x].  The order of the 16 x of one
+// product group over lanes and products is the same for both operands: lane group q takes x0 + 4 q + j.
+// G groups are loaded ahead of the G being multiplied (the rows come from L2 with one wavefront per
+// SIMD).  Returns D[row 4 r + q][column lane & 15].
+template <int G>
+__device__ __forceinline__ doublex4 cas_tile(const double* X, int pitch, int n, const double* tab, int k0, int y0, int lane)
+{
+    const int i = lane & 15, q = lane >> 4;
+    const int k = min(k0 + i, n - 1), y = min(y0 + i, n - 1);
+    const double* row = X + (size_t)y * pitch;
+    const int step = (16 * k) % n;
+    int idx = (4 * q * k) % n;
+    doublex4 acc = {0.0, 0.0, 0.0, 0.0};
+    doublex2 nxt[G][2];
+    auto load = [&](int x0) {
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {                // beyond the row: zeros (n is even)
+                const int x = x0 + 16 * g + 4 * q + 2 * h;
+                nxt[g][h] = doublex2{0.0, 0.0};
+                if (x < n) nxt[g][h] = *(const doublex2*)(row + x);
+            }
+    };
+    load(0);
+    for (int x0 = 0; x0 < n; x0 += 16 * G) {
+        doublex2 cur[G][2];
+#pragma unroll
+        for (int g = 0; g < G; ++g) { cur[g][0] = nxt[g][0]; cur[g][1] = nxt[g][1]; }
+        load(x0 + 16 * G);
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            int id = idx;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(tab[id], cur[g][j >> 1][j & 1], acc, 0, 0, 0);
+                id += k;
+                id -= id >= n ? n : 0;
+            }
+            idx += step;
+            idx -= idx >= n ? n : 0;
+        }
+    }
+    return acc;
+}
+
+// Grids up to 64 x 64: all four passes in one block, a wavefront per 16 x 16 tile.
+__global__ void __launch_bounds__(1024) meanfield_block_kernel(double* __restrict__ rho, int n, double a, int steps)
+{
+    constexpr int PMAX = kOneBlock + 2;
+    __shared__ __align__(16) double fld[2][kOneBlock * PMAX];
+    __shared__ double tab[kOneBlock];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int P = n + 2;                                  // rows start two banks apart
+    const int T = (n + 15) / 16;
+    const int k0 = 16 * (wave / T), y0 = 16 * (wave % T);
+    cas_table(tab, n);
+    for (int e = threadIdx.x; e < n * n; e += blockDim.x) fld[0][(e / n) * P + e % n] = rho[e];
+    __syncthreads();
+#pragma unroll 1
+    for (int pass = 0; pass < 4; ++pass) {
+        const doublex4 d = cas_tile<1>(fld[pass & 1], P, n, tab, k0, y0, lane);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int k = k0 + 4 * r + (lane >> 4), y = y0 + (lane & 15);
+            if (k >= n || y >= n) continue;
+            const double v = pass == 1 ? d[r] * (mode_power(y, k, n, a, steps) / ((double)n * n)) : d[r];
+            fld[(pass + 1) & 1][k * P + y] = v;
+        }
+        __syncthreads();
+    }
+    for (int e = threadIdx.x; e < n * n; e += blockDim.x) rho[e] = fld[0][(e / n) * P + e % n];
+}
+
+// Larger grids: one pass per launch.  The four wavefronts of a block share their columns y, so the rows
+// of X are read through one L1.
+__global__ void __launch_bounds__(256) cas_pass_kernel(const double* __restrict__ X, double* __restrict__ out, int n, double a,
+                                                       int steps /* > 0: multiply by g^steps / n^2 */)
+{
+    extern __shared__ double tab[];
+    cas_table(tab, n);
+    __syncthreads();
+    const int lane = threadIdx.x & 63;
+    const int T = (n + 15) / 16, TK = (T + 3) / 4;
+    const int kt = 4 * (blockIdx.x % TK) + (threadIdx.x >> 6);
+    if (kt >= T) return;
+    const int k0 = 16 * kt, y0 = 16 * (blockIdx.x / TK);
+    const doublex4 d = cas_tile<4>(X, n, n, tab, k0, y0, lane);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int k = k0 + 4 * r + (lane >> 4), y = y0 + (lane & 15);
+        if (k < n && y < n)
+            out[(size_t)k * n + y] = steps > 0 ? d[r] * (mode_power(y, k, n, a, steps) / ((double)n * n)) : d[r];
+    }
+}
+
+// One step, for the few steps that cost less than four passes
+__global__ void heat_step_kernel(const double* __restrict__ in, double* __restrict__ out, int n, double a)
+{
+    const int x = blockIdx.x * blockDim.x + threadIdx.x;
+    const int y = blockIdx.y;
+    if (x >= n) return;
+    const int xm = x == 0 ? n - 1 : x - 1, xp = x == n - 1 ? 0 : x + 1;
+    const int ym = y == 0 ? n - 1 : y - 1, yp = y == n - 1 ? 0 : y + 1;
+    const double c = in[(size_t)y * n + x];
+    const double lap = (in[(size_t)y * n + xm] + in[(size_t)y * n + xp]) + (in[(size_t)ym * n + x] + in[(size_t)yp * n + x]) - 4.0 * c;
+    out[(size_t)y * n + x] = c + a * lap;
+}
+
+__device__ __forceinline__ double block_sum(double v, double* sh)
+{
+    sh[threadIdx.x] = v;
+    __syncthreads();
+    for (int w = 128; w >= 1; w >>= 1) {
+        if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
+        __syncthreads();
+    }
+    return sh[0];
+}
+
+// part p of the inner product with observable j (grid: parts x observables); one part: the result itself
+__global__ void __launch_bounds__(256) inner_kernel(const double* __restrict__ rho, int nn, const double* __restrict__ phi,
+                                                    double h2, double* __restrict__ out)
+{
+    __shared__ double sh[256];
+    const int j = blockIdx.y, parts = gridDim.x;
+    const double* ph = phi + (size_t)j * nn;
+    double acc = 0.0;
+#pragma unroll 4
+    for (int i = blockIdx.x * 256 + threadIdx.x; i < nn; i += 256 * parts) acc = fma(rho[i], ph[i], acc);
+    const double s = block_sum(acc, sh);
+    if (threadIdx.x == 0) {
+        if (parts == 1) out[j] = h2 * s;
+        else out[gridDim.y + j * parts + blockIdx.x] = s;
+    }
+}
+
+__global__ void __launch_bounds__(256) inner_finish_kernel(int parts, double h2, double* __restrict__ out)
+{
+    __shared__ double sh[256];
+    const int j = blockIdx.x, nobs = gridDim.x;
+    const double s = block_sum((int)threadIdx.x < parts ? out[nobs + j * parts + threadIdx.x] : 0.0, sh);
+    if (threadIdx.x == 0) out[j] = h2 * s;
+}
+
+}  // namespace
+
+hipError_t launch_meanfield_stream(int n, double a, int steps, double* buf0, double* buf1, double** result, hipStream_t s)
+{
+    if (n < 2 || (n & 1) || n > 4096 || steps < 0) return hipErrorInvalidValue;
+    // Four passes against one launch per step, microseconds measured on MI355X: one block 8 (16^2) .. 28
+    // (64^2); four launches of 6 (128^2), 18 (512^2), 70 (1024^2), 3600 (4096^2); a step 2.4 (to 256^2), 4.6
+    // (512^2), 8 (1024^2), 60 (4096^2)
+    const double passes = n <= kOneBlock ? 2.0 + 0.4 * n : 24.0 + 2.2e-7 * (double)n * n * n;
+    const double stepping = steps * (2.4 + 3.5e-6 * (double)n * n);
+    *result = buf0;
+    if (stepping <= passes) {
+        double *in = buf0, *out = buf1;
+        const dim3 grid((n + 255) / 256, n);
+        for (int m = 0; m < steps; ++m) {
+            hipLaunchKernelGGL(heat_step_kernel, grid, dim3(256), 0, s, in, out, n, a);
+            double* t = in; in = out; out = t;
+        }
+        *result = in;
+        return hipGetLastError();
+    }
+    const int T = (n + 15) / 16;
+    if (n <= kOneBlock) {
+        hipLaunchKernelGGL(meanfield_block_kernel, dim3(1), dim3(64 * T * T), 0, s, buf0, n, a, steps);
+        return hipGetLastError();
+    }
+    const dim3 grid((unsigned)(T * ((T + 3) / 4)));
+    for (int pass = 0; pass < 4; ++pass)
+        hipLaunchKernelGGL(cas_pass_kernel, grid, dim3(256), sizeof(double) * n, s, pass & 1 ? buf1 : buf0, pass & 1 ? buf0 : buf1,
+                           n, a, pass == 1 ? steps : 0);
+    return hipGetLastError();
+}
+
+hipError_t launch_inner_products(const double* rho, int n, const double* phi, int n_obs, double h2, double* out,
+                                 hipStream_t s)
+{
+    // above 128 x 128 one block per observable would read its megabytes alone (320 us at 512 x 512)
+    const int parts = n <= 128 ? 1 : kInnerParts;
+    hipLaunchKernelGGL(inner_kernel, dim3(parts, n_obs), dim3(256), 0, s, rho, n * n, phi, h2, out);
+    if (parts > 1) hipLaunchKernelGGL(inner_finish_kernel, dim3(n_obs), dim3(256), 0, s, parts, h2, out);
+    return hipGetLastError();
+}
+
+}  // namespace dk
