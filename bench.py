@@ -724,7 +724,9 @@ def bench_config5(args):
     for n, batch in (() if args.depth_only else ((256, 4096), (1024, 256))):
         x = torch.ones((batch, n, n), dtype=torch.float32, device="cuda")
         dk.heat_steps(x, 4, p.mu, ctx=ctx)
-        dt = dk.heat_steps(x, 64, p.mu, ctx=ctx) / 1e3      # kernel time of the 64 steps
+        # kernel time of the 64 steps; the GB/s are those of a pass per step (8 B a cell and step), of which
+        # the kernel needs one in 64 (256^2) or one in 16 (1024^2)
+        dt = dk.heat_steps(x, 64, p.mu, ctx=ctx) / 1e3
         heat[f"{n}"] = {"batch": batch, "GB_per_s": 8.0 * batch * n * n * 64 / dt / 1e9,
                         "frac_of_8TBps": 8.0 * batch * n * n * 64 / dt / 8e12}
         del x
@@ -742,8 +744,8 @@ def bench_counters(args):
     """One launch of each hot kernel at the size it runs in production, for HBM byte counters
     (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE / request sizes, one pass per counter set):
       1. a 256 MiB device copy, twice (the calibration: 256 MiB read and 256 MiB written per launch);
-      2. the noise-free FP32 stencil (heat_f32_kernel), 8 steps at 256^2 x 4096 and at 1024^2 x 256
-         (one launch per step: 1 GiB read and 1 GiB written algorithmically);
+      2. the noise-free FP32 stencil (heat_kernel), 8 steps at 256^2 x 4096 (one launch, 1 GiB read and
+         written) and at 1024^2 x 256 (two passes over 256^2 windows);
       3. the streaming kernel on 4 pairs and 4 single paths of the 1024^2 / 512^2 pair over 128 fine
          steps at each depth D = 1, 2, 4, 8;
       4. the resident 128^2 pair kernel: one launch of 14024 pairs (the production chunk of the

@@ -442,7 +442,8 @@ int dk_context_set_launch_cap(dk_context* ctx, double cells);
 /* Noise-free scheme (rho <- rho + (mu/2) Lap_h rho, the discrete mean-field dynamics of Sec. 3)
  * for `steps` steps on a batch of FP32 fields rho (DEVICE [batch][n][n], updated in place;
  * work: DEVICE scratch of the same size).  n a multiple of 4.  kernel_ms (optional) receives
- * the event time of the steps.  Memory-bound: 8 B of HBM traffic per cell update. */
+ * the event time of the steps.  Fields up to 256 x 256 are read and written once for all steps
+ * (work is not used); larger ones once per up to 16 steps. */
 int dk_heat_steps(dk_context* ctx, int32_t n, int32_t batch, int32_t steps, double mu, float* rho, float* work,
                   double* kernel_ms, void* stream);
 

@@ -324,35 +324,6 @@ int dk_shape_rows(int32_t n, int32_t variant) { return dk::shape_rows(n, variant
 
 int dk_shape_spw(int32_t n, int32_t variant) { return dk::shape_spw(n, variant); }
 
-int dk_heat_steps(dk_context* ctx, int32_t n, int32_t batch, int32_t steps, double mu, float* rho, float* work,
-                  double* kernel_ms, void* stream)
-{
-    if (!ctx || !rho || !work) return fail(DK_EINVAL, "NULL argument");
-    if (n < 4 || n % 4 || batch < 1 || steps < 0) return fail(DK_EINVAL, "n must be a multiple of 4, batch >= 1");
-    if (!(mu > 0) || mu > 0.5) return fail(DK_EINVAL, "mu outside (0, 1/2]");
-    HIP_TRY(hipSetDevice(ctx->device));
-    hipStream_t s = (hipStream_t)stream;
-    hipEvent_t e0, e1;
-    HIP_TRY(hipEventCreate(&e0));
-    HIP_TRY(hipEventCreate(&e1));
-    HIP_TRY(hipEventRecord(e0, s));
-    float* a = rho;
-    float* b = work;
-    for (int m = 0; m < steps; ++m) {
-        HIP_TRY(dk::launch_heat_f32(a, b, n, batch, (float)(0.5 * mu), s));
-        std::swap(a, b);
-    }
-    HIP_TRY(hipEventRecord(e1, s));
-    if (a != rho) HIP_TRY(hipMemcpyAsync(rho, a, sizeof(float) * (size_t)n * n * batch, hipMemcpyDeviceToDevice, s));
-    HIP_TRY(hipEventSynchronize(e1));
-    float ms = 0.f;
-    HIP_TRY(hipEventElapsedTime(&ms, e0, e1));
-    if (kernel_ms) *kernel_ms = ms;
-    (void)hipEventDestroy(e0);
-    (void)hipEventDestroy(e1);
-    return DK_OK;
-}
-
 int dk_context_set_launch_cap(dk_context* ctx, double cells)
 {
     if (!ctx) return fail(DK_EINVAL, "context is NULL");

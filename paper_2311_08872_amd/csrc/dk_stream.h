@@ -28,7 +28,6 @@ struct StreamArgs {
     float *rhoc_out, *cmpc_out;
 };
 bool stream_supported(int nf);
-hipError_t launch_heat_f32(const float* in, float* out, int n, int batch, float a, hipStream_t s);
 bool stream_depth_supported(int depth);
 hipError_t launch_stream_step(const StreamArgs& A, bool pair, int flux, int depth, hipStream_t s);
 hipError_t launch_stream_coarse(int nc, int count, float a, float kc, int flux, const float* rho_in, const float* cmp_in,

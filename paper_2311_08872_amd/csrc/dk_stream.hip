@@ -481,57 +481,6 @@ __global__ void zero_slot_kernel(double* out, int count, int n_obs, int slot)
     out[(size_t)i * 2 + slot] = 0.0;
 }
 
-// Noise-free FP32 step of a batch of fields (the scheme without noise, i.e. the discrete mean
-// field of many initial data at once).  A thread owns 4 consecutive columns and marches down a
-// strip of HRY rows, keeping the rows above, at and below in registers, so every row is read
-// from memory once per strip plus the two halo rows (18 reads per 16 rows) instead of once per
-// neighbouring row: consecutive blocks are spread over the XCDs, whose L2s do not share lines,
-// so re-reads of a neighbour's rows would otherwise come from HBM.  The two outer neighbours of
-// the 4 columns are scalar loads that hit the lines of the adjacent threads.
-constexpr int HRY = 16;
-
-__global__ void __launch_bounds__(256) heat_f32_kernel(const float* __restrict__ in, float* __restrict__ out, int n,
-                                                       size_t total, float a)
-{
-    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= total) return;
-    const int q = n / 4;
-    const int strips = (n + HRY - 1) / HRY;
-    const int x0 = (int)(i % q) * 4;
-    const size_t rest = i / q;
-    const int strip = (int)(rest % strips);
-    const size_t b = rest / strips;
-    const size_t nn = (size_t)n * n;
-    const float* f = in + b * nn;
-    float* g = out + b * nn;
-    const int y0 = strip * HRY, y1 = y0 + HRY < n ? y0 + HRY : n;
-    const int xl = x0 == 0 ? n - 1 : x0 - 1, xr = x0 + 4 == n ? 0 : x0 + 4;
-    float4 u = *(const float4*)(f + (size_t)(y0 == 0 ? n - 1 : y0 - 1) * n + x0);
-    float4 c = *(const float4*)(f + (size_t)y0 * n + x0);
-#pragma unroll 4
-    for (int y = y0; y < y1; ++y) {
-        const int yp = y == n - 1 ? 0 : y + 1;
-        const float4 d = *(const float4*)(f + (size_t)yp * n + x0);
-        const float l = f[(size_t)y * n + xl];
-        const float rr = f[(size_t)y * n + xr];
-        float4 o;
-        o.x = c.x + a * fmaf(-4.0f, c.x, (l + c.y) + (u.x + d.x));
-        o.y = c.y + a * fmaf(-4.0f, c.y, (c.x + c.z) + (u.y + d.y));
-        o.z = c.z + a * fmaf(-4.0f, c.z, (c.y + c.w) + (u.z + d.z));
-        o.w = c.w + a * fmaf(-4.0f, c.w, (c.z + rr) + (u.w + d.w));
-        *(float4*)(g + (size_t)y * n + x0) = o;
-        u = c;
-        c = d;
-    }
-}
-
-hipError_t launch_heat_f32(const float* in, float* out, int n, int batch, float a, hipStream_t s)
-{
-    const size_t total = (size_t)(n / 4) * ((n + HRY - 1) / HRY) * batch;
-    hipLaunchKernelGGL(heat_f32_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, in, out, n, total, a);
-    return hipGetLastError();
-}
-
 bool stream_supported(int nf) { return nf >= 64 && nf % TT == 0; }
 
 template <int FLUX, bool PAIR>
