@@ -37,8 +37,8 @@ struct LevelKind {
     int precision;          // DK_PREC_*
     bool pair;              // coupled fine/coarse pair
     int flux;               // DK_FLUX_*
-    bool noise;             // false: noise-free mean-field run
-    int shape = 0;          // tile-shape variant (FP32 noisy kernels; see shape_rows)
+    bool noise;             // always true: the noise-free field has its own launch (launch_meanfield_stream)
+    int shape = 0;          // tile-shape variant (see shape_rows)
 };
 
 // Returns hipSuccess, or hipErrorInvalidValue when no kernel exists for the size.

@@ -16,22 +16,21 @@ namespace dk {
 // ---------------------------------------------------------------------------------------
 // The resident level kernel: one block-iteration per block.
 // ---------------------------------------------------------------------------------------
-template <typename Real, int NF, int R, int C, bool PAIR, int FLUX, bool NOISE, int SPW>
+template <typename Real, int NF, int R, int C, bool PAIR, int FLUX, int SPW>
 __global__ void __launch_bounds__(SPW * (NF / C) * (NF / R))
 level_kernel(const LevelArgs A)
 {
-    constexpr int TS = (NF / C) * (NF / R);
-    __shared__ Real halo[SPW * halo_elems<NF, R, PAIR>()];
-    __shared__ double red[(SPW * TS + 63) / 64];
-    level_body<Real, NF, R, C, PAIR, FLUX, NOISE, SPW>(A, (uint64_t)blockIdx.x * SPW, halo, red, (int)threadIdx.x);
+    __shared__ __align__(16) Real halo[SPW * halo_elems<Real, NF, R, PAIR, SPW>()];
+    level_body<Real, NF, R, C, PAIR, FLUX, SPW>(A, (uint64_t)blockIdx.x * SPW, halo, (int)threadIdx.x);
 }
 
 // ---------------------------------------------------------------------------------------
 // Tile shapes.  A lane owns C = 2 columns and R rows; a sample uses (NF/2) x (NF/R) lanes and a
 // block holds SPW samples (about 256 lanes, or four times as many samples in 1024-lane blocks).
-// Several (R, SPW) per grid size are compiled for the FP32 noisy kernels; the host picks one by
-// timing them (autotuning).  The other variants (FP64 state, noise-free mean field) use the
-// first shape.
+// Several (R, SPW) per grid size are compiled; the host picks one by the size of the batch, or by
+// timing them for large jobs (choose_shape).  FP64 states have the shapes of at most 8 rows and 256
+// lanes per block's worth of samples (16 rows at 128 x 128); the others stand for their shape 0.  One-row
+// shapes are for single paths (a pair's coarse cell needs two rows): pairs run them with two.
 // ---------------------------------------------------------------------------------------
 // rows per lane of shape variant v for grid size nf (0 = no such variant); variant 0 is the
 // default (8 rows: the fastest measured on MI355X for every grid size of the hierarchy)
@@ -39,10 +38,10 @@ int shape_rows(int nf, int v)
 {
     switch (nf) {
         case 4: return v == 0 ? 4 : 0;
-        case 8: { const int r[] = {8, 2, 4, 8}; return v < 4 ? r[v] : 0; }
-        case 16: { const int r[] = {8, 4, 2, 8}; return v < 4 ? r[v] : 0; }
-        case 32: { const int r[] = {8, 4, 16, 8}; return v < 4 ? r[v] : 0; }
-        case 64: { const int r[] = {8, 16, 8}; return v < 3 ? r[v] : 0; }
+        case 8: { const int r[] = {8, 2, 4, 8, 1}; return v < 5 ? r[v] : 0; }
+        case 16: { const int r[] = {8, 4, 2, 8, 1}; return v < 5 ? r[v] : 0; }
+        case 32: { const int r[] = {8, 4, 16, 8, 2}; return v < 5 ? r[v] : 0; }
+        case 64: { const int r[] = {8, 16, 8, 4, 2}; return v < 5 ? r[v] : 0; }
         case 128: { const int r[] = {8, 16}; return v < 2 ? r[v] : 0; }
         default: return 0;
     }
@@ -60,74 +59,69 @@ int shape_spw(int nf, int v)
     return wide ? 4 * base : base;
 }
 
-template <typename Real, int NF, int R, bool PAIR, int FLUX, bool NOISE, int X = 1>
+template <typename Real, int NF, int R, bool PAIR, int FLUX, int X = 1>
 static hipError_t launch_R(const LevelArgs& A, hipStream_t s)
 {
     using S = ShapeOf<NF, R, X>;
     const uint64_t blocks = (A.count + S::SPW - 1) / S::SPW;
     if (blocks == 0) return hipSuccess;
     if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((level_kernel<Real, NF, R, S::C, PAIR, FLUX, NOISE, S::SPW>), dim3((unsigned)blocks),
-                       dim3(S::SPW * S::TS), 0, s, A);
+    hipLaunchKernelGGL((level_kernel<Real, NF, R, S::C, PAIR, FLUX, S::SPW>), dim3((unsigned)blocks), dim3(S::SPW * S::TS), 0, s,
+                       A);
     return hipGetLastError();
 }
 
-template <typename Real, int NF, bool PAIR, int FLUX, bool NOISE>
+template <typename Real, int NF, bool PAIR, int FLUX>
 static hipError_t launch_variants(const LevelArgs& A, int v, hipStream_t s)
 {
-    constexpr bool TUNED = std::is_same<Real, float>::value && NOISE;
-    if (!TUNED) v = 0;
+    constexpr bool F32 = std::is_same<Real, float>::value;
     if constexpr (NF == 4) {
         // 4 x 4 (the level 0 of the paper's own hierarchy): 2 lanes per sample, 4 rows each
-        return launch_R<Real, 4, 4, PAIR, FLUX, NOISE>(A, s);
+        return launch_R<Real, 4, 4, PAIR, FLUX>(A, s);
     } else if constexpr (NF == 8) {
-        if constexpr (TUNED) {
-            if (v == 1) return launch_R<Real, 8, 2, PAIR, FLUX, NOISE>(A, s);
-            if (v == 2) return launch_R<Real, 8, 4, PAIR, FLUX, NOISE>(A, s);
-            if (v == 3) return launch_R<Real, 8, 8, PAIR, FLUX, NOISE, 4>(A, s);
-        }
-        return launch_R<Real, 8, 8, PAIR, FLUX, NOISE>(A, s);
+        if constexpr (!PAIR) if (v == 4) return launch_R<Real, 8, 1, PAIR, FLUX>(A, s);
+        if (v == 1 || v == 4) return launch_R<Real, 8, 2, PAIR, FLUX>(A, s);
+        if (v == 2) return launch_R<Real, 8, 4, PAIR, FLUX>(A, s);
+        if constexpr (F32) if (v == 3) return launch_R<Real, 8, 8, PAIR, FLUX, 4>(A, s);
+        return launch_R<Real, 8, 8, PAIR, FLUX>(A, s);
     } else if constexpr (NF == 16) {
-        if constexpr (TUNED) {
-            if (v == 1) return launch_R<Real, 16, 4, PAIR, FLUX, NOISE>(A, s);
-            if (v == 2) return launch_R<Real, 16, 2, PAIR, FLUX, NOISE>(A, s);
-            if (v == 3) return launch_R<Real, 16, 8, PAIR, FLUX, NOISE, 4>(A, s);
-        }
-        return launch_R<Real, 16, 8, PAIR, FLUX, NOISE>(A, s);
+        if (v == 1) return launch_R<Real, 16, 4, PAIR, FLUX>(A, s);
+        if constexpr (!PAIR) if (v == 4) return launch_R<Real, 16, 1, PAIR, FLUX>(A, s);
+        if (v == 2 || v == 4) return launch_R<Real, 16, 2, PAIR, FLUX>(A, s);
+        if constexpr (F32) if (v == 3) return launch_R<Real, 16, 8, PAIR, FLUX, 4>(A, s);
+        return launch_R<Real, 16, 8, PAIR, FLUX>(A, s);
     } else if constexpr (NF == 32) {
-        if constexpr (TUNED) {
-            if (v == 1) return launch_R<Real, 32, 4, PAIR, FLUX, NOISE>(A, s);
-            if (v == 2) return launch_R<Real, 32, 16, PAIR, FLUX, NOISE>(A, s);
-            if (v == 3) return launch_R<Real, 32, 8, PAIR, FLUX, NOISE, 4>(A, s);
+        if (v == 1) return launch_R<Real, 32, 4, PAIR, FLUX>(A, s);
+        if (v == 4) return launch_R<Real, 32, 2, PAIR, FLUX>(A, s);
+        if constexpr (F32) {
+            if (v == 2) return launch_R<Real, 32, 16, PAIR, FLUX>(A, s);
+            if (v == 3) return launch_R<Real, 32, 8, PAIR, FLUX, 4>(A, s);
         }
-        return launch_R<Real, 32, 8, PAIR, FLUX, NOISE>(A, s);
+        return launch_R<Real, 32, 8, PAIR, FLUX>(A, s);
     } else if constexpr (NF == 64) {
-        if constexpr (TUNED) {
-            if (v == 1) return launch_R<Real, 64, 16, PAIR, FLUX, NOISE>(A, s);
-            if (v == 2) return launch_R<Real, 64, 8, PAIR, FLUX, NOISE, 4>(A, s);
+        if (v == 3) return launch_R<Real, 64, 4, PAIR, FLUX>(A, s);
+        if (v == 4) return launch_R<Real, 64, 2, PAIR, FLUX>(A, s);
+        if constexpr (F32) {
+            if (v == 1) return launch_R<Real, 64, 16, PAIR, FLUX>(A, s);
+            if (v == 2) return launch_R<Real, 64, 8, PAIR, FLUX, 4>(A, s);
         }
-        return launch_R<Real, 64, 8, PAIR, FLUX, NOISE>(A, s);
+        return launch_R<Real, 64, 8, PAIR, FLUX>(A, s);
     } else {
-        if constexpr (TUNED) {
-            if (v == 1) return launch_R<Real, 128, 16, PAIR, FLUX, NOISE>(A, s);
-            return launch_R<Real, 128, 8, PAIR, FLUX, NOISE>(A, s);
-        } else {
-            // FP64 states: 8-row groups would need more LDS than a CU has
-            return launch_R<Real, 128, 16, PAIR, FLUX, NOISE>(A, s);
-        }
+        if (v == 1) return launch_R<Real, 128, 16, PAIR, FLUX>(A, s);
+        return launch_R<Real, 128, 8, PAIR, FLUX>(A, s);
     }
 }
 
-template <typename Real, bool PAIR, int FLUX, bool NOISE>
+template <typename Real, bool PAIR, int FLUX>
 static hipError_t launch_nf(const LevelArgs& A, int v, hipStream_t s)
 {
     switch (A.nf) {
-        case 4: return launch_variants<Real, 4, PAIR, FLUX, NOISE>(A, v, s);
-        case 8: return launch_variants<Real, 8, PAIR, FLUX, NOISE>(A, v, s);
-        case 16: return launch_variants<Real, 16, PAIR, FLUX, NOISE>(A, v, s);
-        case 32: return launch_variants<Real, 32, PAIR, FLUX, NOISE>(A, v, s);
-        case 64: return launch_variants<Real, 64, PAIR, FLUX, NOISE>(A, v, s);
-        case 128: return launch_variants<Real, 128, PAIR, FLUX, NOISE>(A, v, s);
+        case 4: return launch_variants<Real, 4, PAIR, FLUX>(A, v, s);
+        case 8: return launch_variants<Real, 8, PAIR, FLUX>(A, v, s);
+        case 16: return launch_variants<Real, 16, PAIR, FLUX>(A, v, s);
+        case 32: return launch_variants<Real, 32, PAIR, FLUX>(A, v, s);
+        case 64: return launch_variants<Real, 64, PAIR, FLUX>(A, v, s);
+        case 128: return launch_variants<Real, 128, PAIR, FLUX>(A, v, s);
         default: return hipErrorInvalidValue;
     }
 }
@@ -136,81 +130,68 @@ bool level_supported(int nf) { return nf == 4 || nf == 8 || nf == 16 || nf == 32
 
 hipError_t launch_level(const LevelKind& k, const LevelArgs& A, hipStream_t s)
 {
+    if (!k.noise) return hipErrorInvalidValue;   // noise-free runs: dk_meanfield.hip
     const int v = k.shape;
-    if (!k.noise) {
-        // noise-free FP64 mean field, single path
-        return launch_nf<double, false, DK_FLUX_CENTRAL, false>(A, 0, s);
-    }
     const bool f64 = k.precision == DK_PREC_F64;
     const bool stag = k.flux == DK_FLUX_STAGGERED;
-    if (!f64 && !stag) return k.pair ? launch_nf<float, true, DK_FLUX_CENTRAL, true>(A, v, s)
-                                     : launch_nf<float, false, DK_FLUX_CENTRAL, true>(A, v, s);
-    if (!f64 && stag) return k.pair ? launch_nf<float, true, DK_FLUX_STAGGERED, true>(A, v, s)
-                                    : launch_nf<float, false, DK_FLUX_STAGGERED, true>(A, v, s);
-    if (f64 && !stag) return k.pair ? launch_nf<double, true, DK_FLUX_CENTRAL, true>(A, 0, s)
-                                    : launch_nf<double, false, DK_FLUX_CENTRAL, true>(A, 0, s);
-    return k.pair ? launch_nf<double, true, DK_FLUX_STAGGERED, true>(A, 0, s)
-                  : launch_nf<double, false, DK_FLUX_STAGGERED, true>(A, 0, s);
+    if (!f64 && !stag) return k.pair ? launch_nf<float, true, DK_FLUX_CENTRAL>(A, v, s)
+                                     : launch_nf<float, false, DK_FLUX_CENTRAL>(A, v, s);
+    if (!f64 && stag) return k.pair ? launch_nf<float, true, DK_FLUX_STAGGERED>(A, v, s)
+                                    : launch_nf<float, false, DK_FLUX_STAGGERED>(A, v, s);
+    if (f64 && !stag) return k.pair ? launch_nf<double, true, DK_FLUX_CENTRAL>(A, v, s)
+                                    : launch_nf<double, false, DK_FLUX_CENTRAL>(A, v, s);
+    return k.pair ? launch_nf<double, true, DK_FLUX_STAGGERED>(A, v, s)
+                  : launch_nf<double, false, DK_FLUX_STAGGERED>(A, v, s);
 }
 
 // ---------------------------------------------------------------------------------------
-// Ordered compensated moment sums.  One block per observable; thread k reduces a contiguous
-// slice of samples in index order with Neumaier's compensated summation, then the slices
-// are merged in a fixed pairwise tree.  The result depends only on (count, data).
+// Ordered compensated moment sums.  One block per observable and moment; thread t sums the samples
+// t, t + T, t + 2T, .. with compensated summation, then the threads' sums are merged in a fixed pairwise
+// tree.  The result depends only on (count, data).  One block for all six moments of an observable ran
+// at the FP64 rate of one compute unit and read with a stride: 47 us on average over the batches of an
+// Algorithm-1 run (up to 8e4 samples), now 4 us (up to 4096 samples) and 18 us (above).
 // ---------------------------------------------------------------------------------------
-
-constexpr int MOM_THREADS = 256;
-
-__global__ void __launch_bounds__(MOM_THREADS) moments_kernel(const double* __restrict__ ps, uint64_t count, int n_obs,
-                                                             double* __restrict__ out)
+template <int T>
+__global__ void __launch_bounds__(T) moments_kernel(const double* __restrict__ ps, uint64_t count, int n_obs,
+                                                    double* __restrict__ out)
 {
-    const int j = blockIdx.x;
+    const int j = blockIdx.x, k = blockIdx.y;
     const int t = threadIdx.x;
-    const uint64_t per = (count + MOM_THREADS - 1) / MOM_THREADS;
-    const uint64_t b = per * t, e = (b + per < count) ? b + per : count;
-    double s[DK_NMOM], c[DK_NMOM];
-#pragma unroll
-    for (int k = 0; k < DK_NMOM; ++k) { s[k] = 0.0; c[k] = 0.0; }
-    for (uint64_t i = b; i < e; ++i) {
+    const int q = k / 2;                             // Y, P_fine, P_coarse
+    double s = 0.0, c = 0.0;
+#pragma unroll 4
+    for (uint64_t i = t; i < count; i += T) {
         const double pf = ps[(i * n_obs + j) * 2 + 0];
         const double pc = ps[(i * n_obs + j) * 2 + 1];
-        const double y = pf - pc;
-        neumaier(s[DK_MOM_Y], c[DK_MOM_Y], y);
-        neumaier(s[DK_MOM_Y2], c[DK_MOM_Y2], y * y);
-        neumaier(s[DK_MOM_PF], c[DK_MOM_PF], pf);
-        neumaier(s[DK_MOM_PF2], c[DK_MOM_PF2], pf * pf);
-        neumaier(s[DK_MOM_PC], c[DK_MOM_PC], pc);
-        neumaier(s[DK_MOM_PC2], c[DK_MOM_PC2], pc * pc);
+        const double v = q == 0 ? pf - pc : (q == 1 ? pf : pc);
+        neumaier(s, c, (k & 1) ? v * v : v);
     }
-    __shared__ double sh[MOM_THREADS][2 * DK_NMOM];
-#pragma unroll
-    for (int k = 0; k < DK_NMOM; ++k) { sh[t][2 * k] = s[k]; sh[t][2 * k + 1] = c[k]; }
+    __shared__ double sh[T][2];
+    sh[t][0] = s;
+    sh[t][1] = c;
     __syncthreads();
-    for (int w = MOM_THREADS / 2; w >= 1; w >>= 1) {
+    for (int w = T / 2; w >= 1; w >>= 1) {
         if (t < w) {
-#pragma unroll
-            for (int k = 0; k < DK_NMOM; ++k) {
-                double ss = sh[t][2 * k], cc = sh[t][2 * k + 1];
-                neumaier(ss, cc, sh[t + w][2 * k]);
-                cc += sh[t + w][2 * k + 1];
-                sh[t][2 * k] = ss;
-                sh[t][2 * k + 1] = cc;
-            }
+            neumaier(s, c, sh[t + w][0]);
+            c += sh[t + w][1];
+            sh[t][0] = s;
+            sh[t][1] = c;
         }
         __syncthreads();
     }
     if (t == 0) {
-#pragma unroll
-        for (int k = 0; k < DK_NMOM; ++k) {
-            out[(j * DK_NMOM + k) * 2 + 0] = sh[0][2 * k];
-            out[(j * DK_NMOM + k) * 2 + 1] = sh[0][2 * k + 1];
-        }
+        out[(j * DK_NMOM + k) * 2 + 0] = s;
+        out[(j * DK_NMOM + k) * 2 + 1] = c;
     }
 }
 
 hipError_t launch_moments(const double* per_sample, uint64_t count, int n_obs, double* out, hipStream_t s)
 {
-    hipLaunchKernelGGL(moments_kernel, dim3(n_obs), dim3(MOM_THREADS), 0, s, per_sample, count, n_obs, out);
+    const dim3 grid(n_obs, DK_NMOM);
+    if (count <= 4096)
+        hipLaunchKernelGGL(moments_kernel<256>, grid, dim3(256), 0, s, per_sample, count, n_obs, out);
+    else
+        hipLaunchKernelGGL(moments_kernel<1024>, grid, dim3(1024), 0, s, per_sample, count, n_obs, out);
     return hipGetLastError();
 }
 

@@ -127,16 +127,6 @@ struct CoarseNoise {
     }
 };
 
-template <typename Real, int C>
-struct NoNoise {
-    template <int I>
-    __device__ __forceinline__ void row(Real (&w0)[C], Real (&w1)[C])
-    {
-#pragma unroll
-        for (int c = 0; c < C; ++c) { w0[c] = Real(0); w1[c] = Real(0); }
-    }
-};
-
 // compile-time row loop
 template <int I, int N>
 struct RowLoop {
@@ -179,7 +169,7 @@ __device__ __forceinline__ void progress_prio()
 
 constexpr int row_prio(int i, int R) { return i < 2 ? 3 : 2 - (i - 2) * 3 / (R - 2); }
 
-template <typename Real, int R, int C, int FLUX, bool NOISE, bool COMP, bool ONE_BARRIER, bool WAVE_LOCAL, class Noise>
+template <typename Real, int R, int C, int FLUX, bool COMP, bool ONE_BARRIER, bool WAVE_LOCAL, class Noise>
 __device__ __forceinline__ void tile_step(Real (&rho)[R][C], Real (&cmp)[R][C], Noise& noise, const Real a, const Real kappa,
                                           Real* __restrict__ halo, const int g, const int G, const int cl,
                                           const int NN, const int addr_l, const int addr_r)
@@ -190,20 +180,16 @@ __device__ __forceinline__ void tile_step(Real (&rho)[R][C], Real (&cmp)[R][C], 
     constexpr bool BALANCE = !WAVE_LOCAL;
     progress_prio<BALANCE, 3>();
     Real w0_first[C], w1_first[C], w0_last[C], w1_last[C];
-    if constexpr (NOISE) {
-        noise.template row<0>(w0_first, w1_first);
-        if constexpr (R > 1) noise.template row<R - 1>(w0_last, w1_last);
-    }
+    noise.template row<0>(w0_first, w1_first);
+    if constexpr (R > 1) noise.template row<R - 1>(w0_last, w1_last);
     Real* top = halo + (g * 2 + 0) * 2 * NN + C * cl;
     Real* bot = halo + (g * 2 + 1) * 2 * NN + C * cl;
 #pragma unroll
     for (int c = 0; c < C; ++c) {
         top[c] = rho[0][c];
         bot[c] = rho[R - 1][c];
-        if constexpr (NOISE) {
-            top[NN + c] = w1_first[c];
-            bot[NN + c] = (R > 1) ? w1_last[c] : w1_first[c];
-        }
+        top[NN + c] = w1_first[c];
+        bot[NN + c] = (R > 1) ? w1_last[c] : w1_first[c];
     }
     sample_sync<WAVE_LOCAL>();
     const int gu = g == 0 ? G - 1 : g - 1;
@@ -215,10 +201,8 @@ __device__ __forceinline__ void tile_step(Real (&rho)[R][C], Real (&cmp)[R][C], 
     for (int c = 0; c < C; ++c) {
         rho_up[c] = above[c];
         rho_dn[c] = below[c];
-        if constexpr (NOISE) {
-            w1_up[c] = above[NN + c];
-            w1_dn[c] = below[NN + c];
-        }
+        w1_up[c] = above[NN + c];
+        w1_dn[c] = below[NN + c];
     }
     // With a double-buffered halo (alternating by step) the next step writes the other buffer,
     // and its barrier orders those writes after every lane's reads of this one.
@@ -231,16 +215,14 @@ __device__ __forceinline__ void tile_step(Real (&rho)[R][C], Real (&cmp)[R][C], 
 #pragma unroll
     for (int c = 0; c < C; ++c) {
         rprev[c] = rho_up[c];
-        if constexpr (NOISE) {
-            if constexpr (FLUX == DK_FLUX_CENTRAL) {
-                F1prev[c] = pos_sqrt(rho_up[c]) * w1_up[c];
-                F1cur[c] = pos_sqrt(rho[0][c]) * w1_first[c];
-            } else {
-                F1prev[c] = pos_sqrt(Real(0.5) * (rho_up[c] + rho[0][c])) * w1_up[c];
-            }
-            w0c[c] = w0_first[c];
-            w1c[c] = w1_first[c];
+        if constexpr (FLUX == DK_FLUX_CENTRAL) {
+            F1prev[c] = pos_sqrt(rho_up[c]) * w1_up[c];
+            F1cur[c] = pos_sqrt(rho[0][c]) * w1_first[c];
+        } else {
+            F1prev[c] = pos_sqrt(Real(0.5) * (rho_up[c] + rho[0][c])) * w1_up[c];
         }
+        w0c[c] = w0_first[c];
+        w1c[c] = w1_first[c];
     }
 
     RowLoop<0, R>::run([&](auto Ic) {
@@ -250,56 +232,48 @@ __device__ __forceinline__ void tile_step(Real (&rho)[R][C], Real (&cmp)[R][C], 
 #pragma unroll
         for (int c = 0; c < C; ++c) rnext[c] = (i + 1 < R) ? rho[(i + 1 < R) ? i + 1 : 0][c] : rho_dn[c];
         Real w0n[C], w1n[C];
-        if constexpr (NOISE) {
-            if constexpr (i + 1 <= R - 2) {
-                noise.template row<(i + 1 <= R - 2) ? i + 1 : 0>(w0n, w1n);
-            } else if constexpr (i + 1 == R - 1) {
+        if constexpr (i + 1 <= R - 2) {
+            noise.template row<(i + 1 <= R - 2) ? i + 1 : 0>(w0n, w1n);
+        } else if constexpr (i + 1 == R - 1) {
 #pragma unroll
-                for (int c = 0; c < C; ++c) { w0n[c] = w0_last[c]; w1n[c] = w1_last[c]; }
-            } else {
+            for (int c = 0; c < C; ++c) { w0n[c] = w0_last[c]; w1n[c] = w1_last[c]; }
+        } else {
 #pragma unroll
-                for (int c = 0; c < C; ++c) { w0n[c] = Real(0); w1n[c] = w1_dn[c]; }
-            }
+            for (int c = 0; c < C; ++c) { w0n[c] = Real(0); w1n[c] = w1_dn[c]; }
         }
         // x-halo of the density
         const Real rl = lane_get(addr_l, rho[i][C - 1]);
         const Real rr = lane_get(addr_r, rho[i][0]);
         Real F0[C], F1n[C];
-        Real F0l = Real(0), F0r = Real(0);
-        if constexpr (NOISE) {
+        Real F0r = Real(0);
 #pragma unroll
-            for (int c = 0; c < C; ++c) {
-                if constexpr (FLUX == DK_FLUX_CENTRAL) {
-                    F0[c] = pos_sqrt(rho[i][c]) * w0c[c];
-                    F1n[c] = pos_sqrt(rnext[c]) * w1n[c];
-                } else {
-                    const Real right = (c + 1 < C) ? rho[i][(c + 1 < C) ? c + 1 : 0] : rr;
-                    F0[c] = pos_sqrt(Real(0.5) * (rho[i][c] + right)) * w0c[c];
-                    F1n[c] = pos_sqrt(Real(0.5) * (rho[i][c] + rnext[c])) * w1c[c];   // edge (i, i+1)
-                }
+        for (int c = 0; c < C; ++c) {
+            if constexpr (FLUX == DK_FLUX_CENTRAL) {
+                F0[c] = pos_sqrt(rho[i][c]) * w0c[c];
+                F1n[c] = pos_sqrt(rnext[c]) * w1n[c];
+            } else {
+                const Real right = (c + 1 < C) ? rho[i][(c + 1 < C) ? c + 1 : 0] : rr;
+                F0[c] = pos_sqrt(Real(0.5) * (rho[i][c] + right)) * w0c[c];
+                F1n[c] = pos_sqrt(Real(0.5) * (rho[i][c] + rnext[c])) * w1c[c];   // edge (i, i+1)
             }
-            F0l = lane_get(addr_l, F0[C - 1]);
-            if constexpr (FLUX == DK_FLUX_CENTRAL) F0r = lane_get(addr_r, F0[0]);
         }
+        const Real F0l = lane_get(addr_l, F0[C - 1]);
+        if constexpr (FLUX == DK_FLUX_CENTRAL) F0r = lane_get(addr_r, F0[0]);
         Real rnew[C];
 #pragma unroll
         for (int c = 0; c < C; ++c) {
             const Real left = (c > 0) ? rho[i][(c > 0) ? c - 1 : 0] : rl;
             const Real right = (c + 1 < C) ? rho[i][(c + 1 < C) ? c + 1 : 0] : rr;
             const Real lap = fma(Real(-4), rho[i][c], (left + right) + (rprev[c] + rnext[c]));
-            Real d = a * lap;
-            if constexpr (NOISE) {
-                Real div;
-                if constexpr (FLUX == DK_FLUX_CENTRAL) {
-                    const Real fl = (c > 0) ? F0[(c > 0) ? c - 1 : 0] : F0l;
-                    const Real fr = (c + 1 < C) ? F0[(c + 1 < C) ? c + 1 : 0] : F0r;
-                    div = (fr - fl) + (F1n[c] - F1prev[c]);
-                } else {
-                    const Real fl = (c > 0) ? F0[(c > 0) ? c - 1 : 0] : F0l;
-                    div = (F0[c] - fl) + (F1n[c] - F1prev[c]);
-                }
-                d = fma(kappa, div, d);
+            const Real fl = (c > 0) ? F0[(c > 0) ? c - 1 : 0] : F0l;
+            Real div;
+            if constexpr (FLUX == DK_FLUX_CENTRAL) {
+                const Real fr = (c + 1 < C) ? F0[(c + 1 < C) ? c + 1 : 0] : F0r;
+                div = (fr - fl) + (F1n[c] - F1prev[c]);
+            } else {
+                div = (F0[c] - fl) + (F1n[c] - F1prev[c]);
             }
+            const Real d = fma(kappa, div, a * lap);
             if constexpr (COMP) {
                 // compensated (Kahan) accumulation of the increment: the rounding error of the
                 // FP32 state is carried in cmp and fed back the next step
@@ -315,86 +289,100 @@ __device__ __forceinline__ void tile_step(Real (&rho)[R][C], Real (&cmp)[R][C], 
         for (int c = 0; c < C; ++c) {
             rprev[c] = rho[i][c];
             rho[i][c] = rnew[c];
-            if constexpr (NOISE) {
-                if constexpr (FLUX == DK_FLUX_CENTRAL) {
-                    F1prev[c] = F1cur[c];
-                    F1cur[c] = F1n[c];
-                } else {
-                    F1prev[c] = F1n[c];
-                }
-                w0c[c] = w0n[c];
-                w1c[c] = w1n[c];
+            if constexpr (FLUX == DK_FLUX_CENTRAL) {
+                F1prev[c] = F1cur[c];
+                F1cur[c] = F1n[c];
+            } else {
+                F1prev[c] = F1n[c];
             }
+            w0c[c] = w0n[c];
+            w1c[c] = w1n[c];
         }
     });
 }
 
 // ---------------------------------------------------------------------------------------
-// Segmented sum over the TS lanes of one sample (TS a power of two); result valid in the
-// sample's first lane.  red: LDS scratch of one double per wavefront of the block.
+// Observables.  (rho, phi_j) is summed in FP64 by one binary tree whatever the tile shape, so that a
+// sample's values do not depend on how a batch was cut or which shape ran it: the two columns of a lane,
+// then the rows of the grid by the bits of their index, lowest first (within the lane, across the row
+// groups of the wavefront, across wavefronts through LDS), then the columns by the bits of theirs.
+//   scratch: LDS, TS / 64 * NPL doubles per sample that spans several wavefronts (the halo area, free
+//   after the last step).
 // ---------------------------------------------------------------------------------------
-template <int TS>
-__device__ __forceinline__ double sample_sum(double v, double* red, int tid)
-{
-    constexpr int W = TS < 64 ? TS : 64;
-#pragma unroll
-    for (int off = W / 2; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-    if constexpr (TS > 64) {
-        constexpr int NW = TS / 64;
-        const int wave = tid >> 6;
-        if ((tid & 63) == 0) red[wave] = v;
-        __syncthreads();
-        double s = 0.0;
-        if ((tid % TS) == 0) {
-            const int w0 = wave;   // first wavefront of this sample
-            for (int w = 0; w < NW; ++w) s += red[w0 + w];
-        }
-        __syncthreads();
-        return s;
-    }
-    return v;
-}
-
-template <typename Real, int R, int C, int TS>
+template <typename Real, int R, int C, int NPL, int TS>
 __device__ __forceinline__ void observe(const Real (&rho)[R][C], const double* __restrict__ phi, const double* obs,
-                                        int n_obs, int NN, int row0, int col0, double h2, double* red, int tid,
+                                        int n_obs, int NN, int row0, int col0, double h2, double* scratch, int t,
                                         double* dst, bool write)
 {
+#pragma clang fp contract(off)
+    constexpr int NW = TS <= 64 ? 1 : TS / 64;      // wavefronts of a sample
+    constexpr int W = TS < 64 ? TS : 64;
     for (int j = 0; j < n_obs; ++j) {
         const double* ph = phi + (size_t)j * NN * NN;
-        double acc = 0.0;
+        double v[R];
 #pragma unroll
-        for (int i = 0; i < R; ++i)
+        for (int i = 0; i < R; ++i) {
+            const double* p = ph + (row0 + i) * NN + col0;
+            v[i] = (double)rho[i][0] * p[0];
+            if constexpr (C == 2) v[i] = fma((double)rho[i][C - 1], p[C - 1], v[i]);
+        }
 #pragma unroll
-            for (int c = 0; c < C; ++c) acc = fma((double)rho[i][c], ph[(row0 + i) * NN + col0 + c], acc);
-        const double L = sample_sum<TS>(acc, red, tid);
+        for (int w = 1; w < R; w <<= 1)
+#pragma unroll
+            for (int i = 0; i + w < R; i += 2 * w) v[i] += v[i + w];
+        double s = v[0];
+#pragma unroll
+        for (int off = NPL; off < W; off <<= 1) s += __shfl_xor(s, off, 64);
+        if constexpr (NW > 1) {
+            __syncthreads();                        // the last step's halo, the last observable's sums are read
+            if ((t & 63) < NPL) scratch[(t >> 6) * NPL + (t & 63)] = s;
+            __syncthreads();
+            double u[NW];
+#pragma unroll
+            for (int w = 0; w < NW; ++w) u[w] = scratch[w * NPL + (t & (NPL - 1))];
+#pragma unroll
+            for (int w = 1; w < NW; w <<= 1)
+#pragma unroll
+                for (int i = 0; i + w < NW; i += 2 * w) u[i] += u[i + w];
+            s = u[0];
+        }
+#pragma unroll
+        for (int off = 1; off < NPL; off <<= 1) s += __shfl_xor(s, off, 64);
         if (write) {
             const double scale = obs[3 * j + 0], centre = obs[3 * j + 1];
-            const double X = scale * (h2 * L - centre);
+            const double X = scale * fma(h2, s, -centre);
             dst[2 * j] = (obs[3 * j + 2] != 0.0) ? X * X : X;
         }
     }
 }
 
 // ---------------------------------------------------------------------------------------
-// LDS elements one sample needs: the fine halo rows double-buffered by step parity, then the
-// coarse halo rows.
+// LDS elements one sample needs: the fine halo rows double-buffered by step parity, and the coarse
+// halo rows behind them.  Where those do not fit (FP64 states whose fine halo fills the compute unit's
+// LDS) the coarse step uses the fine buffer of even steps: it follows an odd step, whose barrier every
+// wavefront passed after its last read of that buffer, and closes with a barrier before the next even
+// step writes it.
 // ---------------------------------------------------------------------------------------
-template <int NF, int R, bool PAIR>
+template <typename Real, int NF, int R, int SPW>
+constexpr bool coarse_halo_shared()
+{
+    return (size_t)SPW * (2 * (NF / R) * 4 * NF + (NF / R) * 4 * (NF / 2)) * sizeof(Real) > 128 * 1024;
+}
+template <typename Real, int NF, int R, bool PAIR, int SPW>
 constexpr int halo_elems()
 {
-    return 2 * (NF / R) * 4 * NF + (PAIR ? (NF / R) * 4 * (NF / 2) : 0);
+    return 2 * (NF / R) * 4 * NF + (PAIR && !coarse_halo_shared<Real, NF, R, SPW>() ? (NF / R) * 4 * (NF / 2) : 0);
 }
 
 // ---------------------------------------------------------------------------------------
 // One block-iteration of the resident level kernel: the block's SPW samples (local indices
 // local0 + s, s < SPW; those at or beyond A.count run but write nothing) advanced over the
 // whole time horizon, then reduced to their observables.
-//   halo: LDS, SPW * halo_elems<NF, R, PAIR>() elements;  red: LDS, one double per wavefront;
+//   halo: LDS, SPW * halo_elems<Real, NF, R, PAIR, SPW>() elements, 8-byte aligned;
 //   tid: the lane's index in the block (threadIdx.x).
 // ---------------------------------------------------------------------------------------
-template <typename Real, int NF, int R, int C, bool PAIR, int FLUX, bool NOISE, int SPW>
-__device__ __forceinline__ void level_body(const LevelArgs& A, uint64_t local0, Real* halo, double* red, const int tid)
+template <typename Real, int NF, int R, int C, bool PAIR, int FLUX, int SPW>
+__device__ __forceinline__ void level_body(const LevelArgs& A, uint64_t local0, Real* halo, const int tid)
 {
     constexpr int NPL = NF / C;            // lanes per row group
     constexpr int G = NF / R;              // row groups
@@ -406,7 +394,8 @@ __device__ __forceinline__ void level_body(const LevelArgs& A, uint64_t local0, 
     static_assert(!PAIR || (R % 2 == 0 && C % 2 == 0), "pairs need even tiles");
     static_assert(TS <= 64 || TS % 64 == 0, "sample lanes");
 
-    constexpr int HALO = halo_elems<NF, R, PAIR>();
+    constexpr int HALO = halo_elems<Real, NF, R, PAIR, SPW>();
+    constexpr bool SHARED = coarse_halo_shared<Real, NF, R, SPW>();
     constexpr bool WL = TS <= 64;     // the sample's lanes lie inside one wavefront
 
     const int sw = tid / TS;
@@ -422,7 +411,7 @@ __device__ __forceinline__ void level_body(const LevelArgs& A, uint64_t local0, 
     const int row0 = R * g, col0 = C * cl;
 
     // FP32 states carry a Kahan compensation term per cell; FP64 states do not need one
-    constexpr bool COMP = std::is_same<Real, float>::value && NOISE;
+    constexpr bool COMP = std::is_same<Real, float>::value;
     Real rho[R][C], rho_cmp[R][C];
 #pragma unroll
     for (int i = 0; i < R; ++i)
@@ -459,17 +448,10 @@ __device__ __forceinline__ void level_body(const LevelArgs& A, uint64_t local0, 
     // are kept rolled so that the compiler does not interleave the (state-independent) noise
     // of several steps, which would multiply the live registers.
     auto fine_step = [&](int m) {
-        if constexpr (NOISE) {
-            FineNoise<Real, R, C, PAIR> fn{key, (uint32_t)m, (uint32_t)(col0 / 2 + row0 * (NF / 2)),
-                                           (uint32_t)(NF / 2), PAIR ? (Real(*)[C / 2 > 0 ? C / 2 : 1][2])Z : nullptr,
-                                           pend};
-            tile_step<Real, R, C, FLUX, true, COMP, true, WL>(rho, rho_cmp, fn, a, kf, my_halo + (m & 1) * G * 4 * NF, g, G,
-                                                          cl, NF, addr_l, addr_r);
-        } else {
-            NoNoise<Real, C> nn;
-            tile_step<Real, R, C, FLUX, false, false, true, WL>(rho, rho_cmp, nn, a, Real(0), my_halo + (m & 1) * G * 4 * NF, g,
-                                                            G, cl, NF, addr_l, addr_r);
-        }
+        FineNoise<Real, R, C, PAIR> fn{key, (uint32_t)m, (uint32_t)(col0 / 2 + row0 * (NF / 2)), (uint32_t)(NF / 2),
+                                       PAIR ? (Real(*)[C / 2 > 0 ? C / 2 : 1][2])Z : nullptr, pend};
+        tile_step<Real, R, C, FLUX, COMP, true, WL>(rho, rho_cmp, fn, a, kf, my_halo + (m & 1) * G * 4 * NF, g, G, cl, NF,
+                                                    addr_l, addr_r);
     };
     if constexpr (PAIR) {
         const int Mc = A.steps / 4;
@@ -478,8 +460,9 @@ __device__ __forceinline__ void level_body(const LevelArgs& A, uint64_t local0, 
 #pragma unroll 1
             for (int j = 0; j < 4; ++j) fine_step(4 * mc + j);
             CoarseNoise<Real, RC, CCc> cn{Z};
-            tile_step<Real, RC, CCc, FLUX, NOISE, COMP, false, WL>(rhoc, rhoc_cmp, cn, a, kc, my_halo + 2 * G * 4 * NF, g, G,
-                                                                 cl, NC, addr_l, addr_r);
+            // its own halo area is next written four fine steps (and their barriers) later: one barrier
+            tile_step<Real, RC, CCc, FLUX, COMP, !SHARED, WL>(rhoc, rhoc_cmp, cn, a, kc, my_halo + (SHARED ? 0 : 2 * G * 4 * NF),
+                                                              g, G, cl, NC, addr_l, addr_r);
 #pragma unroll
             for (int i = 0; i < RC; ++i)
 #pragma unroll
@@ -500,10 +483,11 @@ __device__ __forceinline__ void level_body(const LevelArgs& A, uint64_t local0, 
 
     double* dst = A.out + (size_t)(active ? local : 0) * A.n_obs * 2;
     const bool writer = active && t == 0;
-    observe<Real, R, C, TS>(rho, A.phi_f, A.obs_f, A.n_obs, NF, row0, col0, A.h2f, red, tid, dst, writer);
+    double* scratch = (double*)my_halo;
+    observe<Real, R, C, NPL, TS>(rho, A.phi_f, A.obs_f, A.n_obs, NF, row0, col0, A.h2f, scratch, t, dst, writer);
     if constexpr (PAIR) {
-        observe<Real, RC, CCc, TS>(rhoc, A.phi_c, A.obs_c, A.n_obs, NC, RC * g, CCc * cl, A.h2c, red, tid, dst + 1,
-                                   writer);
+        observe<Real, RC, CCc, NPL, TS>(rhoc, A.phi_c, A.obs_c, A.n_obs, NC, RC * g, CCc * cl, A.h2c, scratch, t, dst + 1,
+                                        writer);
     } else {
         if (writer)
             for (int j = 0; j < A.n_obs; ++j) dst[2 * j + 1] = 0.0;
@@ -535,12 +519,14 @@ struct ShapeOf {
     static constexpr int SPW = (TS >= 256 ? 1 : 256 / TS) * X;
 };
 
-// Neumaier's compensated summation step: s + c accumulates x.
+// Compensated summation step: s + c accumulates x.  The rounding error of s + x is formed without a
+// comparison (Knuth's two-sum); it is the same exact value that Neumaier's branch gives.
 __device__ __forceinline__ void neumaier(double& s, double& c, double x)
 {
+#pragma clang fp contract(off)
     const double t = s + x;
-    if (fabs(s) >= fabs(x)) c += (s - t) + x;
-    else c += (x - t) + s;
+    const double b = t - s;
+    c += (s - (t - b)) + (x - b);
     s = t;
 }
 

@@ -637,7 +637,7 @@ int run_level(dk_context* ctx, const dk_problem* p, int level, bool pair, uint64
         }
         st.launches += nchunks;
         st.samples += count;
-        st.rows = p->precision == DK_PREC_F32 ? dk::shape_rows(nf, variant) : (nf == 128 ? 16 : dk::shape_rows(nf, 0));
+        st.rows = dk::shape_rows(nf, variant);
         st.cells += (double)nf * nf * (double)Tf->steps * (pair ? 1.0 + 1.0 / 16.0 : 1.0) * (double)count;
     }
     for (uint64_t k = 0; k < nchunks; ++k) {

@@ -28,7 +28,7 @@ template <int NF>
 constexpr int round_spw() { return RT / ((NF / RC) * (NF / RR)); }
 
 template <int NF, bool PAIR>
-constexpr int round_lds() { return round_spw<NF>() * halo_elems<NF, RR, PAIR>(); }
+constexpr int round_lds() { return round_spw<NF>() * halo_elems<float, NF, RR, PAIR, round_spw<NF>()>(); }
 
 constexpr int cmax(int a, int b) { return a > b ? a : b; }
 constexpr int RHALO = cmax(cmax(cmax(round_lds<8, false>(), round_lds<16, false>()),
@@ -40,12 +40,12 @@ static_assert(RHALO * 4 <= 96 * 1024, "round kernel LDS");
 // The lane index is passed through an empty asm statement so that the compiler cannot hoist the
 // lane constants of all nine level kinds out of the task loop (they would all stay live at once).
 template <int NF, bool PAIR, int FLUX>
-__device__ __forceinline__ void body(const LevelArgs& A, float* halo, double* red)
+__device__ __forceinline__ void body(const LevelArgs& A, float* halo)
 {
     int tid = (int)threadIdx.x;
     asm volatile("" : "+v"(tid));
     __builtin_assume(tid >= 0 && tid < RT);
-    level_body<float, NF, RR, RC, PAIR, FLUX, true, round_spw<NF>()>(A, 0, halo, red, tid);
+    level_body<float, NF, RR, RC, PAIR, FLUX, round_spw<NF>()>(A, 0, halo, tid);
 }
 }  // namespace
 
@@ -82,8 +82,7 @@ __global__ void round_reset_kernel(uint32_t* head)
 template <int FLUX>
 __global__ void __launch_bounds__(RT) round_kernel(const RoundArgs P)
 {
-    __shared__ float halo[RHALO];
-    __shared__ double red[RT / 64];
+    __shared__ __align__(16) float halo[RHALO];
     __shared__ uint32_t s_task;
     const int tid = threadIdx.x;
     const int nobs = P.n_obs;
@@ -109,15 +108,15 @@ __global__ void __launch_bounds__(RT) round_kernel(const RoundArgs P)
             A.field_f = nullptr;
             A.field_c = nullptr;
             switch (kind) {
-                case 0: body<8, false, FLUX>(A, halo, red); break;
-                case 1: body<16, false, FLUX>(A, halo, red); break;
-                case 2: body<32, false, FLUX>(A, halo, red); break;
-                case 3: body<64, false, FLUX>(A, halo, red); break;
-                case 4: body<128, false, FLUX>(A, halo, red); break;
-                case 5: body<16, true, FLUX>(A, halo, red); break;
-                case 6: body<32, true, FLUX>(A, halo, red); break;
-                case 7: body<64, true, FLUX>(A, halo, red); break;
-                case 8: body<128, true, FLUX>(A, halo, red); break;
+                case 0: body<8, false, FLUX>(A, halo); break;
+                case 1: body<16, false, FLUX>(A, halo); break;
+                case 2: body<32, false, FLUX>(A, halo); break;
+                case 3: body<64, false, FLUX>(A, halo); break;
+                case 4: body<128, false, FLUX>(A, halo); break;
+                case 5: body<16, true, FLUX>(A, halo); break;
+                case 6: body<32, true, FLUX>(A, halo); break;
+                case 7: body<64, true, FLUX>(A, halo); break;
+                case 8: body<128, true, FLUX>(A, halo); break;
                 default: break;   // no such kind: the host never lists one
             }
             __syncthreads();

@@ -107,9 +107,39 @@ void save_tuning_cache(const dk_context* ctx)
     std::rename(tmp.c_str(), path);
 }
 
-// Tile-shape choice for the FP32 noisy kernels: a forced variant, a cached choice, or the
-// fastest variant on a short tuning batch (same tables, at most 2048 fine steps, samples from
-// the requested range; the outputs are discarded).  Small jobs use the default shape.
+// Rows per lane for a batch that leaves the GPU's wavefront slots partly empty (1024 SIMDs, 4 wavefronts
+// each at these register counts).  A step then takes a wavefront's own latency, about 0.4 us a row, so the
+// fewest rows are the fastest until the extra wavefronts of the smaller tiles (which repeat the halo and
+// lane-exchange work more often) fill the chip.  The lines lie where the measured times of one step cross
+// (MI355X, pairs; us at 2 / 4 / 8 rows):
+//   FP32   8^2: 4096 samples 1.2 / 2.0 / 3.5, 32768 4.8 / 4.7 / 5.1, 65536 8.7 / 8.2 / 8.6
+//         16^2: 1024 samples 1.1 / 1.9 / 3.6, 8192 4.7 / 5.1 / 5.2, 32768 15.9 / 16.7 / 15.2
+//         32^2: 1024 samples 2.7 / 2.8 / 3.9, 3456 7.5 / 7.5 / 8.5, 7776 15.8 / 15.7 / 15.1
+//         64^2: 256 samples 2.9 / 2.9 / 3.9, 512 5.3 / 4.8 / 4.8, 1536 14.8 / 12.8 / 11.7
+//   FP64   8^2: 4096 samples 1.7 / 2.7 / 4.2, 16384 4.5 / 4.3 / 4.6, 32768 8.3 / 7.5 / 7.1
+//         16^2: 2048 samples 2.5 / 2.6 / 4.5, 8192 7.9 / 7.2 / 7.4, 16384 14.6 / 13.1 / 13.0
+//         32^2: 512 samples 2.5 / 2.8 / 4.5, 1024 4.3 / 4.0 / 4.8, 7776 27.4 / 25.3 / 23.9
+//         64^2: 256 samples 4.5 / 4.1 / 4.9, 512 8.8 / 7.1 / 6.9
+// (4^2 and 128^2 have no smaller tile.)  Single paths cross at the same sizes within a few percent, and
+// can run one row per lane:
+//   FP32   8^2: 1024 samples 0.69 against 1.0 at 2 rows, 8192 1.5 / 1.4;  16^2: 512 samples 0.72 / 0.98, 2048 1.6 / 1.5
+//   FP64   8^2: 1024 samples 1.1 / 1.5, 4096 1.6 / 1.6;  16^2: 512 samples 1.1 / 1.4, 1024 1.6 / 1.6
+// FP64 pairs of 64^2 fit three 8-row blocks on a compute unit, so 769 to 1024 samples would open a second
+// round for the rest: 15.5 us a step against 13.4 with the 4-row shape's two full ones.
+int small_batch_rows(int nf, bool f64, bool pair, uint64_t count)
+{
+    struct Line { int n; uint64_t one, two, four; };
+    static const Line f32[] = {{8, 6000, 24000, 80000}, {16, 1200, 20000, 0}, {32, 0, 2500, 6000}, {64, 0, 256, 400}};
+    static const Line d64[] = {{8, 3000, 8192, 20000}, {16, 800, 3000, 10000}, {32, 0, 600, 6000}, {64, 0, 0, 300}};
+    if (nf == 64 && f64 && pair && count > 768 && count <= 1024) return 4;
+    for (const Line& l : f64 ? d64 : f32)
+        if (l.n == nf) return !pair && count <= l.one ? 1 : (count <= l.two ? 2 : (count <= l.four ? 4 : 0));
+    return 0;
+}
+
+// Tile-shape choice: a forced variant, a cached choice (FP32), the rows of a small batch, or for large
+// FP32 jobs the fastest variant on a short tuning batch (same tables, at most 2048 fine steps, samples
+// from the requested range; the outputs are discarded).  Otherwise the default shape.
 int choose_shape(dk_context* ctx, const dk_problem* p, bool pair, const dk::LevelArgs& A, uint64_t count,
                  double cells_per_sample, hipStream_t s, int* variant)
 {
@@ -121,11 +151,18 @@ int choose_shape(dk_context* ctx, const dk_problem* p, bool pair, const dk::Leve
         *variant = f->second;
         return DK_OK;
     }
-    if (p->precision != DK_PREC_F32) return DK_OK;
+    const bool f64 = p->precision == DK_PREC_F64;
     const long key = ((long)nf << 8) | ((long)pair << 4) | (long)p->flux;
-    auto t = ctx->tuned.find(key);
-    if (t != ctx->tuned.end()) { *variant = t->second; return DK_OK; }
-    if ((double)count * cells_per_sample < 1e11) return DK_OK;
+    if (!f64) {
+        auto t = ctx->tuned.find(key);
+        if (t != ctx->tuned.end()) { *variant = t->second; return DK_OK; }
+    }
+    if (f64 || (double)count * cells_per_sample < 1e11) {
+        const int rows = small_batch_rows(nf, f64, pair, count);
+        for (int v = 0; rows > 0 && dk::shape_rows(nf, v) > 0; ++v)
+            if (dk::shape_rows(nf, v) == rows) { *variant = v; break; }
+        return DK_OK;
+    }
     int nvar = 0;
     while (dk::shape_rows(nf, nvar) > 0) ++nvar;
     if (nvar < 2) { ctx->tuned[key] = 0; save_tuning_cache(ctx); return DK_OK; }
