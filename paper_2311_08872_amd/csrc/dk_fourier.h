@@ -25,17 +25,14 @@ struct FourierArgs {
     const double* phi_c;    // [n_obs][nc*nc]
     const double* obs_f;    // per observable {scale, centre, psi}, fine
     const double* obs_c;    // coarse
-    const void* K;          // pairs: restriction kernel [nc][nf], state type
-    void* scratch;          // pairs: per block [2 nf^2 + 2 nf nc] state-type elements
+    const void* K;          // pairs: the projection kernel k(d), d = 0 .. nf-1 (K[ic][i] = k(3 ic - i)), state type
     double* out;            // [count][n_obs][2] (P_fine, P_coarse)
 };
 
 // Grid sizes with a compiled kernel (pairs need n divisible by 3 with n/3 even).
 bool fourier_supported(int nf, bool pair);
-// Blocks of one launch for `count` samples (each block strides over samples).
+// Blocks of one launch for `count` samples.
 int fourier_grid(int nf, int precision, uint64_t count);
-// State-type elements of pair scratch per block.
-size_t fourier_scratch_elems(int nf);
 hipError_t launch_fourier(const FourierArgs& A, int precision, bool pair, int grid, hipStream_t s);
 
 }  // namespace dk

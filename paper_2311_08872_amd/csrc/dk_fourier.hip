@@ -7,297 +7,352 @@
 // Sec. 3.1.  The coarse level reuses the coefficients of the frequencies it resolves, summed
 // over its 9 fine steps; in real space that is the fine normals summed over the coarse step,
 // projected onto the coarse frequencies and read at the coarse nodes, i.e. the separable map
-// S -> K S K^T with the [nc][nf] kernel K built on the host (a sum of cosines; on the coarse
-// Nyquist frequency the two fine aliases enter with weight 2^{-1/2} each, which makes the
-// coarse noise real with the coarse level's own law).  The projected sums have unit variance
+// S -> K S K^T with the [nc][nf] kernel K[ic][i] = k(3 ic - i), k even and periodic (a sum of cosines;
+// on the coarse Nyquist frequency the two fine aliases enter with weight 2^{-1/2} each, which makes
+// the coarse noise real with the coarse level's own law).  The projected sums have unit variance
 // per coarse node, so the coarse noise coefficient is kc = kf h_f / h_c.
 //
-// Layout: one block per sample (blocks stride over the batch).  The fine state lives in LDS
-// (state type), with one direction of the step's normals beside it (binary32: the normals
-// are binary32 values, so this loses nothing); a thread owns horizontal site pairs (one
-// generator call each) and keeps their compensation terms and, for pairs, their running
-// noise sums in registers.  A fine step is: normals -> x-divergence -> y normals ->
-// y-divergence, Laplacian and update -> store, with a barrier between phases.  At the end of
-// each coarse step the sums go to a per-block scratch area (L2), K is applied along x and
-// then along y, and the coarse step runs on the coarse state in LDS with the projected sums
-// in the normals' LDS area.  FP32 states use the compensated increment of the other kernels;
-// FP64 states add the increment directly.
+// Layout: the register tiles of the resident level kernel (tile_step in dk_level.h) on grids that are
+// not powers of two.  A lane owns C columns and R rows; a row group of n / C lanes sits inside one
+// wavefront (54 of 64 lanes at 108 x 108), whose remaining lanes repeat its first lane's work, writes
+// included.  A lane keeps the running sums of its cells' normals beside the state.  At the end of a
+// coarse step the sums of one direction go to LDS and the matrix cores form K S K^T in one go: a
+// wavefront multiplies 16 rows of S by K^T (A = S from LDS, B from the table k), and the product's
+// registers are, as they stand, the right operand of the product by K that follows
+// (v_mfma_f64_16x16x4_f64 returns row 4 i + q of its result where it takes row 4 i + q of its second
+// factor), so the half-projected sums are never stored.  The coarse state is in LDS, a cell per lane.
+//
+// Bound by the vector ALU (Philox, Box--Muller, one FP64 root per cell).  The first kernel held the
+// state and the normals in LDS, four roots a cell and five barriers a step, and projected through L2:
+// 500 pairs of 108 x 108 took 63.8 ms (6.7e10 cell updates/s), now 16.8 ms (2.5e11).  Rows per lane: the most
+// that leave the sums in registers at 108 x 108 (9 x 2 cells, three wavefronts per SIMD); four on the
+// small grids, whose batches rarely fill the chip.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "dk_fourier.h"
-#include "dk_rng.h"
+#include "dk_level.h"
 
 namespace dk {
 
 namespace {
 template <int NF>
 struct FG {
-    static constexpr int NC = NF / 3;
-    static constexpr int THREADS = NF >= 108 ? 1024 : (NF >= 72 ? 512 : (NF >= 36 ? 256 : (NF >= 24 ? 128 : 64)));
-    static constexpr int NPR = NF / 2;            // site pairs per row
-    static constexpr int NPAIRS = NF * NF / 2;
-    static constexpr int SLOTS = (NPAIRS + THREADS - 1) / THREADS;
-    static constexpr int NCC = NC * NC;
-    static constexpr int CSLOTS = (NCC + THREADS - 1) / THREADS;
+    static constexpr int C = NF == 72 ? 4 : 2;                       // 72: 18 lanes a row, three rows a wavefront
+    static constexpr int R = NF == 108 ? 9 : (NF == 24 || NF == 72 ? 6 : 4);
+    static constexpr int NPL = NF / C, G = NF / R;                   // lanes per row group, row groups
+    static constexpr int GPW = 64 / NPL;                             // row groups a wavefront can hold
+    static constexpr bool WL = G <= GPW;                             // a sample (or several) per wavefront
+    static constexpr int SEG = NPL * (WL ? G : GPW);                 // lanes of a sample in a wavefront
+    static constexpr int SPW = WL ? 64 / SEG : 1;                    // samples per wavefront
+    static constexpr int W = WL ? 1 : G / GPW;                       // wavefronts of a sample
+    static constexpr int WPB = WL ? 4 : W;                           // wavefronts of a block
+    static constexpr int SPB = WL ? WPB * SPW : 1;                   // samples of a block
+    static constexpr int NC = NF / 3, NCC = NC * NC;
+    static constexpr int PITCH = NF + 2;                             // sums in LDS: 16 rows without bank conflicts
+    static constexpr int YT = (NF + 15) / 16, CT = (NC + 15) / 16;   // 16 x 16 tiles of the products
+    static constexpr int PARTS = W / CT > 0 ? W / CT : 1;            // wavefronts that share a column tile
+    static_assert(NF % R == 0 && (WL || G % GPW == 0) && (WL || W % CT == 0), "whole tiles");
+    // Reals of one sample's LDS: halo rows, the sums of one direction or partial products; z, rho_c
+    static constexpr int HALO = 2 * G * 4 * NF;
+    static constexpr int SUMS = NF * PITCH;
+    static constexpr int PARTIAL = WL ? 0 : PARTS * CT * CT * 256;
+    static constexpr int AREA1 = HALO;                               // single paths
+    static constexpr int AREA2 = HALO > SUMS ? (HALO > PARTIAL ? HALO : PARTIAL) : (SUMS > PARTIAL ? SUMS : PARTIAL);
 };
 
-template <typename Real>
-__device__ __forceinline__ Real psqr(Real x) { return sqrt(x > Real(0) ? x : Real(0)); }
+// The fine normals of a tile, added to the running sums of the coarse step.
+template <typename Real, int R, int C, bool PAIR>
+struct FourierNoise {
+    NoiseKey key;
+    uint32_t step, pair_base, pairs_per_row;
+    Real (*S)[C][2];
+    using W = float;
+    // correctly rounded roots in both state types
+    static __device__ __forceinline__ Real root(Real x)
+    {
+        if constexpr (std::is_same<Real, double>::value) return pos_sqrt_f64(x);
+        else return sqrt(x > Real(0) ? x : Real(0));
+    }
 
-// t, made to depend on v: the next slot's addresses (and loads) wait for this slot's result,
-// so the compiler does not issue the loads of every slot at once and run out of registers
-template <typename V>
-__device__ __forceinline__ int after(int t, V v)
-{
-    asm volatile("" : "+v"(t) : "v"(v));
-    return t;
-}
+    template <int I>
+    __device__ __forceinline__ void row(W (&w0)[C], W (&w1)[C])
+    {
+#pragma unroll
+        for (int cp = 0; cp < C / 2; ++cp) {
+            float a0, a1, b0, b1;
+            uint32_t idx = pair_base + (uint32_t)I * pairs_per_row + cp;
+            asm volatile("" : "+v"(idx));      // recomputed every step rather than kept live (see FineNoise)
+            site_pair_normals(key, idx, step, a0, a1, b0, b1);
+            w0[2 * cp] = a0;
+            w1[2 * cp] = a1;
+            w0[2 * cp + 1] = b0;
+            w1[2 * cp + 1] = b1;
+            if constexpr (PAIR) {
+                S[I][2 * cp][0] += Real(a0);
+                S[I][2 * cp][1] += Real(a1);
+                S[I][2 * cp + 1][0] += Real(b0);
+                S[I][2 * cp + 1][1] += Real(b1);
+            }
+        }
+    }
+};
 
-template <int THREADS>
-__device__ __forceinline__ int opaque_tid(int t)
-{
-    asm volatile("" : "+v"(t));
-    __builtin_assume(t >= 0 && t < THREADS);
-    return t;
-}
+// 16 x 16 x 4 products; row(i, q): the row of the result in register i of lane group q
+template <typename Real> struct Mma;
+template <> struct Mma<double> {
+    typedef double Acc __attribute__((ext_vector_type(4)));
+    static __device__ __forceinline__ Acc mul(double a, double b, Acc c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
+    static __device__ __forceinline__ int row(int i, int q) { return 4 * i + q; }
+};
+template <> struct Mma<float> {
+    typedef float Acc __attribute__((ext_vector_type(4)));
+    static __device__ __forceinline__ Acc mul(float a, float b, Acc c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+    static __device__ __forceinline__ int row(int i, int q) { return 4 * q + i; }
+};
 
-__device__ __forceinline__ double wave_sum(double v)
+// acc[jt] += K[16 jt ..][y] (S K^T)[y][16 ct ..] over the row tiles part, part + parts, ..
+template <typename Real, int NF>
+__device__ __forceinline__ void project(const Real* S, const Real* ktab, int ct, int part, int lane,
+                                        typename Mma<Real>::Acc (&acc)[FG<NF>::CT])
 {
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
+    typedef Mma<Real> M;
+    typedef FG<NF> F;
+    const int i16 = lane & 15, q = lane >> 4;
+    const int ic = 3 * (16 * ct + i16) % NF;
+#pragma unroll 1
+    for (int yt = part; yt < F::YT; yt += F::PARTS) {
+        const Real* row = S + min(16 * yt + i16, NF - 1) * F::PITCH + q;
+        int d = ic - q;
+        d += d < 0 ? NF : 0;
+        typename M::Acc t = {0, 0, 0, 0};
+#pragma unroll 3
+        for (int x = 0; x < NF; x += 4) {
+            t = M::mul(row[x], ktab[d], t);
+            d -= 4;
+            d += d < 0 ? NF : 0;
+        }
+#pragma unroll
+        for (int jt = 0; jt < F::CT; ++jt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int y = 16 * yt + M::row(i, q);
+                int e = 3 * (16 * jt + i16) % NF - (y < NF ? y : 0);
+                e += e < 0 ? NF : 0;
+                acc[jt] = M::mul(y < NF ? ktab[e] : Real(0), t[i], acc[jt]);
+            }
+    }
 }
 }  // namespace
 
 template <typename Real, int NF, bool PAIR>
-__global__ void __launch_bounds__(FG<NF>::THREADS) fourier_kernel(const FourierArgs A)
+__global__ void __launch_bounds__(64 * FG<NF>::WPB) fourier_kernel(const FourierArgs A)
 {
 #pragma clang fp contract(off)
-    constexpr int THREADS = FG<NF>::THREADS, NPAIRS = FG<NF>::NPAIRS, SLOTS = FG<NF>::SLOTS;
-    constexpr int NC = FG<NF>::NC, NCC = FG<NF>::NCC, CSLOTS = FG<NF>::CSLOTS;
-    constexpr bool KAHAN = sizeof(Real) == 4;
-    constexpr int NN = NF * NF;
-    static_assert(!PAIR || (NF % 3 == 0 && NC % 2 == 0), "pairs need n = 3 n_c with n_c even");
-    static_assert(!PAIR || 2 * NCC * sizeof(Real) <= NN * sizeof(float), "projected sums must fit the normals' area");
-    __shared__ Real rho[NN];
-    __shared__ float zr[NN];                       // one direction of the normals; coarse step: Real zc[2][NCC]
-    __shared__ Real rhoc[PAIR ? NCC : 1];
-    __shared__ double red[THREADS / 64];
-    Real* zc = reinterpret_cast<Real*>(zr);
-    const int t = threadIdx.x;
-    auto opaque = [](int v) { return opaque_tid<THREADS>(v); };
-    const Real a = (Real)A.a, kf = (Real)A.kf, kc = (Real)A.kc;
-    const Real* r0f = (const Real*)A.rho0_f;
-    const Real* r0c = (const Real*)A.rho0_c;
-    const Real* K = (const Real*)A.K;
-    Real* gS = PAIR ? (Real*)A.scratch + (size_t)blockIdx.x * (2 * NN + 2 * NF * NC) : nullptr;
-    Real* gT = PAIR ? gS + 2 * NN : nullptr;
+    typedef FG<NF> F;
+    typedef Mma<Real> M;
+    constexpr int R = F::R, C = F::C, NPL = F::NPL, G = F::G, NC = F::NC, NCC = F::NCC;
+    constexpr bool WL = F::WL, COMP = std::is_same<Real, float>::value;
+    constexpr int AREA = PAIR ? F::AREA2 : F::AREA1;
+    constexpr int CSLOTS = (NCC + F::SEG * F::W - 1) / (F::SEG * F::W);    // coarse cells per lane
+    __shared__ __align__(16) Real area[F::SPB * AREA];
+    __shared__ Real zc_[PAIR ? F::SPB * 2 * NCC : 1];
+    __shared__ Real rhoc_[PAIR ? F::SPB * NCC : 1];
+    __shared__ Real ktab[PAIR ? NF : 1];
+    __shared__ double red[F::WPB * 64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    // lanes beyond the wavefront's samples repeat lane 0
+    const bool own = lane < F::SPW * F::SEG;
+    const int l = own ? lane : 0;
+    const int slot = l / F::SEG, ls = l % F::SEG;
+    const int g = (WL ? 0 : wave * F::GPW) + ls / NPL, cl = ls % NPL;
+    const int addr_l = (l - cl + (cl + NPL - 1) % NPL) * 4, addr_r = (l - cl + (cl + 1) % NPL) * 4;
+    const int row0 = R * g, col0 = C * cl;
+    const int sb = WL ? wave * F::SPW + slot : 0;            // sample of the block
+    const uint64_t local = (uint64_t)blockIdx.x * F::SPB + sb;
+    const bool active = local < A.count;
+    const uint64_t si = active ? local : 0;
+    Real* my = area + sb * AREA;
+    Real* zc = zc_ + (PAIR ? sb * 2 * NCC : 0);
+    Real* rhoc = rhoc_ + (PAIR ? sb * NCC : 0);
+    const int cc0 = WL ? ls : wave * F::SEG + ls;            // first coarse cell of the lane
 
-    for (uint64_t si = blockIdx.x; si < A.count; si += gridDim.x) {
-        const NoiseKey key = make_key(A.seed, A.tag, A.level_id, A.first + si);
-        Real cmp[SLOTS][2], S[SLOTS][4], cmpc[CSLOTS];
+    Real rho[R][C], cmp[R][C], S[PAIR ? R : 1][C][2], cmpc[CSLOTS];
+    {
+        const Real* r0 = (const Real*)A.rho0_f;
 #pragma unroll
-        for (int k = 0; k < SLOTS; ++k) {
-            const int p = t + k * THREADS;
-            cmp[k][0] = cmp[k][1] = Real(0);
-            S[k][0] = S[k][1] = S[k][2] = S[k][3] = Real(0);
-            if (p < NPAIRS) {
-                rho[2 * p] = r0f[2 * p];
-                rho[2 * p + 1] = r0f[2 * p + 1];
+        for (int i = 0; i < R; ++i)
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                rho[i][c] = r0[(row0 + i) * NF + col0 + c];
+                cmp[i][c] = Real(0);
+                if constexpr (PAIR) S[i][c][0] = S[i][c][1] = Real(0);
             }
+    }
+    if constexpr (PAIR) {
+        const Real* r0 = (const Real*)A.rho0_c;
+        for (int k = 0; k < CSLOTS; ++k) {
+            cmpc[k] = Real(0);
+            const int c = cc0 + k * F::SEG * F::W;
+            if (c < NCC) rhoc[c] = r0[c];
         }
-        if constexpr (PAIR) {
+        for (int e = threadIdx.x; e < NF; e += blockDim.x) ktab[e] = ((const Real*)A.K)[e];
+        __syncthreads();
+    }
+    const NoiseKey key = make_key(A.seed, A.tag, A.level_id, A.first + si);
+    const Real a = (Real)A.a, kf = (Real)A.kf, kc = (Real)A.kc;
+
+    auto fine_step = [&](int m) {
+        FourierNoise<Real, R, C, PAIR> fn{key, (uint32_t)m, (uint32_t)(col0 / 2 + row0 * (NF / 2)), (uint32_t)(NF / 2),
+                                          PAIR ? S : nullptr};
+        tile_step<Real, R, C, DK_FLUX_CENTRAL, COMP, true, WL>(rho, cmp, fn, a, kf, my + (m & 1) * G * 4 * NF, g, G, cl, NF, addr_l,
+                                                               addr_r);
+    };
+    if constexpr (!PAIR) {
+#pragma unroll 1
+        for (int m = 0; m < A.steps; ++m) fine_step(m);
+    } else {
+#pragma unroll 1
+        for (int m0 = 0; m0 < A.steps; m0 += 9) {
+#pragma unroll 1
+            for (int j = 0; j < 9; ++j) fine_step(m0 + j);
+            // the coarse step: its noise, one direction after the other
+            // Everything the coarse step derives from the lane index is derived again here: kept across the
+            // fine steps it would take the registers that the sums need.
+            int tid = threadIdx.x;
+            asm volatile("" : "+v"(tid));
+            const int lane = tid & 63, wave = tid >> 6;
+            const int l = lane < F::SPW * F::SEG ? lane : 0;
+            const int slot = l / F::SEG, ls = l % F::SEG;
+            const int g = (WL ? 0 : wave * F::GPW) + ls / NPL, cl = ls % NPL, row0 = R * g, col0 = C * cl;
+            const int sb = WL ? wave * F::SPW + slot : 0, cc0 = WL ? ls : wave * F::SEG + ls;
+            Real* my = area + sb * AREA;
+            Real* zc = zc_ + sb * 2 * NCC;
+            Real* rhoc = rhoc_ + sb * NCC;
+            sample_sync<WL>();                               // the last step's halo is read
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {
+#pragma unroll
+                for (int i = 0; i < R; ++i)
+#pragma unroll
+                    for (int c = 0; c < C; ++c) {
+                        my[(row0 + i) * F::PITCH + col0 + c] = S[i][c][r];
+                        S[i][c][r] = Real(0);
+                    }
+                sample_sync<WL>();
+                const int ct = WL ? 0 : wave % F::CT, part = WL ? 0 : wave / F::CT;
+                if constexpr (WL) {
+                    for (int s = 0; s < F::SPW; ++s) {       // every sample of the wavefront in turn
+                        typename M::Acc z[F::CT] = {};
+                        project<Real, NF>(area + (wave * F::SPW + s) * AREA, ktab, 0, 0, lane, z);
+                        Real* zs = zc_ + (wave * F::SPW + s) * 2 * NCC + r * NCC;
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            const int jc = M::row(i, lane >> 4), ic = lane & 15;
+                            if (jc < NC && ic < NC) zs[jc * NC + ic] = z[0][i];
+                        }
+                    }
+                    sample_sync<WL>();
+                } else {
+                    typename M::Acc z[F::CT] = {};
+                    project<Real, NF>(my, ktab, ct, part, lane, z);
+                    __syncthreads();                         // the sums are read; their place takes the partial products
+#pragma unroll
+                    for (int jt = 0; jt < F::CT; ++jt)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            my[((part * F::CT + ct) * F::CT + jt) * 256 + M::row(i, lane >> 4) * 16 + (lane & 15)] = z[jt][i];
+                    __syncthreads();
+                    for (int c = tid; c < NCC; c += 64 * F::WPB) {
+                        const int jc = c / NC, ic = c % NC;
+                        Real v = Real(0);
+#pragma unroll
+                        for (int p = 0; p < F::PARTS; ++p)
+                            v += my[((p * F::CT + ic / 16) * F::CT + jc / 16) * 256 + (jc % 16) * 16 + ic % 16];
+                        zc[r * NCC + c] = v;
+                    }
+                    __syncthreads();
+                }
+            }
+            Real nv[CSLOTS];
 #pragma unroll
             for (int k = 0; k < CSLOTS; ++k) {
-                const int c = t + k * THREADS;
-                cmpc[k] = Real(0);
-                if (c < NCC) rhoc[c] = r0c[c];
-            }
-        }
-        __syncthreads();
-
-        for (int m = 0; m < A.steps; ++m) {
-            // the thread index is made opaque in every phase: otherwise the compiler computes the
-            // cell and neighbour addresses of all slots once and keeps them in registers across
-            // the phases (and the steps)
-            int tq = opaque(t);
-            float z1[SLOTS][2];
-            Real dv[SLOTS][2];
-            // normals of the step (site pair p = cells 2p, 2p + 1); direction 0 to LDS
-#pragma unroll
-            for (int k = 0; k < SLOTS; ++k) {
-                const int p = tq + k * THREADS;
-                if (p >= NPAIRS) continue;
-                float a0, a1, b0, b1;
-                site_pair_normals(key, (uint32_t)p, (uint32_t)m, a0, a1, b0, b1);
-                zr[2 * p] = a0;
-                zr[2 * p + 1] = b0;
-                z1[k][0] = a1;
-                z1[k][1] = b1;
-                if constexpr (PAIR) {
-                    S[k][0] += (Real)a0;
-                    S[k][1] += (Real)b0;
-                    S[k][2] += (Real)a1;
-                    S[k][3] += (Real)b1;
-                }
-                tq = after(tq, b1);     // one generator call at a time
-            }
-            __syncthreads();
-            // x-divergence of sqrt(rho+) z: central difference
-            tq = opaque(t);
-#pragma unroll
-            for (int k = 0; k < SLOTS; ++k) {
-                const int p = tq + k * THREADS;
-                if (p >= NPAIRS) continue;
-                const int c = 2 * p, x = c % NF;
-                const int cl = x == 0 ? c + NF - 1 : c - 1;
-                const int cr = x + 2 == NF ? c + 2 - NF : c + 2;
-                dv[k][0] = psqr(rho[c + 1]) * (Real)zr[c + 1] - psqr(rho[cl]) * (Real)zr[cl];
-                dv[k][1] = psqr(rho[cr]) * (Real)zr[cr] - psqr(rho[c]) * (Real)zr[c];
-                tq = after(tq, dv[k][1]);
-            }
-            __syncthreads();
-            tq = opaque(t);
-#pragma unroll
-            for (int k = 0; k < SLOTS; ++k) {
-                const int p = tq + k * THREADS;
-                if (p >= NPAIRS) continue;
-                zr[2 * p] = z1[k][0];
-                zr[2 * p + 1] = z1[k][1];
-            }
-            __syncthreads();
-            // y-divergence, Laplacian and the update (new values kept in dv)
-            tq = opaque(t);
-#pragma unroll
-            for (int k = 0; k < SLOTS; ++k) {
-                const int p = tq + k * THREADS;
-                if (p >= NPAIRS) continue;
-#pragma unroll
-                for (int q = 0; q < 2; ++q) {
-                    const int c = 2 * p + q, x = c % NF, y = c / NF;
-                    const int cl = x == 0 ? c + NF - 1 : c - 1, cr = x == NF - 1 ? c + 1 - NF : c + 1;
-                    const int cu = y == 0 ? c + NN - NF : c - NF, cd = y == NF - 1 ? c + NF - NN : c + NF;
-                    const Real rv = rho[c];
-                    const Real dy = psqr(rho[cd]) * (Real)zr[cd] - psqr(rho[cu]) * (Real)zr[cu];
-                    const Real lap = fma(Real(-4), rv, (rho[cl] + rho[cr]) + (rho[cu] + rho[cd]));
-                    const Real d = fma(kf, dv[k][q] + dy, a * lap);
-                    if constexpr (KAHAN) {
-                        const Real yk = d - cmp[k][q];
-                        const Real tv = rv + yk;
-                        cmp[k][q] = (tv - rv) - yk;
-                        dv[k][q] = tv;
-                    } else {
-                        dv[k][q] = rv + d;
-                    }
-                }
-                tq = after(tq, dv[k][1]);
-            }
-            __syncthreads();
-            tq = opaque(t);
-#pragma unroll
-            for (int k = 0; k < SLOTS; ++k) {
-                const int p = tq + k * THREADS;
-                if (p >= NPAIRS) continue;
-                rho[2 * p] = dv[k][0];
-                rho[2 * p + 1] = dv[k][1];
-            }
-            if constexpr (PAIR) {
-                if (m % 9 == 8) {
-                    // the coarse step: sums of the 9 fine steps -> scratch [r][y][x]
-#pragma unroll
-                    for (int k = 0; k < SLOTS; ++k) {
-                        const int p = tq + k * THREADS;
-                        if (p < NPAIRS) {
-                            gS[2 * p] = S[k][0];
-                            gS[2 * p + 1] = S[k][1];
-                            gS[NN + 2 * p] = S[k][2];
-                            gS[NN + 2 * p + 1] = S[k][3];
-                        }
-                        S[k][0] = S[k][1] = S[k][2] = S[k][3] = Real(0);
-                    }
-                    __syncthreads();
-                    // along x: T_r[y][ic] = sum_x K[ic][x] S_r[y][x]
-                    for (int o = tq; o < 2 * NF * NC; o += THREADS) {
-                        const int r = o / (NF * NC), rem = o - r * NF * NC, y = rem / NC, ic = rem - y * NC;
-                        const Real* srow = gS + r * NN + y * NF;
-                        const Real* krow = K + ic * NF;
-                        Real acc = Real(0);
-#pragma unroll 4
-                        for (int x = 0; x < NF; ++x) acc = fma(krow[x], srow[x], acc);
-                        gT[o] = acc;
-                    }
-                    __syncthreads();
-                    // along y: Zc_r[jc][ic] = sum_y K[jc][y] T_r[y][ic]  (into the normals' LDS area)
-                    for (int o = tq; o < 2 * NCC; o += THREADS) {
-                        const int r = o / NCC, rem = o - r * NCC, jc = rem / NC, ic = rem - jc * NC;
-                        const Real* col = gT + r * NF * NC + ic;
-                        const Real* krow = K + jc * NF;
-                        Real acc = Real(0);
-#pragma unroll 4
-                        for (int y = 0; y < NF; ++y) acc = fma(krow[y], col[y * NC], acc);
-                        zc[o] = acc;
-                    }
-                    __syncthreads();
-                    Real nvc[CSLOTS];
-#pragma unroll
-                    for (int k = 0; k < CSLOTS; ++k) {
-                        const int c = tq + k * THREADS;
-                        nvc[k] = Real(0);
-                        if (c >= NCC) continue;
-                        const int x = c % NC, y = c / NC;
-                        const int cl = x == 0 ? c + NC - 1 : c - 1, cr = x == NC - 1 ? c + 1 - NC : c + 1;
-                        const int cu = y == 0 ? c + NCC - NC : c - NC, cd = y == NC - 1 ? c + NC - NCC : c + NC;
-                        const Real rv = rhoc[c];
-                        const Real dx = psqr(rhoc[cr]) * zc[cr] - psqr(rhoc[cl]) * zc[cl];
-                        const Real dy = psqr(rhoc[cd]) * zc[NCC + cd] - psqr(rhoc[cu]) * zc[NCC + cu];
-                        const Real lap = fma(Real(-4), rv, (rhoc[cl] + rhoc[cr]) + (rhoc[cu] + rhoc[cd]));
-                        const Real d = fma(kc, dx + dy, a * lap);
-                        if constexpr (KAHAN) {
-                            const Real yk = d - cmpc[k];
-                            const Real tv = rv + yk;
-                            cmpc[k] = (tv - rv) - yk;
-                            nvc[k] = tv;
-                        } else {
-                            nvc[k] = rv + d;
-                        }
-                        tq = after(tq, nvc[k]);
-                    }
-                    __syncthreads();
-#pragma unroll
-                    for (int k = 0; k < CSLOTS; ++k) {
-                        const int c = tq + k * THREADS;
-                        if (c < NCC) rhoc[c] = nvc[k];
-                    }
-                }
-            }
-            __syncthreads();
-        }
-
-        // observables of eq. (eqn_MLMCLevels): FP64 inner products, ordered block reduction
-        for (int j = 0; j < A.n_obs; ++j) {
-            for (int slot = 0; slot < (PAIR ? 2 : 1); ++slot) {
-                double acc = 0.0;
-                if (slot == 0) {
-                    const double* ph = A.phi_f + (size_t)j * NN;
-                    for (int c = t; c < NN; c += THREADS) acc = fma((double)rho[c], ph[c], acc);
+                const int c = cc0 + k * F::SEG * F::W;
+                nv[k] = Real(0);
+                if (c >= NCC) continue;
+                const int x = c % NC, y = c / NC;
+                const int xl = x == 0 ? c + NC - 1 : c - 1, xr = x == NC - 1 ? c + 1 - NC : c + 1;
+                const int yu = y == 0 ? c + NCC - NC : c - NC, yd = y == NC - 1 ? c + NC - NCC : c + NC;
+                auto flux = [&](int r, int at) { return FourierNoise<Real, R, C, PAIR>::root(rhoc[at]) * zc[r * NCC + at]; };
+                const Real rv = rhoc[c];
+                const Real dx = flux(0, xr) - flux(0, xl), dy = flux(1, yd) - flux(1, yu);
+                const Real lap = fma(Real(-4), rv, (rhoc[xl] + rhoc[xr]) + (rhoc[yu] + rhoc[yd]));
+                const Real d = fma(kc, dx + dy, a * lap);
+                if constexpr (COMP) {
+                    const Real yk = d - cmpc[k];
+                    const Real tv = rv + yk;
+                    cmpc[k] = (tv - rv) - yk;
+                    nv[k] = tv;
                 } else {
-                    const double* ph = A.phi_c + (size_t)j * NCC;
-                    for (int c = t; c < NCC; c += THREADS) acc = fma((double)rhoc[c], ph[c], acc);
+                    nv[k] = rv + d;
                 }
-                acc = wave_sum(acc);
-                if ((t & 63) == 0) red[t >> 6] = acc;
-                __syncthreads();
-                if (t == 0) {
-                    double L = 0.0;
-                    for (int w = 0; w < THREADS / 64; ++w) L += red[w];
-                    const double* ob = (slot == 0 ? A.obs_f : A.obs_c) + 3 * j;
-                    const double X = ob[0] * ((slot == 0 ? A.h2f : A.h2c) * L - ob[1]);
-                    A.out[(si * A.n_obs + j) * 2 + slot] = ob[2] != 0.0 ? X * X : X;
-                    if (!PAIR) A.out[(si * A.n_obs + j) * 2 + 1] = 0.0;
+            }
+            sample_sync<WL>();
+#pragma unroll
+            for (int k = 0; k < CSLOTS; ++k) {
+                const int c = cc0 + k * F::SEG * F::W;
+                if (c < NCC) rhoc[c] = nv[k];
+            }
+            // read again after the next coarse step's barriers
+        }
+    }
+
+    // observables of eq. (eqn_MLMCLevels): FP64 inner products; the lanes' sums in lane order, then the
+    // wavefronts' in theirs
+    __syncthreads();
+    for (int j = 0; j < A.n_obs; ++j) {
+#pragma unroll
+        for (int grid = 0; grid < (PAIR ? 2 : 1); ++grid) {
+            double acc = 0.0;
+            if (grid == 0) {
+                const double* ph = A.phi_f + (size_t)j * NF * NF;
+#pragma unroll
+                for (int i = 0; i < R; ++i)
+#pragma unroll
+                    for (int c = 0; c < C; ++c) acc = fma((double)rho[i][c], ph[(row0 + i) * NF + col0 + c], acc);
+            } else {
+                const double* ph = A.phi_c + (size_t)j * NCC;
+                for (int c = cc0; c < NCC; c += F::SEG * F::W) acc = fma((double)rhoc[c], ph[c], acc);
+            }
+            double L = 0.0;
+            if constexpr (F::SPW > 1) {
+                red[threadIdx.x] = acc;
+                sample_sync<WL>();
+                if (own && ls == 0)
+                    for (int k = 0; k < F::SEG; ++k) L += red[threadIdx.x + k];
+                sample_sync<WL>();
+            } else {
+                acc = own ? acc : 0.0;
+#pragma unroll
+                for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off, 64);
+                L = acc;
+                if constexpr (F::W > 1) {
+                    if (lane == 0) red[wave] = acc;
+                    __syncthreads();
+                    L = 0.0;
+                    for (int w = 0; w < F::W; ++w) L += red[w];
+                    __syncthreads();
                 }
-                __syncthreads();
+            }
+            if (own && active && ls == 0 && (WL || wave == 0)) {
+                const double* ob = (grid == 0 ? A.obs_f : A.obs_c) + 3 * j;
+                const double X = ob[0] * ((grid == 0 ? A.h2f : A.h2c) * L - ob[1]);
+                double* dst = A.out + (si * A.n_obs + j) * 2;
+                dst[grid] = ob[2] != 0.0 ? X * X : X;
+                if (!PAIR) dst[1] = 0.0;
             }
         }
     }
@@ -313,55 +368,49 @@ bool fourier_supported(int nf, bool pair)
 }
 
 template <int NF>
-static size_t lds_bytes(int precision)
-{
-    const size_t e = precision == DK_PREC_F64 ? 8 : 4;
-    return NF * NF * (e + 4) + (NF / 3) * (NF / 3) * e + 8 * (FG<NF>::THREADS / 64);
-}
+static int blocks_of(uint64_t count) { return (int)std::min<uint64_t>((count + FG<NF>::SPB - 1) / FG<NF>::SPB, 0x7FFFFFFFull); }
 
 int fourier_grid(int nf, int precision, uint64_t count)
 {
-    int threads = 64;
-    size_t lds = 0;
+    (void)precision;
     switch (nf) {
-    case 4: threads = FG<4>::THREADS; lds = lds_bytes<4>(precision); break;
-    case 8: threads = FG<8>::THREADS; lds = lds_bytes<8>(precision); break;
-    case 12: threads = FG<12>::THREADS; lds = lds_bytes<12>(precision); break;
-    case 24: threads = FG<24>::THREADS; lds = lds_bytes<24>(precision); break;
-    case 36: threads = FG<36>::THREADS; lds = lds_bytes<36>(precision); break;
-    case 72: threads = FG<72>::THREADS; lds = lds_bytes<72>(precision); break;
-    default: threads = FG<108>::THREADS; lds = lds_bytes<108>(precision); break;
+    case 4: return blocks_of<4>(count);
+    case 8: return blocks_of<8>(count);
+    case 12: return blocks_of<12>(count);
+    case 24: return blocks_of<24>(count);
+    case 36: return blocks_of<36>(count);
+    case 72: return blocks_of<72>(count);
+    default: return blocks_of<108>(count);
     }
-    // resident blocks per CU (160 KB of LDS, 2048 threads), 256 CUs, a few waves of blocks
-    const size_t per_cu = std::max<size_t>(1, std::min<size_t>((160u * 1024u) / lds, 2048u / threads));
-    const uint64_t cap = 256ull * per_cu * 4ull;
-    return (int)std::max<uint64_t>(1, std::min<uint64_t>(count, cap));
 }
 
-size_t fourier_scratch_elems(int nf) { return 2 * (size_t)nf * nf + 2 * (size_t)nf * (nf / 3); }
+template <typename Real, int NF, bool PAIR>
+static hipError_t launch(const FourierArgs& A, int grid, hipStream_t s)
+{
+    if ((uint64_t)grid * FG<NF>::SPB < A.count) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((fourier_kernel<Real, NF, PAIR>), dim3(grid), dim3(64 * FG<NF>::WPB), 0, s, A);
+    return hipGetLastError();
+}
 
 template <typename Real, bool PAIR>
 static hipError_t launch_nf(const FourierArgs& A, int grid, hipStream_t s)
 {
     switch (A.nf) {
-    case 4: if constexpr (!PAIR) { hipLaunchKernelGGL((fourier_kernel<Real, 4, false>), dim3(grid), dim3(FG<4>::THREADS), 0, s, A); break; } return hipErrorInvalidValue;
-    case 8: if constexpr (!PAIR) { hipLaunchKernelGGL((fourier_kernel<Real, 8, false>), dim3(grid), dim3(FG<8>::THREADS), 0, s, A); break; } return hipErrorInvalidValue;
-    case 12: hipLaunchKernelGGL((fourier_kernel<Real, 12, PAIR>), dim3(grid), dim3(FG<12>::THREADS), 0, s, A); break;
-    case 24: hipLaunchKernelGGL((fourier_kernel<Real, 24, PAIR>), dim3(grid), dim3(FG<24>::THREADS), 0, s, A); break;
-    case 36: hipLaunchKernelGGL((fourier_kernel<Real, 36, PAIR>), dim3(grid), dim3(FG<36>::THREADS), 0, s, A); break;
-    case 72: hipLaunchKernelGGL((fourier_kernel<Real, 72, PAIR>), dim3(grid), dim3(FG<72>::THREADS), 0, s, A); break;
-    case 108: hipLaunchKernelGGL((fourier_kernel<Real, 108, PAIR>), dim3(grid), dim3(FG<108>::THREADS), 0, s, A); break;
+    case 4: if constexpr (!PAIR) return launch<Real, 4, false>(A, grid, s); return hipErrorInvalidValue;
+    case 8: if constexpr (!PAIR) return launch<Real, 8, false>(A, grid, s); return hipErrorInvalidValue;
+    case 12: return launch<Real, 12, PAIR>(A, grid, s);
+    case 24: return launch<Real, 24, PAIR>(A, grid, s);
+    case 36: return launch<Real, 36, PAIR>(A, grid, s);
+    case 72: return launch<Real, 72, PAIR>(A, grid, s);
+    case 108: return launch<Real, 108, PAIR>(A, grid, s);
     default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
 }
 
 hipError_t launch_fourier(const FourierArgs& A, int precision, bool pair, int grid, hipStream_t s)
 {
-    if (!fourier_supported(A.nf, pair) || grid < 1 || (pair && (A.steps % 9 != 0 || !A.K || !A.scratch)))
-        return hipErrorInvalidValue;
-    if (precision == DK_PREC_F64)
-        return pair ? launch_nf<double, true>(A, grid, s) : launch_nf<double, false>(A, grid, s);
+    if (!fourier_supported(A.nf, pair) || grid < 1 || (pair && (A.steps % 9 != 0 || !A.K))) return hipErrorInvalidValue;
+    if (precision == DK_PREC_F64) return pair ? launch_nf<double, true>(A, grid, s) : launch_nf<double, false>(A, grid, s);
     return pair ? launch_nf<float, true>(A, grid, s) : launch_nf<float, false>(A, grid, s);
 }
 

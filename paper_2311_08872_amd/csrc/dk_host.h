@@ -85,7 +85,7 @@ struct LevelTables {
     bool have_centre = false;
     DevBuf rbar;                  // FP64 discrete mean field at the final time [n*n]
     bool have_rbar = false;
-    DevBuf fourier_K;             // Fourier pairs with this fine level: projection kernel [n/3][n], state type
+    DevBuf fourier_K;             // Fourier pairs with this fine level: projection kernel k(d) [n], state type
     DevBuf theta_tw, theta_sol;   // b0 > 0: twiddles exp(-2 pi i k/n) [n/2][2] and the solve multipliers [n][n]
 };
 
@@ -138,7 +138,6 @@ struct dk_context {
     dkh::DevBuf scratch_c;      // inner products
     dkh::DevBuf st_f[2][2], st_c[2][2];   // streaming state: [buffer][rho, cmp] fine / coarse
     dkh::DevBuf st_z;                     // streaming pairs: restricted-noise sums of split depths
-    dkh::DevBuf fourier_scratch;          // Fourier pairs: per-block sums and half-projected sums
     std::vector<double> host_mom;
     // learned control variate
     dk::cnn::Workspace cnn;

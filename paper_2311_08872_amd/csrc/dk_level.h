@@ -50,8 +50,23 @@ __device__ __forceinline__ double lane_get(int addr, double v)
     return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
+// sqrt([x]^+) in FP64: the hardware's reciprocal root (relative error 2^-24.2, measured), one Goldschmidt
+// iteration for the root and half its reciprocal (2^-47), and one residual correction, which leaves the
+// rounding of its own last operation.  Equal to the correctly rounded root on 2^24 arguments from 2^-1000
+// to 4.  The general library root also scales tiny arguments and corrects twice (18 instructions against
+// 9); here arguments below 2^-1000 count as 0, an error of at most 2^-500 of a flux.
+__device__ __forceinline__ double pos_sqrt_f64(double x)
+{
+    const double y = __builtin_amdgcn_rsq(x);
+    double g = x * y, h = 0.5 * y;
+    const double r = fma(-h, g, 0.5);
+    g = fma(g, r, g);
+    h = fma(h, r, h);
+    const double v = fma(fma(-g, g, x), h, g);
+    return x > 0x1p-1000 ? v : 0.0;
+}
 template <typename Real>
-__device__ __forceinline__ Real pos_sqrt(Real x) { return x > Real(0) ? sqrt(x) : Real(0); }
+__device__ __forceinline__ Real pos_sqrt(Real x) { return pos_sqrt_f64(x); }
 // [x]^+ as a signed integer maximum of the bits: a negative binary32 (and -0) has a negative bit
 // pattern and becomes +0, a positive one is kept; one instruction, where fmaxf in IEEE mode
 // adds a NaN-quieting step (the state is finite, so the two agree)
@@ -72,11 +87,14 @@ struct FineNoise {
     Real (*Z)[C / 2 > 0 ? C / 2 : 1][2];
     Real (*pend)[C / 2 > 0 ? C / 2 : 1][2];   // row sums waiting for the other row of their coarse cell
 
+    using W = float;         // the normals are binary32 values: FP64 states widen them where they multiply
+    static __device__ __forceinline__ Real root(Real x) { return pos_sqrt(x); }   // sqrt([x]^+) of the flux
+
     // order in which tile_step draws the rows: 0, R-1, then 1 .. R-2
     static constexpr int gen(int i) { return i == 0 ? 0 : (i == R - 1 ? 1 : i + 1); }
 
     template <int I>
-    __device__ __forceinline__ void row(Real (&w0)[C], Real (&w1)[C])
+    __device__ __forceinline__ void row(W (&w0)[C], W (&w1)[C])
     {
 #pragma unroll
         for (int cp = 0; cp < C / 2; ++cp) {
@@ -116,6 +134,8 @@ struct FineNoise {
 template <typename Real, int R, int C>
 struct CoarseNoise {
     Real (*Z)[C][2];
+    using W = Real;
+    static __device__ __forceinline__ Real root(Real x) { return pos_sqrt(x); }
     template <int I>
     __device__ __forceinline__ void row(Real (&w0)[C], Real (&w1)[C])
     {
@@ -179,7 +199,8 @@ __device__ __forceinline__ void tile_step(Real (&rho)[R][C], Real (&cmp)[R][C], 
 #pragma clang fp contract(off)
     constexpr bool BALANCE = !WAVE_LOCAL;
     progress_prio<BALANCE, 3>();
-    Real w0_first[C], w1_first[C], w0_last[C], w1_last[C];
+    using W = typename Noise::W;
+    W w0_first[C], w1_first[C], w0_last[C], w1_last[C];
     noise.template row<0>(w0_first, w1_first);
     if constexpr (R > 1) noise.template row<R - 1>(w0_last, w1_last);
     Real* top = halo + (g * 2 + 0) * 2 * NN + C * cl;
@@ -188,38 +209,40 @@ __device__ __forceinline__ void tile_step(Real (&rho)[R][C], Real (&cmp)[R][C], 
     for (int c = 0; c < C; ++c) {
         top[c] = rho[0][c];
         bot[c] = rho[R - 1][c];
-        top[NN + c] = w1_first[c];
-        bot[NN + c] = (R > 1) ? w1_last[c] : w1_first[c];
+        top[NN + c] = (Real)w1_first[c];
+        bot[NN + c] = (Real)((R > 1) ? w1_last[c] : w1_first[c]);
     }
     sample_sync<WAVE_LOCAL>();
     const int gu = g == 0 ? G - 1 : g - 1;
     const int gd = g == G - 1 ? 0 : g + 1;
     const Real* above = halo + (gu * 2 + 1) * 2 * NN + C * cl;
     const Real* below = halo + (gd * 2 + 0) * 2 * NN + C * cl;
-    Real rho_up[C], rho_dn[C], w1_up[C], w1_dn[C];
+    // FP64 states read the row below the tile one row before it is needed: its registers are short
+    // (FP32 states are 2 % faster with both rows read here)
+    constexpr bool LATE = sizeof(Real) == 8;
+    Real rho_up[C], rho_dn[C];
+    W w1_up[C], w1_dn[C];
 #pragma unroll
     for (int c = 0; c < C; ++c) {
         rho_up[c] = above[c];
-        rho_dn[c] = below[c];
-        w1_up[c] = above[NN + c];
-        w1_dn[c] = below[NN + c];
+        w1_up[c] = (W)above[NN + c];
+        if constexpr (!LATE) {
+            rho_dn[c] = below[c];
+            w1_dn[c] = (W)below[NN + c];
+        }
     }
-    // With a double-buffered halo (alternating by step) the next step writes the other buffer,
-    // and its barrier orders those writes after every lane's reads of this one.
-    if constexpr (!ONE_BARRIER) sample_sync<WAVE_LOCAL>();
-
     Real rprev[C];     // old density of row i-1
     Real F1prev[C];    // y-flux of row i-1 (central) / of edge (i-1, i) (staggered)
     Real F1cur[C];     // central: y-flux of row i (carried from the previous iteration)
-    Real w0c[C], w1c[C];
+    W w0c[C], w1c[C];
 #pragma unroll
     for (int c = 0; c < C; ++c) {
         rprev[c] = rho_up[c];
         if constexpr (FLUX == DK_FLUX_CENTRAL) {
-            F1prev[c] = pos_sqrt(rho_up[c]) * w1_up[c];
-            F1cur[c] = pos_sqrt(rho[0][c]) * w1_first[c];
+            F1prev[c] = Noise::root(rho_up[c]) * (Real)w1_up[c];
+            F1cur[c] = Noise::root(rho[0][c]) * (Real)w1_first[c];
         } else {
-            F1prev[c] = pos_sqrt(Real(0.5) * (rho_up[c] + rho[0][c])) * w1_up[c];
+            F1prev[c] = Noise::root(Real(0.5) * (rho_up[c] + rho[0][c])) * (Real)w1_up[c];
         }
         w0c[c] = w0_first[c];
         w1c[c] = w1_first[c];
@@ -228,10 +251,14 @@ __device__ __forceinline__ void tile_step(Real (&rho)[R][C], Real (&cmp)[R][C], 
     RowLoop<0, R>::run([&](auto Ic) {
         constexpr int i = decltype(Ic)::value;
         if constexpr (i >= 2 && row_prio(i, R) != row_prio(i - 1, R)) progress_prio<BALANCE, row_prio(i, R)>();
+        if constexpr (LATE && i == (R > 1 ? R - 2 : 0)) {
+#pragma unroll
+            for (int c = 0; c < C; ++c) { rho_dn[c] = below[c]; w1_dn[c] = (W)below[NN + c]; }
+        }
         Real rnext[C];
 #pragma unroll
         for (int c = 0; c < C; ++c) rnext[c] = (i + 1 < R) ? rho[(i + 1 < R) ? i + 1 : 0][c] : rho_dn[c];
-        Real w0n[C], w1n[C];
+        W w0n[C], w1n[C];
         if constexpr (i + 1 <= R - 2) {
             noise.template row<(i + 1 <= R - 2) ? i + 1 : 0>(w0n, w1n);
         } else if constexpr (i + 1 == R - 1) {
@@ -239,7 +266,7 @@ __device__ __forceinline__ void tile_step(Real (&rho)[R][C], Real (&cmp)[R][C], 
             for (int c = 0; c < C; ++c) { w0n[c] = w0_last[c]; w1n[c] = w1_last[c]; }
         } else {
 #pragma unroll
-            for (int c = 0; c < C; ++c) { w0n[c] = Real(0); w1n[c] = w1_dn[c]; }
+            for (int c = 0; c < C; ++c) { w0n[c] = W(0); w1n[c] = w1_dn[c]; }
         }
         // x-halo of the density
         const Real rl = lane_get(addr_l, rho[i][C - 1]);
@@ -249,12 +276,12 @@ __device__ __forceinline__ void tile_step(Real (&rho)[R][C], Real (&cmp)[R][C], 
 #pragma unroll
         for (int c = 0; c < C; ++c) {
             if constexpr (FLUX == DK_FLUX_CENTRAL) {
-                F0[c] = pos_sqrt(rho[i][c]) * w0c[c];
-                F1n[c] = pos_sqrt(rnext[c]) * w1n[c];
+                F0[c] = Noise::root(rho[i][c]) * (Real)w0c[c];
+                F1n[c] = Noise::root(rnext[c]) * (Real)w1n[c];
             } else {
                 const Real right = (c + 1 < C) ? rho[i][(c + 1 < C) ? c + 1 : 0] : rr;
-                F0[c] = pos_sqrt(Real(0.5) * (rho[i][c] + right)) * w0c[c];
-                F1n[c] = pos_sqrt(Real(0.5) * (rho[i][c] + rnext[c])) * w1c[c];   // edge (i, i+1)
+                F0[c] = Noise::root(Real(0.5) * (rho[i][c] + right)) * (Real)w0c[c];
+                F1n[c] = Noise::root(Real(0.5) * (rho[i][c] + rnext[c])) * (Real)w1c[c];   // edge (i, i+1)
             }
         }
         const Real F0l = lane_get(addr_l, F0[C - 1]);
@@ -299,6 +326,9 @@ __device__ __forceinline__ void tile_step(Real (&rho)[R][C], Real (&cmp)[R][C], 
             w1c[c] = w1n[c];
         }
     });
+    // With a double-buffered halo (alternating by step) the next step writes the other buffer,
+    // and its barrier orders those writes after every lane's reads of this one.
+    if constexpr (!ONE_BARRIER) sample_sync<WAVE_LOCAL>();
 }
 
 // ---------------------------------------------------------------------------------------

@@ -225,18 +225,16 @@ int run_fourier(dk_context* ctx, const dk_problem* p, int level, bool pair, uint
     const size_t esize = f64 ? 8 : 4;
     int rc;
     if (pair && !Tf->fourier_K.p) {
-        // K[ic][i] = (1/nf) [1 + 2 sum_{k=1}^{nc/2-1} cos(2 pi k d / nf) + sqrt(2) cos(pi nc d / nf)], d = 3 ic - i:
-        // projection onto the coarse frequencies (weight 2^{-1/2} on +-nc/2) read at coarse node ic
-        std::vector<double> K((size_t)nc * nf);
+        // k(d) = (1/nf) [1 + 2 sum_{j=1}^{nc/2-1} cos(2 pi j d / nf) + sqrt(2) cos(pi nc d / nf)]: projection onto
+        // the coarse frequencies (weight 2^{-1/2} on +-nc/2) read at coarse node ic is K[ic][i] = k(3 ic - i)
+        std::vector<double> K(nf);
         const double pi = 3.14159265358979323846;
-        for (int ic = 0; ic < nc; ++ic)
-            for (int i = 0; i < nf; ++i) {
-                const double d = (double)(3 * ic - i);
-                double v = 1.0;
-                for (int k = 1; k < nc / 2; ++k) v += 2.0 * std::cos(2.0 * pi * k * d / nf);
-                v += std::sqrt(2.0) * std::cos(pi * nc * d / nf);
-                K[(size_t)ic * nf + i] = v / nf;
-            }
+        for (int d = 0; d < nf; ++d) {
+            double v = 1.0;
+            for (int j = 1; j < nc / 2; ++j) v += 2.0 * std::cos(2.0 * pi * j * d / nf);
+            v += std::sqrt(2.0) * std::cos(pi * nc * d / nf);
+            K[d] = v / nf;
+        }
         if ((rc = Tf->fourier_K.ensure(esize * K.size()))) return rc;
         std::vector<float> Kf(K.begin(), K.end());
         if (f64) HIP_TRY(hipMemcpyAsync(Tf->fourier_K.p, K.data(), 8 * K.size(), hipMemcpyHostToDevice, s));
@@ -251,9 +249,6 @@ int run_fourier(dk_context* ctx, const dk_problem* p, int level, bool pair, uint
     F.h2f = A.h2f; F.h2c = A.h2c;
     F.rho0_f = A.rho0_f; F.rho0_c = A.rho0_c; F.phi_f = A.phi_f; F.phi_c = A.phi_c; F.obs_f = A.obs_f; F.obs_c = A.obs_c;
     F.K = pair ? Tf->fourier_K.p : nullptr;
-    const int grid = dk::fourier_grid(nf, p->precision, ch);
-    if (pair && (rc = ctx->fourier_scratch.ensure(esize * dk::fourier_scratch_elems(nf) * (size_t)grid))) return rc;
-    F.scratch = pair ? ctx->fourier_scratch.p : nullptr;
     while (ctx->ev_pool.size() < 2 * nchunks) {
         hipEvent_t e;
         HIP_TRY(hipEventCreate(&e));
@@ -267,7 +262,7 @@ int run_fourier(dk_context* ctx, const dk_problem* p, int level, bool pair, uint
         F.count = c;
         F.out = per_sample_out ? per_sample_out + b * nobs * 2 : (double*)ctx->per_sample.p;
         HIP_TRY(hipEventRecord(ctx->ev_pool[2 * k], s));
-        HIP_TRY(dk::launch_fourier(F, p->precision, pair, std::min(grid, dk::fourier_grid(nf, p->precision, c)), s));
+        HIP_TRY(dk::launch_fourier(F, p->precision, pair, dk::fourier_grid(nf, p->precision, c), s));
         HIP_TRY(hipEventRecord(ctx->ev_pool[2 * k + 1], s));
         HIP_TRY(dk::launch_moments(F.out, c, nobs, (double*)ctx->moments.p + k * mom_stride, s));
         if (log && nchunks > 1) {
@@ -291,7 +286,7 @@ int run_fourier(dk_context* ctx, const dk_problem* p, int level, bool pair, uint
         }
         st.launches += nchunks;
         st.samples += count;
-        st.rows = 0;   // Fourier kernel: the fine state in LDS, no tile shapes
+        st.rows = 0;   // Fourier kernel: one tile shape per grid
         st.cells += per * (double)count;
     }
     for (uint64_t k = 0; k < nchunks; ++k) {
