@@ -86,7 +86,7 @@ struct LevelTables {
     DevBuf rbar;                  // FP64 discrete mean field at the final time [n*n]
     bool have_rbar = false;
     DevBuf fourier_K;             // Fourier pairs with this fine level: projection kernel k(d) [n], state type
-    DevBuf theta_tw, theta_sol;   // b0 > 0: twiddles exp(-2 pi i k/n) [n/2][2] and the solve multipliers [n][n]
+    DevBuf theta_cas, theta_sol;  // b0 > 0: cas(2 pi k/n) [n] and the solve multipliers [n][n]
 };
 
 struct ProblemTables {

@@ -300,29 +300,27 @@ int run_fourier(dk_context* ctx, const dk_problem* p, int level, bool pair, uint
     return DK_OK;
 }
 
-// Levels with b0 > 0: per-level tables (twiddles, solve multipliers), then chunks of samples
-// with blocks striding over each chunk, the moments in chunk order.
+// Levels with b0 > 0: per-level tables (transform entries, solve multipliers), then chunks of samples,
+// the moments in chunk order.
 int theta_tables(const dk_problem* p, LevelTables* T, hipStream_t s)
 {
-    if (T->theta_tw.p) return DK_OK;
+    if (T->theta_cas.p) return DK_OK;
     const int n = T->n;
     const bool f64 = p->precision == DK_PREC_F64;
     const size_t esize = f64 ? 8 : 4;
     const double pi = 3.14159265358979323846;
-    std::vector<double> tw(n), sol((size_t)n * n);
-    for (int k = 0; k < n / 2; ++k) {
-        tw[2 * k] = std::cos(2.0 * pi * k / n);
-        tw[2 * k + 1] = -std::sin(2.0 * pi * k / n);
-    }
-    for (int ky = 0; ky < n; ++ky)
-        for (int kx = 0; kx < n; ++kx) {
-            const double sx = std::sin(pi * kx / n), sy = std::sin(pi * ky / n);
-            sol[(size_t)ky * n + kx] = 1.0 / (1.0 + 2.0 * p->b0 * p->mu * (sx * sx + sy * sy));
+    std::vector<double> cas(n), sol((size_t)n * n);
+    for (int k = 0; k < n; ++k) cas[k] = std::cos(2.0 * pi * k / n) + std::sin(2.0 * pi * k / n);
+    for (int py = 0; py < n; ++py)
+        for (int px = 0; px < n; ++px) {
+            const double sx = std::sin(pi * dk::theta_frequency(n, px) / n), sy = std::sin(pi * dk::theta_frequency(n, py) / n);
+            const double e = 2.0 * p->b0 * p->mu * (sx * sx + sy * sy);
+            sol[(size_t)py * n + px] = (f64 ? 1.0 : -e) / (1.0 + e) / ((double)n * n);
         }
     int rc;
-    if ((rc = T->theta_tw.ensure(esize * tw.size())) || (rc = T->theta_sol.ensure(esize * sol.size()))) return rc;
-    std::vector<float> twf(tw.begin(), tw.end()), solf(sol.begin(), sol.end());
-    HIP_TRY(hipMemcpyAsync(T->theta_tw.p, f64 ? (const void*)tw.data() : (const void*)twf.data(), esize * tw.size(),
+    if ((rc = T->theta_cas.ensure(esize * cas.size())) || (rc = T->theta_sol.ensure(esize * sol.size()))) return rc;
+    std::vector<float> casf(cas.begin(), cas.end()), solf(sol.begin(), sol.end());
+    HIP_TRY(hipMemcpyAsync(T->theta_cas.p, f64 ? (const void*)cas.data() : (const void*)casf.data(), esize * cas.size(),
                            hipMemcpyHostToDevice, s));
     HIP_TRY(hipMemcpyAsync(T->theta_sol.p, f64 ? (const void*)sol.data() : (const void*)solf.data(), esize * sol.size(),
                            hipMemcpyHostToDevice, s));
@@ -343,7 +341,7 @@ int run_theta(dk_context* ctx, const dk_problem* p, int level, bool pair, uint64
     F.a = A.a; F.kf = A.kf; F.kc = A.kc;
     F.h2f = A.h2f; F.h2c = A.h2c;
     F.rho0_f = A.rho0_f; F.rho0_c = A.rho0_c; F.phi_f = A.phi_f; F.phi_c = A.phi_c; F.obs_f = A.obs_f; F.obs_c = A.obs_c;
-    F.tw = Tf->theta_tw.p;
+    F.cas = Tf->theta_cas.p;
     F.sol_f = Tf->theta_sol.p;
     F.sol_c = pair ? Tc->theta_sol.p : nullptr;
     while (ctx->ev_pool.size() < 2 * nchunks) {

@@ -24,11 +24,20 @@ struct ThetaArgs {
     const double* phi_c;
     const double* obs_f;
     const double* obs_c;
-    const void* tw;         // exp(-2 pi i k / n), k < n/2: [n/2][2] (re, im), state type
-    const void* sol_f;      // 1 / (1 + 2 b0 mu (sin^2(pi kx/n) + sin^2(pi ky/n))) [n][n], state type
+    const void* cas;        // cos(2 pi k / n) + sin(2 pi k / n), k < n, state type
+    const void* sol_f;      // n^-2 s, s = 1 / (1 + 2 b0 mu (sin^2(pi kx/n) + sin^2(pi ky/n))) (FP32 state: s - 1)
+                            // [n][n], state type, the frequencies in the order of theta_frequency
     const void* sol_c;      // the same on the coarse grid [n/2][n/2]
     double* out;            // [count][n_obs][2]
 };
+
+// Frequency at position p of a transform over n points (a power of two) as the kernel leaves it: halving down
+// to 16 points, the even frequencies come first, then the odd ones.
+inline int theta_frequency(int n, int p)
+{
+    if (n <= 16) return p;
+    return p < n / 2 ? 2 * theta_frequency(n / 2, p) : 2 * (p - n / 2) + 1;
+}
 
 bool theta_supported(int n, bool pair);
 int theta_grid(int n, int precision, uint64_t count);

@@ -8,25 +8,39 @@
 // eigenvalue 1 / (1 + 2 b0 mu (sin^2(pi kx/n) + sin^2(pi ky/n))) from a host table -- and adds
 // the filtered increment with the compensated sum of the FP32 kernels (FP64: plain sum).
 // Pairs are NN-coupled (Sec. 3.2): the coarse grid takes the same scheme every 4 fine steps
-// with the restricted noise (the sum over the 2 x 2 block and the 4 steps, kept in registers
-// by the thread that owns the block, in state precision).
+// with the restricted noise (the sum over the 2 x 2 block and the 4 steps, in state precision).
 //
-// Layout: one block per sample (blocks stride over the batch), n <= 64.  LDS holds the state,
-// one direction of the step's normals (binary32, exact) and a complex work array.  The 2-D
-// transform runs one row (or column) per group of n lanes with the butterflies across lanes by
-// shuffles: rows forward, then per column the forward transform, the multiplier and the inverse
-// without leaving registers, then rows inverse -- four barriers per filter.  Decimation in time
-// from bit-reversed input for the forward transforms and in frequency to bit-reversed output
-// for the inverse ones, so each pass reads or writes its own row or column in permuted order
-// and no separate reordering is needed.  The coarse step reuses the work array (its transform
-// and its restricted noise sums use disjoint parts of it).  A thread owns 2 x 2 cell blocks (two
-// generator calls per step).
+// The filter on the matrix cores.  cas t = cos t + sin t diagonalises the periodic second difference as
+// the complex exponential does, with a real symmetric matrix C[k][x] = cas(2 pi k x/n), C C = n I, so
+// S d = n^-2 C (s .* (C d C)) C: four real n x n products.  The even frequencies of a transform over n
+// points are a transform over n/2 of the sums f(x) + f(x + n/2), the odd ones a product by n/2 columns of
+// C with the differences, down to one tile of 16: for n = 64 a product costs 24 instead of 64 instructions
+// per 16 columns.  The frequencies stay in the order this leaves (theta_frequency).
+//
+// FP32 adds d and (S - I) d, with the products on the second part only: S - I is small where the observables
+// look, at long waves, and so are the rounding errors that pass it (a sum of 32 products rounds more often
+// than five butterflies; 4000 pairs of 32 x 32 at N = 1e4: 6.8e-7 of the observable's RMS with S d, 4.2e-7 so,
+// 6.1e-7 by butterflies).
+//
+// Bound by the vector ALU (generator and addresses, two thirds of the issue slots at 64 x 64) and the FP64
+// matrix cores (a quarter); two wavefronts per SIMD overlap the two in part.  1000 pairs of 64 x 64 in FP64
+// with one lane per butterfly point: 38.3 ms; here 7.9 ms (1.5e11 cell updates/s).
+//
+// Layout: cells are owned as the products return them: register i of lane (q, c) = (lane / 16, lane % 16)
+// of a 16 x 16 tile is row M::row(i, q) of column c.  The same register is the operand B of a product that
+// contracts over those rows (C X) and, as A, of the transposed one (X^T C), so a grid of one tile goes
+// through all four products in registers: X^T C, C (.), s, (.)^T C, C (.).  A wavefront owns the n/16
+// tiles of 16 columns; between the two directions the tiles change hands through LDS.  Grids below
+// 16 x 16 share a tile, with C block-diagonal.  C's entries come from a table of n values in LDS.
+// Density and fluxes reach the neighbouring cells through two LDS planes.  The horizontal site pair of
+// one generator call lies in two neighbouring lanes: each draws one of two rows, and they swap.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
 #include <algorithm>
+#include <type_traits>
 
-#include "dk_rng.h"
+#include "dk_level.h"
 #include "dk_theta.h"
 
 namespace dk {
@@ -34,368 +48,510 @@ namespace dk {
 namespace {
 template <int N>
 struct TG {
-    static constexpr int NC = N / 2;
-    static constexpr int NB = NC * NC;                                // 2 x 2 blocks
-    static constexpr int THREADS = N >= 64 ? 512 : (N >= 32 ? 256 : 64);
-    static constexpr int SLOTS = (NB + THREADS - 1) / THREADS;
+    static constexpr int TN = N < 16 ? 16 : N;        // extent of the tiles of a wavefront group
+    static constexpr int T = TN / 16;                 // tiles per column, wavefronts of a group
+    static constexpr int SIDE = TN / N;               // samples per tile side
+    static constexpr int SLOTS = SIDE * SIDE;         // samples of a group
+    static constexpr bool WL = T == 1;                // a group inside one wavefront
+    static constexpr int WPB = WL ? 4 : T;            // wavefronts of a block
+    static constexpr int GPB = WL ? WPB : 1;          // groups of a block
+    static constexpr int SPB = GPB * SLOTS;           // samples of a block
+    // 64 x 64 in FP64: 64 KB of planes, two blocks of four wavefronts per compute unit
+    static constexpr int WAVES = T == 4 ? 2 : 4;
 };
 
-template <typename Real>
-__device__ __forceinline__ Real tpsq(Real x) { return sqrt(x > Real(0) ? x : Real(0)); }
+// 16 x 16 x 4 products; row(i, q): the row of the result in register i of lane group q
+template <typename Real> struct Mma;
+template <> struct Mma<double> {
+    typedef double Acc __attribute__((ext_vector_type(4)));
+    static __device__ __forceinline__ Acc mul(double a, double b, Acc c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
+    static constexpr __host__ __device__ int row(int i, int q) { return 4 * i + q; }
+    static __device__ __forceinline__ double root(double x) { return pos_sqrt_f64(x); }
+};
+template <> struct Mma<float> {
+    typedef float Acc __attribute__((ext_vector_type(4)));
+    static __device__ __forceinline__ Acc mul(float a, float b, Acc c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+    static constexpr __host__ __device__ int row(int i, int q) { return 4 * q + i; }
+    static __device__ __forceinline__ float root(float x) { return sqrt(x > 0.0f ? x : 0.0f); }
+};
 
-template <typename V>
-__device__ __forceinline__ int t_after(int t, V v)
-{
-    asm volatile("" : "+v"(t) : "v"(v));
-    return t;
-}
-
-__device__ __forceinline__ double t_wave_sum(double v)
-{
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
-}
-
-// Radix-2 transform of M points held one per lane, in groups of M lanes (M <= 64), butterflies
-// across lanes by shuffles.  Forward: decimation in time, input in bit-reversed order, output in
-// natural order.  Inverse (unnormalised, conjugate twiddles): decimation in frequency, input in
-// natural order, output in bit-reversed order.  l is the lane's index in its group;
-// tw[k] = exp(-2 pi i k / NT), k < NT/2, M <= NT.
-template <typename Real, int M, int NT, bool INVERSE>
-__device__ __forceinline__ void lane_fft(Real& xr, Real& xi, int l, const Real* tw)
-{
+// a sum and its rounding errors
+struct Sum {
+    double hi = 0.0, lo = 0.0;
+    __device__ __forceinline__ void add(double v, double e)
+    {
 #pragma clang fp contract(off)
-    if constexpr (!INVERSE) {
+        const double s = hi + v, b = s - hi;
+        lo += ((hi - (s - b)) + (v - b)) + e;
+        hi = s;
+    }
+};
+
+// the value of the neighbouring lane of an even-odd pair
+__device__ __forceinline__ float swap_pair(float v)
+{
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xF, 0xF, true));
+}
+
+// The lanes' view of one grid of N x N: its planes in LDS and the lane's place.  NT: length of the table of
+// C's entries (N, or 2 N for the coarse grid of a pair).
+template <typename Real, int N, int NT>
+struct Grid {
+    typedef Mma<Real> M;
+    typedef typename M::Acc Acc;
+    typedef TG<N> G;
+    static constexpr int T = G::T, TN = G::TN;
+    static constexpr bool F64 = std::is_same<Real, double>::value;
+    // Planes are [TN][P].  The 16 columns of four (FP32) or two (FP64, half a wavefront at a time) rows that
+    // one access touches lie in different banks: by the pitch for one tile, else by swapping groups of 16.
+    static constexpr int P = T == 1 && !F64 ? 20 : TN;
+    static constexpr int PLANE = TN * P;
+    static __device__ __forceinline__ int cell(int y, int x)
+    {
+        const int swap = T == 1 ? 0 : 16 * (F64 ? (y & 1) : (y >> 2) & (T - 1));
+        return y * P + (x ^ swap);
+    }
+
+    // cell(row(t, i), x), and the cells above and below it: one address for a lane and a constant, but for the
+    // rows where a sample's edge or the swap of the next four rows falls
+    __device__ __forceinline__ int at(int t, int i, int x) const
+    {
+        const int swap = T == 1 ? 0 : 16 * (F64 ? (q & 1) : q & (T - 1));
+        return M::row(0, q) * P + (x ^ swap) + (16 * t + (F64 ? 4 * i : i)) * P;
+    }
+    __device__ __forceinline__ int above(int t, int i, int x) const
+    {
+        const int y = row(t, i);
+        if (F64 ? (16 * t + 4 * i) % N == 0 : i == 0) return cell(y % N == 0 ? y + N - 1 : y - 1, x);
+        if (!F64) return at(t, i, x) - P;
+        return (q - 1) * P + (x ^ (T == 1 ? 0 : 16 * (1 - (q & 1)))) + (16 * t + 4 * i) * P;
+    }
+    __device__ __forceinline__ int below(int t, int i, int x) const
+    {
+        const int y = row(t, i);
+        if (F64 ? (16 * t + 4 * i + 4) % N == 0 : i == 3) return cell(y % N == N - 1 ? y + 1 - N : y + 1, x);
+        if (!F64) return at(t, i, x) + P;
+        return (q + 1) * P + (x ^ (T == 1 ? 0 : 16 * (1 - (q & 1)))) + (16 * t + 4 * i) * P;
+    }
+
+    Real *p0, *p1;
+    const Real* cas;           // cas(2 pi j / NT), j < NT, in LDS
+    int w, q, c;               // column tile, lane group, lane column
+    Real creg[4];              // one tile: C[row(i, q)][c], block-diagonal for N < 16
+
+    // The place is derived again for every step: the addresses that follow from it, kept across the steps,
+    // would take the registers of the tiles.
+    __device__ __forceinline__ void place()
+    {
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        w = TG<NT>::WL ? 0 : tid >> 6;
+        q = (tid >> 4) & 3;
+        c = tid & 15;
+    }
+    __device__ __forceinline__ int col() const { return 16 * w + c; }
+    __device__ __forceinline__ int row(int t, int i) const { return 16 * t + M::row(i, q); }
+
+    __device__ __forceinline__ void init()
+    {
+        if constexpr (T == 1)
 #pragma unroll
-        for (int h = 1; h < M; h <<= 1) {
-            const Real pr = __shfl_xor(xr, h, 64), pi = __shfl_xor(xi, h, 64);
-            const int k = (l & (h - 1)) * (NT / (2 * h));
-            const Real wr = tw[2 * k], wi = tw[2 * k + 1];
-            if ((l & h) == 0) {            // x[i] + w x[i + h]
-                xr = xr + (wr * pr - wi * pi);
-                xi = xi + (wr * pi + wi * pr);
-            } else {                       // x[i] - w x[i + h]
-                const Real tr = wr * xr - wi * xi, ti = wr * xi + wi * xr;
-                xr = pr - tr;
-                xi = pi - ti;
+            for (int i = 0; i < 4; ++i) {
+                const int r = M::row(i, q);
+                creg[i] = r / N == c / N ? cas[(r % N) * (c % N) * (NT / N) & (NT - 1)] : Real(0);
+            }
+    }
+
+    // D += the part of H tiles of a product with frequencies FS * position + F0 (in units of the table),
+    // the rows of X contracted: over the points (INV: the frequencies).  LEFT: D = C X, else X^T C.
+    template <int H, int FS, int F0, bool INV, bool LEFT>
+    __device__ __forceinline__ void part(const Acc* X, Acc* D) const
+    {
+#pragma unroll
+        for (int J = 0; J < H; ++J) {
+            Acc acc = {0, 0, 0, 0};
+#pragma unroll
+            for (int t = 0; t < H; ++t)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    Real e;
+                    if constexpr (T == 1) {
+                        e = creg[i];
+                    } else {
+                        const int o = 16 * J + c, k = 16 * t + M::row(i, q);
+                        e = cas[(INV ? (FS * k + F0) * o : (FS * o + F0) * k) & (NT - 1)];
+                    }
+                    acc = LEFT ? M::mul(e, X[t][i], acc) : M::mul(X[t][i], e, acc);
+                }
+            D[J] = acc;
+        }
+    }
+
+    // one direction of the transform of H tiles (16 H points of the N), forward or inverse
+    template <int H, bool INV, bool LEFT>
+    __device__ __forceinline__ void transform(const Acc* X, Acc* D) const
+    {
+        constexpr int STEP = NT / (16 * H);              // its first frequency
+        if constexpr (H == 1) {
+            part<1, STEP, 0, INV, LEFT>(X, D);
+        } else {
+            constexpr int L = H / 2;
+            Acc e[L], o[L];
+            if constexpr (!INV) {
+#pragma unroll
+                for (int t = 0; t < L; ++t) {
+                    e[t] = X[t] + X[t + L];
+                    o[t] = X[t] - X[t + L];
+                }
+                transform<L, INV, LEFT>(e, D);
+                part<L, 2 * STEP, STEP, INV, LEFT>(o, D + L);
+            } else {
+                transform<L, INV, LEFT>(X, e);
+                part<L, 2 * STEP, STEP, INV, LEFT>(X + L, o);
+#pragma unroll
+                for (int t = 0; t < L; ++t) {
+                    D[t] = e[t] + o[t];
+                    D[t + L] = e[t] - o[t];
+                }
             }
         }
-    } else {
-#pragma unroll
-        for (int h = M / 2; h >= 1; h >>= 1) {
-            const Real pr = __shfl_xor(xr, h, 64), pi = __shfl_xor(xi, h, 64);
-            const int k = (l & (h - 1)) * (NT / (2 * h));
-            const Real wr = tw[2 * k], wi = -tw[2 * k + 1];
-            if ((l & h) == 0) {            // u + v
-                xr = xr + pr;
-                xi = xi + pi;
-            } else {                       // (u - v) conj(w)
-                const Real dr = pr - xr, di = pi - xi;
-                xr = dr * wr - di * wi;
-                xi = dr * wi + di * wr;
-            }
-        }
     }
-}
 
-// re <- (1/M^2) F^-1 (sol .* F re) for a real M x M array in LDS (natural order, [y][x]); im is
-// scratch.  Rows, then columns (forward transform, the multiplier and the inverse in registers),
-// then rows again: four barriers.  Every lane takes part in every shuffle; lanes past the last
-// row or column compute on zeros and store nothing.
-template <typename Real, int M, int NT, int THREADS>
-__device__ void filter2d(Real* re, Real* im, const Real* sol, const Real* tw, int t)
-{
-#pragma clang fp contract(off)
-    constexpr int PER = 64 / M;                       // rows (columns) per wavefront
-    constexpr int LOG = __builtin_ctz(M);
-    const int lane = t & 63, l = lane & (M - 1), g = lane / M, w = t >> 6;
-    const int rl = (int)(__builtin_bitreverse32((uint32_t)l) >> (32 - LOG));
-    constexpr int WAVES = THREADS / 64;
-    __syncthreads();
-    // rows: input at bit-reversed x, output natural kx
-    for (int r0 = w * PER; r0 < M; r0 += WAVES * PER) {
-        const int row = r0 + g;
-        Real xr = row < M ? re[row * M + rl] : Real(0), xi = Real(0);
-        lane_fft<Real, M, NT, false>(xr, xi, l, tw);
-        if (row < M) { re[row * M + l] = xr; im[row * M + l] = xi; }
+    // hand the tiles over: D (this wavefront's 16 rows, all columns) -> X (all rows, its 16 columns)
+    __device__ __forceinline__ void exchange(Real* p, const Acc* D, Acc* X, bool on) const
+    {
+        if (on)
+#pragma unroll
+            for (int J = 0; J < T; ++J)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) p[cell(16 * w + M::row(i, q), 16 * J + c)] = D[J][i];
+        __syncthreads();
+        if (on)
+#pragma unroll
+            for (int t = 0; t < T; ++t)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) X[t][i] = p[at(t, i, col())];
     }
-    __syncthreads();
-    // columns: forward from bit-reversed ky, multiplier, inverse to bit-reversed y
-    for (int c0 = w * PER; c0 < M; c0 += WAVES * PER) {
-        const int col = c0 + g;
-        Real xr = Real(0), xi = Real(0);
-        if (col < M) { xr = re[rl * M + col]; xi = im[rl * M + col]; }
-        lane_fft<Real, M, NT, false>(xr, xi, l, tw);
-        if (col < M) {
-            const Real sv = sol[l * M + col];
-            xr = xr * sv;
-            xi = xi * sv;
+
+    // v <- S v (FP32: S v - v); sol: [position of kx][position of ky], 1 / N^2 included.  Every wavefront of a block comes
+    // here; those that are not `on` own no tile of this grid.  Issued ahead of the other wavefronts' vector work,
+    // so that the matrix cores' queue does not run dry (1000 pairs of 64 x 64: 9.5 to 8.5 ms).
+    __device__ __forceinline__ void filter(Acc (&v)[T], const Real* __restrict__ sol, bool on) const
+    {
+        Acc u[T];
+        __builtin_amdgcn_s_setprio(2);
+        if (on) transform<T, false, false>(v, u);
+        if constexpr (T > 1) exchange(p0, u, v, on);
+        if (on) {
+            if constexpr (T == 1) v[0] = u[0];
+            transform<T, false, true>(v, u);
+#pragma unroll
+            for (int t = 0; t < T; ++t)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) u[t][i] *= sol[(row(t, i) % N) * N + col() % N];
+            transform<T, true, false>(u, v);
         }
-        lane_fft<Real, M, NT, true>(xr, xi, l, tw);
-        if (col < M) { re[rl * M + col] = xr; im[rl * M + col] = xi; }
+        if constexpr (T > 1) exchange(p1, v, u, on);
+        if (on) {
+            if constexpr (T == 1) u[0] = v[0];
+            transform<T, true, true>(u, v);
+        }
+        __builtin_amdgcn_s_setprio(0);
     }
-    __syncthreads();
-    // rows: inverse from natural kx to bit-reversed x; real part, scaled
-    for (int r0 = w * PER; r0 < M; r0 += WAVES * PER) {
-        const int row = r0 + g;
-        Real xr = Real(0), xi = Real(0);
-        if (row < M) { xr = re[row * M + l]; xi = im[row * M + l]; }
-        lane_fft<Real, M, NT, true>(xr, xi, l, tw);
-        if (row < M) re[row * M + rl] = xr * (Real(1) / Real(M * M));
+
+    // d <- the explicit increment of rho with the unit noise w0, w1 (float: fine normals; Real: restricted
+    // sums).  The first barrier ends the reads of the planes before it.
+    template <bool WL, typename NW>
+    __device__ __forceinline__ void increment(const Real (&rho)[T][4], const NW (&w0)[T][4], const NW (&w1)[T][4], Real a,
+                                              Real kappa, Acc (&d)[T], bool on) const
+    {
+#pragma clang fp contract(off)
+        Real f1[T][4], dx[T][4];
+        const int x = col(), xl = x % N == 0 ? x + N - 1 : x - 1, xr = x % N == N - 1 ? x + 1 - N : x + 1;
+        sample_sync<WL>();
+        if (on)
+#pragma unroll
+            for (int t = 0; t < T; ++t)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int k = at(t, i, x);
+                    const Real s = M::root(rho[t][i]);
+                    p0[k] = rho[t][i];
+                    p1[k] = s * (Real)w0[t][i];
+                    f1[t][i] = s * (Real)w1[t][i];
+                }
+        sample_sync<WL>();
+        if (on)
+#pragma unroll
+            for (int t = 0; t < T; ++t)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int l = at(t, i, xl), r = at(t, i, xr);
+                    const Real lap = fma(Real(-4), rho[t][i], (p0[l] + p0[r]) + (p0[above(t, i, x)] + p0[below(t, i, x)]));
+                    d[t][i] = a * lap;
+                    dx[t][i] = p1[r] - p1[l];
+                }
+        sample_sync<WL>();
+        if (on)
+#pragma unroll
+            for (int t = 0; t < T; ++t)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) p1[at(t, i, x)] = f1[t][i];
+        sample_sync<WL>();
+        if (on)
+#pragma unroll
+            for (int t = 0; t < T; ++t)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const Real dy = p1[below(t, i, x)] - p1[above(t, i, x)];
+                    d[t][i] = fma(kappa, dx[t][i] + dy, d[t][i]);
+                }
     }
-    __syncthreads();
-}
+
+    // rho += u
+    static __device__ __forceinline__ void advance(Real (&rho)[T][4], Real (&cmp)[T][4], const Acc (&u)[T])
+    {
+#pragma clang fp contract(off)
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if constexpr (F64) {
+                    rho[t][i] = rho[t][i] + u[t][i];
+                } else {
+                    const Real yk = u[t][i] - cmp[t][i];
+                    const Real tv = rho[t][i] + yk;
+                    cmp[t][i] = (tv - rho[t][i]) - yk;
+                    rho[t][i] = tv;
+                }
+            }
+    }
+
+    // sum of rho * phi over the sample in row sr of the tile's samples, valid in the lanes of lane group 0.
+    // Products and sums carry their rounding errors: the centring that follows cancels most digits.
+    __device__ __forceinline__ Sum inner(const Real (&rho)[T][4], const double* __restrict__ phi, int sr, bool on) const
+    {
+        Sum acc;
+        if (on)
+#pragma unroll
+            for (int t = 0; t < T; ++t)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int y = row(t, i);
+                    if (T == 1 && y / N != sr) continue;
+                    const double r = (double)rho[t][i], f = phi[(y % N) * N + col() % N], v = r * f;
+                    acc.add(v, fma(r, f, -v));
+                }
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1)
+            if (off >= 16 || off < N) acc.add(__shfl_xor(acc.hi, off, 64), __shfl_xor(acc.lo, off, 64));
+        return acc;
+    }
+};
 }  // namespace
 
 template <typename Real, int N, bool PAIR>
-__global__ void __launch_bounds__(TG<N>::THREADS) theta_kernel(const ThetaArgs A)
+__global__ void __launch_bounds__(64 * TG<N>::WPB, TG<N>::WAVES) theta_kernel(const ThetaArgs A)
 {
 #pragma clang fp contract(off)
-    constexpr int THREADS = TG<N>::THREADS, NC = TG<N>::NC, NB = TG<N>::NB, SLOTS = TG<N>::SLOTS;
-    constexpr int NN = N * N, NCC = NC * NC;
-    constexpr bool KAHAN = sizeof(Real) == 4;
-    __shared__ Real rho[NN];
-    __shared__ float zr[NN];
-    __shared__ Real wre[NN], wim[NN];
-    __shared__ Real rhoc[PAIR ? NCC : 1];
-    __shared__ double red[THREADS / 64];
-    Real* zc0 = wre + NCC;                     // coarse step: restricted sums beside the coarse transform
-    Real* zc1 = wre + 2 * NCC;
-    const int t = threadIdx.x;
+    constexpr int NC = PAIR ? N / 2 : N;                     // single paths: names a grid that is not used
+    typedef TG<N> G;
+    typedef Grid<Real, N, N> Fine;
+    typedef Grid<Real, NC, N> Coarse;
+    constexpr int T = G::T, TC = Coarse::T, TN = G::TN;
+    constexpr bool WL = G::WL;
+    constexpr int PLANE = Fine::PLANE > Coarse::PLANE ? Fine::PLANE : Coarse::PLANE;
+    __shared__ Real planes[G::GPB * 2 * PLANE];
+    __shared__ Real cas[N];
+    __shared__ double red[G::WPB][2];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int q = lane >> 4, c = lane & 15, w = WL ? 0 : wave, p = c & 1;
+    Real* p0 = planes + (WL ? wave : 0) * 2 * PLANE;
+    Fine F{p0, p0 + PLANE, cas, w, q, c, {}};
+    Coarse K{p0, p0 + PLANE, cas, w, q, c, {}};
+    const bool on_c = w < TC;                                // wavefronts that own a tile of the coarse grid
     const Real a = (Real)A.a, kf = (Real)A.kf, kc = (Real)A.kc;
-    const Real* r0f = (const Real*)A.rho0_f;
-    const Real* r0c = (const Real*)A.rho0_c;
-    const Real* tw = (const Real*)A.tw;
-    const Real* solf = (const Real*)A.sol_f;
-    const Real* solc = (const Real*)A.sol_c;
 
-    for (uint64_t si = blockIdx.x; si < A.count; si += gridDim.x) {
-        const NoiseKey key = make_key(A.seed, A.tag, A.level_id, A.first + si);
-        Real cmp[SLOTS][4], Z[SLOTS][2], cmpc[SLOTS];
+    for (int e = threadIdx.x; e < N; e += blockDim.x) cas[e] = ((const Real*)A.cas)[e];
+    __syncthreads();
+    F.init();
+    if constexpr (PAIR) K.init();
+
+    // sample of a tile slot; slots past the batch repeat its first sample and write nothing
+    const uint64_t base = ((uint64_t)blockIdx.x * G::GPB + (WL ? wave : 0)) * G::SLOTS;
+    auto sample = [&](int y, int x) { return base + (uint64_t)((y / N) * G::SIDE + x / N); };
+
+    Real rho[T][4], cmp[T][4], rhoc[TC][4], cmpc[TC][4];
+    Real Z[PAIR ? T : 1][2][2];                              // sums over the drawn site pairs and the steps
 #pragma unroll
-        for (int k = 0; k < SLOTS; ++k) {
-            const int bq = t + k * THREADS;
-            cmp[k][0] = cmp[k][1] = cmp[k][2] = cmp[k][3] = Real(0);
-            Z[k][0] = Z[k][1] = Real(0);
-            cmpc[k] = Real(0);
-            if (bq < NB) {
-                const int bx = bq % NC, by = bq / NC;
+    for (int t = 0; t < T; ++t) {
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int c = (2 * by + (q >> 1)) * N + 2 * bx + (q & 1);
-                    rho[c] = r0f[c];
-                }
-                if (PAIR) rhoc[bq] = r0c[bq];
-            }
+        for (int i = 0; i < 4; ++i) {
+            rho[t][i] = ((const Real*)A.rho0_f)[(F.row(t, i) % N) * N + F.col() % N];
+            cmp[t][i] = Real(0);
         }
-        __syncthreads();
+        if constexpr (PAIR) Z[t][0][0] = Z[t][0][1] = Z[t][1][0] = Z[t][1][1] = Real(0);
+    }
+    if constexpr (PAIR)
+#pragma unroll
+        for (int t = 0; t < TC; ++t)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                rhoc[t][i] = on_c ? ((const Real*)A.rho0_c)[(K.row(t, i) % NC) * NC + K.col() % NC] : Real(0);
+                cmpc[t][i] = Real(0);
+            }
+    // rows 16 t + row(2 d + p, q), d = 0, 1, are the lane's to draw
+    NoiseKey key[2];
+#pragma unroll
+    for (int d = 0; d < 2; ++d) {
+        const uint64_t s = sample(Mma<Real>::row(2 * d + p, q), F.col());
+        key[d] = make_key(A.seed, A.tag, A.level_id, A.first + (s < A.count ? s : 0));
+    }
 
-        for (int m = 0; m < A.steps; ++m) {
-            int tq = t;
-            float z1[SLOTS][4];
-            Real dv[SLOTS][4];
-            // normals of the 2 x 2 blocks; direction 0 to LDS
+#pragma unroll 1
+    for (int m = 0; m < A.steps; ++m) {
+        F.place();
+        const int q = F.q, p = F.c & 1;
+        float w0[T][4], w1[T][4];
 #pragma unroll
-            for (int k = 0; k < SLOTS; ++k) {
-                const int bq = tq + k * THREADS;
-                if (bq >= NB) continue;
-                const int bx = bq % NC, by = bq / NC;
-                float w0[4], w1[4];
+        for (int t = 0; t < T; ++t)
 #pragma unroll
-                for (int r = 0; r < 2; ++r) {
-                    float a0, a1, b0, b1;
-                    site_pair_normals(key, (uint32_t)(bx + NC * (2 * by + r)), (uint32_t)m, a0, a1, b0, b1);
-                    w0[2 * r] = a0; w1[2 * r] = a1; w0[2 * r + 1] = b0; w1[2 * r + 1] = b1;
-                }
+            for (int d = 0; d < 2; ++d) {
+                const int y = 16 * t + Mma<Real>::row(2 * d + p, q);
+                uint32_t idx = (uint32_t)((F.col() % N) / 2 + (N / 2) * (y % N));
+                asm volatile("" : "+v"(idx));                // recomputed every step rather than kept live
+                float a0, a1, b0, b1;
+                site_pair_normals(key[G::SIDE > 1 ? d : 0], idx, (uint32_t)m, a0, a1, b0, b1);
                 if constexpr (PAIR) {
-                    Z[k][0] += ((Real)w0[0] + (Real)w0[1]) + ((Real)w0[2] + (Real)w0[3]);
-                    Z[k][1] += ((Real)w1[0] + (Real)w1[1]) + ((Real)w1[2] + (Real)w1[3]);
+                    Z[t][d][0] += (Real)a0 + (Real)b0;
+                    Z[t][d][1] += (Real)a1 + (Real)b1;
                 }
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    zr[(2 * by + (q >> 1)) * N + 2 * bx + (q & 1)] = w0[q];
-                    z1[k][q] = w1[q];
-                }
-                tq = t_after(tq, w1[3]);
+                const float r0 = swap_pair(p ? a0 : b0), r1 = swap_pair(p ? a1 : b1);
+                w0[t][2 * d] = p ? r0 : a0;
+                w0[t][2 * d + 1] = p ? b0 : r0;
+                w1[t][2 * d] = p ? r1 : a1;
+                w1[t][2 * d + 1] = p ? b1 : r1;
             }
-            __syncthreads();
-            tq = t;
-            // x-divergence of sqrt(rho+) z (central difference)
+        typename Fine::Acc u[T];
+        F.template increment<WL, float>(rho, w0, w1, a, kf, u, true);
+        if constexpr (!Fine::F64) Fine::advance(rho, cmp, u);
+        F.filter(u, (const Real*)A.sol_f, true);
+        Fine::advance(rho, cmp, u);
+        if constexpr (PAIR) {
+            if ((m & 3) == 3) {
+                constexpr int H = TN / 2;                    // the coarse cells are the first H rows and columns
+                F.place();
+                K.place();
+                const int q = F.q, p = F.c & 1;
+                sample_sync<WL>();                           // the planes are read
 #pragma unroll
-            for (int k = 0; k < SLOTS; ++k) {
-                const int bq = tq + k * THREADS;
-                if (bq >= NB) continue;
-                const int bx = bq % NC, by = bq / NC;
+                for (int t = 0; t < T; ++t)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int x = 2 * bx + (q & 1), y = 2 * by + (q >> 1), c = y * N + x;
-                    const int cl = x == 0 ? c + N - 1 : c - 1, cr = x == N - 1 ? c + 1 - N : c + 1;
-                    dv[k][q] = tpsq(rho[cr]) * (Real)zr[cr] - tpsq(rho[cl]) * (Real)zr[cl];
-                }
-                tq = t_after(tq, dv[k][3]);
-            }
-            __syncthreads();
-            tq = t;
-#pragma unroll
-            for (int k = 0; k < SLOTS; ++k) {
-                const int bq = tq + k * THREADS;
-                if (bq >= NB) continue;
-                const int bx = bq % NC, by = bq / NC;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) zr[(2 * by + (q >> 1)) * N + 2 * bx + (q & 1)] = z1[k][q];
-            }
-            __syncthreads();
-            tq = t;
-            // the explicit increment d, written to bit-reversed positions of the work array
-#pragma unroll
-            for (int k = 0; k < SLOTS; ++k) {
-                const int bq = tq + k * THREADS;
-                if (bq >= NB) continue;
-                const int bx = bq % NC, by = bq / NC;
-                Real dlast = Real(0);
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int x = 2 * bx + (q & 1), y = 2 * by + (q >> 1), c = y * N + x;
-                    const int cl = x == 0 ? c + N - 1 : c - 1, cr = x == N - 1 ? c + 1 - N : c + 1;
-                    const int cu = y == 0 ? c + NN - N : c - N, cd = y == N - 1 ? c + N - NN : c + N;
-                    const Real rv = rho[c];
-                    const Real dy = tpsq(rho[cd]) * (Real)zr[cd] - tpsq(rho[cu]) * (Real)zr[cu];
-                    const Real lap = fma(Real(-4), rv, (rho[cl] + rho[cr]) + (rho[cu] + rho[cd]));
-                    const Real d = fma(kf, dv[k][q] + dy, a * lap);
-                    wre[c] = d;
-                    dlast = d;
-                }
-                tq = t_after(tq, dlast);
-            }
-            filter2d<Real, N, N, THREADS>(wre, wim, solf, tw, t);
-            // rho += S d (own cells only: every read of rho this step is behind a barrier)
-            tq = t;
-#pragma unroll
-            for (int k = 0; k < SLOTS; ++k) {
-                const int bq = tq + k * THREADS;
-                if (bq >= NB) continue;
-                const int bx = bq % NC, by = bq / NC;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int x = 2 * bx + (q & 1), y = 2 * by + (q >> 1), c = y * N + x;
-                    const Real u = wre[c];
-                    const Real rv = rho[c];
-                    if constexpr (KAHAN) {
-                        const Real yk = u - cmp[k][q];
-                        const Real tv = rv + yk;
-                        cmp[k][q] = (tv - rv) - yk;
-                        rho[c] = tv;
-                    } else {
-                        rho[c] = rv + u;
+                    for (int d = 0; d < 2; ++d) {
+                        const int k = (16 * t + Mma<Real>::row(2 * d + p, q)) * H + F.col() / 2;
+                        F.p0[k] = Z[t][d][0];
+                        F.p1[k] = Z[t][d][1];
+                        Z[t][d][0] = Z[t][d][1] = Real(0);
                     }
-                }
-            }
-            if constexpr (PAIR) {
-                if ((m & 3) == 3) {
-                    __syncthreads();          // the work array is read above
+                sample_sync<WL>();
+                Real z0[TC][4], z1[TC][4];
 #pragma unroll
-                    for (int k = 0; k < SLOTS; ++k) {
-                        const int bq = t + k * THREADS;
-                        if (bq < NB) {
-                            zc0[bq] = Z[k][0];
-                            zc1[bq] = Z[k][1];
-                        }
-                        Z[k][0] = Z[k][1] = Real(0);
-                    }
-                    __syncthreads();
+                for (int t = 0; t < TC; ++t)
 #pragma unroll
-                    for (int k = 0; k < SLOTS; ++k) {
-                        const int c = t + k * THREADS;
-                        if (c >= NCC) continue;
-                        const int x = c % NC, y = c / NC;
-                        const int cl = x == 0 ? c + NC - 1 : c - 1, cr = x == NC - 1 ? c + 1 - NC : c + 1;
-                        const int cu = y == 0 ? c + NCC - NC : c - NC, cd = y == NC - 1 ? c + NC - NCC : c + NC;
-                        const Real rv = rhoc[c];
-                        const Real dx = tpsq(rhoc[cr]) * zc0[cr] - tpsq(rhoc[cl]) * zc0[cl];
-                        const Real dy = tpsq(rhoc[cd]) * zc1[cd] - tpsq(rhoc[cu]) * zc1[cu];
-                        const Real lap = fma(Real(-4), rv, (rhoc[cl] + rhoc[cr]) + (rhoc[cu] + rhoc[cd]));
-                        const Real d = fma(kc, dx + dy, a * lap);
-                        wre[c] = d;
+                    for (int i = 0; i < 4; ++i) {
+                        const int y = K.row(t, i), x = K.col(), k = 2 * y * H + x;
+                        const bool in = y < H && x < H;
+                        z0[t][i] = in ? F.p0[k] + F.p0[k + H] : Real(0);
+                        z1[t][i] = in ? F.p1[k] + F.p1[k + H] : Real(0);
                     }
-                    filter2d<Real, NC, N, THREADS>(wre, wim, solc, tw, t);
-#pragma unroll
-                    for (int k = 0; k < SLOTS; ++k) {
-                        const int c = t + k * THREADS;
-                        if (c >= NCC) continue;
-                        const int x = c % NC, y = c / NC;
-                        const Real u = wre[c];
-                        const Real rv = rhoc[c];
-                        if constexpr (KAHAN) {
-                            const Real yk = u - cmpc[k];
-                            const Real tv = rv + yk;
-                            cmpc[k] = (tv - rv) - yk;
-                            rhoc[c] = tv;
-                        } else {
-                            rhoc[c] = rv + u;
-                        }
-                    }
-                }
-            }
-            __syncthreads();
-        }
-
-        // observables of eq. (eqn_MLMCLevels): FP64 inner products, ordered block reduction
-        for (int j = 0; j < A.n_obs; ++j) {
-            for (int slot = 0; slot < (PAIR ? 2 : 1); ++slot) {
-                double acc = 0.0;
-                if (slot == 0) {
-                    const double* ph = A.phi_f + (size_t)j * NN;
-                    for (int c = t; c < NN; c += THREADS) acc = fma((double)rho[c], ph[c], acc);
-                } else {
-                    const double* ph = A.phi_c + (size_t)j * NCC;
-                    for (int c = t; c < NCC; c += THREADS) acc = fma((double)rhoc[c], ph[c], acc);
-                }
-                acc = t_wave_sum(acc);
-                if ((t & 63) == 0) red[t >> 6] = acc;
-                __syncthreads();
-                if (t == 0) {
-                    double L = 0.0;
-                    for (int w = 0; w < THREADS / 64; ++w) L += red[w];
-                    const double* ob = (slot == 0 ? A.obs_f : A.obs_c) + 3 * j;
-                    const double X = ob[0] * ((slot == 0 ? A.h2f : A.h2c) * L - ob[1]);
-                    A.out[(si * A.n_obs + j) * 2 + slot] = ob[2] != 0.0 ? X * X : X;
-                    if (!PAIR) A.out[(si * A.n_obs + j) * 2 + 1] = 0.0;
-                }
-                __syncthreads();
+                typename Coarse::Acc v[TC];
+                K.template increment<WL, Real>(rhoc, z0, z1, a, kc, v, on_c);
+                if constexpr (!Fine::F64)
+                    if (on_c) Coarse::advance(rhoc, cmpc, v);
+                K.filter(v, (const Real*)A.sol_c, on_c);
+                if (on_c) Coarse::advance(rhoc, cmpc, v);
             }
         }
     }
+
+    // observables of eq. (eqn_MLMCLevels): FP64 inner products, the wavefronts' sums in their order
+    auto write = [&](int j, int grid, uint64_t si, Sum L) {
+        const double* ob = (grid == 0 ? A.obs_f : A.obs_c) + 3 * j;
+        const double h2 = grid == 0 ? A.h2f : A.h2c, X = ob[0] * (fma(h2, L.hi, -ob[1]) + h2 * L.lo);
+        double* dst = A.out + (si * A.n_obs + j) * 2;
+        dst[grid] = ob[2] != 0.0 ? X * X : X;
+        if (!PAIR) dst[1] = 0.0;
+    };
+    for (int j = 0; j < A.n_obs; ++j)
+#pragma unroll
+        for (int grid = 0; grid < (PAIR ? 2 : 1); ++grid)
+#pragma unroll 1
+            for (int sr = 0; sr < G::SIDE; ++sr) {
+                Sum L;
+                if (grid == 0) L = F.inner(rho, A.phi_f + (size_t)j * N * N, sr, true);
+                else L = K.inner(rhoc, A.phi_c + (size_t)j * NC * NC, sr, on_c);
+                const int n = grid == 0 ? N : NC;
+                if constexpr (WL) {
+                    const int sc = c / n;
+                    const uint64_t si = base + (uint64_t)(sr * G::SIDE + sc);
+                    if (q == 0 && c % n == 0 && sc < G::SIDE && si < A.count) write(j, grid, si, L);
+                } else {
+                    if (lane == 0) {
+                        red[wave][0] = L.hi;
+                        red[wave][1] = L.lo;
+                    }
+                    __syncthreads();
+                    if (threadIdx.x == 0) {
+                        Sum sum;
+                        for (int k = 0; k < (grid == 0 ? T : TC); ++k) sum.add(red[k][0], red[k][1]);
+                        if (base < A.count) write(j, grid, base, sum);
+                    }
+                    __syncthreads();
+                }
+            }
 }
 
 bool theta_supported(int n, bool pair) { return (n == 4 && !pair) || n == 8 || n == 16 || n == 32 || n == 64; }
 
+template <int N>
+static int blocks_of(uint64_t count) { return (int)std::min<uint64_t>((count + TG<N>::SPB - 1) / TG<N>::SPB, 0x7FFFFFFFull); }
+
 int theta_grid(int n, int precision, uint64_t count)
 {
-    const size_t e = precision == DK_PREC_F64 ? 8 : 4;
-    const size_t lds = (size_t)n * n * (3 * e + 4) + (size_t)(n / 2) * (n / 2) * e + 64;
-    const int threads = n >= 64 ? 512 : (n >= 32 ? 256 : 64);
-    const size_t per_cu = std::max<size_t>(1, std::min<size_t>((160u * 1024u) / lds, 2048u / threads));
-    const uint64_t cap = 256ull * per_cu * 4ull;
-    return (int)std::max<uint64_t>(1, std::min<uint64_t>(count, cap));
+    (void)precision;
+    switch (n) {
+    case 4: return blocks_of<4>(count);
+    case 8: return blocks_of<8>(count);
+    case 16: return blocks_of<16>(count);
+    case 32: return blocks_of<32>(count);
+    default: return blocks_of<64>(count);
+    }
+}
+
+template <typename Real, int N, bool PAIR>
+static hipError_t launch(const ThetaArgs& A, int grid, hipStream_t s)
+{
+    if ((uint64_t)grid * TG<N>::SPB < A.count) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((theta_kernel<Real, N, PAIR>), dim3(grid), dim3(64 * TG<N>::WPB), 0, s, A);
+    return hipGetLastError();
 }
 
 template <typename Real, bool PAIR>
 static hipError_t launch_n(const ThetaArgs& A, int grid, hipStream_t s)
 {
     switch (A.n) {
-    case 4: if constexpr (!PAIR) { hipLaunchKernelGGL((theta_kernel<Real, 4, false>), dim3(grid), dim3(TG<4>::THREADS), 0, s, A); break; } return hipErrorInvalidValue;
-    case 8: hipLaunchKernelGGL((theta_kernel<Real, 8, PAIR>), dim3(grid), dim3(TG<8>::THREADS), 0, s, A); break;
-    case 16: hipLaunchKernelGGL((theta_kernel<Real, 16, PAIR>), dim3(grid), dim3(TG<16>::THREADS), 0, s, A); break;
-    case 32: hipLaunchKernelGGL((theta_kernel<Real, 32, PAIR>), dim3(grid), dim3(TG<32>::THREADS), 0, s, A); break;
-    case 64: hipLaunchKernelGGL((theta_kernel<Real, 64, PAIR>), dim3(grid), dim3(TG<64>::THREADS), 0, s, A); break;
+    case 4: if constexpr (!PAIR) return launch<Real, 4, false>(A, grid, s); return hipErrorInvalidValue;
+    case 8: return launch<Real, 8, PAIR>(A, grid, s);
+    case 16: return launch<Real, 16, PAIR>(A, grid, s);
+    case 32: return launch<Real, 32, PAIR>(A, grid, s);
+    case 64: return launch<Real, 64, PAIR>(A, grid, s);
     default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
 }
 
 hipError_t launch_theta(const ThetaArgs& A, int precision, bool pair, int grid, hipStream_t s)
 {
-    if (!theta_supported(A.n, pair) || grid < 1 || (pair && A.steps % 4 != 0) || !A.tw || !A.sol_f || (pair && !A.sol_c))
+    if (!theta_supported(A.n, pair) || grid < 1 || (pair && A.steps % 4 != 0) || !A.cas || !A.sol_f || (pair && !A.sol_c))
         return hipErrorInvalidValue;
     if (precision == DK_PREC_F64) return pair ? launch_n<double, true>(A, grid, s) : launch_n<double, false>(A, grid, s);
     return pair ? launch_n<float, true>(A, grid, s) : launch_n<float, false>(A, grid, s);
