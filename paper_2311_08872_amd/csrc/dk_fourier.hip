@@ -35,6 +35,7 @@
 
 #include "dk_fourier.h"
 #include "dk_level.h"
+#include "dk_sum.h"
 
 namespace dk {
 
@@ -162,7 +163,7 @@ __global__ void __launch_bounds__(64 * FG<NF>::WPB) fourier_kernel(const Fourier
     __shared__ Real zc_[PAIR ? F::SPB * 2 * NCC : 1];
     __shared__ Real rhoc_[PAIR ? F::SPB * NCC : 1];
     __shared__ Real ktab[PAIR ? NF : 1];
-    __shared__ double red[F::WPB * 64];
+    __shared__ double red[F::SPW > 1 ? F::WPB * 64 : F::WPB][2];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     // lanes beyond the wavefront's samples repeat lane 0
     const bool own = lane < F::SPW * F::SEG;
@@ -316,40 +317,45 @@ __global__ void __launch_bounds__(64 * FG<NF>::WPB) fourier_kernel(const Fourier
     for (int j = 0; j < A.n_obs; ++j) {
 #pragma unroll
         for (int grid = 0; grid < (PAIR ? 2 : 1); ++grid) {
-            double acc = 0.0;
+            Sum acc;
             if (grid == 0) {
                 const double* ph = A.phi_f + (size_t)j * NF * NF;
 #pragma unroll
                 for (int i = 0; i < R; ++i)
 #pragma unroll
-                    for (int c = 0; c < C; ++c) acc = fma((double)rho[i][c], ph[(row0 + i) * NF + col0 + c], acc);
+                    for (int c = 0; c < C; ++c) acc.add_product((double)rho[i][c], ph[(row0 + i) * NF + col0 + c]);
             } else {
                 const double* ph = A.phi_c + (size_t)j * NCC;
-                for (int c = cc0; c < NCC; c += F::SEG * F::W) acc = fma((double)rhoc[c], ph[c], acc);
+                for (int c = cc0; c < NCC; c += F::SEG * F::W) acc.add_product((double)rhoc[c], ph[c]);
             }
-            double L = 0.0;
+            Sum L;
             if constexpr (F::SPW > 1) {
-                red[threadIdx.x] = acc;
+                red[threadIdx.x][0] = acc.hi;
+                red[threadIdx.x][1] = acc.lo;
                 sample_sync<WL>();
                 if (own && ls == 0)
-                    for (int k = 0; k < F::SEG; ++k) L += red[threadIdx.x + k];
+                    for (int k = 0; k < F::SEG; ++k) L.add(red[threadIdx.x + k][0], red[threadIdx.x + k][1]);
                 sample_sync<WL>();
             } else {
-                acc = own ? acc : 0.0;
+                acc.hi = own ? acc.hi : 0.0;
+                acc.lo = own ? acc.lo : 0.0;
 #pragma unroll
-                for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off, 64);
+                for (int off = 32; off >= 1; off >>= 1) acc.add(__shfl_xor(acc.hi, off, 64), __shfl_xor(acc.lo, off, 64));
                 L = acc;
                 if constexpr (F::W > 1) {
-                    if (lane == 0) red[wave] = acc;
+                    if (lane == 0) {
+                        red[wave][0] = acc.hi;
+                        red[wave][1] = acc.lo;
+                    }
                     __syncthreads();
-                    L = 0.0;
-                    for (int w = 0; w < F::W; ++w) L += red[w];
+                    L = Sum();
+                    for (int w = 0; w < F::W; ++w) L.add(red[w][0], red[w][1]);
                     __syncthreads();
                 }
             }
             if (own && active && ls == 0 && (WL || wave == 0)) {
                 const double* ob = (grid == 0 ? A.obs_f : A.obs_c) + 3 * j;
-                const double X = ob[0] * ((grid == 0 ? A.h2f : A.h2c) * L - ob[1]);
+                const double X = ob[0] * L.centred(grid == 0 ? A.h2f : A.h2c, ob[1]);
                 double* dst = A.out + (si * A.n_obs + j) * 2;
                 dst[grid] = ob[2] != 0.0 ? X * X : X;
                 if (!PAIR) dst[1] = 0.0;

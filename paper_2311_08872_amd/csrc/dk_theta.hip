@@ -41,6 +41,7 @@
 #include <type_traits>
 
 #include "dk_level.h"
+#include "dk_sum.h"
 #include "dk_theta.h"
 
 namespace dk {
@@ -73,18 +74,6 @@ template <> struct Mma<float> {
     static __device__ __forceinline__ Acc mul(float a, float b, Acc c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
     static constexpr __host__ __device__ int row(int i, int q) { return 4 * q + i; }
     static __device__ __forceinline__ float root(float x) { return sqrt(x > 0.0f ? x : 0.0f); }
-};
-
-// a sum and its rounding errors
-struct Sum {
-    double hi = 0.0, lo = 0.0;
-    __device__ __forceinline__ void add(double v, double e)
-    {
-#pragma clang fp contract(off)
-        const double s = hi + v, b = s - hi;
-        lo += ((hi - (s - b)) + (v - b)) + e;
-        hi = s;
-    }
 };
 
 // the value of the neighbouring lane of an even-odd pair
@@ -339,8 +328,7 @@ struct Grid {
                 for (int i = 0; i < 4; ++i) {
                     const int y = row(t, i);
                     if (T == 1 && y / N != sr) continue;
-                    const double r = (double)rho[t][i], f = phi[(y % N) * N + col() % N], v = r * f;
-                    acc.add(v, fma(r, f, -v));
+                    acc.add_product((double)rho[t][i], phi[(y % N) * N + col() % N]);
                 }
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1)
@@ -477,7 +465,7 @@ __global__ void __launch_bounds__(64 * TG<N>::WPB, TG<N>::WAVES) theta_kernel(co
     // observables of eq. (eqn_MLMCLevels): FP64 inner products, the wavefronts' sums in their order
     auto write = [&](int j, int grid, uint64_t si, Sum L) {
         const double* ob = (grid == 0 ? A.obs_f : A.obs_c) + 3 * j;
-        const double h2 = grid == 0 ? A.h2f : A.h2c, X = ob[0] * (fma(h2, L.hi, -ob[1]) + h2 * L.lo);
+        const double X = ob[0] * L.centred(grid == 0 ? A.h2f : A.h2c, ob[1]);
         double* dst = A.out + (si * A.n_obs + j) * 2;
         dst[grid] = ob[2] != 0.0 ? X * X : X;
         if (!PAIR) dst[1] = 0.0;
