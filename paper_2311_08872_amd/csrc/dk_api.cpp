@@ -268,6 +268,9 @@ void dk_context_destroy(dk_context* ctx)
     }
     if (ctx->fork_ev) (void)hipEventDestroy(ctx->fork_ev);
     if (ctx->cap_stream) (void)hipStreamDestroy(ctx->cap_stream);
+    if (ctx->half_stream) (void)hipStreamDestroy(ctx->half_stream);
+    for (hipEvent_t e : {ctx->half_fork, ctx->half_join})
+        if (e) (void)hipEventDestroy(e);
     if (ctx->rnd_t0) (void)hipEventDestroy(ctx->rnd_t0);
     if (ctx->rnd_t1) (void)hipEventDestroy(ctx->rnd_t1);
     if (ctx->pr_exec) (void)hipGraphExecDestroy(ctx->pr_exec);

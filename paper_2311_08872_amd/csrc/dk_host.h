@@ -136,6 +136,8 @@ struct dk_context {
     dkh::DevBuf moments;        // [chunks][n_obs][DK_NMOM][2]
     dkh::DevBuf mf0, mf1;       // mean-field streaming buffers
     dkh::DevBuf scratch_c;      // inner products
+    hipStream_t half_stream = nullptr;        // the second half of a streamed batch
+    hipEvent_t half_fork = nullptr, half_join = nullptr;
     dkh::DevBuf st_f[2][2], st_c[2][2];   // streaming state: [buffer][rho, cmp] fine / coarse
     dkh::DevBuf st_z;                     // streaming pairs: restricted-noise sums of split depths
     std::vector<double> host_mom;

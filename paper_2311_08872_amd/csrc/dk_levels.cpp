@@ -53,47 +53,91 @@ void theta_meanfield_host(int n, double mu, double b0, long M, std::vector<doubl
         }
 }
 
+// coarse steps that the coarse kernel takes after a launch of `ksteps` steps from m0
+int stream_groups(bool pair, int depth, int m0, int ksteps)
+{
+    if (!pair || depth == 4) return 0;
+    return depth == 8 ? ksteps / 4 : ((m0 + ksteps) % 4 == 0 ? 1 : 0);
+}
+
+// streams that a batch of `count` samples advances on
+int stream_parts(int n, int count)
+{
+    const size_t tiles = (size_t)(n / 64) * (n / 64);
+    return count >= 2 && tiles * count > 256 ? 2 : 1;
+}
+
 // Grids beyond the resident kernel: state in HBM, batches of samples, launches of `depth` fine
 // steps (the last one shorter if the step count is not a multiple), coarse steps fused into the
 // depth-4 launches or taken by the coarse kernel after each group of 4, then the observables.
 // The depth is forced (dk_context_set_stream_depth), cached, or chosen by timing the four depths
 // on a short batch the first time a large job runs a grid size.
+//
+// A launch boundary waits for the launch's last blocks, and a batch rarely fills the compute units evenly (40
+// pairs of 256 x 256 are 640 blocks for 512 places).  The samples are independent, so a batch of more
+// than 256 blocks advances as two halves on two streams, and one half's blocks fill the places that the
+// other's last ones leave.  Time in ms of 32768 steps of 256 x 256 pairs:
+//   pairs          8    16    24    32    40    64   128
+//   one stream   157   163   242   250   354   446   836
+//   two          175   176   197   206   261   399   786
+// The line lies at one block per compute unit: below it the halves have no place to fill.
 int stream_pass(dk_context* ctx, const dk_problem* p, bool pair, int depth, const dk::LevelArgs& A, uint64_t first,
                 int c, int steps, size_t zgroup, hipStream_t s, int* cur_f, int* cur_c)
 {
     const int nf = A.nf, nc = nf / 2;
+    const size_t nn = (size_t)nf * nf, ncc = (size_t)nc * nc;
     HIP_TRY(dk::launch_stream_init((const float*)A.rho0_f, nf, c, (float*)ctx->st_f[0][0].p, (float*)ctx->st_f[0][1].p, s));
     if (pair)
         HIP_TRY(dk::launch_stream_init((const float*)A.rho0_c, nc, c, (float*)ctx->st_c[0][0].p, (float*)ctx->st_c[0][1].p, s));
-    dk::StreamArgs S{};
-    S.n = nf; S.level_id = A.level_id; S.tag = A.tag; S.seed = A.seed; S.first = first; S.count = c;
-    S.a = (float)A.a; S.kf = (float)A.kf; S.kc = (float)A.kc;
-    S.z = pair && depth != 4 ? (float*)ctx->st_z.p : nullptr;
-    S.zgroup = zgroup;
-    int cf = 0, cc = 0;
-    for (int m0 = 0; m0 < steps; m0 += depth) {
+    const int parts = stream_parts(nf, c);
+    if (parts == 2) {
+        if (!ctx->half_stream) HIP_TRY(hipStreamCreateWithFlags(&ctx->half_stream, hipStreamNonBlocking));
+        for (hipEvent_t* e : {&ctx->half_fork, &ctx->half_join})
+            if (!*e) HIP_TRY(hipEventCreateWithFlags(e, hipEventDisableTiming));
+        HIP_TRY(hipEventRecord(ctx->half_fork, s));
+        HIP_TRY(hipStreamWaitEvent(ctx->half_stream, ctx->half_fork, 0));
+    }
+    // launches of one stretch of steps for the samples [b, b + k); cf, cc: current buffers
+    auto advance = [&](int m0, int b, int k, int cf, int cc, hipStream_t q) {
+        auto fine = [&](int buf, int i) { return (float*)ctx->st_f[buf][i].p + b * nn; };
+        auto coarse = [&](int buf, int i) { return pair ? (float*)ctx->st_c[buf][i].p + b * ncc : nullptr; };
+        dk::StreamArgs S{};
+        S.n = nf; S.level_id = A.level_id; S.tag = A.tag; S.seed = A.seed; S.first = first + b; S.count = k;
+        S.a = (float)A.a; S.kf = (float)A.kf; S.kc = (float)A.kc;
+        S.z = pair && depth != 4 ? (float*)ctx->st_z.p + 2 * b * ncc : nullptr;
+        S.zgroup = zgroup;
         S.m0 = m0;
         S.ksteps = std::min(depth, steps - m0);
         S.do_coarse = pair && depth == 4 ? 1 : 0;
         S.z_load = pair && depth != 4 && m0 % 4 != 0 ? 1 : 0;
-        S.rho_in = (const float*)ctx->st_f[cf][0].p; S.cmp_in = (const float*)ctx->st_f[cf][1].p;
-        S.rho_out = (float*)ctx->st_f[1 - cf][0].p; S.cmp_out = (float*)ctx->st_f[1 - cf][1].p;
+        S.rho_in = fine(cf, 0); S.cmp_in = fine(cf, 1);
+        S.rho_out = fine(1 - cf, 0); S.cmp_out = fine(1 - cf, 1);
         if (pair) {
-            S.rhoc_in = (const float*)ctx->st_c[cc][0].p; S.cmpc_in = (const float*)ctx->st_c[cc][1].p;
-            S.rhoc_out = (float*)ctx->st_c[1 - cc][0].p; S.cmpc_out = (float*)ctx->st_c[1 - cc][1].p;
+            S.rhoc_in = coarse(cc, 0); S.cmpc_in = coarse(cc, 1);
+            S.rhoc_out = coarse(1 - cc, 0); S.cmpc_out = coarse(1 - cc, 1);
         }
-        HIP_TRY(dk::launch_stream_step(S, pair, p->flux, depth, s));
-        cf = 1 - cf;
-        if (!pair) continue;
-        if (depth == 4) { cc = 1 - cc; continue; }
-        const int groups = depth == 8 ? S.ksteps / 4 : ((m0 + S.ksteps) % 4 == 0 ? 1 : 0);
-        for (int g = 0; g < groups; ++g) {
-            HIP_TRY(dk::launch_stream_coarse(nc, c, S.a, S.kc, p->flux, (const float*)ctx->st_c[cc][0].p,
-                                             (const float*)ctx->st_c[cc][1].p, (const float*)ctx->st_z.p + 2 * g * zgroup,
-                                             (float*)ctx->st_c[1 - cc][0].p, (float*)ctx->st_c[1 - cc][1].p, s));
+        hipError_t e = dk::launch_stream_step(S, pair, p->flux, depth, q);
+        for (int g = 0; e == hipSuccess && g < stream_groups(pair, depth, m0, S.ksteps); ++g) {
+            e = dk::launch_stream_coarse(nc, k, S.a, S.kc, p->flux, coarse(cc, 0), coarse(cc, 1), S.z + 2 * g * zgroup,
+                                         coarse(1 - cc, 0), coarse(1 - cc, 1), q);
             cc = 1 - cc;
         }
+        return e;
+    };
+    int cf = 0, cc = 0;
+    hipError_t e = hipSuccess;
+    for (int m0 = 0; e == hipSuccess && m0 < steps; m0 += depth) {
+        const int half = parts == 2 ? c / 2 : c;
+        e = advance(m0, 0, half, cf, cc, s);
+        if (e == hipSuccess && parts == 2) e = advance(m0, half, c - half, cf, cc, ctx->half_stream);
+        cf = 1 - cf;
+        if (pair) cc ^= depth == 4 ? 1 : stream_groups(pair, depth, m0, std::min(depth, steps - m0)) & 1;
     }
+    if (parts == 2) {      // also after a failed launch: what runs on the second stream uses the context's buffers
+        HIP_TRY(hipEventRecord(ctx->half_join, ctx->half_stream));
+        HIP_TRY(hipStreamWaitEvent(s, ctx->half_join, 0));
+    }
+    HIP_TRY(e);
     *cur_f = cf;
     *cur_c = cc;
     return DK_OK;
