@@ -1,8 +1,8 @@
 // dk_stream.hip -- the level kernel for grids that do not fit on chip (n >= 256; any multiple
 // of 64 works), with the state in HBM and temporal blocking of depth D in {1, 2, 4, 8}.
 //
-// One launch advances a batch of samples by up to D fine steps.  Each block owns a 64 x 64 fine
-// tile of one sample and loads it with a halo of H = max(D, 2) cells (H is even so that
+// One launch advances a batch of samples by up to D fine steps.  Each block owns a 64 x 64 (small
+// batches at D = 4: 32 x 32) fine tile of one sample and loads it with a halo of H = max(D, 2) cells (H is even so that
 // the 2 x 2 blocks below line up with the coarse cells and with the horizontal site pairs that
 // share a generator call).  The noise of the halo is regenerated from the counter-based
 // generator (it is a pure function of site and step), so no noise is exchanged; the valid
@@ -21,8 +21,8 @@
 // as (even-row block sum + odd-row block sum)) is the same operation sequence as the resident
 // kernel, so every depth produces bit-identical fields.
 //
-// Lane work: a block of 512 threads (640 at D = 8) owns the (32 + H)^2 2x2 blocks of the extended
-// tile, up to three per thread, and keeps their cells in registers for the whole launch; LDS only
+// Lane work: a block of 512 threads (640 at D = 8; 448 on the small tile) owns the 2x2 blocks of the
+// extended tile, up to three (one) per thread, and keeps their cells in registers for the whole launch; LDS only
 // passes the cells and fluxes that neighbouring blocks read (two barriers per fine step).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -33,13 +33,13 @@
 namespace dk {
 
 namespace {
-constexpr int TT = 64;               // fine tile interior
-
-template <int D>
+// TT: side of a block's fine tile
+template <int D, int TT>
 struct Geo {
     // 3 blocks per thread at every depth (448 threads would idle fewer slots at D <= 4 but hold 14
     // wavefronts per compute unit instead of 16)
-    static constexpr int THREADS = D == 8 ? 640 : 512;
+    // (one per thread on the small tile, whose launches are short chains on idle compute units)
+    static constexpr int THREADS = TT == 32 ? 448 : D == 8 ? 640 : 512;
     static constexpr int HH = D < 2 ? 2 : D;                  // halo width
     static constexpr int EXT = TT + 2 * HH;                   // extended tile side
     static constexpr int NBS = EXT / 2;                       // 2x2 blocks per side
@@ -86,13 +86,13 @@ __device__ __forceinline__ void em_cell(float& r, float& cm, float l, float rt, 
 // step's region: blocks at block distance L from the extended tile's edge hold cells at distances
 // 2L and 2L + 1, the fluxes are needed at distance >= j and the updates at distance >= j + 1.
 // Cells a block computes outside those regions hold values no valid cell reads.
-template <int FLUX, bool PAIR, int D>
-__global__ void __launch_bounds__(Geo<D>::THREADS, Geo<D>::WAVES_PER_SIMD) stream_kernel(const StreamArgs A)
+template <int FLUX, bool PAIR, int D, int TT>
+__global__ void __launch_bounds__((Geo<D, TT>::THREADS), (Geo<D, TT>::WAVES_PER_SIMD)) stream_kernel(const StreamArgs A)
 {
 #pragma clang fp contract(off)
-    constexpr int THREADS = Geo<D>::THREADS;
-    constexpr int HH = Geo<D>::HH, EXT = Geo<D>::EXT, NBS = Geo<D>::NBS, NBLK = Geo<D>::NBLK, BPT = Geo<D>::BPT;
-    constexpr int P = Geo<D>::P, PLANE = Geo<D>::PLANE;
+    typedef Geo<D, TT> G;
+    constexpr int THREADS = G::THREADS, HH = G::HH, EXT = G::EXT, NBS = G::NBS, NBLK = G::NBLK, BPT = G::BPT;
+    constexpr int P = G::P, PLANE = G::PLANE;
     constexpr bool FUSED = PAIR && D == 4;     // coarse step taken by this kernel
     constexpr bool SPLIT = PAIR && D != 4;     // noise sums kept in HBM, coarse step by its own kernel
     constexpr int HB = HH / 2;                 // first block of the tile interior
@@ -481,19 +481,35 @@ __global__ void zero_slot_kernel(double* out, int count, int n_obs, int slot)
     out[(size_t)i * 2 + slot] = 0.0;
 }
 
-bool stream_supported(int nf) { return nf >= 64 && nf % TT == 0; }
+bool stream_supported(int nf) { return nf >= 64 && nf % 64 == 0; }
 
+template <int FLUX, bool PAIR, int D, int TT>
+static hipError_t launch_tile(const StreamArgs& A, hipStream_t s)
+{
+    const uint64_t blocks = (uint64_t)(A.n / TT) * (A.n / TT) * (uint64_t)A.count;
+    if (blocks == 0 || blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((stream_kernel<FLUX, PAIR, D, TT>), dim3((unsigned)blocks), dim3(Geo<D, TT>::THREADS), 0, s, A);
+    return hipGetLastError();
+}
+
+// Depth-4 launches of few tiles take 32 x 32 tiles: the halo costs 1.56 of the interior's cells instead of 1.27,
+// but there are four times the blocks, each with one 2 x 2 block per thread instead of three in turn.
+// Time in ms of 32768 steps of 256 x 256 pairs (16 tiles of 64 x 64 each; 24 and 32 pairs run as two halves):
+//   pairs     1     4     8    12    16    24    32    40
+//   64      157   155   157   160   163   197   206   261
+//   32       70    71   100   130   165   186   246   306
 template <int FLUX, bool PAIR>
-static hipError_t launch_depth(const StreamArgs& A, int depth, dim3 grid, hipStream_t s)
+static hipError_t launch_depth(const StreamArgs& A, int depth, hipStream_t s)
 {
     switch (depth) {
-    case 1: hipLaunchKernelGGL((stream_kernel<FLUX, PAIR, 1>), grid, dim3(Geo<1>::THREADS), 0, s, A); break;
-    case 2: hipLaunchKernelGGL((stream_kernel<FLUX, PAIR, 2>), grid, dim3(Geo<2>::THREADS), 0, s, A); break;
-    case 4: hipLaunchKernelGGL((stream_kernel<FLUX, PAIR, 4>), grid, dim3(Geo<4>::THREADS), 0, s, A); break;
-    case 8: hipLaunchKernelGGL((stream_kernel<FLUX, PAIR, 8>), grid, dim3(Geo<8>::THREADS), 0, s, A); break;
+    case 1: return launch_tile<FLUX, PAIR, 1, 64>(A, s);
+    case 2: return launch_tile<FLUX, PAIR, 2, 64>(A, s);
+    case 4:
+        if ((uint64_t)(A.n / 64) * (A.n / 64) * (uint64_t)A.count <= 192) return launch_tile<FLUX, PAIR, 4, 32>(A, s);
+        return launch_tile<FLUX, PAIR, 4, 64>(A, s);
+    case 8: return launch_tile<FLUX, PAIR, 8, 64>(A, s);
     default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
 }
 
 bool stream_depth_supported(int depth) { return depth == 1 || depth == 2 || depth == 4 || depth == 8; }
@@ -501,15 +517,12 @@ bool stream_depth_supported(int depth) { return depth == 1 || depth == 2 || dept
 hipError_t launch_stream_step(const StreamArgs& A, bool pair, int flux, int depth, hipStream_t s)
 {
     if (A.ksteps < 1 || A.ksteps > depth || (pair && depth != 4 && !A.z)) return hipErrorInvalidValue;
-    const uint64_t blocks = (uint64_t)(A.n / TT) * (A.n / TT) * (uint64_t)A.count;
-    if (blocks == 0 || blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)blocks);
     if (pair) {
-        if (flux == DK_FLUX_CENTRAL) return launch_depth<DK_FLUX_CENTRAL, true>(A, depth, grid, s);
-        return launch_depth<DK_FLUX_STAGGERED, true>(A, depth, grid, s);
+        if (flux == DK_FLUX_CENTRAL) return launch_depth<DK_FLUX_CENTRAL, true>(A, depth, s);
+        return launch_depth<DK_FLUX_STAGGERED, true>(A, depth, s);
     }
-    if (flux == DK_FLUX_CENTRAL) return launch_depth<DK_FLUX_CENTRAL, false>(A, depth, grid, s);
-    return launch_depth<DK_FLUX_STAGGERED, false>(A, depth, grid, s);
+    if (flux == DK_FLUX_CENTRAL) return launch_depth<DK_FLUX_CENTRAL, false>(A, depth, s);
+    return launch_depth<DK_FLUX_STAGGERED, false>(A, depth, s);
 }
 
 hipError_t launch_stream_coarse(int nc, int count, float a, float kc, int flux, const float* rho_in, const float* cmp_in,

@@ -34,3 +34,21 @@ def test_halves_match_one_stream(depth, coupled, flux):
         again = run(p, 1, 3, 35, per_sample=True, ctx=ctx)[1]
     assert torch.equal(again, whole)
     ctx.close()
+
+
+@pytest.mark.parametrize("coupled", [True, False])
+@pytest.mark.parametrize("flux", [W.FLUX_CENTRAL, W.FLUX_STAGGERED])
+def test_small_tiles_match_large(coupled, flux):
+    """Depth 4 in 32 x 32 tiles (up to 192 tiles of 64 x 64 a launch) and in 64 x 64 tiles; 13 steps of single
+    paths end on a partial launch."""
+    level = 1 if coupled else 0
+    p = W.config2(N=3e3).with_(flux=flux, n0=320 >> level, levels=level + 1)
+    p = p.with_(T=p.tau(level) * (12 if coupled else 13), steps_policy=W.STEPS_EXACT)
+    print(f"[gpu] stream tile sizes coupled={coupled} flux={flux}", flush=True)
+    run = dk.level_pair if coupled else dk.mc_level
+    ctx = dk.Context(0)
+    ctx.set_stream_depth(4)
+    large = run(p, level, 0, 8, per_sample=True, ctx=ctx)[1]         # 320 x 320: 200 tiles
+    for first, count in ((0, 7), (7, 1)):
+        assert torch.equal(run(p, level, first, count, per_sample=True, ctx=ctx)[1], large[first:first + count])
+    ctx.close()
