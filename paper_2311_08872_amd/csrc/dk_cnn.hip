@@ -8,20 +8,21 @@
 //
 // Numbers: the 16->16 convolutions multiply BF16 operands on v_mfma_f32_16x16x32_bf16 with FP32
 // accumulation; each layer's output (and each gradient at a layer's output) is rounded to BF16
-// once; the first layer, pooling and the dense head are FP32 throughout, as is the first layer's
-// weight gradient (v_mfma_f32_16x16x4_f32).
+// once; the first layer and its weight gradient (v_mfma_f32_16x16x4_f32), pooling and the dense head
+// are FP32 throughout.
 //
 // Forward (one block per tile of at most 32 x 16 pixels): the tile of x with a halo of 3 comes to
 // LDS once, the first layer writes its 16 channels there with a halo of 2, the second reads it and
-// writes beside it, the third overwrites the first, and the tile's channel sums are formed from
-// LDS: nothing but x is read from HBM and nothing but 16 sums per tile is written (the training
+// writes beside it, the third adds its outputs to the tile's channel sums (several samples in a block: by
+// way of LDS): nothing but x is read from HBM and nothing but 16 sums per tile is written (the training
 // pass also writes the two activations and a 16-bit ReLU mask per pixel).  Grids of at most 16 x 16
 // put several samples into one block.  A layer as its own pass over HBM moved 64 B per pixel and
 // layer and summed the pool in one thread per (sample, channel): 4.64 ms for 4000 inputs of 64 x 64
-// (0.85 ms per 1024 of it the pool) against 0.52 ms now.
+// (0.85 ms per 1024 of it the pool) against 0.49 ms now: the vector ALU is busy two thirds of it (addresses,
+// roundings and packing, ReLU), the matrix cores and LDS a third each.
 // An activation image is two planes of 8 channels, 16 B per pixel each, so the 16 pixels of an MFMA
-// operand are 256 consecutive bytes; the convolution runs over the image's linear index (tile rows
-// and their halo columns alike) and the results in halo columns are not used.
+// operand are 256 consecutive bytes.  The register bounds keep the accumulators among the vector registers:
+// without them the compiler puts them into the second file and moves every result (4 % of the kernel).
 //
 // Backward: per layer one kernel whose blocks stride over tiles (halo 1) and hold the weight
 // gradient in MFMA accumulators for their whole run: A = gradient [o][pixel], B = activation
@@ -30,11 +31,12 @@
 // piece.  The bias gradient is a tenth product with a column of ones.  The same kernel convolves the
 // gradient back to the layer's input.  Per-block partial sums are added in block order by the last
 // kernel, which also forms the dense head's gradients.  Loss and gradient at 64 x 64, batch 256:
-// 4.01 ms with one kernel per product (2-byte gathers, serial column sums, 27 launches), 0.28 ms now.
+// 4.01 ms with one kernel per product (2-byte gathers, serial column sums, 27 launches), 0.27 ms now.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "dk_cnn.h"
 
@@ -55,12 +57,12 @@ __device__ __forceinline__ uint32_t pack2(float lo, float hi)
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(floatx2{lo, hi}, bf16x2));
 }
 
-// x / d for 0 <= x < 2^16 and 1 <= d < 2^11 by one high product (exact: the error x / 2^32 of the
-// rounded reciprocal stays below 1/d)
+// x / d for 0 <= x < 2^16 and 1 <= d < 2^11 in three full-rate instructions: (x + 1/2) / d is at least 1 / (2 d)
+// away from an integer, its two roundings at most x / d 2^-22 (a 32-bit high product takes four times as long)
 struct Div {
-    uint32_t d, m;
-    __host__ __device__ Div(uint32_t v = 1) : d(v), m(v <= 1 ? 0u : 0xFFFFFFFFu / v + 1u) {}
-    __device__ __forceinline__ uint32_t q(uint32_t x) const { return m == 0u ? x : __umulhi(x, m); }
+    float inv, half;
+    __host__ __device__ Div(uint32_t v = 1) : inv(1.0f / (float)(v < 1 ? 1 : v)), half(0.5f * inv) {}
+    __device__ __forceinline__ int q(int x) const { return (int)fmaf((float)x, inv, half); }
 };
 
 __device__ __forceinline__ int wrapn(int v, int n) { return v < 0 ? v + n : (v >= n ? v - n : v); }
@@ -75,6 +77,9 @@ struct Geo {
     int P, img, L;      // image pitch, pixels of one sample's image, of all S
     int groups;         // ceil(batch / S) x tiles per sample: work items
     Div dP, dImg, dTiles, dTx, dTw, dTile;
+    // forward: row pairs of one sample and pixels of a row that the second and third layer compute
+    int pairs[2], cols[2];
+    Div dCols[2], dPairs[2];
 };
 
 constexpr int kTileW = 32, kTileH = 16;
@@ -119,6 +124,12 @@ static Geo make_geo(int n, int batch, int H)
     g.dTx = Div(g.tx);
     g.dTw = Div(g.tw);
     g.dTile = Div(g.tw * g.th);
+    for (int k = 0; k < 2; ++k) {
+        g.pairs[k] = cdiv(g.th + 2 - 2 * k, 2);
+        g.cols[k] = g.tw + 2 - 2 * k;
+        g.dCols[k] = Div(g.cols[k]);
+        g.dPairs[k] = Div(g.pairs[k] * g.cols[k]);
+    }
     return g;
 }
 
@@ -175,13 +186,36 @@ __device__ __forceinline__ void neighbour_offsets(int (&off)[5], int P, int lane
     }
 }
 
+// The forward convolutions take two rows of output at once.  An operand of the image holds 16 pixels of two
+// consecutive rows, 16 channels each (K = 32): the rows above and at the first output row (A), or the two rows
+// below it (B).  w[dx]: their weights {A, B} -> first output row, {A, B} -> second one, zero where the row is
+// not a neighbour.  Six operands and twelve products per 2 x 16 outputs: per 16 pixels 3 reads of 1 KB from LDS
+// instead of the 5 of conv16.
+struct RowWeights {
+    uint4 w[3][4];
+    __device__ __forceinline__ void load(const uint16_t* __restrict__ Wk, int lane)
+    {
+        const bool second = lane >= 32;
+        const uint16_t* p = Wk + (lane & 15) * 160 + 8 * ((lane >> 4) & 1);
+        const uint4 zero = make_uint4(0, 0, 0, 0);
+#pragma unroll
+        for (int dx = 0; dx < 3; ++dx) {
+            const uint4 a = *(const uint4*)(p + 16 * dx), m = *(const uint4*)(p + 16 * (dx + 3)), b = *(const uint4*)(p + 16 * (dx + 6));
+            w[dx][0] = second ? m : a;
+            w[dx][1] = second ? zero : b;
+            w[dx][2] = second ? a : zero;
+            w[dx][3] = second ? b : m;
+        }
+    }
+};
+
 // ---------------------------------------------------------------------------------------
 // Forward: the three convolutions of one tile.  KEEP: also writes the activations a1, a2 ([pixel][16]
 // BF16) and the third layer's ReLU mask for the backward pass.  gpart[sample][tile][16] receives the
 // tile's channel sums.
 // ---------------------------------------------------------------------------------------
 template <bool KEEP>
-__global__ void __launch_bounds__(kFwdThreads) conv_fwd(const Geo g, const float* __restrict__ x, const float* __restrict__ prm,
+__global__ void __launch_bounds__(kFwdThreads, 3) conv_fwd(const Geo g, const float* __restrict__ x, const float* __restrict__ prm,
                                                 const uint16_t* __restrict__ wt2, const uint16_t* __restrict__ wt3,
                                                 float* __restrict__ gpart, uint16_t* __restrict__ a1g,
                                                 uint16_t* __restrict__ a2g, uint16_t* __restrict__ m3g)
@@ -206,51 +240,88 @@ __global__ void __launch_bounds__(kFwdThreads) conv_fwd(const Geo g, const float
             sx[e] = x[b * nn + (size_t)wrapn(T.y0 + yy - 3, n) * n + wrapn(T.x0 + xx - 3, n)];
         }
     }
-    uint4 w2[5], w3[5];
-    load_weights(w2, wt2, lane);
-    load_weights(w3, wt3, lane);
+    RowWeights w2, w3;
+    w2.load(wt2, lane);
+    w3.load(wt3, lane);
     __syncthreads();
-    // first layer on the whole image (halo 2)
+    const int i = lane & 15, kg = lane >> 4;
+    // First layer on the whole image (halo 2): 16 pixels by 16 outputs, K = 9 neighbours padded to 12 on the FP32
+    // matrix instruction.  A fused multiply-add of its own per product took a third of the kernel's vector
+    // instructions.
     {
         const int xp = g.tw + 6, xi = xp * (g.th + 6);
-        for (int e = t; e < L; e += kFwdThreads) {
-            const int s = g.dImg.q(e), r = e - s * g.img, yy = g.dP.q(r), xx = r - yy * P;
+        float w1[3], b1[4];
+        int o[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const int pos = min(4 * k + kg, 8);
+            w1[k] = 4 * k + kg < 9 ? prm[OFF_W1 + 9 * i + pos] : 0.0f;
+            o[k] = (pos / 3) * xp + pos % 3;
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) b1[r] = prm[OFF_B1 + 4 * kg + r];
+        for (int g0 = 16 * wave; g0 < L; g0 += 16 * WAVES) {
+            const int e = min(g0 + i, L - 1), s = g.dImg.q(e), r = e - s * g.img, yy = g.dP.q(r), xx = r - yy * P;
             const float* c = sx + s * xi + yy * xp + xx;
-            float v[9];
+            floatx4 acc = {b1[0], b1[1], b1[2], b1[3]};
 #pragma unroll
-            for (int pos = 0; pos < 9; ++pos) v[pos] = c[(pos / 3) * xp + pos % 3];
-            // 8 outputs at a time: their 80 weights fit the scalar registers, 160 would spill
-#pragma unroll 1
-            for (int h = 0; h < 2; ++h) {
-                const float* w1 = prm + OFF_W1 + 72 * h;
-                const float* b1 = prm + OFF_B1 + 8 * h;
-                float o8[8];
-#pragma unroll
-                for (int o = 0; o < 8; ++o) {
-                    float a = b1[o];
-#pragma unroll
-                    for (int pos = 0; pos < 9; ++pos) a = fmaf(w1[o * 9 + pos], v[pos], a);
-                    o8[o] = fmaxf(a, 0.0f);
-                }
-                sA[h * PL + e] = make_uint4(pack2(o8[0], o8[1]), pack2(o8[2], o8[3]), pack2(o8[4], o8[5]), pack2(o8[6], o8[7]));
+            for (int k = 0; k < 3; ++k) {
+                float v = c[o[k]];
+                if (k == 2 && kg > 0) v = 0.0f;
+                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w1[k], v, acc, 0, 0, 0);
             }
+            ((uint2*)&sA[(kg >> 1) * PL + e])[kg & 1] =
+                make_uint2(pack2(fmaxf(acc[0], 0.0f), fmaxf(acc[1], 0.0f)), pack2(fmaxf(acc[2], 0.0f), fmaxf(acc[3], 0.0f)));
         }
     }
     __syncthreads();
-    int off[5];
-    neighbour_offsets(off, P, lane, 1);
-    const int i = lane & 15, kg = lane >> 4;
-    // one layer: image pixels [lo, hi) of src -> dst
-    auto layer = [&](const uint4* src, uint4* dst, const uint4 (&w)[5], const float* bias, int lo, int hi) {
+    // layer k (0: the second, 1: the third): rows 1 + k .. th + 2 - k, columns 1 + k .. tw + 2 - k of src -> dst.
+    // Where the last pair has no second row, its row below the image (times zero weights) is the image's last:
+    // the next sample's values or unwritten ones could be non-finite.
+    // POOL (one sample a block): the outputs inside the tile are added to v; dst is written where it is read.
+    float v4[4] = {0.f, 0.f, 0.f, 0.f};
+    auto layer = [&](const uint4* src, uint4* dst, const RowWeights& W, const float* bias, int k, auto pool) {
+        constexpr bool POOL = decltype(pool)::value;
         float b4[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) b4[r] = bias[4 * kg + r];
-        for (int g0 = lo + 16 * wave; g0 < hi; g0 += 16 * WAVES) {
-            const floatx4 acc = conv16(src, PL, g0, off, w, lane);
-            uint2 o;
-            o.x = pack2(fmaxf(acc[0] + b4[0], 0.0f), fmaxf(acc[1] + b4[1], 0.0f));
-            o.y = pack2(fmaxf(acc[2] + b4[2], 0.0f), fmaxf(acc[3] + b4[3], 0.0f));
-            ((uint2*)&dst[(kg >> 1) * PL + g0 + i])[kg & 1] = o;
+        const int per = g.pairs[k] * g.cols[k], total = g.S * per, last = g.th + 2 - k;
+        for (int g0 = 16 * wave; g0 < total; g0 += 16 * WAVES) {
+            const int u = min(g0 + i, total - 1), s = g.dPairs[k].q(u), r = u - s * per, j = g.dCols[k].q(r);
+            const int row = 1 + k + 2 * j, q = s * g.img + row * P + 1 + k + (r - j * g.cols[k]);
+            const uint4* p = src + (kg & 1) * PL + q;
+            const uint4* pa = p + (kg >> 1 ? 0 : -P);
+            const uint4* pb = p + (kg >> 1 && row + 2 <= last + 1 ? 2 * P : P);
+            floatx4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int dx = 0; dx < 3; ++dx) {
+                const bf16x8 a = __builtin_bit_cast(bf16x8, pa[dx - 1]), b = __builtin_bit_cast(bf16x8, pb[dx - 1]);
+                auto w = [&](int e) { return __builtin_bit_cast(bf16x8, W.w[dx][e]); };
+                acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w(0), a, acc0, 0, 0, 0);
+                acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w(2), a, acc1, 0, 0, 0);
+                acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w(1), b, acc0, 0, 0, 0);
+                acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w(3), b, acc1, 0, 0, 0);
+            }
+            uint2* o = (uint2*)&dst[(kg >> 1) * PL + q] + (kg & 1);
+            const uint2 o0 = make_uint2(pack2(fmaxf(acc0[0] + b4[0], 0.0f), fmaxf(acc0[1] + b4[1], 0.0f)),
+                                        pack2(fmaxf(acc0[2] + b4[2], 0.0f), fmaxf(acc0[3] + b4[3], 0.0f)));
+            const uint2 o1 = make_uint2(pack2(fmaxf(acc1[0] + b4[0], 0.0f), fmaxf(acc1[1] + b4[1], 0.0f)),
+                                        pack2(fmaxf(acc1[2] + b4[2], 0.0f), fmaxf(acc1[3] + b4[3], 0.0f)));
+            if (!POOL || KEEP) {
+                *o = o0;
+                if (row < last) o[2 * P] = o1;
+            }
+            if constexpr (POOL) {
+                const bool in = g0 + i < total && r - j * g.cols[k] < T.tw;
+                auto add = [&](uint2 d, bool use) {
+                    v4[0] += __uint_as_float(use ? d.x << 16 : 0u);
+                    v4[1] += __uint_as_float(use ? d.x & 0xFFFF0000u : 0u);
+                    v4[2] += __uint_as_float(use ? d.y << 16 : 0u);
+                    v4[3] += __uint_as_float(use ? d.y & 0xFFFF0000u : 0u);
+                };
+                add(o0, in && row - 2 < T.th);
+                add(o1, in && row - 1 < T.th && row < last);
+            }
         }
     };
     // interior pixels of an image in LDS to global memory, 16 B per thread
@@ -263,10 +334,11 @@ __global__ void __launch_bounds__(kFwdThreads) conv_fwd(const Geo g, const float
                     src[h * PL + s * g.img + (yy + 2) * P + xx + 2];
         }
     };
-    layer(sA, sB, w2, prm + OFF_B2, P + 1, L - P - 1);
+    layer(sA, sB, w2, prm + OFF_B2, 0, std::false_type());
     if constexpr (KEEP) keep(sA, a1g);
     __syncthreads();
-    layer(sB, sA, w3, prm + OFF_B3, 2 * P + 2, L - 2 * P - 2);
+    if (g.S == 1) layer(sB, sA, w3, prm + OFF_B3, 1, std::true_type());
+    else layer(sB, sA, w3, prm + OFF_B3, 1, std::false_type());
     if constexpr (KEEP) keep(sB, a2g);
     __syncthreads();
     if constexpr (KEEP) {
@@ -289,18 +361,33 @@ __global__ void __launch_bounds__(kFwdThreads) conv_fwd(const Geo g, const float
                 m3g[(T.b0 + s) * nn + (size_t)(T.y0 + yy) * n + T.x0 + xx] = (uint16_t)m;
         }
     }
-    // channel sums of the tile: lanes of one parity hold one plane's 8 channels.  One sample: its
-    // pixels over the whole block; several: a sample per wavefront.
-    const int h = t & 1;
-    const int ntile = g.tx * g.ty;
-    const int step = g.S == 1 ? kFwdThreads / 2 : 32;
-    const int px = T.tw * T.th;
+    // channel sums.  One sample a block: of the third layer's lanes, over the block
+    if (g.S == 1) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int o = 8; o >= 1; o >>= 1) v4[k] += __shfl_xor(v4[k], o, 64);
+        if (i == 0)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) sred[wave * 16 + 4 * kg + k] = v4[k];
+        __syncthreads();
+        if (t < 16) {
+            const int ntile = g.tx * g.ty;
+            float a = 0.f;
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) a += sred[16 * w + t];
+            gpart[((size_t)T.b0 * ntile + blockIdx.x % ntile) * 16 + t] = a;
+        }
+        return;
+    }
+    // several: of the image in LDS, a sample per wavefront; lanes of one parity hold one plane's 8 channels
+    const int h = t & 1, px = T.tw * T.th;
     const Div dw(T.tw);
-    for (int s = g.S == 1 ? 0 : wave; s < g.S; s += g.S == 1 ? 1 : WAVES) {
+    for (int s = wave; s < g.S; s += WAVES) {
         float v[8];
 #pragma unroll
         for (int k = 0; k < 8; ++k) v[k] = 0.f;
-        for (int q = (g.S == 1 ? t : lane) >> 1; q < px; q += step) {
+        for (int q = lane >> 1; q < px; q += 32) {
             const int yy = dw.q(q), xx = q - yy * T.tw;
             const uint4 u = sA[h * PL + s * g.img + (yy + 2) * P + xx + 2];
             const uint32_t d[4] = {u.x, u.y, u.z, u.w};
@@ -314,21 +401,9 @@ __global__ void __launch_bounds__(kFwdThreads) conv_fwd(const Geo g, const float
         for (int k = 0; k < 8; ++k)
 #pragma unroll
             for (int o = 32; o >= 2; o >>= 1) v[k] += __shfl_xor(v[k], o, 64);
-        if (g.S == 1) {
-            if (lane < 2)
-#pragma unroll
-                for (int k = 0; k < 8; ++k) sred[wave * 16 + 8 * h + k] = v[k];
-            __syncthreads();
-            if (t < 16) {
-                float a = 0.f;
-#pragma unroll
-                for (int w = 0; w < WAVES; ++w) a += sred[16 * w + t];
-                gpart[((size_t)T.b0 * ntile + blockIdx.x % ntile) * 16 + t] = a;
-            }
-        } else if (lane < 2 && T.b0 + s < g.batch) {
+        if (lane < 2 && T.b0 + s < g.batch)
 #pragma unroll
             for (int k = 0; k < 8; ++k) gpart[(size_t)(T.b0 + s) * 16 + 8 * h + k] = v[k];
-        }
     }
 }
 
@@ -407,7 +482,7 @@ __global__ void __launch_bounds__(256) head_bwd(const float* __restrict__ g, con
 // column 0; part1 [block][256]: the first layer's [o][position 0..8 | 9: bias].
 // ---------------------------------------------------------------------------------------
 template <int LAYER>
-__global__ void __launch_bounds__(256) conv_bwd(const Geo g, const uint16_t* __restrict__ wb, const uint16_t* __restrict__ act,
+__global__ void __launch_bounds__(256, 2) conv_bwd(const Geo g, const uint16_t* __restrict__ wb, const uint16_t* __restrict__ act,
                                                 const uint16_t* __restrict__ m3, const uint16_t* __restrict__ dgs,
                                                 const uint16_t* __restrict__ dzi, uint16_t* __restrict__ dzo,
                                                 const float* __restrict__ x, float* __restrict__ part,

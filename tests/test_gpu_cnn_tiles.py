@@ -70,3 +70,17 @@ def test_forward_and_gradient_at_tile_edges(n, batch):
     loss2, g2 = dk.cnn_loss_grad(p, xd, yd)
     assert loss2 == loss and np.array_equal(g2, g)
     assert np.array_equal(dk.cnn_forward(p, xd).cpu().numpy(), r)
+
+
+@pytest.mark.parametrize("n,batch", [(4, 1500), (8, 3001), (16, 2000)])
+def test_samples_of_a_block_do_not_mix(n, batch):
+    """An input that is not finite changes its own output only (several samples share a block's image)."""
+    print(f"[gpu] cnn one infinite input of {batch}, n={n}", flush=True)
+    p = dk.cnn_init(n).astype(np.float32)
+    x = torch.from_numpy(np.random.default_rng(n).standard_normal((batch, n, n)).astype(np.float32)).cuda()
+    want = dk.cnn_forward(p, x)
+    bad = x.clone()
+    bad[7] = float("inf")
+    got = dk.cnn_forward(p, bad)
+    keep = torch.arange(batch, device="cuda") != 7
+    assert torch.equal(got[keep], want[keep])
