@@ -80,7 +80,7 @@ int stream_parts(int n, int count)
 //   pairs          8    16    24    32    40    64   128
 //   one stream   157   163   242   250   354   446   836
 //   two          175   176   197   206   261   399   786
-// The line lies at one block per compute unit: below it the halves have no place to fill.
+// (64 x 64 tiles, before small launches took smaller ones).  The line lies at one block per compute unit: below it the halves have no place to fill.
 int stream_pass(dk_context* ctx, const dk_problem* p, bool pair, int depth, const dk::LevelArgs& A, uint64_t first,
                 int c, int steps, size_t zgroup, hipStream_t s, int* cur_f, int* cur_c)
 {
