@@ -388,13 +388,12 @@ int dk_context_stats(dk_context* ctx, dk_kernel_stats* out, int32_t max);
 int dk_context_reset(dk_context* ctx, int32_t drop_tables);
 
 /* Tile shapes of the resident kernel: a lane owns 2 columns and R rows of an n x n grid, and a
- * block holds S samples (about 256 lanes, or four times as many samples in 1024-lane blocks).
- * dk_shape_rows(n, v) gives R of variant v and dk_shape_spw(n, v) its S (both 0 if the variant
- * does not exist).  By default the
- * context times the variants on a short batch the first time a large job (>= 1e11 cell updates)
- * runs a grid size, and keeps the fastest; dk_context_set_shape forces variant v for grid size
- * n (v < 0 restores the automatic choice).  Per-sample fields do not depend on the shape; the
- * observables' FP64 lane reduction order does (last-bit differences). */
+ * block holds S samples.  dk_shape_rows(n, v) gives R of variant v and dk_shape_spw(n, v) its S
+ * (both 0 if the variant does not exist).  By default a batch that leaves wavefronts idle at 8 rows
+ * per lane runs at fewer, and the context times the variants on a short batch the first time a large
+ * job (>= 1e11 cell updates) runs a grid size, and keeps the fastest; dk_context_set_shape forces
+ * variant v for grid size n (v < 0 restores the automatic choice).  Values do not depend on the
+ * shape: observables are added in one order. */
 int dk_context_set_shape(dk_context* ctx, int32_t n, int32_t variant);
 int dk_shape_rows(int32_t n, int32_t variant);
 int dk_shape_spw(int32_t n, int32_t variant);

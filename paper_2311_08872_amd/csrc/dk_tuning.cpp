@@ -116,16 +116,16 @@ void save_tuning_cache(const dk_context* ctx)
 //         16^2: 1024 samples 1.1 / 1.9 / 3.6, 8192 4.7 / 5.1 / 5.2, 32768 15.9 / 16.7 / 15.2
 //         32^2: 1024 samples 2.7 / 2.8 / 3.9, 3456 7.5 / 7.5 / 8.5, 7776 15.8 / 15.7 / 15.1
 //         64^2: 256 samples 2.9 / 2.9 / 3.9, 512 5.3 / 4.8 / 4.8, 1536 14.8 / 12.8 / 11.7
-//   FP64   8^2: 4096 samples 1.7 / 2.7 / 4.2, 16384 4.5 / 4.3 / 4.6, 32768 8.3 / 7.5 / 7.1
-//         16^2: 2048 samples 2.5 / 2.6 / 4.5, 8192 7.9 / 7.2 / 7.4, 16384 14.6 / 13.1 / 13.0
-//         32^2: 512 samples 2.5 / 2.8 / 4.5, 1024 4.3 / 4.0 / 4.8, 7776 27.4 / 25.3 / 23.9
-//         64^2: 256 samples 4.5 / 4.1 / 4.9, 512 8.8 / 7.1 / 6.9
+//   FP64   8^2: 4096 samples 1.5 / 2.4 / 3.9, 16384 3.9 / 3.8 / 4.2, 32768 7.2 / 6.6 / 6.5
+//         16^2: 2048 samples 2.4 / 2.4 / 4.1, 8192 7.3 / 6.9 / 7.2, 16384 13.4 / 12.5 / 12.7
+//         32^2: 512 samples 2.2 / 2.4 / 4.0, 1024 3.8 / 3.7 / 4.2, 7776 23.5 / 22.8 / 21.3
+//         64^2: 256 samples 4.0 / 3.8 / 4.4, 512 7.8 / 6.6 / 6.3
 // (4^2 and 128^2 have no smaller tile.)  Single paths cross at the same sizes within a few percent, and
 // can run one row per lane:
 //   FP32   8^2: 1024 samples 0.69 against 1.0 at 2 rows, 8192 1.5 / 1.4;  16^2: 512 samples 0.72 / 0.98, 2048 1.6 / 1.5
 //   FP64   8^2: 1024 samples 1.1 / 1.5, 4096 1.6 / 1.6;  16^2: 512 samples 1.1 / 1.4, 1024 1.6 / 1.6
 // FP64 pairs of 64^2 fit three 8-row blocks on a compute unit, so 769 to 1024 samples would open a second
-// round for the rest: 15.5 us a step against 13.4 with the 4-row shape's two full ones.
+// round for the rest: 14.1 us a step against 12.4 with the 4-row shape's two full ones.
 int small_batch_rows(int nf, bool f64, bool pair, uint64_t count)
 {
     struct Line { int n; uint64_t one, two, four; };
