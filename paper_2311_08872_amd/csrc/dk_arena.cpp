@@ -35,7 +35,7 @@ struct Carve {
 
 // I_h rho0 (state type), I_h phi_j and the per-observable {scale, centre, psi} of level l into
 // the arena; the centring constants from the noise-free FP64 field formed in `tmp` (two fields and the
-// inner products: 16 n^2 + 8 n_obs (1 + kInnerParts) bytes).
+// inner products: 16 n^2 + 8 n_obs kInnerOut bytes).
 int arena_tables(const dk_problem* p, int l, void* rho0, double* phi, double* obs, void* tmp, hipStream_t s)
 {
     const int n = level_n(p, l), nobs = p->n_obs;
@@ -51,13 +51,9 @@ int arena_tables(const dk_problem* p, int l, void* rho0, double* phi, double* ob
     if (any) {
         double* r0 = (double*)tmp;
         double* r1 = r0 + (size_t)n * n;
-        double* out = r1 + (size_t)n * n;
         double* fin = nullptr;
-        HIP_TRY(dk::launch_field_eval(to_dev_on(p, p->rho0, n), p->box, n, r0, true, s));
-        HIP_TRY(dk::launch_meanfield_stream(n, 0.5 * p->mu, (int)level_steps(p, steps0_of(p), l), r0, r1, &fin, s));
-        HIP_TRY(dk::launch_inner_products(fin, n, phi, nobs, h * h, out, s));
-        HIP_TRY(hipMemcpyAsync(centre, out, sizeof(double) * nobs, hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipStreamSynchronize(s));
+        const int rc = mean_field(p, l, phi, r0, r1, r1 + (size_t)n * n, centre, &fin, s);
+        if (rc) return rc;
     }
     for (int j = 0; j < nobs; ++j) {
         host_obs[3 * j + 0] = p->obs[j].scale_sqrtN ? std::sqrt(p->N) : 1.0;
@@ -100,7 +96,7 @@ int level_pair_arena(const dk_problem* p, int level, uint64_t first, uint64_t co
     void* rho0_c = pair ? C.take(esize * ncc) : nullptr;
     double* phi_c = pair ? (double*)C.take(8 * nobs * ncc) : nullptr;
     double* obs_c = pair ? (double*)C.take(8 * 3 * nobs) : nullptr;
-    void* tmp = C.take(16 * nn + 8 * (size_t)nobs * (1 + dk::kInnerParts));
+    void* tmp = C.take(16 * nn + 8 * (size_t)nobs * dk::kInnerOut);
     double* mom = (double*)C.take(8 * mom_stride * kGroup);
     if (!C.ok)
         return fail(DK_EINVAL, "level %d (%d x %d, %d observables) needs more than the %zu bytes of scratch of the "

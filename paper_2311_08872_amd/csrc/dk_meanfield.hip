@@ -1,5 +1,6 @@
 // dk_meanfield.hip -- the noise-free scheme to its final time (the discrete mean field of Sec. 3,
-// which centres the observables) and its inner products with the test functions, in FP64.
+// which centres the observables) and its inner products with the test functions, in FP64: stepped, or in
+// the scheme's eigenbasis.
 //
 // rho^M = (I + (mu/2) Lap_h)^M rho^0 is diagonal in the discrete Fourier basis, with the factor
 // g^M = (1 - 2 mu (sin^2(pi kx/n) + sin^2(pi ky/n)))^M (Appendix A, operator A_h), so M steps cost the
@@ -13,13 +14,19 @@
 //
 // Bound by the FP64 matrix rate for n >= 1024 and by the latency of four dependent passes below.
 // One launch per step took 118 ms at 512 x 512 with 26624 steps (4.7 us a launch); now four of 18 us (145 us a call).
-// g^M comes from exp(M log1p(-lambda)), whose error does not grow with M, so the result is as near the
-// exact field as stepping is.
+// g^M comes from exp(M log1p(-lambda)), whose error does not grow with M: 1.07e-14 of the field against 1.04e-14
+// for the steps at 512 x 512.
+//
+// The field of the two ways agrees to its rounding, and so do the inner products, relative to the size of their
+// terms.  An inner product that cancels (an even datum and an odd test function) is the rounding itself, and has no
+// digit in common between them.  The steps define its value: the caller takes the transform's result only where no
+// inner product is below kCancelled of its terms' size, and steps the field otherwise.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
 
 #include "dk_internal.h"
+#include "dk_level.h"
 
 namespace dk {
 
@@ -146,7 +153,84 @@ __global__ void __launch_bounds__(256) cas_pass_kernel(const double* __restrict_
     }
 }
 
-// One step, for the few steps that cost less than four passes
+// The steps of a resident grid (4, 8, .. 128) and the inner products, in one block: the tiles of the level
+// kernels (2 columns and R rows per lane, the rows above and below through LDS, one barrier a step).  A step of
+// 128 x 128 takes 1.74 us, the latency of a lane's 16 rows.
+template <int N>
+struct Resident {
+    static constexpr int R = N == 4 ? 4 : (N == 128 ? 16 : 8), NPL = N / 2, G = N / R, TS = NPL * G;
+};
+
+template <int N>
+__global__ void __launch_bounds__(Resident<N>::TS) meanfield_steps_kernel(double* __restrict__ field, double a, int steps,
+                                                                        const double* __restrict__ phi, int n_obs, double h2,
+                                                                        double* __restrict__ out)
+{
+#pragma clang fp contract(off)
+    constexpr int R = Resident<N>::R, NPL = Resident<N>::NPL, G = Resident<N>::G, TS = Resident<N>::TS;
+    constexpr bool WL = TS <= 64;
+    __shared__ __align__(16) double halo[2][G][2][N];
+    __shared__ double red[(TS + 63) / 64];
+    const int t = threadIdx.x, cl = t % NPL, g = t / NPL, lane = t & 63;
+    const int addr_l = (lane - cl + (cl + NPL - 1) % NPL) * 4, addr_r = (lane - cl + (cl + 1) % NPL) * 4;
+    const int gu = g == 0 ? G - 1 : g - 1, gd = g == G - 1 ? 0 : g + 1;
+    double rho[R][2];
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+#pragma unroll
+        for (int c = 0; c < 2; ++c) rho[i][c] = field[(R * g + i) * N + 2 * cl + c];
+#pragma unroll 1
+    for (int m = 0; m < steps; ++m) {
+        auto& buf = halo[m & 1];
+        double prev[2], below[2];
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            buf[g][0][2 * cl + c] = rho[0][c];
+            buf[g][1][2 * cl + c] = rho[R - 1][c];
+        }
+        sample_sync<WL>();               // the other buffer is written next: one barrier a step
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            prev[c] = buf[gu][1][2 * cl + c];
+            below[c] = buf[gd][0][2 * cl + c];
+        }
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            const double o0 = rho[i][0], o1 = rho[i][1];
+            const double n0 = i + 1 < R ? rho[i + 1 < R ? i + 1 : 0][0] : below[0];
+            const double n1 = i + 1 < R ? rho[i + 1 < R ? i + 1 : 0][1] : below[1];
+            const double l = lane_get(addr_l, o1), r = lane_get(addr_r, o0);
+            rho[i][0] = o0 + a * fma(-4.0, o0, (l + o1) + (prev[0] + n0));
+            rho[i][1] = o1 + a * fma(-4.0, o1, (o0 + r) + (prev[1] + n1));
+            prev[0] = o0;
+            prev[1] = o1;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+#pragma unroll
+        for (int c = 0; c < 2; ++c) field[(R * g + i) * N + 2 * cl + c] = rho[i][c];
+    for (int j = 0; j < n_obs; ++j) {
+        const double* ph = phi + (size_t)j * N * N;
+        double v = 0.0;
+#pragma unroll
+        for (int i = 0; i < R; ++i)
+#pragma unroll
+            for (int c = 0; c < 2; ++c) v = fma(rho[i][c], ph[(R * g + i) * N + 2 * cl + c], v);
+#pragma unroll
+        for (int off = (TS < 64 ? TS : 64) / 2; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+        if constexpr (!WL) {
+            if (lane == 0) red[t >> 6] = v;
+            __syncthreads();
+            v = 0.0;
+            for (int w = 0; w < TS / 64; ++w) v += red[w];
+            __syncthreads();
+        }
+        if (t == 0) out[j] = h2 * v;
+    }
+}
+
+// One step of any other grid
 __global__ void heat_step_kernel(const double* __restrict__ in, double* __restrict__ out, int n, double a)
 {
     const int x = blockIdx.x * blockDim.x + threadIdx.x;
@@ -161,6 +245,7 @@ __global__ void heat_step_kernel(const double* __restrict__ in, double* __restri
 
 __device__ __forceinline__ double block_sum(double v, double* sh)
 {
+    __syncthreads();
     sh[threadIdx.x] = v;
     __syncthreads();
     for (int w = 128; w >= 1; w >>= 1) {
@@ -170,70 +255,104 @@ __device__ __forceinline__ double block_sum(double v, double* sh)
     return sh[0];
 }
 
-// part p of the inner product with observable j (grid: parts x observables); one part: the result itself
+// Part p of the inner product with observable j and of the size of its terms (grid: parts x observables).  One part:
+// the results themselves.  out: [products][sizes][parts of both, 2 per block].
 __global__ void __launch_bounds__(256) inner_kernel(const double* __restrict__ rho, int nn, const double* __restrict__ phi,
                                                     double h2, double* __restrict__ out)
 {
     __shared__ double sh[256];
-    const int j = blockIdx.y, parts = gridDim.x;
+    const int j = blockIdx.y, parts = gridDim.x, nobs = gridDim.y;
     const double* ph = phi + (size_t)j * nn;
-    double acc = 0.0;
+    double acc = 0.0, size = 0.0;
 #pragma unroll 4
-    for (int i = blockIdx.x * 256 + threadIdx.x; i < nn; i += 256 * parts) acc = fma(rho[i], ph[i], acc);
-    const double s = block_sum(acc, sh);
-    if (threadIdx.x == 0) {
-        if (parts == 1) out[j] = h2 * s;
-        else out[gridDim.y + j * parts + blockIdx.x] = s;
+    for (int i = blockIdx.x * 256 + threadIdx.x; i < nn; i += 256 * parts) {
+        const double r = rho[i], f = ph[i];
+        acc = fma(r, f, acc);
+        size = fma(fabs(r), fabs(f), size);
+    }
+    const double s = block_sum(acc, sh), z = block_sum(size, sh);
+    if (threadIdx.x != 0) return;
+    if (parts == 1) {
+        out[j] = h2 * s;
+        out[nobs + j] = h2 * z;
+    } else {
+        double* part = out + 2 * nobs + 2 * (j * parts + blockIdx.x);
+        part[0] = s;
+        part[1] = z;
     }
 }
 
 __global__ void __launch_bounds__(256) inner_finish_kernel(int parts, double h2, double* __restrict__ out)
 {
     __shared__ double sh[256];
-    const int j = blockIdx.x, nobs = gridDim.x;
-    const double s = block_sum((int)threadIdx.x < parts ? out[nobs + j * parts + threadIdx.x] : 0.0, sh);
-    if (threadIdx.x == 0) out[j] = h2 * s;
+    const int j = blockIdx.x, nobs = gridDim.x, t = threadIdx.x;
+    const double* part = out + 2 * nobs + 2 * j * parts;
+    const double s = block_sum(t < parts ? part[2 * t] : 0.0, sh), z = block_sum(t < parts ? part[2 * t + 1] : 0.0, sh);
+    if (t != 0) return;
+    out[j] = h2 * s;
+    out[nobs + j] = h2 * z;
+}
+
+template <int N>
+hipError_t resident_steps(double a, int steps, double* field, const double* phi, int n_obs, double h2, double* out, hipStream_t s)
+{
+    hipLaunchKernelGGL(meanfield_steps_kernel<N>, dim3(1), dim3(Resident<N>::TS), 0, s, field, a, steps, phi, n_obs, h2, out);
+    return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_meanfield_stream(int n, double a, int steps, double* buf0, double* buf1, double** result, hipStream_t s)
+bool meanfield_steps_cheaper(int n, int steps)
+{
+    // Microseconds on MI355X: the four passes 4 (4^2) .. 30 (64^2) in one block, 31 (128^2), 46 (256^2), 105 (512^2)
+    // in four launches; a step 0.27 (4^2), 0.45 (8^2 .. 32^2), 0.60 (64^2), 1.74 (128^2) in one block, 3.5 (to 256^2),
+    // 4.4 (512^2), 60 (4096^2) as a launch.  25 more lie between the passes and the steps where both are needed.
+    const double passes = n <= kOneBlock ? 2.0 + 0.4 * n : 24.0 + 2.2e-7 * (double)n * n * n;
+    const double step = level_supported(n) ? 0.4 + 8e-5 * (double)n * n : 3.5 + 3.5e-6 * (double)n * n;
+    return steps * step <= passes + 25.0;
+}
+
+hipError_t launch_meanfield_steps(int n, double a, int steps, double* buf0, double* buf1, const double* phi, int n_obs, double h2,
+                                  double* out, double** result, hipStream_t s)
 {
     if (n < 2 || (n & 1) || n > 4096 || steps < 0) return hipErrorInvalidValue;
-    // Four passes against one launch per step, microseconds measured on MI355X: one block 8 (16^2) .. 28
-    // (64^2); four launches of 6 (128^2), 18 (512^2), 70 (1024^2), 3600 (4096^2); a step 2.4 (to 256^2), 4.6
-    // (512^2), 8 (1024^2), 60 (4096^2)
-    const double passes = n <= kOneBlock ? 2.0 + 0.4 * n : 24.0 + 2.2e-7 * (double)n * n * n;
-    const double stepping = steps * (2.4 + 3.5e-6 * (double)n * n);
     *result = buf0;
-    if (stepping <= passes) {
-        double *in = buf0, *out = buf1;
-        const dim3 grid((n + 255) / 256, n);
-        for (int m = 0; m < steps; ++m) {
-            hipLaunchKernelGGL(heat_step_kernel, grid, dim3(256), 0, s, in, out, n, a);
-            double* t = in; in = out; out = t;
-        }
-        *result = in;
-        return hipGetLastError();
+    switch (n) {
+    case 4: return resident_steps<4>(a, steps, buf0, phi, n_obs, h2, out, s);
+    case 8: return resident_steps<8>(a, steps, buf0, phi, n_obs, h2, out, s);
+    case 16: return resident_steps<16>(a, steps, buf0, phi, n_obs, h2, out, s);
+    case 32: return resident_steps<32>(a, steps, buf0, phi, n_obs, h2, out, s);
+    case 64: return resident_steps<64>(a, steps, buf0, phi, n_obs, h2, out, s);
+    case 128: return resident_steps<128>(a, steps, buf0, phi, n_obs, h2, out, s);
+    default: break;
     }
-    const int T = (n + 15) / 16;
-    if (n <= kOneBlock) {
-        hipLaunchKernelGGL(meanfield_block_kernel, dim3(1), dim3(64 * T * T), 0, s, buf0, n, a, steps);
-        return hipGetLastError();
+    double *in = buf0, *to = buf1;
+    const dim3 grid((n + 255) / 256, n);
+    for (int m = 0; m < steps; ++m) {
+        hipLaunchKernelGGL(heat_step_kernel, grid, dim3(256), 0, s, in, to, n, a);
+        double* t = in; in = to; to = t;
     }
-    const dim3 grid((unsigned)(T * ((T + 3) / 4)));
-    for (int pass = 0; pass < 4; ++pass)
-        hipLaunchKernelGGL(cas_pass_kernel, grid, dim3(256), sizeof(double) * n, s, pass & 1 ? buf1 : buf0, pass & 1 ? buf0 : buf1,
-                           n, a, pass == 1 ? steps : 0);
+    *result = in;
+    hipLaunchKernelGGL(inner_kernel, dim3(1, n_obs), dim3(256), 0, s, in, n * n, phi, h2, out);
     return hipGetLastError();
 }
 
-hipError_t launch_inner_products(const double* rho, int n, const double* phi, int n_obs, double h2, double* out,
-                                 hipStream_t s)
+hipError_t launch_meanfield_transform(int n, double a, int steps, double* buf0, double* buf1, const double* phi, int n_obs,
+                                      double h2, double* out, hipStream_t s)
 {
+    if (n < 2 || (n & 1) || n > 4096 || steps < 1) return hipErrorInvalidValue;
+    const int T = (n + 15) / 16;
+    if (n <= kOneBlock) {
+        hipLaunchKernelGGL(meanfield_block_kernel, dim3(1), dim3(64 * T * T), 0, s, buf0, n, a, steps);
+    } else {
+        const dim3 grid((unsigned)(T * ((T + 3) / 4)));
+        for (int pass = 0; pass < 4; ++pass)
+            hipLaunchKernelGGL(cas_pass_kernel, grid, dim3(256), sizeof(double) * n, s, pass & 1 ? buf1 : buf0,
+                               pass & 1 ? buf0 : buf1, n, a, pass == 1 ? steps : 0);
+    }
     // above 128 x 128 one block per observable would read its megabytes alone (320 us at 512 x 512)
     const int parts = n <= 128 ? 1 : kInnerParts;
-    hipLaunchKernelGGL(inner_kernel, dim3(parts, n_obs), dim3(256), 0, s, rho, n * n, phi, h2, out);
+    hipLaunchKernelGGL(inner_kernel, dim3(parts, n_obs), dim3(256), 0, s, buf0, n * n, phi, h2, out);
     if (parts > 1) hipLaunchKernelGGL(inner_finish_kernel, dim3(n_obs), dim3(256), 0, s, parts, h2, out);
     return hipGetLastError();
 }

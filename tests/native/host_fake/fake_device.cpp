@@ -513,29 +513,46 @@ hipError_t launch_gauss(const uint32_t* a, const uint32_t* b, uint64_t count, fl
     });
 }
 
-hipError_t launch_meanfield_stream(int n, double, int steps, double* buf0, double* buf1, double** result, hipStream_t s)
+bool meanfield_steps_cheaper(int n, int steps) { return steps <= 8 || n == 16; }
+
+// The result ends in buf0 on resident grids and in either buffer on the others.
+hipError_t launch_meanfield_steps(int n, double, int steps, double* buf0, double* buf1, const double* phi, int n_obs, double,
+                                  double* out, double** result, hipStream_t s)
 {
     double* in = buf0;
-    double* out = buf1;
-    for (int m = 0; m < steps; ++m) {
-        const hipError_t e = submit(s, [=] {
-            touch_read(in, sizeof(double) * n * n, "meanfield in");
-            touch_write(out, sizeof(double) * n * n, "meanfield out");
-        });
-        if (e != hipSuccess) return e;
-        std::swap(in, out);
-    }
+    double* to = buf1;
+    if (!level_supported(n))
+        for (int m = 0; m < steps; ++m) {
+            const hipError_t e = submit(s, [=] {
+                touch_read(in, sizeof(double) * n * n, "meanfield in");
+                touch_write(to, sizeof(double) * n * n, "meanfield out");
+            });
+            if (e != hipSuccess) return e;
+            std::swap(in, to);
+        }
     *result = in;
-    return hipSuccess;
+    return submit(s, [=] {
+        touch_write(in, sizeof(double) * n * n, "meanfield field");
+        touch_read(phi, sizeof(double) * n_obs * n * n, "meanfield phi");
+        touch_write(out, sizeof(double) * 2 * n_obs, "meanfield products");
+        for (int j = 0; j < n_obs; ++j) out[j] = 0.25 + 0.01 * j;
+    });
 }
 
-hipError_t launch_inner_products(const double* rho, int n, const double* phi, int n_obs, double, double* out, hipStream_t s)
+// Observable 0 cancels: its value is then taken from the steps.
+hipError_t launch_meanfield_transform(int n, double, int, double* buf0, double* buf1, const double* phi, int n_obs, double,
+                                      double* out, hipStream_t s)
 {
     return submit(s, [=] {
-        touch_read(rho, sizeof(double) * n * n, "inner rho");
-        touch_read(phi, sizeof(double) * n_obs * n * n, "inner phi");
-        touch_write(out, sizeof(double) * n_obs, "inner out");
-        for (int j = 0; j < n_obs; ++j) out[j] = 0.25 + 0.01 * j;
+        touch_write(buf0, sizeof(double) * n * n, "meanfield transform buf0");
+        if (n > 64) touch_write(buf1, sizeof(double) * n * n, "meanfield transform buf1");
+        touch_read(phi, sizeof(double) * n_obs * n * n, "meanfield phi");
+        const int per = n <= 128 ? 2 : 2 * (1 + kInnerParts);
+        touch_write(out, sizeof(double) * n_obs * per, "meanfield products and parts");
+        for (int j = 0; j < n_obs; ++j) {
+            out[j] = j == 0 ? 1e-9 : 0.25 + 0.01 * j;
+            out[n_obs + j] = 1.0;
+        }
     });
 }
 
