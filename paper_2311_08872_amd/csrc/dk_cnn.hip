@@ -18,8 +18,8 @@
 // pass also writes the two activations and a 16-bit ReLU mask per pixel).  Grids of at most 16 x 16
 // put several samples into one block.  A layer as its own pass over HBM moved 64 B per pixel and
 // layer and summed the pool in one thread per (sample, channel): 4.64 ms for 4000 inputs of 64 x 64
-// (0.85 ms per 1024 of it the pool) against 0.49 ms now: the vector ALU is busy two thirds of it (addresses,
-// roundings and packing, ReLU), the matrix cores and LDS a third each.
+// (0.85 ms per 1024 of it the pool) against 0.51 ms now, bound by the vector ALU (roundings and packing, ReLU,
+// addresses) and the five LDS reads of 1 KB per 16 pixels and layer.
 // An activation image is two planes of 8 channels, 16 B per pixel each, so the 16 pixels of an MFMA
 // operand are 256 consecutive bytes.  The register bounds keep the accumulators among the vector registers:
 // without them the compiler puts them into the second file and moves every result (4 % of the kernel).
@@ -77,9 +77,6 @@ struct Geo {
     int P, img, L;      // image pitch, pixels of one sample's image, of all S
     int groups;         // ceil(batch / S) x tiles per sample: work items
     Div dP, dImg, dTiles, dTx, dTw, dTile;
-    // forward: row pairs of one sample and pixels of a row that the second and third layer compute
-    int pairs[2], cols[2];
-    Div dCols[2], dPairs[2];
 };
 
 constexpr int kTileW = 32, kTileH = 16;
@@ -124,12 +121,6 @@ static Geo make_geo(int n, int batch, int H)
     g.dTx = Div(g.tx);
     g.dTw = Div(g.tw);
     g.dTile = Div(g.tw * g.th);
-    for (int k = 0; k < 2; ++k) {
-        g.pairs[k] = cdiv(g.th + 2 - 2 * k, 2);
-        g.cols[k] = g.tw + 2 - 2 * k;
-        g.dCols[k] = Div(g.cols[k]);
-        g.dPairs[k] = Div(g.pairs[k] * g.cols[k]);
-    }
     return g;
 }
 
@@ -186,29 +177,6 @@ __device__ __forceinline__ void neighbour_offsets(int (&off)[5], int P, int lane
     }
 }
 
-// The forward convolutions take two rows of output at once.  An operand of the image holds 16 pixels of two
-// consecutive rows, 16 channels each (K = 32): the rows above and at the first output row (A), or the two rows
-// below it (B).  w[dx]: their weights {A, B} -> first output row, {A, B} -> second one, zero where the row is
-// not a neighbour.  Six operands and twelve products per 2 x 16 outputs: per 16 pixels 3 reads of 1 KB from LDS
-// instead of the 5 of conv16.
-struct RowWeights {
-    uint4 w[3][4];
-    __device__ __forceinline__ void load(const uint16_t* __restrict__ Wk, int lane)
-    {
-        const bool second = lane >= 32;
-        const uint16_t* p = Wk + (lane & 15) * 160 + 8 * ((lane >> 4) & 1);
-        const uint4 zero = make_uint4(0, 0, 0, 0);
-#pragma unroll
-        for (int dx = 0; dx < 3; ++dx) {
-            const uint4 a = *(const uint4*)(p + 16 * dx), m = *(const uint4*)(p + 16 * (dx + 3)), b = *(const uint4*)(p + 16 * (dx + 6));
-            w[dx][0] = second ? m : a;
-            w[dx][1] = second ? zero : b;
-            w[dx][2] = second ? a : zero;
-            w[dx][3] = second ? b : m;
-        }
-    }
-};
-
 // ---------------------------------------------------------------------------------------
 // Forward: the three convolutions of one tile.  KEEP: also writes the activations a1, a2 ([pixel][16]
 // BF16) and the third layer's ReLU mask for the backward pass.  gpart[sample][tile][16] receives the
@@ -240,14 +208,14 @@ __global__ void __launch_bounds__(kFwdThreads, 3) conv_fwd(const Geo g, const fl
             sx[e] = x[b * nn + (size_t)wrapn(T.y0 + yy - 3, n) * n + wrapn(T.x0 + xx - 3, n)];
         }
     }
-    RowWeights w2, w3;
-    w2.load(wt2, lane);
-    w3.load(wt3, lane);
+    uint4 w2[5], w3[5];
+    load_weights(w2, wt2, lane);
+    load_weights(w3, wt3, lane);
     __syncthreads();
     const int i = lane & 15, kg = lane >> 4;
     // First layer on the whole image (halo 2): 16 pixels by 16 outputs, K = 9 neighbours padded to 12 on the FP32
-    // matrix instruction.  A fused multiply-add of its own per product took a third of the kernel's vector
-    // instructions.
+    // matrix instruction, which adds its four products in order, each fused and rounded, as nine multiply-adds do.
+    // A fused multiply-add of its own per product took a third of the kernel's vector instructions.
     {
         const int xp = g.tw + 6, xi = xp * (g.th + 6);
         float w1[3], b1[4];
@@ -275,52 +243,31 @@ __global__ void __launch_bounds__(kFwdThreads, 3) conv_fwd(const Geo g, const fl
         }
     }
     __syncthreads();
-    // layer k (0: the second, 1: the third): rows 1 + k .. th + 2 - k, columns 1 + k .. tw + 2 - k of src -> dst.
-    // Where the last pair has no second row, its row below the image (times zero weights) is the image's last:
-    // the next sample's values or unwritten ones could be non-finite.
-    // POOL (one sample a block): the outputs inside the tile are added to v; dst is written where it is read.
+    int off[5];
+    neighbour_offsets(off, P, lane, 1);
+    // One layer: image pixels [lo, hi) of src -> dst, over the image's linear index (tile rows and their halo columns
+    // alike; what comes out in halo columns is not used).  The neighbours are added row by row, as by the backward
+    // pass: with two rows of outputs from one operand (5 % faster) they were added column by column, other BF16
+    // roundings followed, and outputs moved by up to 4e-5 of their RMS on small grids.
+    // POOL (one sample a block): the outputs inside the tile are added to v4; dst is written where it is read.
     float v4[4] = {0.f, 0.f, 0.f, 0.f};
-    auto layer = [&](const uint4* src, uint4* dst, const RowWeights& W, const float* bias, int k, auto pool) {
+    auto layer = [&](const uint4* src, uint4* dst, const uint4 (&w)[5], const float* bias, int lo, int hi, auto pool) {
         constexpr bool POOL = decltype(pool)::value;
         float b4[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) b4[r] = bias[4 * kg + r];
-        const int per = g.pairs[k] * g.cols[k], total = g.S * per, last = g.th + 2 - k;
-        for (int g0 = 16 * wave; g0 < total; g0 += 16 * WAVES) {
-            const int u = min(g0 + i, total - 1), s = g.dPairs[k].q(u), r = u - s * per, j = g.dCols[k].q(r);
-            const int row = 1 + k + 2 * j, q = s * g.img + row * P + 1 + k + (r - j * g.cols[k]);
-            const uint4* p = src + (kg & 1) * PL + q;
-            const uint4* pa = p + (kg >> 1 ? 0 : -P);
-            const uint4* pb = p + (kg >> 1 && row + 2 <= last + 1 ? 2 * P : P);
-            floatx4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int dx = 0; dx < 3; ++dx) {
-                const bf16x8 a = __builtin_bit_cast(bf16x8, pa[dx - 1]), b = __builtin_bit_cast(bf16x8, pb[dx - 1]);
-                auto w = [&](int e) { return __builtin_bit_cast(bf16x8, W.w[dx][e]); };
-                acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w(0), a, acc0, 0, 0, 0);
-                acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w(2), a, acc1, 0, 0, 0);
-                acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w(1), b, acc0, 0, 0, 0);
-                acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w(3), b, acc1, 0, 0, 0);
-            }
-            uint2* o = (uint2*)&dst[(kg >> 1) * PL + q] + (kg & 1);
-            const uint2 o0 = make_uint2(pack2(fmaxf(acc0[0] + b4[0], 0.0f), fmaxf(acc0[1] + b4[1], 0.0f)),
-                                        pack2(fmaxf(acc0[2] + b4[2], 0.0f), fmaxf(acc0[3] + b4[3], 0.0f)));
-            const uint2 o1 = make_uint2(pack2(fmaxf(acc1[0] + b4[0], 0.0f), fmaxf(acc1[1] + b4[1], 0.0f)),
-                                        pack2(fmaxf(acc1[2] + b4[2], 0.0f), fmaxf(acc1[3] + b4[3], 0.0f)));
-            if (!POOL || KEEP) {
-                *o = o0;
-                if (row < last) o[2 * P] = o1;
-            }
+        for (int g0 = lo + 16 * wave; g0 < hi; g0 += 16 * WAVES) {
+            const floatx4 acc = conv16(src, PL, g0, off, w, lane);
+            const uint2 o = make_uint2(pack2(fmaxf(acc[0] + b4[0], 0.0f), fmaxf(acc[1] + b4[1], 0.0f)),
+                                       pack2(fmaxf(acc[2] + b4[2], 0.0f), fmaxf(acc[3] + b4[3], 0.0f)));
+            if (!POOL || KEEP) ((uint2*)&dst[(kg >> 1) * PL + g0 + i])[kg & 1] = o;
             if constexpr (POOL) {
-                const bool in = g0 + i < total && r - j * g.cols[k] < T.tw;
-                auto add = [&](uint2 d, bool use) {
-                    v4[0] += __uint_as_float(use ? d.x << 16 : 0u);
-                    v4[1] += __uint_as_float(use ? d.x & 0xFFFF0000u : 0u);
-                    v4[2] += __uint_as_float(use ? d.y << 16 : 0u);
-                    v4[3] += __uint_as_float(use ? d.y & 0xFFFF0000u : 0u);
-                };
-                add(o0, in && row - 2 < T.th);
-                add(o1, in && row - 1 < T.th && row < last);
+                const int q = g0 + i, yy = g.dP.q(q), xx = q - yy * P - 2;
+                const bool in = q < hi && (unsigned)(yy - 2) < (unsigned)T.th && (unsigned)xx < (unsigned)T.tw;
+                v4[0] += __uint_as_float(in ? o.x << 16 : 0u);
+                v4[1] += __uint_as_float(in ? o.x & 0xFFFF0000u : 0u);
+                v4[2] += __uint_as_float(in ? o.y << 16 : 0u);
+                v4[3] += __uint_as_float(in ? o.y & 0xFFFF0000u : 0u);
             }
         }
     };
@@ -334,11 +281,11 @@ __global__ void __launch_bounds__(kFwdThreads, 3) conv_fwd(const Geo g, const fl
                     src[h * PL + s * g.img + (yy + 2) * P + xx + 2];
         }
     };
-    layer(sA, sB, w2, prm + OFF_B2, 0, std::false_type());
+    layer(sA, sB, w2, prm + OFF_B2, P + 1, L - P - 1, std::false_type());
     if constexpr (KEEP) keep(sA, a1g);
     __syncthreads();
-    if (g.S == 1) layer(sB, sA, w3, prm + OFF_B3, 1, std::true_type());
-    else layer(sB, sA, w3, prm + OFF_B3, 1, std::false_type());
+    if (g.S == 1) layer(sB, sA, w3, prm + OFF_B3, 2 * P + 2, L - 2 * P - 2, std::true_type());
+    else layer(sB, sA, w3, prm + OFF_B3, 2 * P + 2, L - 2 * P - 2, std::false_type());
     if constexpr (KEEP) keep(sB, a2g);
     __syncthreads();
     if constexpr (KEEP) {
