@@ -26,7 +26,7 @@ struct Workspace {
     bool keep = true;
     float *gpart = nullptr, *g_ = nullptr;                                      // pool: per tile, per sample
     uint16_t *wt2 = nullptr, *wb2 = nullptr, *wt3 = nullptr, *wb3 = nullptr;    // BF16 GEMM weights
-    uint16_t *a1 = nullptr, *a2 = nullptr, *dz2 = nullptr;                      // BF16 [pixels][16]
+    uint16_t *a1 = nullptr, *a2 = nullptr, *a3 = nullptr, *dz2 = nullptr;       // BF16 [pixels][16]
     uint16_t *m3 = nullptr, *dgs = nullptr;                                     // ReLU mask [pixels], BF16 [batch][16]
     float *sq = nullptr, *drs = nullptr, *dh = nullptr, *da = nullptr, *part = nullptr;
     hipError_t reserve(int n, int batch);

@@ -15,7 +15,7 @@
 // LDS once, the first layer writes its 16 channels there with a halo of 2, the second reads it and
 // writes beside it, the third adds its outputs to the tile's channel sums (several samples in a block: by
 // way of LDS): nothing but x is read from HBM and nothing but 16 sums per tile is written (the training
-// pass also writes the two activations and a 16-bit ReLU mask per pixel).  Grids of at most 16 x 16
+// pass writes the three activations and a 16-bit ReLU mask per pixel instead).  Grids of at most 16 x 16
 // put several samples into one block.  A layer as its own pass over HBM moved 64 B per pixel and
 // layer and summed the pool in one thread per (sample, channel): 4.64 ms for 4000 inputs of 64 x 64
 // (0.85 ms per 1024 of it the pool) against 0.51 ms now, bound by the vector ALU (roundings and packing, ReLU,
@@ -31,7 +31,7 @@
 // piece.  The bias gradient is a tenth product with a column of ones.  The same kernel convolves the
 // gradient back to the layer's input.  Per-block partial sums are added in block order by the last
 // kernel, which also forms the dense head's gradients.  Loss and gradient at 64 x 64, batch 256:
-// 4.01 ms with one kernel per product (2-byte gathers, serial column sums, 27 launches), 0.27 ms now.
+// 4.01 ms with one kernel per product (2-byte gathers, serial column sums, 27 launches), 0.29 ms now.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -178,15 +178,15 @@ __device__ __forceinline__ void neighbour_offsets(int (&off)[5], int P, int lane
 }
 
 // ---------------------------------------------------------------------------------------
-// Forward: the three convolutions of one tile.  KEEP: also writes the activations a1, a2 ([pixel][16]
-// BF16) and the third layer's ReLU mask for the backward pass.  gpart[sample][tile][16] receives the
-// tile's channel sums.
+// Forward: the three convolutions of one tile.  KEEP (training): writes the activations a1, a2, a3 ([pixel][16]
+// BF16) and the third layer's ReLU mask.  Else gpart[sample][tile][16] receives the tile's channel sums.
 // ---------------------------------------------------------------------------------------
 template <bool KEEP>
 __global__ void __launch_bounds__(kFwdThreads, 3) conv_fwd(const Geo g, const float* __restrict__ x, const float* __restrict__ prm,
                                                 const uint16_t* __restrict__ wt2, const uint16_t* __restrict__ wt3,
                                                 float* __restrict__ gpart, uint16_t* __restrict__ a1g,
-                                                uint16_t* __restrict__ a2g, uint16_t* __restrict__ m3g)
+                                                uint16_t* __restrict__ a2g, uint16_t* __restrict__ a3g,
+                                                uint16_t* __restrict__ m3g)
 {
     constexpr int PL = kFwdL + 16;                 // plane: the last group of 16 reads past the image
     __shared__ float sx[kFwdX];
@@ -249,7 +249,7 @@ __global__ void __launch_bounds__(kFwdThreads, 3) conv_fwd(const Geo g, const fl
     // alike; what comes out in halo columns is not used).  The neighbours are added row by row, as by the backward
     // pass: with two rows of outputs from one operand (5 % faster) they were added column by column, other BF16
     // roundings followed, and outputs moved by up to 4e-5 of their RMS on small grids.
-    // POOL (one sample a block): the outputs inside the tile are added to v4; dst is written where it is read.
+    // POOL (one sample a block): the outputs inside the tile are added to v4 and not written.
     float v4[4] = {0.f, 0.f, 0.f, 0.f};
     auto layer = [&](const uint4* src, uint4* dst, const uint4 (&w)[5], const float* bias, int lo, int hi, auto pool) {
         constexpr bool POOL = decltype(pool)::value;
@@ -260,7 +260,7 @@ __global__ void __launch_bounds__(kFwdThreads, 3) conv_fwd(const Geo g, const fl
             const floatx4 acc = conv16(src, PL, g0, off, w, lane);
             const uint2 o = make_uint2(pack2(fmaxf(acc[0] + b4[0], 0.0f), fmaxf(acc[1] + b4[1], 0.0f)),
                                        pack2(fmaxf(acc[2] + b4[2], 0.0f), fmaxf(acc[3] + b4[3], 0.0f)));
-            if (!POOL || KEEP) ((uint2*)&dst[(kg >> 1) * PL + g0 + i])[kg & 1] = o;
+            if constexpr (!POOL) ((uint2*)&dst[(kg >> 1) * PL + g0 + i])[kg & 1] = o;
             if constexpr (POOL) {
                 const int q = g0 + i, yy = g.dP.q(q), xx = q - yy * P - 2;
                 const bool in = q < hi && (unsigned)(yy - 2) < (unsigned)T.th && (unsigned)xx < (unsigned)T.tw;
@@ -284,11 +284,12 @@ __global__ void __launch_bounds__(kFwdThreads, 3) conv_fwd(const Geo g, const fl
     layer(sA, sB, w2, prm + OFF_B2, P + 1, L - P - 1, std::false_type());
     if constexpr (KEEP) keep(sA, a1g);
     __syncthreads();
-    if (g.S == 1) layer(sB, sA, w3, prm + OFF_B3, 2 * P + 2, L - 2 * P - 2, std::true_type());
+    if (!KEEP && g.S == 1) layer(sB, sA, w3, prm + OFF_B3, 2 * P + 2, L - 2 * P - 2, std::true_type());
     else layer(sB, sA, w3, prm + OFF_B3, 2 * P + 2, L - 2 * P - 2, std::false_type());
     if constexpr (KEEP) keep(sB, a2g);
     __syncthreads();
     if constexpr (KEEP) {
+        keep(sA, a3g);
         const int tile = g.tw * g.th;
         for (int q = t; q < g.S * tile; q += kFwdThreads) {
             const int s = g.dTile.q(q), r = q - s * tile, yy = g.dTw.q(r), xx = r - yy * g.tw;
@@ -307,6 +308,7 @@ __global__ void __launch_bounds__(kFwdThreads, 3) conv_fwd(const Geo g, const fl
             if (T.b0 + s < g.batch && yy < T.th && xx < T.tw)
                 m3g[(T.b0 + s) * nn + (size_t)(T.y0 + yy) * n + T.x0 + xx] = (uint16_t)m;
         }
+        return;
     }
     // channel sums.  One sample a block: of the third layer's lanes, over the block
     if (g.S == 1) {
@@ -365,10 +367,19 @@ __device__ __forceinline__ float head_hidden(const float* gs, const float* __res
     return s;
 }
 
+__device__ __forceinline__ float head_out(const float* hs, const float* __restrict__ prm)
+{
+    float v = prm[OFF_C2];
+#pragma unroll 16
+    for (int q = 0; q < 64; ++q) v = fmaf(prm[OFF_U2 + q], hs[q], v);
+    return v;
+}
+
 __global__ void __launch_bounds__(256) head_fwd(const float* __restrict__ gpart, int ntile, float nn, const float* __restrict__ prm,
                                                 int batch, float* __restrict__ gout, float* __restrict__ r)
 {
     __shared__ float sg[4][16];
+    __shared__ __align__(16) float sh[4][64];
     const int k = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int b = blockIdx.x * 4 + w;
     const bool on = b < batch;
@@ -380,11 +391,69 @@ __global__ void __launch_bounds__(256) head_fwd(const float* __restrict__ gpart,
         gout[(size_t)b * 16 + k] = s;
     }
     __syncthreads();
-    if (!on) return;
-    float v = prm[OFF_U2 + k] * fmaxf(head_hidden(sg[w], prm, k), 0.f);
+    if (on) sh[w][k] = fmaxf(head_hidden(sg[w], prm, k), 0.f);
+    __syncthreads();
+    if (on && k == 0) r[b] = head_out(sh[w], prm);
+}
+
+// The head of a training pass, a block per sample.  The gradient at the third layer is rounded to BF16, so the last
+// bit of an output turns one of its roundings in 20000 and moves the gradient of a small batch by up to 1e-4: in
+// training a channel's mean adds its pixels one after the other, whatever the tiles are, and the output its hidden
+// units.  Bound by that chain: 19 us for 4096 pixels.  Three wavefronts load 384 pixels ahead and turn them over
+// in LDS, the fourth adds (its own loads, or all four taking turns, left the chain waiting: 65 to 115 us).
+__global__ void __launch_bounds__(256) head_train(const uint16_t* __restrict__ a3, int nn, const float* __restrict__ prm,
+                                                  float* __restrict__ gout, float* __restrict__ r)
+{
+    constexpr int PX = 384, PITCH = PX + 4, LOADS = PX * 2 / 192;
+    __shared__ __align__(16) float sp[2][16 * PITCH];            // [channel][pixel]
+    __shared__ float sg[16];
+    __shared__ __align__(16) float sh[64];
+    const int k = threadIdx.x & 63, w = threadIdx.x >> 6, t = (int)threadIdx.x - 64;
+    const uint4* src = (const uint4*)(a3 + (size_t)blockIdx.x * nn * 16);
+    uint4 next[LOADS];
+    auto load = [&](int p0) {
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-    if (k == 0) r[b] = prm[OFF_C2] + v;
+        for (int q = 0; q < LOADS; ++q) next[q] = src[min(2 * p0 + t + 192 * q, 2 * nn - 1)];
+    };
+    if (w > 0) load(0);
+    float s = 0.f;
+    for (int p0 = 0, par = 0; p0 < nn; p0 += PX, par ^= 1) {
+        if (w > 0) {
+#pragma unroll
+            for (int q = 0; q < LOADS; ++q) {
+                const int e = t + 192 * q, px = e >> 1, h = e & 1;
+                const uint32_t d[4] = {next[q].x, next[q].y, next[q].z, next[q].w};
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    sp[par][(8 * h + 2 * j) * PITCH + px] = __uint_as_float(d[j] << 16);
+                    sp[par][(8 * h + 2 * j + 1) * PITCH + px] = __uint_as_float(d[j] & 0xFFFF0000u);
+                }
+            }
+            load(p0 + PX);
+        }
+        __syncthreads();          // the other buffer's reader came here, too, after its last read
+        if (w == 0 && k < 16) {
+            const float4* v = (const float4*)(sp[par] + k * PITCH);
+            const int m = min(PX, nn - p0) >> 2;                 // a multiple of 4
+#pragma unroll 8
+            for (int q = 0; q < m; ++q) {
+                const float4 d = v[q];
+                s += d.x;
+                s += d.y;
+                s += d.z;
+                s += d.w;
+            }
+        }
+    }
+    if (w == 0 && k < 16) {
+        s /= (float)nn;
+        sg[k] = s;
+        gout[(size_t)blockIdx.x * 16 + k] = s;
+    }
+    __syncthreads();
+    if (w == 0) sh[k] = fmaxf(head_hidden(sg, prm, k), 0.f);
+    __syncthreads();
+    if (threadIdx.x == 0) r[blockIdx.x] = head_out(sh, prm);
 }
 
 // Per sample: squared error, dL/dr, the hidden layer's gradient dh and dr relu(h) (for U1, c1, U2), and
@@ -806,6 +875,7 @@ hipError_t Workspace::reserve(int n_, int batch_)
         const size_t npix = (size_t)batch_ * n_ * n_;
         TAKE(a1, npix * 16 * 2);
         TAKE(a2, npix * 16 * 2);
+        TAKE(a3, npix * 16 * 2);
         TAKE(dz2, npix * 16 * 2);
         TAKE(m3, npix * 2);
         TAKE(sq, (size_t)batch_ * 4);
@@ -822,11 +892,11 @@ hipError_t Workspace::reserve(int n_, int batch_)
 
 void Workspace::release()
 {
-    void* ptrs[] = {gpart, g_, wt2, wb2, wt3, wb3, a1, a2, dz2, m3, sq, drs, dh, da, dgs, part};
+    void* ptrs[] = {gpart, g_, wt2, wb2, wt3, wb3, a1, a2, a3, dz2, m3, sq, drs, dh, da, dgs, part};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
     gpart = g_ = sq = drs = dh = da = part = nullptr;
-    wt2 = wb2 = wt3 = wb3 = a1 = a2 = dz2 = m3 = dgs = nullptr;
+    wt2 = wb2 = wt3 = wb3 = a1 = a2 = a3 = dz2 = m3 = dgs = nullptr;
     n = batch = kept = 0;
 }
 
@@ -841,13 +911,15 @@ hipError_t forward(Workspace& W, const float* prm, const float* x, int batch, fl
     if (batch < 1) return hipSuccess;
     const Geo g = make_geo(W.n, batch, 2);
     const dim3 grid((unsigned)g.groups);
-    if (W.keep)
-        hipLaunchKernelGGL(conv_fwd<true>, grid, dim3(kFwdThreads), 0, s, g, x, prm, W.wt2, W.wt3, W.gpart, W.a1, W.a2, W.m3);
-    else
-        hipLaunchKernelGGL(conv_fwd<false>, grid, dim3(kFwdThreads), 0, s, g, x, prm, W.wt2, W.wt3, W.gpart, (uint16_t*)nullptr,
-                           (uint16_t*)nullptr, (uint16_t*)nullptr);
-    hipLaunchKernelGGL(head_fwd, dim3(blocks_for(batch, 4)), dim3(256), 0, s, W.gpart, g.tx * g.ty, (float)(W.n * W.n), prm, batch,
-                       W.g_, r);
+    uint16_t* none = nullptr;
+    if (W.keep) {
+        hipLaunchKernelGGL(conv_fwd<true>, grid, dim3(kFwdThreads), 0, s, g, x, prm, W.wt2, W.wt3, W.gpart, W.a1, W.a2, W.a3, W.m3);
+        hipLaunchKernelGGL(head_train, dim3(batch), dim3(256), 0, s, W.a3, W.n * W.n, prm, W.g_, r);
+    } else {
+        hipLaunchKernelGGL(conv_fwd<false>, grid, dim3(kFwdThreads), 0, s, g, x, prm, W.wt2, W.wt3, W.gpart, none, none, none, none);
+        hipLaunchKernelGGL(head_fwd, dim3(blocks_for(batch, 4)), dim3(256), 0, s, W.gpart, g.tx * g.ty, (float)(W.n * W.n), prm, batch,
+                           W.g_, r);
+    }
     return hipGetLastError();
 }
 
