@@ -227,8 +227,42 @@ struct Grid {
     // so that the matrix cores' queue does not run dry (1000 pairs of 64 x 64: 9.5 to 8.5 ms).
     __device__ __forceinline__ void filter(Acc (&v)[T], const Real* __restrict__ sol, bool on) const
     {
-        Acc u[T];
         __builtin_amdgcn_s_setprio(2);
+        if constexpr (G::SIDE == 1) {
+            products(v, sol, on);
+        } else {
+            // The zeros of C beside the samples' blocks do not keep a value that is not finite from the other samples
+            // of the tile: then each sample is filtered alone, with zeros in the others' places.
+            const Acc in = v[0];
+            products(v, sol, on);
+            bool finite = true;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) finite = finite && isfinite(v[0][i]);
+            if (__any(!finite)) {
+                Acc all = v[0];
+#pragma unroll 1
+                for (int s = 0; s < G::SLOTS; ++s) {
+                    bool mine[4];
+                    Acc one[1];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        mine[i] = (row(0, i) / N) * G::SIDE + c / N == s;
+                        one[0][i] = mine[i] ? in[i] : Real(0);
+                    }
+                    products(one, sol, on);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) all[i] = mine[i] ? one[0][i] : all[i];
+                }
+                v[0] = all;
+            }
+        }
+        __builtin_amdgcn_s_setprio(0);
+    }
+
+    // the four products and the multipliers between them
+    __device__ __forceinline__ void products(Acc (&v)[T], const Real* __restrict__ sol, bool on) const
+    {
+        Acc u[T];
         if (on) transform<T, false, false>(v, u);
         if constexpr (T > 1) exchange(p0, u, v, on);
         if (on) {
@@ -245,7 +279,6 @@ struct Grid {
             if constexpr (T == 1) u[0] = v[0];
             transform<T, true, true>(u, v);
         }
-        __builtin_amdgcn_s_setprio(0);
     }
 
     // d <- the explicit increment of rho with the unit noise w0, w1 (float: fine normals; Real: restricted
