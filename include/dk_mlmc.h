@@ -314,6 +314,10 @@ int dk_noise_dump(dk_context* ctx, uint64_t seed, uint32_t tag, int32_t level, i
 int dk_gauss_transform(dk_context* ctx, const uint32_t* a, const uint32_t* b, uint64_t count,
                        float* z0, float* z1, void* stream);
 
+/* The root of the fluxes of FP64 states alone: out[i] = sqrt([x[i]]^+) for i < count, x and out
+ * DEVICE arrays.  For checks of its rounding; DK_EINVAL on NULL arrays. */
+int dk_root_f64(dk_context* ctx, const double* x, uint64_t count, double* out, void* stream);
+
 /* Final density fields of a batch (for field-level checks): rho_f_out [n_samples][n_l^2] and,
  * for coupled pairs, rho_c_out [n_samples][n_{l-1}^2], DEVICE, element type float for
  * DK_PREC_F32 and double for DK_PREC_F64.  coupled = 0 runs uncoupled level-l paths. */

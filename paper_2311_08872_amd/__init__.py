@@ -333,6 +333,18 @@ def noise_dump(seed: int, tag: int, level: int, n: int, first_sample: int, n_sam
     return out
 
 
+def root_f64(x, ctx: Context | None = None):
+    """dk_root_f64: sqrt([x]^+) of a float64 device tensor as the FP64 kernels form it."""
+    ctx = ctx or default_context()
+    torch = _torch()
+    if x.dtype != torch.float64 or not x.is_cuda:
+        raise DKError(-1, "x must be a float64 CUDA tensor")
+    x = x.contiguous()
+    out = torch.empty_like(x)
+    _check(ctx.lib.dk_root_f64(ctx.h, _ptr(x), x.numel(), _ptr(out), ctx.stream()))
+    return out
+
+
 def gauss_transform(a, b, ctx: Context | None = None):
     """dk_gauss_transform: the generator's two normals of each word pair (a[i], b[i]).  a, b:
     int32 device tensors holding the uint32 words (same length); returns float32 (z0, z1)."""

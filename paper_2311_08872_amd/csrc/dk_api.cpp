@@ -447,6 +447,16 @@ int dk_gauss_transform(dk_context* ctx, const uint32_t* a, const uint32_t* b, ui
     return DK_OK;
 }
 
+int dk_root_f64(dk_context* ctx, const double* x, uint64_t count, double* out, void* stream)
+{
+    if (!ctx) return fail(DK_EINVAL, "context is NULL");
+    if (count == 0) return DK_OK;
+    if (!x || !out) return fail(DK_EINVAL, "NULL argument");
+    HIP_TRY(hipSetDevice(ctx->device));
+    HIP_TRY(dk::launch_root(x, count, out, (hipStream_t)stream));
+    return DK_OK;
+}
+
 int dk_alg1_host(double eps, int32_t L_max, const double* cost, const dk_mlmc_opts* opts, dk_level_sampler sampler,
                  void* user, dk_mlmc_result* out)
 {

@@ -72,7 +72,6 @@ struct FourierNoise {
     uint32_t step, pair_base, pairs_per_row;
     Real (*S)[C][2];
     using W = float;
-    // correctly rounded roots in both state types
     static __device__ __forceinline__ Real root(Real x)
     {
         if constexpr (std::is_same<Real, double>::value) return pos_sqrt_f64(x);

@@ -67,6 +67,7 @@ hipError_t launch_field_eval(const FieldDev& f, double box, int n, void* out, bo
 hipError_t launch_noise_dump(uint64_t seed, uint32_t tag, int level, int n, uint64_t first_sample,
                              uint32_t n_samples, int first_step, int n_steps, float* out,
                              hipStream_t s);
+hipError_t launch_root(const double* x, uint64_t count, double* out, hipStream_t s);
 hipError_t launch_gauss(const uint32_t* a, const uint32_t* b, uint64_t count, float* z0, float* z1, hipStream_t s);
 
 // The noise-free scheme to step `steps` from the FP64 field in buf0 (n even, at most 4096; buf1: scratch of the same

@@ -278,6 +278,21 @@ __global__ void gauss_kernel(const uint32_t* __restrict__ a, const uint32_t* __r
     z1[i] = v;
 }
 
+__global__ void root_kernel(const double* __restrict__ x, uint64_t count, double* __restrict__ out)
+{
+    const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < count) out[i] = pos_sqrt(x[i]);
+}
+
+hipError_t launch_root(const double* x, uint64_t count, double* out, hipStream_t s)
+{
+    const uint64_t blocks = (count + 255) / 256;
+    if (blocks == 0) return hipSuccess;
+    if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(root_kernel, dim3((unsigned)blocks), dim3(256), 0, s, x, count, out);
+    return hipGetLastError();
+}
+
 hipError_t launch_gauss(const uint32_t* a, const uint32_t* b, uint64_t count, float* z0, float* z1, hipStream_t s)
 {
     if (count == 0) return hipSuccess;

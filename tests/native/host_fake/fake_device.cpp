@@ -503,6 +503,14 @@ hipError_t launch_noise_dump(uint64_t, uint32_t, int, int n, uint64_t, uint32_t 
     return submit(s, [=] { touch_write(out, sizeof(float) * 2 * (size_t)n * n * n_steps * n_samples, "launch_noise_dump"); });
 }
 
+hipError_t launch_root(const double* x, uint64_t count, double* out, hipStream_t s)
+{
+    return submit(s, [=] {
+        touch_read(x, 8 * count, "launch_root x");
+        touch_write(out, 8 * count, "launch_root out");
+    });
+}
+
 hipError_t launch_gauss(const uint32_t* a, const uint32_t* b, uint64_t count, float* z0, float* z1, hipStream_t s)
 {
     return submit(s, [=] {
