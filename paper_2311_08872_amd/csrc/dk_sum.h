@@ -22,8 +22,12 @@ struct Sum {
         const double v = a * b;
         add(v, fma(a, b, -v));
     }
-    // h2 * sum - c
-    __device__ __forceinline__ double centred(double h2, double c) const { return fma(h2, hi, -c) + h2 * lo; }
+    // h2 * sum - c.  Where a sum went to infinity its errors are not numbers, and hi is what a plain sum gives.
+    __device__ __forceinline__ double centred(double h2, double c) const
+    {
+        const double e = h2 * lo;
+        return fma(h2, hi, -c) + (e == e ? e : 0.0);
+    }
 };
 
 }  // namespace dk
