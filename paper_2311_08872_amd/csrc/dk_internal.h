@@ -48,6 +48,8 @@ bool level_supported(int nf);
 int shape_rows(int nf, int v);
 // samples per block of tile-shape variant v for grid size nf, 0 if the variant does not exist
 int shape_spw(int nf, int v);
+// the variant that a batch of this kind runs where v is asked for
+int shape_run(int nf, int v, bool f64, bool pair);
 
 // Ordered, compensated per-observable moment sums of a per-sample buffer.
 // out: device [n_obs][DK_NMOM][2] (sum, compensation).

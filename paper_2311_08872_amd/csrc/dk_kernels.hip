@@ -25,40 +25,8 @@ level_kernel(const LevelArgs A)
 }
 
 // ---------------------------------------------------------------------------------------
-// Tile shapes.  A lane owns C = 2 columns and R rows; a sample uses (NF/2) x (NF/R) lanes and a
-// block holds SPW samples (about 256 lanes, or four times as many samples in 1024-lane blocks).
-// Several (R, SPW) per grid size are compiled; the host picks one by the size of the batch, or by
-// timing them for large jobs (choose_shape).  FP64 states have the shapes of at most 8 rows and 256
-// lanes per block's worth of samples (16 rows at 128 x 128); the others stand for their shape 0.  One-row
-// shapes are for single paths (a pair's coarse cell needs two rows): pairs run them with two.
+// Launches: the tile shape of a batch by its variant (shape_rows in dk_tuning.cpp).
 // ---------------------------------------------------------------------------------------
-// rows per lane of shape variant v for grid size nf (0 = no such variant); variant 0 is the
-// default (8 rows: the fastest measured on MI355X for every grid size of the hierarchy)
-int shape_rows(int nf, int v)
-{
-    switch (nf) {
-        case 4: return v == 0 ? 4 : 0;
-        case 8: { const int r[] = {8, 2, 4, 8, 1}; return v < 5 ? r[v] : 0; }
-        case 16: { const int r[] = {8, 4, 2, 8, 1}; return v < 5 ? r[v] : 0; }
-        case 32: { const int r[] = {8, 4, 16, 8, 2}; return v < 5 ? r[v] : 0; }
-        case 64: { const int r[] = {8, 16, 8, 4, 2}; return v < 5 ? r[v] : 0; }
-        case 128: { const int r[] = {8, 16}; return v < 2 ? r[v] : 0; }
-        default: return 0;
-    }
-}
-
-// samples per block of shape variant v (0 = no such variant): the last variant of 8^2 .. 64^2
-// is the default shape with four times the samples per block
-int shape_spw(int nf, int v)
-{
-    const int r = shape_rows(nf, v);
-    if (r == 0) return 0;
-    const int ts = (nf / 2) * (nf / r);
-    const int base = ts >= 256 ? 1 : 256 / ts;
-    const bool wide = (nf == 8 || nf == 16 || nf == 32) ? v == 3 : (nf == 64 ? v == 2 : false);
-    return wide ? 4 * base : base;
-}
-
 template <typename Real, int NF, int R, bool PAIR, int FLUX, int X = 1>
 static hipError_t launch_R(const LevelArgs& A, hipStream_t s)
 {
@@ -80,14 +48,14 @@ static hipError_t launch_variants(const LevelArgs& A, int v, hipStream_t s)
         return launch_R<Real, 4, 4, PAIR, FLUX>(A, s);
     } else if constexpr (NF == 8) {
         if constexpr (!PAIR) if (v == 4) return launch_R<Real, 8, 1, PAIR, FLUX>(A, s);
-        if (v == 1 || v == 4) return launch_R<Real, 8, 2, PAIR, FLUX>(A, s);
+        if (v == 1) return launch_R<Real, 8, 2, PAIR, FLUX>(A, s);
         if (v == 2) return launch_R<Real, 8, 4, PAIR, FLUX>(A, s);
         if constexpr (F32) if (v == 3) return launch_R<Real, 8, 8, PAIR, FLUX, 4>(A, s);
         return launch_R<Real, 8, 8, PAIR, FLUX>(A, s);
     } else if constexpr (NF == 16) {
         if (v == 1) return launch_R<Real, 16, 4, PAIR, FLUX>(A, s);
         if constexpr (!PAIR) if (v == 4) return launch_R<Real, 16, 1, PAIR, FLUX>(A, s);
-        if (v == 2 || v == 4) return launch_R<Real, 16, 2, PAIR, FLUX>(A, s);
+        if (v == 2) return launch_R<Real, 16, 2, PAIR, FLUX>(A, s);
         if constexpr (F32) if (v == 3) return launch_R<Real, 16, 8, PAIR, FLUX, 4>(A, s);
         return launch_R<Real, 16, 8, PAIR, FLUX>(A, s);
     } else if constexpr (NF == 32) {
@@ -131,8 +99,8 @@ bool level_supported(int nf) { return nf == 4 || nf == 8 || nf == 16 || nf == 32
 hipError_t launch_level(const LevelKind& k, const LevelArgs& A, hipStream_t s)
 {
     if (!k.noise) return hipErrorInvalidValue;   // noise-free runs: dk_meanfield.hip
-    const int v = k.shape;
     const bool f64 = k.precision == DK_PREC_F64;
+    const int v = shape_run(A.nf, k.shape, f64, k.pair);
     const bool stag = k.flux == DK_FLUX_STAGGERED;
     if (!f64 && !stag) return k.pair ? launch_nf<float, true, DK_FLUX_CENTRAL>(A, v, s)
                                      : launch_nf<float, false, DK_FLUX_CENTRAL>(A, v, s);

@@ -173,7 +173,11 @@ int run_stream(dk_context* ctx, const dk_problem* p, int level, bool pair, uint6
     const bool log = std::getenv("DK_LOG") != nullptr;
     const int steps = A.steps;
     const double cells_per_sample = (double)nn * (double)steps * (pair ? 1.0 + 1.0 / 16.0 : 1.0);
+    // Launches of few tiles run at depth 4, which has tiles for them; the depth that is timed or loaded is one of launches
+    // that fill the chip.
     int depth = ctx->stream_depth;
+    const uint64_t launch = (B + stream_parts(nf, (int)B) - 1) / stream_parts(nf, (int)B);     // B <= count
+    if (depth == 0 && dk::stream_small(nf, launch)) depth = 4;
     if (depth == 0) {
         const long key = ((long)nf << 8) | ((long)pair << 4) | (long)p->flux;
         auto t = ctx->tuned_depth.find(key);
@@ -702,7 +706,7 @@ int run_level(dk_context* ctx, const dk_problem* p, int level, bool pair, uint64
         }
         st.launches += nchunks;
         st.samples += count;
-        st.rows = dk::shape_rows(nf, variant);
+        st.rows = dk::shape_rows(nf, dk::shape_run(nf, variant, p->precision == DK_PREC_F64, pair));
         st.cells += (double)nf * nf * (double)Tf->steps * (pair ? 1.0 + 1.0 / 16.0 : 1.0) * (double)count;
     }
     for (uint64_t k = 0; k < nchunks; ++k) {

@@ -134,7 +134,7 @@ int run_round(dk_context* ctx, const dk_problem* p, int L, const uint64_t* first
         st.launches += J.nchunks;
         st.samples += J.count;
         st.cells += J.cells_per_sample * (double)J.count;
-        st.rows = dk::shape_rows(J.A.nf, J.K.shape);
+        st.rows = dk::shape_rows(J.A.nf, dk::shape_run(J.A.nf, J.K.shape, J.K.precision == DK_PREC_F64, J.pair));
         if (cell_updates) *cell_updates += J.cells_per_sample * (double)J.count;
     }
     return DK_OK;

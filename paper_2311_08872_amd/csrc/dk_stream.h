@@ -28,6 +28,8 @@ struct StreamArgs {
     float *rhoc_out, *cmpc_out;
 };
 bool stream_supported(int nf);
+// few tiles: a launch of `count` samples leaves compute units idle with 64 x 64 tiles
+bool stream_small(int nf, uint64_t count);
 bool stream_depth_supported(int depth);
 hipError_t launch_stream_step(const StreamArgs& A, bool pair, int flux, int depth, hipStream_t s);
 hipError_t launch_stream_coarse(int nc, int count, float a, float kc, int flux, const float* rho_in, const float* cmp_in,

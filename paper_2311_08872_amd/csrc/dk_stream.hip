@@ -528,6 +528,7 @@ __global__ void zero_slot_kernel(double* out, int count, int n_obs, int slot)
 }
 
 bool stream_supported(int nf) { return nf >= 64 && nf % 64 == 0; }
+bool stream_small(int nf, uint64_t count) { return (uint64_t)(nf / 64) * (nf / 64) * count <= 192; }
 
 template <int FLUX, bool PAIR, int D, int TT>
 static hipError_t launch_tile(const StreamArgs& A, hipStream_t s)
@@ -551,7 +552,7 @@ static hipError_t launch_depth(const StreamArgs& A, int depth, hipStream_t s)
     case 1: return launch_tile<FLUX, PAIR, 1, 64>(A, s);
     case 2: return launch_tile<FLUX, PAIR, 2, 64>(A, s);
     case 4:
-        if ((uint64_t)(A.n / 64) * (A.n / 64) * (uint64_t)A.count <= 192) return launch_tile<FLUX, PAIR, 4, 32>(A, s);
+        if (stream_small(A.n, A.count)) return launch_tile<FLUX, PAIR, 4, 32>(A, s);
         return launch_tile<FLUX, PAIR, 4, 64>(A, s);
     case 8: return launch_tile<FLUX, PAIR, 8, 64>(A, s);
     default: return hipErrorInvalidValue;

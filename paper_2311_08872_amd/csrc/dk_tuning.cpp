@@ -8,6 +8,56 @@
 
 #include "dk_host.h"
 
+// ------------------------------------------------------------------------------------------
+// Tile shapes.  A lane owns C = 2 columns and R rows; a sample uses (n/2) x (n/R) lanes and a
+// block holds S samples (about 256 lanes, or four times as many samples in 1024-lane blocks).
+// Several (R, S) per grid size are compiled; choose_shape picks one by the size of the batch, or by
+// timing them for large jobs.  FP64 states have the shapes of at most 8 rows and 256 lanes per block's worth of
+// samples (16 rows at 128 x 128); the others stand for their shape 0.  One-row shapes are for single paths
+// (a pair's coarse cell needs two rows): pairs run them with two (shape_run).
+// ------------------------------------------------------------------------------------------
+namespace dk {
+
+// rows per lane of shape variant v for grid size nf (0 = no such variant); variant 0 is the
+// default (8 rows: the fastest measured on MI355X for every grid size of the hierarchy)
+int shape_rows(int nf, int v)
+{
+    switch (nf) {
+        case 4: return v == 0 ? 4 : 0;
+        case 8: { const int r[] = {8, 2, 4, 8, 1}; return v >= 0 && v < 5 ? r[v] : 0; }
+        case 16: { const int r[] = {8, 4, 2, 8, 1}; return v >= 0 && v < 5 ? r[v] : 0; }
+        case 32: { const int r[] = {8, 4, 16, 8, 2}; return v >= 0 && v < 5 ? r[v] : 0; }
+        case 64: { const int r[] = {8, 16, 8, 4, 2}; return v >= 0 && v < 5 ? r[v] : 0; }
+        case 128: { const int r[] = {8, 16}; return v >= 0 && v < 2 ? r[v] : 0; }
+        default: return 0;
+    }
+}
+
+namespace {
+bool wide_shape(int nf, int v) { return (nf == 8 || nf == 16 || nf == 32) ? v == 3 : (nf == 64 && v == 2); }
+}  // namespace
+
+// samples per block of shape variant v
+int shape_spw(int nf, int v)
+{
+    const int r = shape_rows(nf, v);
+    if (r == 0) return 0;
+    const int ts = (nf / 2) * (nf / r);
+    const int base = ts >= 256 ? 1 : 256 / ts;
+    return wide_shape(nf, v) ? 4 * base : base;
+}
+
+int shape_run(int nf, int v, bool f64, bool pair)
+{
+    if (pair && shape_rows(nf, v) == 1) {
+        v = 0;
+        while (shape_rows(nf, v) != 2) ++v;
+    }
+    return f64 && nf < 128 && (shape_rows(nf, v) > 8 || wide_shape(nf, v)) ? 0 : v;
+}
+
+}  // namespace dk
+
 namespace dkh {
 
 namespace {
@@ -86,7 +136,7 @@ int load_tuning_json(dk_context* ctx, const std::string& text)
             if (dk::shape_rows(nf, v) == 0)
                 return fail(DK_EINVAL, "tuning JSON: no %d-row shape with %d samples per block for n = %d", rows, spw, nf);
         }
-        got[((long)nf << 8) | ((long)pair << 4) | (long)flux] = v;
+        got[((long)nf << 8) | ((long)pair << 4) | (long)flux] = dk::shape_run(nf, v, false, pair != 0);
     }
     for (const auto& kv : got) ctx->tuned[kv.first] = kv.second;
     for (const auto& kv : gotd) ctx->tuned_depth[kv.first] = kv.second;
@@ -115,31 +165,30 @@ void save_tuning_cache(const dk_context* ctx)
 //   FP32   8^2: 4096 samples 1.2 / 2.0 / 3.5, 32768 4.8 / 4.7 / 5.1, 65536 8.7 / 8.2 / 8.6
 //         16^2: 1024 samples 1.1 / 1.9 / 3.6, 8192 4.7 / 5.1 / 5.2, 32768 15.9 / 16.7 / 15.2
 //         32^2: 1024 samples 2.7 / 2.8 / 3.9, 3456 7.5 / 7.5 / 8.5, 7776 15.8 / 15.7 / 15.1
-//         64^2: 256 samples 2.9 / 2.9 / 3.9, 512 5.3 / 4.8 / 4.8, 1536 14.8 / 12.8 / 11.7
+//         64^2: 256 samples 2.7 / 2.7 / 3.6, 257 4.7 / 4.2 / 4.1, 1536 14.3 / 12.5 / 11.3
 //   FP64   8^2: 4096 samples 1.5 / 2.4 / 3.9, 16384 3.9 / 3.8 / 4.2, 32768 7.2 / 6.6 / 6.5
 //         16^2: 2048 samples 2.4 / 2.4 / 4.1, 8192 7.3 / 6.9 / 7.2, 16384 13.4 / 12.5 / 12.7
 //         32^2: 512 samples 2.2 / 2.4 / 4.0, 1024 3.8 / 3.7 / 4.2, 7776 23.5 / 22.8 / 21.3
-//         64^2: 256 samples 4.0 / 3.8 / 4.4, 512 7.8 / 6.6 / 6.3
+//         64^2: 256 samples 4.0 / 3.6 / 4.0, 257 7.1 / 6.1 / 5.7, 1000 14.4 / 11.9 / 11.9
 // (4^2 and 128^2 have no smaller tile.)  Single paths cross at the same sizes within a few percent, and
 // can run one row per lane:
 //   FP32   8^2: 1024 samples 0.69 against 1.0 at 2 rows, 8192 1.5 / 1.4;  16^2: 512 samples 0.72 / 0.98, 2048 1.6 / 1.5
 //   FP64   8^2: 1024 samples 1.1 / 1.5, 4096 1.6 / 1.6;  16^2: 512 samples 1.1 / 1.4, 1024 1.6 / 1.6
-// FP64 pairs of 64^2 fit three 8-row blocks on a compute unit, so 769 to 1024 samples would open a second
-// round for the rest: 14.1 us a step against 12.4 with the 4-row shape's two full ones.
 int small_batch_rows(int nf, bool f64, bool pair, uint64_t count)
 {
     struct Line { int n; uint64_t one, two, four; };
-    static const Line f32[] = {{8, 6000, 24000, 80000}, {16, 1200, 20000, 0}, {32, 0, 2500, 6000}, {64, 0, 256, 400}};
-    static const Line d64[] = {{8, 3000, 8192, 20000}, {16, 800, 3000, 10000}, {32, 0, 600, 6000}, {64, 0, 0, 300}};
-    if (nf == 64 && f64 && pair && count > 768 && count <= 1024) return 4;
+    static const Line f32[] = {{8, 6000, 24000, 80000}, {16, 1200, 20000, 0}, {32, 0, 2500, 6000}, {64, 0, 256, 0}};
+    static const Line d64[] = {{8, 3000, 8192, 20000}, {16, 800, 3000, 10000}, {32, 0, 600, 6000}, {64, 0, 0, 256}};
     for (const Line& l : f64 ? d64 : f32)
         if (l.n == nf) return !pair && count <= l.one ? 1 : (count <= l.two ? 2 : (count <= l.four ? 4 : 0));
     return 0;
 }
 
-// Tile-shape choice: a forced variant, a cached choice (FP32), the rows of a small batch, or for large
-// FP32 jobs the fastest variant on a short tuning batch (same tables, at most 2048 fine steps, samples
-// from the requested range; the outputs are discarded).  Otherwise the default shape.
+// Tile-shape choice: a forced variant, the rows of a small batch, and for batches that fill the chip a choice that
+// was timed or loaded (FP32), the fastest variant on a tuning batch (FP32 jobs of 1e11 cell updates; same tables, at
+// most 2048 fine steps, samples from the requested range, the outputs discarded), or the default shape.  The timed
+// choice is one of full chips, so the batch's size comes first: 1000 pairs of 32 x 32 take 1.28 ms with their two
+// rows and 1.86 ms with the eight of a full chip.
 int choose_shape(dk_context* ctx, const dk_problem* p, bool pair, const dk::LevelArgs& A, uint64_t count,
                  double cells_per_sample, hipStream_t s, int* variant)
 {
@@ -152,25 +201,23 @@ int choose_shape(dk_context* ctx, const dk_problem* p, bool pair, const dk::Leve
         return DK_OK;
     }
     const bool f64 = p->precision == DK_PREC_F64;
-    const long key = ((long)nf << 8) | ((long)pair << 4) | (long)p->flux;
-    if (!f64) {
-        auto t = ctx->tuned.find(key);
-        if (t != ctx->tuned.end()) { *variant = t->second; return DK_OK; }
-    }
-    if (f64 || (double)count * cells_per_sample < 1e11) {
-        const int rows = small_batch_rows(nf, f64, pair, count);
-        for (int v = 0; rows > 0 && dk::shape_rows(nf, v) > 0; ++v)
-            if (dk::shape_rows(nf, v) == rows) { *variant = v; break; }
+    if (const int rows = small_batch_rows(nf, f64, pair, count)) {
+        while (dk::shape_rows(nf, *variant) != rows) ++*variant;
         return DK_OK;
     }
+    if (f64) return DK_OK;
+    const long key = ((long)nf << 8) | ((long)pair << 4) | (long)p->flux;
+    auto t = ctx->tuned.find(key);
+    if (t != ctx->tuned.end()) { *variant = t->second; return DK_OK; }
+    if ((double)count * cells_per_sample < 1e11) return DK_OK;
     int nvar = 0;
     while (dk::shape_rows(nf, nvar) > 0) ++nvar;
     if (nvar < 2) { ctx->tuned[key] = 0; save_tuning_cache(ctx); return DK_OK; }
     // The batch resembles a production launch: the level's own horizon (capped at 2048 steps;
     // a much shorter one favours shapes whose per-sample setup is cheaper, not their time loop)
-    // and about one full round of blocks (256 CUs) of the larger grids.
+    // and at least one full round of blocks (256 CUs), above the sizes of small_batch_rows.
     dk::LevelArgs T = A;
-    T.count = std::min<uint64_t>(count, nf <= 32 ? 8192 : (nf == 64 ? 1024 : 256));
+    T.count = std::min<uint64_t>(count, nf <= 8 ? 131072 : (nf == 16 ? 32768 : (nf == 32 ? 8192 : (nf == 64 ? 1024 : 256))));
     T.steps = std::min(A.steps, 2048);
     T.field_f = nullptr;
     T.field_c = nullptr;
@@ -184,6 +231,7 @@ int choose_shape(dk_context* ctx, const dk_problem* p, bool pair, const dk::Leve
     double best = 1e300;
     int bestv = 0;
     for (int v = 0; v < nvar; ++v) {
+        if (dk::shape_run(nf, v, false, pair) != v) continue;
         dk::LevelKind K{p->precision, pair, p->flux, true, v};
         HIP_TRY(dk::launch_level(K, T, s));   // warm-up
         HIP_TRY(hipEventRecord(e0, s));

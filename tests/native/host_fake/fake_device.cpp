@@ -384,29 +384,6 @@ namespace dk {
 
 bool level_supported(int nf) { return nf == 4 || nf == 8 || nf == 16 || nf == 32 || nf == 64 || nf == 128; }
 
-int shape_rows(int nf, int v)
-{
-    switch (nf) {
-        case 4: return v == 0 ? 4 : 0;
-        case 8: { const int r[] = {8, 2, 4, 8}; return v >= 0 && v < 4 ? r[v] : 0; }
-        case 16: { const int r[] = {8, 4, 2, 8}; return v >= 0 && v < 4 ? r[v] : 0; }
-        case 32: { const int r[] = {8, 4, 16, 8}; return v >= 0 && v < 4 ? r[v] : 0; }
-        case 64: { const int r[] = {8, 16, 8}; return v >= 0 && v < 3 ? r[v] : 0; }
-        case 128: { const int r[] = {8, 16}; return v >= 0 && v < 2 ? r[v] : 0; }
-        default: return 0;
-    }
-}
-
-int shape_spw(int nf, int v)
-{
-    const int r = shape_rows(nf, v);
-    if (r == 0) return 0;
-    const int ts = (nf / 2) * (nf / r);
-    const int base = ts >= 256 ? 1 : 256 / ts;
-    const bool wide = (nf == 8 || nf == 16 || nf == 32) ? v == 3 : (nf == 64 ? v == 2 : false);
-    return wide ? 4 * base : base;
-}
-
 static void level_tables(const LevelArgs& A, bool pair, size_t esize, const char* who)
 {
     const size_t nn = (size_t)A.nf * A.nf, nc = nn / 4;
@@ -622,6 +599,7 @@ hipError_t launch_round(const RoundArgs& P, int, int grid, hipStream_t s)
 
 // ---- streaming kernels: state words 0..4 of each sample hold (sample, level, tag, seed, step) ----
 bool stream_supported(int nf) { return nf >= 64 && nf % 64 == 0; }
+bool stream_small(int nf, uint64_t count) { return (uint64_t)(nf / 64) * (nf / 64) * count <= 192; }
 bool stream_depth_supported(int depth) { return depth == 1 || depth == 2 || depth == 4 || depth == 8; }
 
 static const uint32_t kUnset = 0xFFFFFFFFu;
