@@ -270,7 +270,7 @@ extern "C" int dk_heat_steps(dk_context* ctx, int32_t n, int32_t batch, int32_t 
     }
     HIP_TRY(hipEventRecord(e1, s));
     if (from != rho) HIP_TRY(hipMemcpyAsync(rho, from, sizeof(float) * (size_t)n * n * batch, hipMemcpyDeviceToDevice, s));
-    HIP_TRY(hipEventSynchronize(e1));
+    HIP_TRY(hipStreamSynchronize(s));       // the copy, too: rho and work are the caller's again
     float ms = 0.f;
     HIP_TRY(hipEventElapsedTime(&ms, e0, e1));
     if (kernel_ms) *kernel_ms = ms;
