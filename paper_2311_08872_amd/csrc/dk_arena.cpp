@@ -51,8 +51,7 @@ int arena_tables(const dk_problem* p, int l, void* rho0, double* phi, double* ob
     if (any) {
         double* r0 = (double*)tmp;
         double* r1 = r0 + (size_t)n * n;
-        double* fin = nullptr;
-        const int rc = mean_field(p, l, phi, r0, r1, r1 + (size_t)n * n, centre, &fin, s);
+        const int rc = mean_field(p, l, phi, r0, r1, r1 + (size_t)n * n, centre, nullptr, s);
         if (rc) return rc;
     }
     for (int j = 0; j < nobs; ++j) {

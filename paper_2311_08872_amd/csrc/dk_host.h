@@ -154,10 +154,10 @@ namespace dkh {
 double noise_coeff(const dk_problem* p, double h, double sigma);
 int ensure_level(dk_context* ctx, const dk_problem* p, int level, LevelTables** out, hipStream_t s);
 // Discrete mean field of the explicit scheme and its inner products with the test functions phi [n_obs][n][n], which
-// centre the observables.  buf0, buf1: device fields; out: device [n_obs * kInnerOut]; *field: the buffer with the
-// field.  Waits for the stream.
+// centre the observables.  buf0, buf1: device fields; out: device [n_obs * kInnerOut]; rho_out: device field or NULL.
+// Waits for the stream.
 int mean_field(const dk_problem* p, int level, const double* phi, double* buf0, double* buf1, double* out, double* centre,
-               double** field, hipStream_t s);
+               double* rho_out, hipStream_t s);
 int compute_centre(dk_context* ctx, const dk_problem* p, int level, LevelTables& T, hipStream_t s, double* rho_out);
 uint64_t chunk_size(int n_obs, double cells_per_sample, double max_cells);
 int run_level(dk_context* ctx, const dk_problem* p, int level, bool pair, uint64_t first, uint64_t count,

@@ -458,7 +458,7 @@ double noise_coeff(const dk_problem* p, double h, double sigma)
 constexpr double kCancelled = 1e-4;
 
 int mean_field(const dk_problem* p, int level, const double* phi, double* buf0, double* buf1, double* out, double* centre,
-               double** field, hipStream_t s)
+               double* rho_out, hipStream_t s)
 {
     const int n = level_n(p, level), nobs = p->n_obs, steps = (int)level_steps(p, steps0_of(p), level);
     const double a = 0.5 * p->mu, h = p->box / n;
@@ -466,9 +466,10 @@ int mean_field(const dk_problem* p, int level, const double* phi, double* buf0, 
     bool by_steps = dk::meanfield_steps_cheaper(n, steps);
     for (;;) {
         HIP_TRY(dk::launch_field_eval(to_dev_on(p, p->rho0, n), p->box, n, buf0, true, s));
-        *field = buf0;
-        if (by_steps) HIP_TRY(dk::launch_meanfield_steps(n, a, steps, buf0, buf1, phi, nobs, h * h, out, field, s));
+        double* field = buf0;
+        if (by_steps) HIP_TRY(dk::launch_meanfield_steps(n, a, steps, buf0, buf1, phi, nobs, h * h, out, &field, s));
         else HIP_TRY(dk::launch_meanfield_transform(n, a, steps, buf0, buf1, phi, nobs, h * h, out, s));
+        if (rho_out) HIP_TRY(hipMemcpyAsync(rho_out, field, sizeof(double) * n * n, hipMemcpyDeviceToDevice, s));
         HIP_TRY(hipMemcpyAsync(got, out, sizeof(double) * nobs * (by_steps ? 1 : 2), hipMemcpyDeviceToHost, s));
         HIP_TRY(hipStreamSynchronize(s));
         bool keep = true;
@@ -514,14 +515,9 @@ int compute_centre(dk_context* ctx, const dk_problem* p, int level, LevelTables&
     if (rc) return rc;
     rc = ctx->scratch_c.ensure(sizeof(double) * nobs * dk::kInnerOut);
     if (rc) return rc;
-    double* res = nullptr;
     if ((rc = mean_field(p, level, (const double*)T.phi.p, (double*)ctx->mf0.p, (double*)ctx->mf1.p, (double*)ctx->scratch_c.p,
-                         c.data(), &res, s)))
+                         c.data(), rho_out, s)))
         return rc;
-    if (rho_out) {
-        HIP_TRY(hipMemcpyAsync(rho_out, res, sizeof(double) * n * n, hipMemcpyDeviceToDevice, s));
-        HIP_TRY(hipStreamSynchronize(s));
-    }
     T.centre = c;
     T.have_centre = true;
     return DK_OK;
