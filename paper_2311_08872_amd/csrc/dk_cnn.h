@@ -34,6 +34,8 @@ struct Workspace {
     ~Workspace() { release(); }
 };
 
+// Largest batch of one forward pass of n x n inputs: a pass keeps 64 B per tile and per sample.
+int forward_batch(int n);
 // BF16 GEMM weight layouts from the FP32 parameters (call after every parameter change).
 hipError_t pack(Workspace& W, const float* prm, hipStream_t s);
 // r[batch] = network(x[batch][n][n]); with keep, holds the activations for backward().

@@ -86,6 +86,7 @@ constexpr int kFwdX = 1040;         // x pixels (halo 3)
 constexpr int kBwdL = 616;          // image pixels (halo 1) of a backward block: 34 x 18 fit
 constexpr int kBwdA = 872;          // transposed activation image: pixels per channel (18 rows of 48 fit)
 constexpr int kBwdZ = 520;          // transposed gradient tile: pixels per channel
+constexpr int kForwardTiles = 1 << 17;   // of one forward pass: 8 MB of sums
 constexpr int kBlocks = 512;        // two blocks per compute unit: the backward grid, and what small grids are spread to
 
 static inline int cdiv(int a, int b) { return (a + b - 1) / b; }
@@ -845,6 +846,12 @@ hipError_t accumulate_sq(const Workspace& W, int batch, double* acc, hipStream_t
 // Host-side launch sequences
 // ---------------------------------------------------------------------------------------
 static inline unsigned blocks_for(size_t n, int bs) { return (unsigned)((n + bs - 1) / bs); }
+
+int forward_batch(int n)
+{
+    const Geo g = make_geo(n, 1, 2);
+    return std::max(1, kForwardTiles / (g.tx * g.ty));
+}
 
 // The pool's sums grow with the forward batch, the rest with the training batch, so a program that
 // alternates evaluation and training on one grid size allocates once for each.

@@ -27,13 +27,12 @@ int ensure_rbar(dk_context* ctx, const dk_problem* p, int level, LevelTables** o
     return DK_OK;
 }
 
-// r[count] = network(x[count][n][n]).  A forward pass keeps 64 B per tile of 32 x 16 pixels, so the
-// batch of one launch is bounded by pixels only (2^26: 8 MB of sums), not by activations.
+// r[count] = network(x[count][n][n]).  A forward pass keeps no activations, so the batch of one launch is bounded by
+// the tiles (2^17 of at most 32 x 16 pixels: 8 MB of sums, and as much of means where a sample is one tile).
 int cnn_forward_batched(dk_context* ctx, const float* prm, int n, uint64_t count, const float* x, float* r, hipStream_t s)
 {
     if (count == 0) return DK_OK;
-    const uint64_t most = std::max<uint64_t>(64, (1ull << 26) / ((uint64_t)n * n));
-    const uint64_t batch = std::min(count, most);
+    const uint64_t batch = std::min<uint64_t>(count, dk::cnn::forward_batch(n));
     ctx->cnn.keep = false;
     HIP_TRY(ctx->cnn.reserve(n, (int)batch));
     HIP_TRY(dk::cnn::pack(ctx->cnn, prm, s));

@@ -774,6 +774,7 @@ int theta_grid(int, int, uint64_t) { return 1; }
 hipError_t launch_theta(const ThetaArgs&, int, bool, int, hipStream_t) { return hipErrorInvalidValue; }
 
 namespace cnn {
+int forward_batch(int) { return 1; }
 hipError_t Workspace::reserve(int, int) { return hipErrorInvalidValue; }
 void Workspace::release() {}
 hipError_t pack(Workspace&, const float*, hipStream_t) { return hipErrorInvalidValue; }
