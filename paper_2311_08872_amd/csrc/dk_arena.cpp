@@ -127,7 +127,7 @@ int level_pair_arena(const dk_problem* p, int level, uint64_t first, uint64_t co
     A.h2c = pair ? hc * hc : 0.0;
     A.rho0_f = rho0_f; A.rho0_c = rho0_c; A.phi_f = phi_f; A.phi_c = phi_c; A.obs_f = obs_f; A.obs_c = obs_c;
     A.n_obs = nobs;
-    const dk::LevelKind K{p->precision, pair, p->flux, true, 0};
+    const dk::LevelKind K{p->precision, pair, p->flux, 0};
     const uint64_t nchunks = (count + ch - 1) / ch;
     double host[kGroup * 2 * DK_NMOM * DK_MAX_OBS];
     for (uint64_t g0 = 0; g0 < nchunks; g0 += kGroup) {

@@ -76,7 +76,7 @@ struct Geo {
     int H;              // halo of the image
     int P, img, L;      // image pitch, pixels of one sample's image, of all S
     int groups;         // ceil(batch / S) x tiles per sample: work items
-    Div dP, dImg, dTiles, dTx, dTw, dTile;
+    Div dP, dImg, dTw, dTile;
 };
 
 constexpr int kTileW = 32, kTileH = 16;
@@ -118,8 +118,6 @@ static Geo make_geo(int n, int batch, int H)
     g.groups = cdiv(batch, g.S) * g.tx * g.ty;
     g.dP = Div(g.P);
     g.dImg = Div(g.img);
-    g.dTiles = Div(g.tx * g.ty);
-    g.dTx = Div(g.tx);
     g.dTw = Div(g.tw);
     g.dTile = Div(g.tw * g.th);
     return g;

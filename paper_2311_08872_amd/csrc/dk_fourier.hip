@@ -35,6 +35,7 @@
 
 #include "dk_fourier.h"
 #include "dk_level.h"
+#include "dk_mma.h"
 #include "dk_sum.h"
 
 namespace dk {
@@ -99,19 +100,6 @@ struct FourierNoise {
             }
         }
     }
-};
-
-// 16 x 16 x 4 products; row(i, q): the row of the result in register i of lane group q
-template <typename Real> struct Mma;
-template <> struct Mma<double> {
-    typedef double Acc __attribute__((ext_vector_type(4)));
-    static __device__ __forceinline__ Acc mul(double a, double b, Acc c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
-    static __device__ __forceinline__ int row(int i, int q) { return 4 * i + q; }
-};
-template <> struct Mma<float> {
-    typedef float Acc __attribute__((ext_vector_type(4)));
-    static __device__ __forceinline__ Acc mul(float a, float b, Acc c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
-    static __device__ __forceinline__ int row(int i, int q) { return 4 * q + i; }
 };
 
 // acc[jt] += K[16 jt ..][y] (S K^T)[y][16 ct ..] over the row tiles part, part + parts, ..

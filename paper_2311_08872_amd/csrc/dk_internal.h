@@ -37,7 +37,6 @@ struct LevelKind {
     int precision;          // DK_PREC_*
     bool pair;              // coupled fine/coarse pair
     int flux;               // DK_FLUX_*
-    bool noise;             // always true: the noise-free field has its own launch (launch_meanfield_stream)
     int shape = 0;          // tile-shape variant (see shape_rows)
 };
 

@@ -98,7 +98,6 @@ bool level_supported(int nf) { return nf == 4 || nf == 8 || nf == 16 || nf == 32
 
 hipError_t launch_level(const LevelKind& k, const LevelArgs& A, hipStream_t s)
 {
-    if (!k.noise) return hipErrorInvalidValue;   // noise-free runs: dk_meanfield.hip
     const bool f64 = k.precision == DK_PREC_F64;
     const int v = shape_run(A.nf, k.shape, f64, k.pair);
     const bool stag = k.flux == DK_FLUX_STAGGERED;

@@ -662,7 +662,7 @@ int run_level(dk_context* ctx, const dk_problem* p, int level, bool pair, uint64
     rc = choose_shape(ctx, p, pair, A, count, (double)nf * nf * (double)Tf->steps * (pair ? 1.0 + 1.0 / 16.0 : 1.0), s,
                       &variant);
     if (rc) return rc;
-    dk::LevelKind K{p->precision, pair, p->flux, true, variant};
+    dk::LevelKind K{p->precision, pair, p->flux, variant};
     const size_t esize = p->precision == DK_PREC_F64 ? 8 : 4;
     while (ctx->ev_pool.size() < 2 * nchunks) {
         hipEvent_t e;

@@ -50,7 +50,7 @@ int run_round(dk_context* ctx, const dk_problem* p, int L, const uint64_t* first
         dk::LevelArgs& A = J.A;
         int variant = 0;
         if ((rc = choose_shape(ctx, p, J.pair, A, J.count, J.cells_per_sample, s, &variant))) return rc;
-        J.K = dk::LevelKind{p->precision, J.pair, p->flux, true, variant};
+        J.K = dk::LevelKind{p->precision, J.pair, p->flux, variant};
         if ((rc = ctx->rnd_ps[l].ensure(sizeof(double) * 2 * nobs * std::min(J.ch, J.count)))) return rc;
         if ((rc = ctx->rnd_mom[l].ensure(sizeof(double) * mom_stride * J.nchunks))) return rc;
         if (!ctx->lvl_stream[l]) {

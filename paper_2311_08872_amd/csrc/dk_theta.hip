@@ -41,6 +41,7 @@
 #include <type_traits>
 
 #include "dk_level.h"
+#include "dk_mma.h"
 #include "dk_sum.h"
 #include "dk_theta.h"
 
@@ -61,20 +62,8 @@ struct TG {
     static constexpr int WAVES = T == 4 ? 2 : 4;
 };
 
-// 16 x 16 x 4 products; row(i, q): the row of the result in register i of lane group q
-template <typename Real> struct Mma;
-template <> struct Mma<double> {
-    typedef double Acc __attribute__((ext_vector_type(4)));
-    static __device__ __forceinline__ Acc mul(double a, double b, Acc c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
-    static constexpr __host__ __device__ int row(int i, int q) { return 4 * i + q; }
-    static __device__ __forceinline__ double root(double x) { return pos_sqrt_f64(x); }
-};
-template <> struct Mma<float> {
-    typedef float Acc __attribute__((ext_vector_type(4)));
-    static __device__ __forceinline__ Acc mul(float a, float b, Acc c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
-    static constexpr __host__ __device__ int row(int i, int q) { return 4 * q + i; }
-    static __device__ __forceinline__ float root(float x) { return sqrt(x > 0.0f ? x : 0.0f); }
-};
+__device__ __forceinline__ double root(double x) { return pos_sqrt_f64(x); }
+__device__ __forceinline__ float root(float x) { return sqrt(x > 0.0f ? x : 0.0f); }
 
 // the value of the neighbouring lane of an even-odd pair
 __device__ __forceinline__ float swap_pair(float v)
@@ -297,7 +286,7 @@ struct Grid {
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const int k = at(t, i, x);
-                    const Real s = M::root(rho[t][i]);
+                    const Real s = root(rho[t][i]);
                     p0[k] = rho[t][i];
                     p1[k] = s * (Real)w0[t][i];
                     f1[t][i] = s * (Real)w1[t][i];

@@ -232,7 +232,7 @@ int choose_shape(dk_context* ctx, const dk_problem* p, bool pair, const dk::Leve
     int bestv = 0;
     for (int v = 0; v < nvar; ++v) {
         if (dk::shape_run(nf, v, false, pair) != v) continue;
-        dk::LevelKind K{p->precision, pair, p->flux, true, v};
+        dk::LevelKind K{p->precision, pair, p->flux, v};
         HIP_TRY(dk::launch_level(K, T, s));   // warm-up
         HIP_TRY(hipEventRecord(e0, s));
         HIP_TRY(dk::launch_level(K, T, s));

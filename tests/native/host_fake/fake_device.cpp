@@ -400,26 +400,19 @@ static void level_tables(const LevelArgs& A, bool pair, size_t esize, const char
 hipError_t launch_level(const LevelKind& k, const LevelArgs& A, hipStream_t s)
 {
     if (!level_supported(A.nf)) return hipErrorInvalidValue;
-    if (k.noise && k.precision == DK_PREC_F32 && shape_rows(A.nf, k.shape) == 0) return hipErrorInvalidValue;
+    if (shape_rows(A.nf, k.shape) == 0) return hipErrorInvalidValue;
     if (A.count == 0) return hipSuccess;
     ++g_fake_launches;
     const LevelArgs a = A;
     const LevelKind kk = k;
     return submit(s, [a, kk] {
-        const size_t esize = (!kk.noise || kk.precision == DK_PREC_F64) ? 8 : 4;
+        const size_t esize = kk.precision == DK_PREC_F64 ? 8 : 4;
         const size_t nn = (size_t)a.nf * a.nf;
         level_tables(a, kk.pair, esize, "launch_level tables");
         const int nobs = a.n_obs;
         touch_write(a.out, sizeof(double) * 2 * nobs * a.count, "launch_level out");
         if (a.field_f) touch_write(a.field_f, esize * nn * a.count, "launch_level field_f");
         if (a.field_c) touch_write(a.field_c, esize * nn / 4 * a.count, "launch_level field_c");
-        if (!kk.noise) {
-            for (int j = 0; j < nobs; ++j) {
-                a.out[2 * j] = 0.25 + 0.01 * j;
-                a.out[2 * j + 1] = 0.0;
-            }
-            return;
-        }
         for (uint64_t i = 0; i < a.count; ++i)
             for (int j = 0; j < nobs; ++j) {
                 a.out[(i * nobs + j) * 2 + 0] = fake_value(a.seed, a.tag, a.level_id, a.first + i, j, kk.pair, 0);
@@ -756,18 +749,9 @@ hipError_t launch_zero_slot(double* out, int count, int n_obs, int slot, hipStre
     });
 }
 
-hipError_t launch_heat_f32(const float* in, float* out, int n, int batch, float, hipStream_t s)
-{
-    return submit(s, [=] {
-        touch_read(in, 4 * (size_t)n * n * batch, "heat in");
-        touch_write(out, 4 * (size_t)n * n * batch, "heat out");
-    });
-}
-
 // ---- couplings and schemes the harness does not drive ----
 bool fourier_supported(int, bool) { return false; }
 int fourier_grid(int, int, uint64_t) { return 1; }
-size_t fourier_scratch_elems(int) { return 0; }
 hipError_t launch_fourier(const FourierArgs&, int, bool, int, hipStream_t) { return hipErrorInvalidValue; }
 bool theta_supported(int, bool) { return false; }
 int theta_grid(int, int, uint64_t) { return 1; }
