@@ -446,7 +446,7 @@ int dk_context_set_launch_cap(dk_context* ctx, double cells);
  * for `steps` steps on a batch of FP32 fields rho (DEVICE [batch][n][n], updated in place;
  * work: DEVICE scratch of the same size).  n a multiple of 4.  kernel_ms (optional) receives
  * the event time of the steps.  Fields up to 256 x 256 are read and written once for all steps
- * (work is not used); larger ones once per up to 16 steps. */
+ * of a launch (dk_context_set_launch_cap; work is not used); larger ones once per up to 16 steps. */
 int dk_heat_steps(dk_context* ctx, int32_t n, int32_t batch, int32_t steps, double mu, float* rho, float* work,
                   double* kernel_ms, void* stream);
 

@@ -6,7 +6,7 @@
 // 16 rows x 4 columns, so one block of 1024 lanes holds 256 x 256 cells, half of a compute unit's
 // registers, and takes any number of steps between one read and one write of the field:
 //   n <= 256       a block per field (several fields per wavefront where a field's row groups fit into
-//                  one), in place
+//                  one), in place, all steps in one launch up to the work of one launch
 //   n > 256        256 x 256 windows with a halo of T <= 16 cells, T steps a pass, two buffers in turn
 // Rows of a lane are swept in registers; the columns at a lane's edges come from the neighbouring lanes
 // (ds_bpermute), the rows at its top and bottom through LDS, double-buffered by step, one barrier a step,
@@ -255,7 +255,13 @@ extern "C" int dk_heat_steps(dk_context* ctx, int32_t n, int32_t batch, int32_t 
     HIP_TRY(hipEventRecord(e0, s));
     float* from = rho;
     if (n <= dk::kWin) {
-        if (steps > 0) HIP_TRY(dk::heat_resident(rho, n, batch, steps, a, s));
+        // no launch longer than a level's may be
+        const double most = std::max(1.0, ctx->max_launch_cells / ((double)n * n * batch));
+        for (int done = 0; done < steps;) {
+            const int T = (int)std::min<double>(steps - done, most);
+            HIP_TRY(dk::heat_resident(rho, n, batch, T, a, s));
+            done += T;
+        }
     } else {
         // passes in pairs, so that the fields end in rho; a single step is a pass and a copy
         int passes = (steps + dk::kMaxT - 1) / dk::kMaxT;
