@@ -215,10 +215,12 @@ int choose_shape(dk_context* ctx, const dk_problem* p, bool pair, const dk::Leve
     if (nvar < 2) { ctx->tuned[key] = 0; save_tuning_cache(ctx); return DK_OK; }
     // The batch resembles a production launch: the level's own horizon (capped at 2048 steps;
     // a much shorter one favours shapes whose per-sample setup is cheaper, not their time loop)
-    // and at least one full round of blocks (256 CUs), above the sizes of small_batch_rows.
+    // and about one full round of blocks (256 CUs) of the larger grids.
     dk::LevelArgs T = A;
-    T.count = std::min<uint64_t>(count, nf <= 8 ? 131072 : (nf == 16 ? 32768 : (nf == 32 ? 8192 : (nf == 64 ? 1024 : 256))));
+    T.count = std::min<uint64_t>(count, nf <= 32 ? 8192 : (nf == 64 ? 1024 : 256));
     T.steps = std::min(A.steps, 2048);
+    // on 8^2 and 16^2 it is a small batch itself, on which fewer rows win as they do not on a full chip
+    const bool small = small_batch_rows(nf, false, pair, T.count) != 0;
     T.field_f = nullptr;
     T.field_c = nullptr;
     int rc = ctx->per_sample.ensure(sizeof(double) * 2 * A.n_obs * T.count);
@@ -231,7 +233,7 @@ int choose_shape(dk_context* ctx, const dk_problem* p, bool pair, const dk::Leve
     double best = 1e300;
     int bestv = 0;
     for (int v = 0; v < nvar; ++v) {
-        if (dk::shape_run(nf, v, false, pair) != v) continue;
+        if (dk::shape_run(nf, v, false, pair) != v || (small && dk::shape_rows(nf, v) < 8)) continue;
         dk::LevelKind K{p->precision, pair, p->flux, v};
         HIP_TRY(dk::launch_level(K, T, s));   // warm-up
         HIP_TRY(hipEventRecord(e0, s));

@@ -53,7 +53,7 @@ def test_timed_shape():
     p = problem(16, True, 4096)
     print("[gpu] timed shape n=16", flush=True)
     ctx = dk.Context(0)
-    rows(ctx, p, True, 100000)                        # 1.1e11 cell updates: timed
+    assert rows(ctx, p, True, 100000) == 8            # 1.1e11 cell updates: timed, among the shapes of full chips
     assert [s["n"] for s in json.loads(ctx.tuning_json())["shapes"]] == [16]
     assert rows(ctx, p, True, 1000) == 2
     ctx.close()
