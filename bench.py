@@ -49,7 +49,7 @@ VALU_PEAK_OPS = 256 * 128 * 2.4e9
 # read 1.000 x the bytes of a 256 MiB copy (FETCH_SIZE reads 0.5 x on gfx950).  A constant per
 # dispatch (the level tables, fetched once per compute die) plus bytes per pair (the outputs).  It is
 # reported only while the kernel sources hash to the value the counters were taken on.
-TRAFFIC = {"sha256": "a040728d84eff204a60724d09d2411682c9e98f02bd2ea4686dfa7145c4b28da",
+TRAFFIC = {"sha256": "d703287738bd3025cad49b24e65bbda15b2a0a8a5d8c0f64ffd5728de8cbf5af",
            "read_bytes_per_dispatch": 3313.5 * 1024, "write_bytes_per_pair": 32.0,
            "profile": "profiles/level_kernel_128_pair_counters_workload_hbm.md"}
 KERNEL_SOURCES = ["dk_level.h", "dk_rng.h", "dk_kernels.hip", "dk_internal.h"]

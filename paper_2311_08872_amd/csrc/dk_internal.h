@@ -74,15 +74,15 @@ hipError_t launch_gauss(const uint32_t* a, const uint32_t* b, uint64_t count, fl
 // The noise-free scheme to step `steps` from the FP64 field in buf0 (n even, at most 4096; buf1: scratch of the same
 // size) and the inner products h2 sum rho phi_j with its final field, to the first n_obs values of out (device,
 // [n_obs * kInnerOut]).  _steps: step by step; *result is the buffer that holds the final field.  _transform: in the
-// scheme's eigenbasis, the field in buf0 and behind the products the sizes h2 sum |rho phi_j|; its products are
-// those of the steps to about 1e-14 of these sizes.
+// scheme's eigenbasis, of the field's difference from `shift`, the field in buf0 and behind the products the sizes
+// h2 sum |rho phi_j|; its products are those of the steps to about 1e-14 of these sizes.
 constexpr int kInnerParts = 64;
 constexpr int kInnerOut = 2 * (1 + kInnerParts);
 bool meanfield_steps_cheaper(int n, int steps);
 hipError_t launch_meanfield_steps(int n, double a, int steps, double* buf0, double* buf1, const double* phi, int n_obs, double h2,
                                   double* out, double** result, hipStream_t s);
-hipError_t launch_meanfield_transform(int n, double a, int steps, double* buf0, double* buf1, const double* phi, int n_obs,
-                                      double h2, double* out, hipStream_t s);
+hipError_t launch_meanfield_transform(int n, double a, int steps, double shift, double* buf0, double* buf1, const double* phi,
+                                      int n_obs, double h2, double* out, hipStream_t s);
 
 // Host side of the allocation-free level batch (dk_arena.cpp): samples [first, first + count) of
 // resident level `level` (a pair for level >= 1) with every device buffer, the level tables and

@@ -457,6 +457,16 @@ double noise_coeff(const dk_problem* p, double h, double sigma)
 // bare rounding where a product vanishes) is taken from the steps.
 constexpr double kCancelled = 1e-4;
 
+// a constant near the mean of a field; what the transform's sums lose in it is lost to the field
+static double field_level(const dk_field& f)
+{
+    switch (f.kind) {
+        case DK_FIELD_EXPSIN2: return f.es_scale * (f.es_a + 0.25 * f.es_b);
+        case DK_FIELD_CLIPPED: return f.floor_add + std::max(f.c0, 0.0);
+        default: return f.c0;
+    }
+}
+
 int mean_field(const dk_problem* p, int level, const double* phi, double* buf0, double* buf1, double* out, double* centre,
                double* rho_out, hipStream_t s)
 {
@@ -468,7 +478,7 @@ int mean_field(const dk_problem* p, int level, const double* phi, double* buf0, 
         HIP_TRY(dk::launch_field_eval(to_dev_on(p, p->rho0, n), p->box, n, buf0, true, s));
         double* field = buf0;
         if (by_steps) HIP_TRY(dk::launch_meanfield_steps(n, a, steps, buf0, buf1, phi, nobs, h * h, out, &field, s));
-        else HIP_TRY(dk::launch_meanfield_transform(n, a, steps, buf0, buf1, phi, nobs, h * h, out, s));
+        else HIP_TRY(dk::launch_meanfield_transform(n, a, steps, field_level(p->rho0), buf0, buf1, phi, nobs, h * h, out, s));
         if (rho_out) HIP_TRY(hipMemcpyAsync(rho_out, field, sizeof(double) * n * n, hipMemcpyDeviceToDevice, s));
         HIP_TRY(hipMemcpyAsync(got, out, sizeof(double) * nobs * (by_steps ? 1 : 2), hipMemcpyDeviceToHost, s));
         HIP_TRY(hipStreamSynchronize(s));

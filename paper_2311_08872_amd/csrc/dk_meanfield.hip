@@ -14,8 +14,9 @@
 //
 // Bound by the FP64 matrix rate for n >= 1024 and by the latency of four dependent passes below.
 // One launch per step took 118 ms at 512 x 512 with 26624 steps (4.7 us a launch); now four of 18 us (145 us a call).
-// g^M comes from exp(M log1p(-lambda)), whose error does not grow with M: 1.07e-14 of the field against 1.04e-14
-// for the steps at 512 x 512.
+// g^M comes from exp(M log1p(-lambda)), whose error does not grow with M.  The transform takes the field's difference
+// from a constant near its mean, which no step changes: 0.5 to 1.1e-16 of the field (2-norm, 16 x 16 to 128 x 128)
+// against 1.0 to 1.6e-16 for the steps, and 0.9 to 2.4e-16 with the constant in it.
 //
 // The field of the two ways agrees to its rounding, and so do the inner products, relative to the size of their
 // terms.  An inner product that cancels (an even datum and an odd test function) is the rounding itself, and has no
@@ -60,9 +61,10 @@ __device__ __forceinline__ double mode_power(int kx, int ky, int n, double a, in
 // Tile rows k0.., columns y0.. of C X^T: sum over x of cas(k x) X[y][x].  The order of the 16 x of one
 // product group over lanes and products is the same for both operands: lane group q takes x0 + 4 q + j.
 // G groups are loaded ahead of the G being multiplied (the rows come from L2 with one wavefront per
-// SIMD).  Returns D[row 4 r + q][column lane & 15].
-template <int G>
-__device__ __forceinline__ doublex4 cas_tile(const double* X, int pitch, int n, const double* tab, int k0, int y0, int lane)
+// SIMD).  SHIFT: of X - shift.  Returns D[row 4 r + q][column lane & 15].
+template <int G, bool SHIFT>
+__device__ __forceinline__ doublex4 cas_tile(const double* X, int pitch, int n, const double* tab, int k0, int y0, int lane,
+                                             double shift)
 {
     const int i = lane & 15, q = lane >> 4;
     const int k = min(k0 + i, n - 1), y = min(y0 + i, n - 1);
@@ -78,7 +80,7 @@ __device__ __forceinline__ doublex4 cas_tile(const double* X, int pitch, int n, 
             for (int h = 0; h < 2; ++h) {                // beyond the row: zeros (n is even)
                 const int x = x0 + 16 * g + 4 * q + 2 * h;
                 nxt[g][h] = doublex2{0.0, 0.0};
-                if (x < n) nxt[g][h] = *(const doublex2*)(row + x);
+                if (x < n) nxt[g][h] = *(const doublex2*)(row + x) - (SHIFT ? doublex2{shift, shift} : doublex2{0.0, 0.0});
             }
     };
     load(0);
@@ -104,7 +106,7 @@ __device__ __forceinline__ doublex4 cas_tile(const double* X, int pitch, int n, 
 }
 
 // Grids up to 64 x 64: all four passes in one block, a wavefront per 16 x 16 tile.
-__global__ void __launch_bounds__(1024) meanfield_block_kernel(double* __restrict__ rho, int n, double a, int steps)
+__global__ void __launch_bounds__(1024) meanfield_block_kernel(double* __restrict__ rho, int n, double a, int steps, double shift)
 {
     constexpr int PMAX = kOneBlock + 2;
     __shared__ __align__(16) double fld[2][kOneBlock * PMAX];
@@ -114,11 +116,11 @@ __global__ void __launch_bounds__(1024) meanfield_block_kernel(double* __restric
     const int T = (n + 15) / 16;
     const int k0 = 16 * (wave / T), y0 = 16 * (wave % T);
     cas_table(tab, n);
-    for (int e = threadIdx.x; e < n * n; e += blockDim.x) fld[0][(e / n) * P + e % n] = rho[e];
+    for (int e = threadIdx.x; e < n * n; e += blockDim.x) fld[0][(e / n) * P + e % n] = rho[e] - shift;
     __syncthreads();
 #pragma unroll 1
     for (int pass = 0; pass < 4; ++pass) {
-        const doublex4 d = cas_tile<1>(fld[pass & 1], P, n, tab, k0, y0, lane);
+        const doublex4 d = cas_tile<1, false>(fld[pass & 1], P, n, tab, k0, y0, lane, 0.0);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int k = k0 + 4 * r + (lane >> 4), y = y0 + (lane & 15);
@@ -128,13 +130,14 @@ __global__ void __launch_bounds__(1024) meanfield_block_kernel(double* __restric
         }
         __syncthreads();
     }
-    for (int e = threadIdx.x; e < n * n; e += blockDim.x) rho[e] = fld[0][(e / n) * P + e % n];
+    for (int e = threadIdx.x; e < n * n; e += blockDim.x) rho[e] = fld[0][(e / n) * P + e % n] + shift;
 }
 
 // Larger grids: one pass per launch.  The four wavefronts of a block share their columns y, so the rows
 // of X are read through one L1.
+template <int PASS>
 __global__ void __launch_bounds__(256) cas_pass_kernel(const double* __restrict__ X, double* __restrict__ out, int n, double a,
-                                                       int steps /* > 0: multiply by g^steps / n^2 */)
+                                                       int steps, double shift)
 {
     extern __shared__ double tab[];
     cas_table(tab, n);
@@ -144,12 +147,15 @@ __global__ void __launch_bounds__(256) cas_pass_kernel(const double* __restrict_
     const int kt = 4 * (blockIdx.x % TK) + (threadIdx.x >> 6);
     if (kt >= T) return;
     const int k0 = 16 * kt, y0 = 16 * (blockIdx.x / TK);
-    const doublex4 d = cas_tile<4>(X, n, n, tab, k0, y0, lane);
+    const doublex4 d = cas_tile<4, PASS == 0>(X, n, n, tab, k0, y0, lane, shift);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int k = k0 + 4 * r + (lane >> 4), y = y0 + (lane & 15);
-        if (k < n && y < n)
-            out[(size_t)k * n + y] = steps > 0 ? d[r] * (mode_power(y, k, n, a, steps) / ((double)n * n)) : d[r];
+        if (k >= n || y >= n) continue;
+        double v = d[r];
+        if constexpr (PASS == 1) v *= mode_power(y, k, n, a, steps) / ((double)n * n);
+        if constexpr (PASS == 3) v += shift;
+        out[(size_t)k * n + y] = v;
     }
 }
 
@@ -337,18 +343,20 @@ hipError_t launch_meanfield_steps(int n, double a, int steps, double* buf0, doub
     return hipGetLastError();
 }
 
-hipError_t launch_meanfield_transform(int n, double a, int steps, double* buf0, double* buf1, const double* phi, int n_obs,
-                                      double h2, double* out, hipStream_t s)
+hipError_t launch_meanfield_transform(int n, double a, int steps, double shift, double* buf0, double* buf1, const double* phi,
+                                      int n_obs, double h2, double* out, hipStream_t s)
 {
     if (n < 2 || (n & 1) || n > 4096 || steps < 1) return hipErrorInvalidValue;
     const int T = (n + 15) / 16;
     if (n <= kOneBlock) {
-        hipLaunchKernelGGL(meanfield_block_kernel, dim3(1), dim3(64 * T * T), 0, s, buf0, n, a, steps);
+        hipLaunchKernelGGL(meanfield_block_kernel, dim3(1), dim3(64 * T * T), 0, s, buf0, n, a, steps, shift);
     } else {
         const dim3 grid((unsigned)(T * ((T + 3) / 4)));
-        for (int pass = 0; pass < 4; ++pass)
-            hipLaunchKernelGGL(cas_pass_kernel, grid, dim3(256), sizeof(double) * n, s, pass & 1 ? buf1 : buf0,
-                               pass & 1 ? buf0 : buf1, n, a, pass == 1 ? steps : 0);
+        const size_t lds = sizeof(double) * n;
+        hipLaunchKernelGGL(cas_pass_kernel<0>, grid, dim3(256), lds, s, buf0, buf1, n, a, steps, shift);
+        hipLaunchKernelGGL(cas_pass_kernel<1>, grid, dim3(256), lds, s, buf1, buf0, n, a, steps, shift);
+        hipLaunchKernelGGL(cas_pass_kernel<2>, grid, dim3(256), lds, s, buf0, buf1, n, a, steps, shift);
+        hipLaunchKernelGGL(cas_pass_kernel<3>, grid, dim3(256), lds, s, buf1, buf0, n, a, steps, shift);
     }
     // above 128 x 128 one block per observable would read its megabytes alone (320 us at 512 x 512)
     const int parts = n <= 128 ? 1 : kInnerParts;

@@ -518,7 +518,7 @@ hipError_t launch_meanfield_steps(int n, double, int steps, double* buf0, double
 }
 
 // Observable 0 cancels: its value is then taken from the steps.
-hipError_t launch_meanfield_transform(int n, double, int, double* buf0, double* buf1, const double* phi, int n_obs, double,
+hipError_t launch_meanfield_transform(int n, double, int, double, double* buf0, double* buf1, const double* phi, int n_obs, double,
                                       double* out, hipStream_t s)
 {
     return submit(s, [=] {
