@@ -32,6 +32,7 @@
 
 #include "dk_internal.h"
 #include "dk_rng.h"
+#include "dk_sum.h"
 
 namespace dk {
 
@@ -340,52 +341,86 @@ __device__ __forceinline__ void tile_step(Real (&rho)[R][C], Real (&cmp)[R][C], 
 // Observables.  (rho, phi_j) is summed in FP64 by one binary tree whatever the tile shape, so that a
 // sample's values do not depend on how a batch was cut or which shape ran it: the two columns of a lane,
 // then the rows of the grid by the bits of their index, lowest first (within the lane, across the row
-// groups of the wavefront, across wavefronts through LDS), then the columns by the bits of theirs.
-//   scratch: LDS, TS / 64 * NPL doubles per sample that spans several wavefronts (the halo area, free
+// groups of the wavefront, across wavefronts through LDS), then the columns by the bits of theirs.  FP64 states'
+// sums carry their rounding errors, which is all that such a state's value is off by; an FP32 state's own rounding
+// is 1e5 times theirs.
+//   scratch: LDS, 2 TS / 64 * NPL doubles per sample that spans several wavefronts (the halo area, free
 //   after the last step).
 // ---------------------------------------------------------------------------------------
+// a plain sum, with the interface of Sum
+struct PlainSum {
+    double hi = 0.0;
+    static constexpr int N = 1;
+    __device__ __forceinline__ void add(const PlainSum& o) { hi += o.hi; }
+    __device__ __forceinline__ double centred(double h2, double c) const { return fma(h2, hi, -c); }
+};
+struct TreeSum : Sum {
+    static constexpr int N = 2;
+    using Sum::add;
+    __device__ __forceinline__ void add(const TreeSum& o) { Sum::add(o.hi, o.lo); }
+};
+
+// of rows [I, I + W) of the lane
+template <int I, int W, typename Real, int R, int C, class S>
+__device__ __forceinline__ void row_tree(const Real (&rho)[R][C], const double* p, int NN, S& v)
+{
+#pragma clang fp contract(off)
+    if constexpr (W > 1) {
+        S r;
+        row_tree<I, W / 2>(rho, p, NN, v);
+        row_tree<I + W / 2, W / 2>(rho, p, NN, r);
+        v.add(r);
+    } else if constexpr (S::N == 1) {
+        v.hi = (double)rho[I][0] * p[I * NN];
+        if constexpr (C == 2) v.hi = fma((double)rho[I][C - 1], p[I * NN + C - 1], v.hi);
+    } else {
+        v.add_product(rho[I][0], p[I * NN]);
+        if constexpr (C == 2) v.add_product(rho[I][C - 1], p[I * NN + C - 1]);
+    }
+}
+
+template <class S>
+__device__ __forceinline__ S sum_shuffle(const S& v, int off)
+{
+    S o;
+    o.hi = __shfl_xor(v.hi, off, 64);
+    if constexpr (S::N == 2) o.lo = __shfl_xor(v.lo, off, 64);
+    return o;
+}
+
 template <typename Real, int R, int C, int NPL, int TS>
 __device__ __forceinline__ void observe(const Real (&rho)[R][C], const double* __restrict__ phi, const double* obs,
                                         int n_obs, int NN, int row0, int col0, double h2, double* scratch, int t,
                                         double* dst, bool write)
 {
 #pragma clang fp contract(off)
+    using S = std::conditional_t<std::is_same<Real, double>::value, TreeSum, PlainSum>;
     constexpr int NW = TS <= 64 ? 1 : TS / 64;      // wavefronts of a sample
     constexpr int W = TS < 64 ? TS : 64;
     for (int j = 0; j < n_obs; ++j) {
-        const double* ph = phi + (size_t)j * NN * NN;
-        double v[R];
+        S s;
+        row_tree<0, R>(rho, phi + (size_t)j * NN * NN + row0 * NN + col0, NN, s);
+        // the first lane's value is the tree's: it is the lower half at every step
 #pragma unroll
-        for (int i = 0; i < R; ++i) {
-            const double* p = ph + (row0 + i) * NN + col0;
-            v[i] = (double)rho[i][0] * p[0];
-            if constexpr (C == 2) v[i] = fma((double)rho[i][C - 1], p[C - 1], v[i]);
-        }
-#pragma unroll
-        for (int w = 1; w < R; w <<= 1)
-#pragma unroll
-            for (int i = 0; i + w < R; i += 2 * w) v[i] += v[i + w];
-        double s = v[0];
-#pragma unroll
-        for (int off = NPL; off < W; off <<= 1) s += __shfl_xor(s, off, 64);
+        for (int off = NPL; off < W; off <<= 1) s.add(sum_shuffle(s, off));
         if constexpr (NW > 1) {
+            S* mine = (S*)scratch;
             __syncthreads();                        // the last step's halo, the last observable's sums are read
-            if ((t & 63) < NPL) scratch[(t >> 6) * NPL + (t & 63)] = s;
+            if ((t & 63) < NPL) mine[(t >> 6) * NPL + (t & 63)] = s;
             __syncthreads();
-            double u[NW];
+            S u[NW];
 #pragma unroll
-            for (int w = 0; w < NW; ++w) u[w] = scratch[w * NPL + (t & (NPL - 1))];
+            for (int w = 0; w < NW; ++w) u[w] = mine[w * NPL + (t & (NPL - 1))];
 #pragma unroll
             for (int w = 1; w < NW; w <<= 1)
 #pragma unroll
-                for (int i = 0; i + w < NW; i += 2 * w) u[i] += u[i + w];
+                for (int i = 0; i + w < NW; i += 2 * w) u[i].add(u[i + w]);
             s = u[0];
         }
 #pragma unroll
-        for (int off = 1; off < NPL; off <<= 1) s += __shfl_xor(s, off, 64);
+        for (int off = 1; off < NPL; off <<= 1) s.add(sum_shuffle(s, off));
         if (write) {
-            const double scale = obs[3 * j + 0], centre = obs[3 * j + 1];
-            const double X = scale * fma(h2, s, -centre);
+            const double X = obs[3 * j + 0] * s.centred(h2, obs[3 * j + 1]);
             dst[2 * j] = (obs[3 * j + 2] != 0.0) ? X * X : X;
         }
     }
