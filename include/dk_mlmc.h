@@ -394,8 +394,9 @@ int dk_context_reset(dk_context* ctx, int32_t drop_tables);
 /* Tile shapes of the resident kernel: a lane owns 2 columns and R rows of an n x n grid, and a
  * block holds S samples.  dk_shape_rows(n, v) gives R of variant v and dk_shape_spw(n, v) its S
  * (both 0 if the variant does not exist).  By default a batch that leaves wavefronts idle at 8 rows
- * per lane runs at fewer, and the context times the variants on a short batch the first time a large
- * job (>= 1e11 cell updates) runs a grid size, and keeps the fastest; dk_context_set_shape forces
+ * per lane runs at fewer; for larger batches the context times the variants on a short batch the first
+ * time a large job (>= 1e11 cell updates) runs a grid size, and keeps the fastest (or takes the choice
+ * that was loaded); dk_context_set_shape forces
  * variant v for grid size n (v < 0 restores the automatic choice).  Values do not depend on the
  * shape: observables are added in one order. */
 int dk_context_set_shape(dk_context* ctx, int32_t n, int32_t variant);
@@ -433,7 +434,7 @@ int dk_context_set_streaming(dk_context* ctx, int32_t on);
  * (the default) times the four depths on a short batch (16 fine steps, up to 64 samples) the
  * first time a job of >= 1e11 cell updates runs a grid size, keeps the fastest (listed in the
  * tuning JSON as {"n": .., "pair": .., "flux": .., "depth": D}) and uses depth 4 for smaller
- * jobs.  DK_EINVAL for other values.  The depth changes no result. */
+ * jobs and for launches of few tiles.  DK_EINVAL for other values.  The depth changes no result. */
 int dk_context_set_stream_depth(dk_context* ctx, int32_t depth);
 
 /* Largest work of one sampling launch, in fine + coarse cell updates (default 2e12, about 5 s

@@ -10,7 +10,7 @@
 //   n > 256        256 x 256 windows with a halo of T <= 16 cells, T steps a pass, two buffers in turn
 // Rows of a lane are swept in registers; the columns at a lane's edges come from the neighbouring lanes
 // (ds_bpermute), the rows at its top and bottom through LDS, double-buffered by step, one barrier a step,
-// none where a field lies in one wavefront.  The same 64 steps of 1000 fields now take 0.62 ms (6.7e12 cell
+// none where a field lies in one wavefront.  The same 64 steps of 1000 fields now take 0.58 ms (7.2e12 cell
 // steps/s; 8.3e12 at 128 x 128, where four blocks share a compute unit): bound by the 330 vector and 36 LDS
 // instructions of a wavefront's step and, at one block per compute unit, by its barrier.  Windows: 512 x 512
 // 2.2e12 (7.6e11 with a pass per step), 1024 x 1024 3.5e12 (6.3e11).
@@ -38,7 +38,7 @@ struct HeatGeo {
 };
 
 // A neighbouring lane's value, whatever the row's length.  Whole-wavefront DPP rotations, which a 256-cell
-// row could use, run 14 % slower (0.71 against 0.62 ms); 16-lane ones, for 64-cell rows only, 9 % faster.
+// row could use, run 14 % slower; 16-lane ones, for 64-cell rows only, 9 % faster.
 __device__ __forceinline__ float lane_value(float v, int addr)
 {
     return __int_as_float(__builtin_amdgcn_ds_bpermute(addr, __float_as_int(v)));

@@ -76,11 +76,12 @@ int stream_parts(int n, int count)
 // A launch boundary waits for the launch's last blocks, and a batch rarely fills the compute units evenly (40
 // pairs of 256 x 256 are 640 blocks for 512 places).  The samples are independent, so a batch of more
 // than 256 blocks advances as two halves on two streams, and one half's blocks fill the places that the
-// other's last ones leave.  Time in ms of 32768 steps of 256 x 256 pairs:
-//   pairs          8    16    24    32    40    64   128
-//   one stream   157   163   242   250   354   446   836
-//   two          175   176   197   206   261   399   786
-// (64 x 64 tiles, before small launches took smaller ones).  The line lies at one block per compute unit: below it the halves have no place to fill.
+// other's last ones leave.  Time in ms of 32768 steps of 256 x 256 pairs (16 tiles of 64 x 64 each; up to 12 pairs a
+// launch takes smaller tiles):
+//   pairs         16    24    32    40    64   128
+//   one stream   156   232   241   335   426   805
+//   two            -   188   194   249   378   749
+// The line lies at one block per compute unit: below it the halves have no place to fill.
 int stream_pass(dk_context* ctx, const dk_problem* p, bool pair, int depth, const dk::LevelArgs& A, uint64_t first,
                 int c, int steps, size_t zgroup, hipStream_t s, int* cur_f, int* cur_c)
 {
@@ -263,7 +264,7 @@ int run_stream(dk_context* ctx, const dk_problem* p, int level, bool pair, uint6
 }
 
 // Levels of a Fourier-coupled hierarchy (Sec. 3.1): the projection kernel of the pair, then
-// chunks of samples with blocks striding over each chunk, the moments in chunk order.
+// chunks of samples, the moments in chunk order.
 int run_fourier(dk_context* ctx, const dk_problem* p, int level, bool pair, uint64_t first, uint64_t count,
                 const dk::LevelArgs& A, LevelTables* Tf, LevelTables* Tc, dk_moments* sums_out, double* per_sample_out,
                 hipStream_t s, double* cell_updates, uint64_t nchunks, uint64_t ch, size_t mom_stride)
@@ -429,7 +430,7 @@ int run_theta(dk_context* ctx, const dk_problem* p, int level, bool pair, uint64
         }
         st.launches += nchunks;
         st.samples += count;
-        st.rows = 0;   // b0 > 0 kernel: the state in LDS, no tile shapes
+        st.rows = 0;   // b0 > 0 kernel: one tile shape per grid
         st.cells += per * (double)count;
     }
     for (uint64_t k = 0; k < nchunks; ++k) {

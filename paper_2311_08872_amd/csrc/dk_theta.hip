@@ -22,9 +22,9 @@
 // than five butterflies; 4000 pairs of 32 x 32 at N = 1e4: 6.8e-7 of the observable's RMS with S d, 4.2e-7 so,
 // 6.1e-7 by butterflies).
 //
-// Bound by the vector ALU (generator and addresses, two thirds of the issue slots at 64 x 64) and the FP64
-// matrix cores (a quarter); two wavefronts per SIMD overlap the two in part.  1000 pairs of 64 x 64 in FP64
-// with one lane per butterfly point: 38.3 ms; here 7.9 ms (1.5e11 cell updates/s).
+// Bound by the vector ALU (generator and addresses: instructions active in half of the SIMDs' cycles at 64 x 64)
+// and the FP64 matrix cores (busy in a third); two wavefronts per SIMD overlap the two in part.  1000 pairs of
+// 64 x 64 in FP64 with one lane per butterfly point: 38.3 ms; here 8.0 ms (1.5e11 cell updates/s).
 //
 // Layout: cells are owned as the products return them: register i of lane (q, c) = (lane / 16, lane % 16)
 // of a 16 x 16 tile is row M::row(i, q) of column c.  The same register is the operand B of a product that
